@@ -1,0 +1,453 @@
+// fp32 forward / stride-1 backward-data on the bf16 matrix instruction: every fp32 operand is split into three bfloat16
+// parts whose sum it is, and the six products that matter are accumulated in fp32.
+// Part of convnet_hotpath.hip: included there, inside its anonymous namespace, after conv_bf16_dma_kernels.h.
+//
+// Why: an fp32 matrix instruction occupies the pipe 16 times as long per product as a bf16 one.  x = h + m + l with
+// h = bf16(x), m = bf16(x - h), l = x - h - m is exact (8 + 8 + 8 significand bits, every remainder representable), so
+//   x * w = h h' + h m' + m h' + m m' + h l' + l h'  (+ m l' + l m' + l l', at most 2^-24 |x w|, random in sign, left out)
+// costs six bf16 products: 16 / 6 = 2.7 times the fp32 rate.  The matrix instruction adds its 16 products to the fp32
+// accumulator with one rounding (v_mfma_f32_32x32x2_f32: eight per 16 products); h h' has an accumulator of its own, the
+// five smaller products, whose roundings weigh 2^-8 as much, share another, and the two are added at the end.  Relative
+// error (2-norm) against 64-bit sums, 384 channels 3x3 forward: 2.7e-7; fp32 kernel 6.7e-7; with one accumulator for all
+// six products 8.1e-7.
+//
+// Range: the split is exact for |x| >= 2^-110 and for 0.  A tile whose sums are not finite (infinities, NaN or an
+// overflow in its inputs), or all tiny (below 2^-80, where the parts of the inputs may have been flushed), is computed
+// again by its work-group from the fp32 tensors with the fp32 matrix instruction, so that infinities, NaN and tiny values
+// come out as fp32 arithmetic gives them.
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// two fp32 values -> their bfloat16 parts, two to a word
+__device__ __forceinline__ void split_pair(float a, float b, unsigned &h, unsigned &m, unsigned &l)
+{
+    h = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
+    const float a1 = a - __uint_as_float(h << 16), b1 = b - __uint_as_float(h & 0xffff0000u);
+    m = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a1, b1}, bf16x2));
+    const float a2 = a1 - __uint_as_float(m << 16), b2 = b1 - __uint_as_float(m & 0xffff0000u);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a2, b2}, bf16x2));
+}
+
+// eight consecutive reduction elements -> one 16-byte piece of each part
+__device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
+{
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        unsigned h, m, l;
+        split_pair(v[2 * t], v[2 * t + 1], h, m, l);
+        o[0][t] = h; o[1][t] = m; o[2][t] = l;
+    }
+}
+
+// Whether a wave's sums call for the fp32 computation: bit 0 some sum is not finite, bit 1 some sum is at least 2^-80,
+// bit 2 some sum is not zero.
+template <int TM, int TN>
+__device__ __forceinline__ int split_sum_flags(const f32x16 (&acc)[TM][TN])
+{
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) top = max(top, __float_as_uint(acc[i][jn][v]) & 0x7fffffffu);
+    return (__ballot(top >= 0x7f800000u) ? 1 : 0) | (__ballot(top >= (unsigned)(127 - 80) << 23) ? 2 : 0) |
+           (__ballot(top > 0u) ? 4 : 0);
+}
+__device__ __forceinline__ bool split_redo(int flags) { return (flags & 1) || ((flags & 4) && !(flags & 2)); }
+
+// ---------------------------------------------------------------------------
+// Preparation, one launch:
+//   blocks [0, xb_blocks): xs[n][channel block of 16][part][Hp][Wp][16] from NCHW fp32 src (samples src_bs elements
+//       apart), zeros in the padding and in channels past a column's last; one thread per (position, 8 channels), so
+//       that a wavefront's stores are 1 KB runs and its loads 128-byte runs of two planes
+//   the rest: wt[step = (channel block, r, s)][part][Mpad][16] from KCRS filters, the two 8-channel halves of a row
+//       swapped where (row >> 3) & 1: a linear copy into LDS then lets the 16 lanes of a fragment read cover all banks;
+//       one thread per 8 channels
+// A grouped layer's columns follow each other in both (CBg channel blocks per column, filters one column after another).
+// Bound: HBM, 4 bytes read and 6 * Hp*Wp / (LH*LW) written per activation.
+// ---------------------------------------------------------------------------
+struct SplitPrepArgs {
+    const float *src;
+    u32x4 *xs;
+    int64_t src_bs;
+    int Cg, CBg, CBt;          // channels and channel blocks per column, channel blocks of all columns
+    int LH, LW, Hp, Wp, pad_h, pad_w;
+    unsigned positions;        // N * CBt * Hp * Wp
+    int xb_blocks;
+    const float *w;
+    u32x4 *wt;
+    int M, Mpad, RS, C;        // C: channels per filter (the row stride of w)
+    int transposed;            // backward-data: rows are the filter's channels, reduction runs over the filters
+    unsigned wt_chunks;        // groups * CBg * RS * Mpad * 2
+    int64_t w_gs;              // floats between the columns' filters
+    FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs;
+};
+
+__global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
+{
+    float v[8];
+    u32x4 o[3];
+    if ((int)blockIdx.x < p.xb_blocks) {
+        const unsigned e = blockIdx.x * 256u + threadIdx.x;
+        const unsigned i = e >> 1, half = e & 1;
+        if (i >= p.positions) return;
+        const unsigned t1 = fastdiv(i, p.div_wp);                    // (n*CBt + blk)*Hp + hp
+        const int wp = (int)(i - t1 * (unsigned)p.Wp);
+        const unsigned t2 = fastdiv(t1, p.div_hp);                    // n*CBt + blk
+        const int hp = (int)(t1 - t2 * (unsigned)p.Hp);
+        const unsigned n = fastdiv(t2, p.div_cbt), blk = t2 - n * (unsigned)p.CBt;
+        const unsigned g = fastdiv(blk, p.div_cbg);
+        const int c0 = (int)(blk - g * (unsigned)p.CBg) * 16 + (int)half * 8;     // channel inside the column
+        const int h = hp - p.pad_h, w = wp - p.pad_w;
+        const bool in = (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
+        const int LHW = p.LH * p.LW;
+        const float *s = p.src + (int64_t)n * p.src_bs + (int64_t)((int)g * p.Cg + c0) * LHW + h * p.LW + w;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = in && c0 + k < p.Cg ? s[(int64_t)k * LHW] : 0.f;
+        split_eight(v, o);
+        const unsigned plane = (unsigned)p.Hp * (unsigned)p.Wp;
+        u32x4 *dst = p.xs + ((size_t)t2 * 3 * plane + (i - t2 * plane)) * 2 + half;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dst[(size_t)c * plane * 2] = o[c];
+        return;
+    }
+    const unsigned e = (blockIdx.x - (unsigned)p.xb_blocks) * 256u + threadIdx.x;
+    if (e >= p.wt_chunks) return;
+    const int half = (int)(e & 1);
+    const unsigned t1 = e >> 1;                                        // ((g*CBg + cb)*RS + rs)*Mpad + m
+    const unsigned t2 = fastdiv(t1, p.div_mpad);
+    const int m = (int)(t1 - t2 * (unsigned)p.Mpad);
+    const unsigned t3 = fastdiv(t2, p.div_rs);                         // g*CBg + cb
+    const int rs = (int)(t2 - t3 * (unsigned)p.RS);
+    const unsigned g = fastdiv(t3, p.div_cbg);
+    const int ch0 = (int)(t3 - g * (unsigned)p.CBg) * 16 + half * 8;
+    const float *w = p.w + (int64_t)g * p.w_gs;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int ch = ch0 + k;
+        v[k] = m < p.M && ch < p.Cg ? (p.transposed ? w[((int64_t)ch * p.C + m) * p.RS + rs] : w[((int64_t)m * p.C + ch) * p.RS + rs])
+                                    : 0.f;
+    }
+    split_eight(v, o);
+    u32x4 *dst = p.wt + ((size_t)t2 * 3 * p.Mpad + m) * 2 + (half ^ ((m >> 3) & 1));
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dst[(size_t)c * p.Mpad * 2] = o[c];
+}
+
+// ---------------------------------------------------------------------------
+// The contraction.  Both operands go from global memory straight into LDS (dma16, conv_bf16_dma_kernels.h); one step is
+// one filter tap x 16 channels: BM filter rows and BN positions of 32 bytes in each of three parts, in an LDS buffer of
+// (BM + BN) * 96 bytes, three buffers.  Eight waves, one work-group per CU.  A fragment of a part serves two or three
+// products, so a 128 x 256 tile needs 24 bytes per clock through the vector memory path and 62 from LDS against the
+// 60 and ~190 they deliver: unlike the one-part bf16 kernel (48 and 96) this one is bound by its matrix instructions:
+// 71 % of its cycles, at a clock that the power limit holds to 1.94 GHz (1.38 of the 1.77 that the pipe sustains alone on
+// random operands).  384 -> 384 channels 3x3, N = 128, whole call (preparation 26 us): forward 452 -> 273 us, backward-data
+// 450 -> 269; N = 2: 78 -> 33; two columns 48 -> 128 5x5, N = 128: forward 474 -> 278, backward-data 499 -> 379 (48 rows
+// padded to 64).
+// Order inside a step: h h', h l', l h', h m' while the loads of step + 2 are issued; then every fragment of the step
+// has been read, so the barrier that frees its buffer comes here; m h', m m' cover the barrier and the reads of the next
+// step's h and h' (each into the registers that held this step's).
+// ---------------------------------------------------------------------------
+struct ColGemmSplitArgs {
+    const void *At;            // wt (see above)
+    const void *xs;            // split, blocked, padded activations
+    float *dst;                // y or dx
+    float *part;               // ksplit > 1: partial outputs [ksplit][N][M][OH*OW] per column
+    int M, Mpad, ncols;
+    int OH, OW, mul;
+    int Wp;
+    unsigned plane_bytes;      // one part of one channel block: Hp * Wp * 32
+    unsigned n_bytes;          // one sample: channel blocks of all columns * 3 * plane_bytes
+    int R, S, sign;            // sign +1: tap (r, s) reads padded (oh*mul + r, ow*mul + s); -1: (oh + R-1-r, ow + S-1-s)
+    int cblocks;               // channel blocks per column
+    int dst_bs;
+    int mtiles, ntiles, tiles_per_xcd, ksplit, steps_per_split, groups;
+    int64_t dst_gs, part_gs;   // floats between the columns
+    // the fp32 tensors, for a tile that has to be computed in fp32
+    const float *w, *src;
+    int64_t w_gs, src_gs;
+    int src_bs, LH, LW, add, Cg, C, transposed;
+    int epi_on;
+    Epilogue epi;
+    FastDiv div_plane, div_ow, div_rs, div_s;
+};
+
+template <int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const ColGemmSplitArgs p)
+{
+    constexpr int NW = WM * WN;
+    constexpr int BM = TM * WM * 32, BN = TN * WN * 32;
+    constexpr int QA = BM * 3 / 32, QB = BN * 3 / 32;          // 1 KB loads per step: filters, activations
+    constexpr int NL = (QA + QB + NW - 1) / NW;                // ... per wave (the last may repeat an earlier one)
+    constexpr int BUF = (BM + BN) * 96;
+    constexpr int MPG = TM * TN;                               // matrix instructions per product
+    static_assert(NW == 8, "eight waves");
+    static_assert(3 * BUF <= 160 * 1024, "three LDS buffers");
+
+    extern __shared__ __attribute__((aligned(16))) float lds_fast[];
+    const char *const lds = reinterpret_cast<const char *>(lds_fast);
+    const unsigned lds_base = (unsigned)(size_t)lds_fast;
+
+    const int bid = blockIdx.x;
+    const int idx = bid >> 3;
+    const int unit = (bid & 7) * p.tiles_per_xcd + idx;
+    const int ntile = p.mtiles * p.ntiles;
+    if (idx >= p.tiles_per_xcd || unit >= ntile * p.ksplit * p.groups) return;
+    const int gcol = unit / (ntile * p.ksplit);
+    const int unit_c = unit - gcol * (ntile * p.ksplit);
+    const int ks = unit_c / ntile;
+    const int tile = unit_c - ks * ntile;
+    const int mt = tile % p.mtiles, nt = tile / p.mtiles;
+    const int m0 = mt * BM, n0 = nt * BN;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uniform(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+
+    // Load i of this wave is 1 KB block q of the step: 32 rows of one part, filters first.  LDS block q lies at q * 1024.
+    unsigned voff[NL], lq[NL];
+    bool isa[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        int q = i * NW + wave;
+        if (q >= QA + QB) q -= NW;                               // repeats this wave's previous load
+        lq[i] = (unsigned)q * 1024u;
+        isa[i] = q < QA;
+        if (isa[i]) {
+            const int c = q / (BM / 32), b = q - c * (BM / 32);
+            voff[i] = (unsigned)((c * p.Mpad + b * 32) * 32 + lane * 16);
+        } else {
+            const int qb = q - QA;
+            const int c = qb / (BN / 32), b = qb - c * (BN / 32);
+            const int row = b * 32 + (lane >> 1);
+            const int chunk = (lane & 1) ^ ((row >> 3) & 1);
+            int j = n0 + row;
+            j = j < p.ncols ? j : 0;                             // columns past the end: computed, never stored
+            const int n = (int)fastdiv((uint32_t)j, p.div_plane);
+            const int rem = j - n * (p.OH * p.OW);
+            const int oh = (int)fastdiv((uint32_t)rem, p.div_ow);
+            const int ow = rem - oh * p.OW;
+            voff[i] = (unsigned)n * p.n_bytes + (unsigned)c * p.plane_bytes +
+                      (unsigned)((oh * p.mul * p.Wp + ow * p.mul) * 32 + chunk * 16);
+        }
+    }
+
+    const int step_begin = ks * p.steps_per_split;
+    const int nsteps = min(p.cblocks * p.R * p.S - step_begin, p.steps_per_split);
+    const size_t a_step_bytes = (size_t)p.Mpad * 96;
+    const char *a_base = static_cast<const char *>(p.At) +
+                         ((size_t)gcol * p.cblocks * p.R * p.S + step_begin) * a_step_bytes + (size_t)m0 * 32;
+    const char *const x_base = static_cast<const char *>(p.xs) + (size_t)gcol * p.cblocks * 3 * p.plane_bytes;
+    int r, s, cb;                                                // next step to load
+    {
+        cb = (int)fastdiv((uint32_t)step_begin, p.div_rs);
+        const int rs = step_begin - cb * (p.R * p.S);
+        r = (int)fastdiv((uint32_t)rs, p.div_s);
+        s = rs - r * p.S;
+    }
+    const char *xs = nullptr;
+    unsigned lbuf = 0;
+    auto begin_step_loads = [&](int buf) {
+        const int ar = p.sign > 0 ? r : p.R - 1 - r, as = p.sign > 0 ? s : p.S - 1 - s;
+        xs = x_base + (size_t)cb * 3 * p.plane_bytes + (ar * p.Wp + as) * 32;
+        lbuf = lds_base + buf * BUF;
+    };
+    auto load_one = [&](int i) { dma16(isa[i] ? a_base : xs, voff[i], lbuf + lq[i]); };
+    auto end_step_loads = [&]() {
+        a_base += a_step_bytes;
+        s += 1;
+        if (s == p.S) { s = 0; r += 1; }
+        if (r == p.R) { r = 0; cb += 1; }
+    };
+    auto load_step = [&](int buf) {
+        begin_step_loads(buf);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) load_one(i);
+        end_step_loads();
+    };
+
+    f32x16 acc[TM][TN], low[TM][TN];           // sums of h h'; of the five smaller products
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[i][jn][v] = 0.f; low[i][jn][v] = 0.f; }
+
+    const int l32 = lane & 31, half = lane >> 5;
+    const int choff = (half ^ ((l32 >> 3) & 1)) * 16;
+    const int a_row = (wm * TM * 32 + l32) * 32 + choff;
+    const int b_row = BM * 96 + (wn * TN * 32 + l32) * 32 + choff;
+
+    u32x4 fa[3][TM], fb[3][TN];                                // fragments, by part
+    auto read_a = [&](const char *bufp, int c, u32x4 (&f)[TM]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) f[i] = *reinterpret_cast<const u32x4 *>(bufp + a_row + (c * BM + i * 32) * 32);
+    };
+    auto read_b = [&](const char *bufp, int c, u32x4 (&f)[TN]) {
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) f[jn] = *reinterpret_cast<const u32x4 *>(bufp + b_row + (c * BN + jn * 32) * 32);
+    };
+
+    if (nsteps > 0) load_step(0);
+    if (nsteps > 1) load_step(1);
+    if (nsteps > 1) wait_vmcnt<NL>(); else wait_vmcnt<0>();
+    __syncthreads();
+    if (nsteps > 0) { read_a(lds, 0, fa[0]); read_b(lds, 0, fb[0]); }
+
+    constexpr int SLOTS = 4 * MPG;                              // matrix instructions before the barrier
+    constexpr int SPACING = SLOTS / NL > 0 ? SLOTS / NL : 1;
+    int step = 0, buf = 0;
+    auto do_step = [&](auto more_c) {                           // more: the loads of step + 2 exist
+        constexpr bool more = decltype(more_c)::value;
+        const int buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf1 == 2 ? 0 : buf1 + 1;
+        const char *bufp = lds + buf * BUF;
+        const char *nextp = lds + buf1 * BUF;
+        const bool next = more || step + 1 < nsteps;
+        if (more) begin_step_loads(buf2);
+        // product g of this step: part ca of the filters with part cb of the activations
+        auto product = [&](int ca, int cb, int g) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int jn = 0; jn < TN; ++jn) {
+                    f32x16 &sum = g == 0 ? acc[i][jn] : low[i][jn];
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[ca][i]),
+                                                                  __builtin_bit_cast(bf16x8, fb[cb][jn]), sum, 0, 0, 0);
+                    const int m = g * MPG + i * TN + jn;
+                    if (more && g < 4) {
+#pragma unroll
+                        for (int u = 0; u < NL; ++u)
+                            if ((u * SPACING < SLOTS ? u * SPACING : SLOTS - 1) == m) {
+                                __builtin_amdgcn_sched_barrier(0);
+                                load_one(u);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read_b(bufp, 2, fb[2]);
+        read_a(bufp, 2, fa[2]);
+        __builtin_amdgcn_sched_barrier(0);
+        product(0, 0, 0);
+        read_b(bufp, 1, fb[1]);
+        read_a(bufp, 1, fa[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        product(0, 2, 1);
+        product(2, 0, 2);
+        product(0, 1, 3);
+        if (more) end_step_loads();
+        if (more) wait_vmcnt<NL>(); else wait_vmcnt<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)");
+        __syncthreads();
+        if (next) read_a(nextp, 0, fa[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        product(1, 0, 4);
+        if (next) read_b(nextp, 0, fb[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        product(1, 1, 5);
+        ++step;
+        buf = buf1;
+    };
+    while (step + 2 < nsteps) do_step(std::true_type{});
+    while (step < nsteps) do_step(std::false_type{});
+
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
+
+    // sums that call for fp32 arithmetic: the whole work-group computes its tile again
+    {
+        __syncthreads();                                        // the LDS buffers are free
+        int *const flags = reinterpret_cast<int *>(lds_fast);
+        const int f = split_sum_flags<TM, TN>(acc);
+        if (lane == 0) flags[wave] = f;
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) all |= flags[i];
+        if (split_redo(uniform(all))) {
+            const float *const wg = p.w + (size_t)gcol * p.w_gs;
+            const float *const sg = p.src + (size_t)gcol * p.src_gs;
+            int rowm[TM], hb[TN], wb[TN];
+            int64_t base[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) rowm[i] = m0 + (wm * TM + i) * 32 + l32;
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) {
+                int j = n0 + (wn * TN + jn) * 32 + l32;
+                j = j < p.ncols ? j : 0;
+                const int n = (int)fastdiv((uint32_t)j, p.div_plane);
+                const int rem = j - n * (p.OH * p.OW);
+                const int oh = (int)fastdiv((uint32_t)rem, p.div_ow);
+                hb[jn] = oh * p.mul + p.add;
+                wb[jn] = (rem - oh * p.OW) * p.mul + p.add;
+                base[jn] = (int64_t)n * p.src_bs;
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
+#pragma unroll 1
+            for (int st = step_begin; st < step_begin + nsteps; ++st) {
+                const int cbk = (int)fastdiv((uint32_t)st, p.div_rs);
+                const int rs = st - cbk * (p.R * p.S);
+                const int rr = (int)fastdiv((uint32_t)rs, p.div_s), ss = rs - rr * p.S;
+#pragma unroll 1
+                for (int t = 0; t < 8; ++t) {
+                    const int ch = cbk * 16 + half * 8 + t;
+                    float a[TM], b[TN];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const bool ok = rowm[i] < p.M && ch < p.Cg;
+                        const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * (p.R * p.S) + rs
+                                                       : ((int64_t)rowm[i] * p.C + ch) * (p.R * p.S) + rs;
+                        a[i] = ok ? wg[o] : 0.f;
+                    }
+#pragma unroll
+                    for (int jn = 0; jn < TN; ++jn) {
+                        const int h = hb[jn] + p.sign * rr, w = wb[jn] + p.sign * ss;
+                        const bool ok = ch < p.Cg && (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
+                        b[jn] = ok ? sg[base[jn] + (int64_t)ch * (p.LH * p.LW) + h * p.LW + w] : 0.f;
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int jn = 0; jn < TN; ++jn)
+                            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[jn], acc[i][jn], 0, 0, 0);
+                }
+            }
+        }
+    }
+
+    float *const dst_c = p.dst + (size_t)gcol * p.dst_gs;
+    float *const part_c = p.part + (size_t)gcol * p.part_gs;
+    const int plane = p.OH * p.OW;
+#pragma unroll
+    for (int jn = 0; jn < TN; ++jn) {
+        const int col = n0 + (wn * TN + jn) * 32 + l32;
+        if (col >= p.ncols) continue;
+        const int n = (int)fastdiv((uint32_t)col, p.div_plane);
+        const int rem = col - n * plane;
+        float *out = p.ksplit > 1 ? part_c + ((size_t)ks * (p.ncols / plane) + n) * ((size_t)p.M * plane) + rem
+                                  : dst_c + (size_t)n * p.dst_bs + rem;
+        if (p.epi_on && p.ksplit == 1)            // one column only; split sums get it in reduce_split_outputs
+            epi_tile<TM, TN>(p.epi, acc, jn, m0 + wm * TM * 32 + half * 4, p.M, plane,
+                             (int64_t)n * p.epi.mask_bs + rem);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row0 = m0 + (wm * TM + i) * 32 + half * 4;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = row0 + (v >> 2) * 8 + (v & 3);
+                if (row < p.M) out[(size_t)row * plane] = acc[i][jn][v];
+            }
+        }
+    }
+}

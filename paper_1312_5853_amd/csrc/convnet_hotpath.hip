@@ -42,6 +42,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 #include "device_common.h"
 #include "conv_colgemm_kernels.h"
 #include "conv_bf16_dma_kernels.h"
+#include "conv_split_kernels.h"
 #include "conv_wgrad_rows_kernels.h"
 #include "conv_wgrad_kernels.h"
 #include "fc_kernels.h"
@@ -239,6 +240,79 @@ int run_colgemm_dma(int op, const void *act, const void *w, void *out, const Pro
     else if (tn == 3) launch_dma(colgemm_bf16_dma_kernel<2, 3, 2, 2, 32, 2>, a, grid, lds, st);
     else if (kc == 64) launch_dma(colgemm_bf16_dma_kernel<2, 2, 2, 2, 64, 1>, a, grid, lds, st);
     else launch_dma(colgemm_bf16_dma_kernel<2, 2, 2, 2, 32, 2>, a, grid, lds, st);
+    return check_launch();
+}
+
+// fp32 forward / stride-1 backward-data in three bfloat16 parts: one preparation launch, the contraction, and the sum of
+// the partial outputs where the reduction is split
+int run_colgemm_split(int op, const float *act, const float *w, float *out, const Problem &pb, const Plan &pl, void *ws,
+                      hipStream_t st, const Epilogue *ep, bool *ep_applied)
+{
+    char *wsb = static_cast<char *>(ws);
+    const bool fwd = op == kOpFwd;
+    const int Cr = fwd ? pb.C : pb.K, RS = pb.R * pb.S;
+    const int GF = pl.fused_groups ? pb.groups : 1;              // columns of a grouped layer in these launches
+    SplitPrepArgs q;
+    q.src = act; q.xs = reinterpret_cast<u32x4 *>(wsb + pl.sp_x_off);
+    q.src_bs = fwd ? pb.x_bs : pb.y_bs;
+    q.Cg = Cr; q.CBg = pl.sp_cb; q.CBt = GF * pl.sp_cb;
+    q.LH = fwd ? pb.H : pb.P; q.LW = fwd ? pb.W : pb.Q;
+    q.Hp = pl.sp_hp; q.Wp = pl.sp_wp; q.pad_h = pl.sp_ph; q.pad_w = pl.sp_pw;
+    q.positions = (unsigned)((int64_t)pb.N * q.CBt * q.Hp * q.Wp);
+    q.xb_blocks = grid1d((int64_t)q.positions * 2, 256);
+    q.w = w; q.wt = reinterpret_cast<u32x4 *>(wsb + pl.sp_w_off);
+    q.M = pl.M; q.Mpad = pl.sp_mpad; q.RS = RS; q.C = pb.C; q.transposed = fwd ? 0 : 1;
+    q.wt_chunks = (unsigned)((int64_t)GF * pl.sp_cb * RS * pl.sp_mpad * 2);
+    q.w_gs = pb.w_gs;
+    q.div_wp = make_fastdiv((uint32_t)q.Wp); q.div_hp = make_fastdiv((uint32_t)q.Hp);
+    q.div_cbt = make_fastdiv((uint32_t)q.CBt); q.div_cbg = make_fastdiv((uint32_t)q.CBg);
+    q.div_mpad = make_fastdiv((uint32_t)q.Mpad); q.div_rs = make_fastdiv((uint32_t)RS);
+    hipLaunchKernelGGL(split_prepare, dim3(q.xb_blocks + grid1d(q.wt_chunks, 256)), dim3(256), 0, st, q);
+    int rc = check_launch();
+    if (rc != kStatusOk) return rc;
+
+    ColGemmSplitArgs a;
+    a.At = q.wt; a.xs = q.xs; a.dst = out; a.part = reinterpret_cast<float *>(wsb + pl.part_off);
+    a.M = pl.M; a.Mpad = pl.sp_mpad;
+    a.OH = fwd ? pb.P : pb.H; a.OW = fwd ? pb.Q : pb.W; a.mul = fwd ? pb.stride : 1;
+    a.ncols = pb.N * a.OH * a.OW;
+    a.Wp = q.Wp; a.plane_bytes = (unsigned)q.Hp * (unsigned)q.Wp * 32u; a.n_bytes = (unsigned)q.CBt * 3u * a.plane_bytes;
+    a.R = pb.R; a.S = pb.S; a.sign = fwd ? 1 : -1;
+    a.cblocks = pl.sp_cb;
+    a.dst_bs = (int)(fwd ? pb.y_bs : pb.x_bs);
+    a.mtiles = pl.sp_mpad / pl.sp_bm;
+    a.ntiles = ceil_div(a.ncols, pl.sp_bn);
+    a.ksplit = pl.nsplit; a.steps_per_split = pl.chunks_per_split; a.groups = GF;
+    a.dst_gs = fwd ? pb.y_gs : pb.x_gs; a.part_gs = (int64_t)(pl.part_bytes / 4);
+    a.w = w; a.src = act; a.w_gs = pb.w_gs; a.src_gs = fwd ? pb.x_gs : pb.y_gs;
+    a.src_bs = (int)q.src_bs; a.LH = q.LH; a.LW = q.LW; a.add = fwd ? -pb.pad : pb.pad;
+    a.Cg = Cr; a.C = pb.C; a.transposed = q.transposed;
+    a.epi_on = ep && GF == 1;
+    a.epi = ep ? *ep : Epilogue{};
+    *ep_applied = a.epi_on;
+    a.div_plane = make_fastdiv((uint32_t)(a.OH * a.OW));
+    a.div_ow = make_fastdiv((uint32_t)a.OW);
+    a.div_rs = make_fastdiv((uint32_t)RS);
+    a.div_s = make_fastdiv((uint32_t)pb.S);
+    a.tiles_per_xcd = ceil_div(a.mtiles * a.ntiles * a.ksplit * GF, 8);
+    const int grid = 8 * a.tiles_per_xcd, lds = 3 * (pl.sp_bm + pl.sp_bn) * 96;
+    auto go = [&](auto kern) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
+    };
+    if (pl.sp_bm == 128 && pl.sp_bn == 256) go(colgemm_split_kernel<2, 2, 2, 4>);
+    else if (pl.sp_bm == 128 && pl.sp_bn == 192) go(colgemm_split_kernel<1, 3, 4, 2>);
+    else if (pl.sp_bm == 128) go(colgemm_split_kernel<2, 1, 2, 4>);
+    else if (pl.sp_bm == 96) go(colgemm_split_kernel<3, 1, 1, 8>);
+    else if (pl.sp_bm == 64) go(colgemm_split_kernel<2, 1, 1, 8>);
+    else go(colgemm_split_kernel<1, 2, 1, 8>);
+    rc = check_launch();
+    if (rc != kStatusOk || a.ksplit == 1) return rc;
+    const int per_sample = a.M * a.OH * a.OW;
+    for (int gc = 0; gc < GF; ++gc)
+        hipLaunchKernelGGL(reduce_split_outputs<float>, dim3(2048), dim3(256), 0, st, a.part + gc * a.part_gs,
+                           a.dst + gc * a.dst_gs, a.ksplit, per_sample, pb.N, a.dst_bs,
+                           make_fastdiv((uint32_t)per_sample), a.epi_on, a.epi, a.div_plane);
     return check_launch();
 }
 
@@ -459,6 +533,9 @@ int run_colgemm_f32out(int op, const void *act, const void *w, void *out, const 
     const bool bf = pb.dtype == kDtypeBf16 && !pl.widen_w;   // bf16 MFMA kernel reads the caller's tensors directly
     int64_t w_bs = (int64_t)pb.K * pb.C * RS;
     if (pl.dma) return run_colgemm_dma(op, act, w, out, pb, pl, ws, st, ep, ep_applied);
+    if (pl.sp)
+        return run_colgemm_split(op, static_cast<const float *>(act), static_cast<const float *>(w),
+                                 static_cast<float *>(out), pb, pl, ws, st, ep, ep_applied);
     if (pl.patch && pb.dtype == kDtypeBf16) {
         const int rc = run_patch_bf16(act, w, out, pb, pl, ws, st, ep, ep_applied);
         if (rc != kNotTaken) return rc;

@@ -163,6 +163,13 @@ struct Plan {
     // the same decomposition for fp32 tensors (any stride up to 4): rows_wp = LDS pitch of a staged input row
     bool rows_f32;
     int rows_wp;
+    // fp32 forward / stride-1 backward-data on the bf16 matrix instruction, operands split into three bfloat16 parts
+    // (colgemm_split_kernel): tile sp_bm x sp_bn, sp_cb blocks of 16 channels per column, zero-padded planes of
+    // sp_hp x sp_wp positions with sp_ph / sp_pw rows / columns of zeros before the data.  The workspace then holds
+    // only the regions below (nsplit, chunks_per_split as above).
+    bool sp;
+    int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad;
+    size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
     size_t total;
 };
 
@@ -185,6 +192,45 @@ inline void pick_dma_tile(int channels, int mtiles, int64_t ncols, TileShape &ti
     }
     if (best_rounds > 1 || channels % 64 != 0) { kc = 32; occ = 2; }
     else { kc = 64; occ = 1; }
+}
+
+// Tile, split count and time estimate (us, returned) of the three-part fp32 kernel for one column of `steps` steps;
+// `groups` columns share the launch.  The split count decides the order of the sums, so it must not depend on how many
+// columns run together: it is chosen for one column, the tile width (which changes no sum) for all of them.
+//   Rows per tile: what pads M least, ties to the taller tile.
+//   Time of a round: steps x matrix time of a tile (six products, 4096 FLOP per clock and CU, about 0.75 of it reached)
+//   plus 3 us for the first loads and the stores, which nothing hides with one work-group per CU.
+//   Splits are powers of two (a coarse grid: small shards of a mini-batch then take the same split and give the same
+//   bits), of at least 12 steps.  A split adds the launch that sums the partial outputs and their traffic (about 4.5 MB per us).
+inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &bm, int &bn, int &ksplit)
+{
+    const int rows[4] = {128, 96, 64, 32};
+    bm = rows[0];
+    for (int i = 1; i < 4; ++i)
+        if (round_up(M, rows[i]) < round_up(M, bm)) bm = rows[i];
+    const int64_t mtiles = ceil_div(M, bm);
+    const double out_mb = (double)ncols * M * 4.0 / 1e6;
+    // best width for a split count: its time, rounds of 256 work-groups
+    auto best_width = [&](int ks, int cols, int &width) {
+        const int sps = ceil_div(steps, ks);
+        double best = 1e30;
+        for (int w : {512, 256, 192, 128}) {
+            if ((w == 512) != (bm == 32) || (w < 256 && bm != 128)) continue;
+            const int64_t units = mtiles * ((ncols + w - 1) / w) * ceil_div(steps, sps) * cols;
+            const double us = (double)((units + 255) / 256) * (sps * (double)bm * w * 16 * 12 / 4096.0 / 0.75 / 2200.0 + 3.0);
+            if (us < best) { best = us; width = w; }
+        }
+        return best;
+    };
+    double best = 1e30;
+    ksplit = 1;
+    for (int ks = 1; ks <= 8 && (ks == 1 || steps / ks >= 12); ks *= 2) {
+        double us = best_width(ks, 1, bn);
+        if (ks > 1) us += 5.0 + (ks + 1) * out_mb / 4.5;
+        if (us < best * 0.97) { best = us; ksplit = ceil_div(steps, ceil_div(steps, ks)); }
+    }
+    best_width(ksplit, groups, bn);
+    return best;
 }
 
 inline Plan make_plan(int op, const Problem &pb)
@@ -229,6 +275,7 @@ inline Plan make_plan(int op, const Problem &pb)
     pl.kc = kChunk;
     pl.nsplit = 1;
     pl.chunks_per_split = 0;
+    double fp32_us = 0;                            // forward / backward-data: estimated time of one column in fp32
     size_t off = 0;
     pl.tab_off = off; pl.tab_bytes = (size_t)pl.tab_len * 16; off += round_up64(pl.tab_bytes, 256);
     if (op == kOpBwdFilter) {
@@ -319,28 +366,31 @@ inline Plan make_plan(int op, const Problem &pb)
         const int OH = op == kOpFwd ? pb.P : pb.H, OW = op == kOpFwd ? pb.Q : pb.W;
         if (Cr % kChunk == 0 && (op == kOpFwd || pb.stride == 1) && !pl.dma) {
             const int64_t ncols = (int64_t)pb.N * OH * OW;
-            const int tiles = (pl.Mpad / pl.tile.bm()) * (int)((ncols + pl.tile.bn() - 1) / pl.tile.bn()) * GF;
-            const double out_mb = (double)ncols * pl.M * 4.0 * GF / 1e6;
             // measured fraction of the MFMA rate a CU reaches with c resident work-groups
             const double eff16[5] = {1.0, 0.71, 0.83, 0.87, 0.88};
+            // time of `cols` columns in one launch, and the split that gives it
             // (32-deep steps were measured too: no faster at two work-groups per CU, so steps stay 16 deep)
-            double best = 1e30;
-            for (int kc = kChunk; kc <= kChunk; kc *= 2) {
-                const int steps = (Cr / kc) * RS;
-                const double step_us = pl.tile.bm() * pl.tile.bn() * 2.0 * kc / 64.0 / 4.0 / 2100.0;   // MFMA time
+            auto best_split = [&](int cols, int &nsplit, int &per_split) {
+                const int tiles = (pl.Mpad / pl.tile.bm()) * (int)((ncols + pl.tile.bn() - 1) / pl.tile.bn()) * cols;
+                const double out_mb = (double)ncols * pl.M * 4.0 * cols / 1e6;
+                const int steps = (Cr / kChunk) * RS;
+                const double step_us = pl.tile.bm() * pl.tile.bn() * 2.0 * kChunk / 64.0 / 4.0 / 2100.0;   // MFMA time
+                double best = 1e30;
                 for (int ks = 1; ks <= 4; ++ks) {
-                    if (steps * kc / ks < 256) break;
+                    if (steps * kChunk / ks < 256) break;
                     const int sps = ceil_div(steps, ks);
                     const int units = tiles * ceil_div(steps, sps);
                     const int per_cu = ceil_div(ceil_div(units, 8), 32);
                     const int resident = per_cu < 4 ? per_cu : 4;
                     double us = per_cu * sps * step_us / eff16[resident];
                     if (ks > 1) us += 5.0 + (ks + 1) * out_mb / 4.5;      // launch + partial traffic at ~4.5 MB/us
-                    if (us < best * 0.97) {
-                        best = us; pl.kc = kc; pl.nsplit = ceil_div(steps, sps); pl.chunks_per_split = sps;
-                    }
+                    if (us < best * 0.97) { best = us; nsplit = ceil_div(steps, sps); per_split = sps; }
                 }
-            }
+                return best;
+            };
+            int ns1, ps1;
+            fp32_us = best_split(1, ns1, ps1);
+            best_split(GF, pl.nsplit, pl.chunks_per_split);
             if (pl.nsplit > 1) {
                 pl.part_off = off;
                 pl.part_bytes = (size_t)pl.nsplit * ncols * pl.M * 4;
@@ -399,6 +449,46 @@ inline Plan make_plan(int op, const Problem &pb)
         pl.cvt_off[1] = off; pl.cvt_bytes[1] = need1 ? (size_t)b * 4 : 0; off += round_up64(pl.cvt_bytes[1], 256);
     }
     pl.total = off;
+
+    // fp32 forward / stride-1 backward-data through the bf16 matrix instruction, where that is estimated to be faster
+    // than the fp32 kernels: it needs a pass over the input (4 bytes read, 6 written per padded position and channel)
+    // that layers with little work per input element do not earn back.  The estimate is per column, so that a grouped
+    // layer takes the route its columns would take alone.
+    if (pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride == 1)) && Cr >= 16) {
+        const bool fwd = op == kOpFwd;
+        const int GF = pl.fused_groups ? G : 1;
+        const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W, mul = fwd ? pb.stride : 1;
+        pl.sp_ph = fwd ? pb.pad : pb.R - 1 - pb.pad;
+        pl.sp_pw = fwd ? pb.pad : pb.S - 1 - pb.pad;
+        const int64_t hp = (int64_t)(OH - 1) * mul + pb.R, wp = (int64_t)(OW - 1) * mul + pb.S;
+        const int cb = ceil_div(Cr, 16);
+        const int64_t ncols = (int64_t)pb.N * OH * OW;
+        const int steps = cb * RS;
+        int bm, bn, ks;
+        double us = pick_split_tile(pl.M, ncols, steps, GF, bm, bn, ks);
+        us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 4.5e6;
+        // the few-channel kernel reaches about 90 TFLOP/s on its padded rows, at 1 us or more per 16-deep step; the
+        // tap-table kernel 55 and 1.7 us
+        const double gflop = 2.0 * ncols * Cr * RS / 1e9;          // per row
+        if (pl.patch)
+            fp32_us = std::max(gflop * round_up(pl.M, 32) / 90.0 * 1e3, 1.0 * ceil_div(Cr * RS, kChunk)) + 3.0;
+        else if (Cr % kChunk != 0)
+            fp32_us = std::max(gflop * pl.M / 55.0 * 1e3, 1.7 * ceil_div(Cr * RS, kChunk));
+        const int mpad = round_up(pl.M, bm);
+        const int64_t x_bytes = (int64_t)pb.N * GF * cb * hp * wp * 96, w_bytes = (int64_t)GF * steps * mpad * 96;
+        const int64_t limit = (int64_t)1 << 32;      // 32-bit byte offsets
+        if (us * 1.1 < fp32_us && pl.sp_ph >= 0 && pl.sp_pw >= 0 && x_bytes < limit && w_bytes < limit / 2) {
+            pl.sp = true;
+            pl.sp_bm = bm; pl.sp_bn = bn; pl.sp_cb = cb; pl.sp_hp = (int)hp; pl.sp_wp = (int)wp; pl.sp_mpad = mpad;
+            pl.chunks_per_split = ceil_div(steps, ks);
+            pl.nsplit = ceil_div(steps, pl.chunks_per_split);
+            pl.sp_w_off = 0; pl.sp_w_bytes = (size_t)w_bytes;
+            pl.sp_x_off = round_up64(w_bytes, 256); pl.sp_x_bytes = (size_t)x_bytes;
+            pl.part_off = pl.sp_x_off + round_up64(x_bytes, 256);
+            pl.part_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * ncols * pl.M * 4 : 0;
+            pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
+        }
+    }
     return pl;
 }
 

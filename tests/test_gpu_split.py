@@ -1,0 +1,89 @@
+"""fp32 passes whose operands are split into three bfloat16 parts, at the edges of their tiles and of their value range,
+against the CPU oracle.
+
+Error bound, element by element, for a sum of L products: the products left out are at most 3 * 2^-24 of |x w| each, the
+sum of the leading products is rounded once per 16 products and split range (2^-24 of a partial sum that |x| * |w| summed
+bounds), and the 16 products of an instruction are aligned to the largest of them, at most 2^-24 of it lost per product:
+    |err| <= (L / 16 + 24) * 2^-24 * sum |x w|
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1312_5853_amd import binding as hp
+from paper_1312_5853_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def nan_like(shape):
+    return torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+
+
+def within(got, ref, absref, length):
+    bound = (length / 16.0 + 24.0) * 2.0 ** -24 * absref
+    err = np.abs(got.cpu().numpy().astype(np.float64) - ref)
+    assert np.isfinite(err).all() and (err <= bound).all(), float((err / np.maximum(bound, 1e-300)).max())
+
+
+# N, C, H, W, K, R, stride, pad: rows 1 above and at a tile height (32, 64, 96, 128), a column more and less than a
+# tile (256, 512), channel counts that are no multiple of 16, one position, split reductions (few columns), an even
+# filter, padding beyond half the filter
+SHAPES = [
+    (16, 64, 16, 16, 128, 3, 1, 1),
+    (1, 128, 16, 17, 129, 3, 1, 1),
+    (7, 96, 13, 13, 97, 3, 1, 1),
+    (3, 65, 15, 17, 64, 3, 1, 1),
+    (5, 64, 21, 21, 33, 3, 1, 1),
+    (9, 32, 31, 33, 32, 5, 1, 2),
+    (1, 256, 1, 1, 160, 1, 1, 0),
+    (2, 384, 13, 13, 384, 3, 1, 1),
+    (2, 112, 12, 10, 100, 4, 1, 3),
+    (4, 100, 24, 19, 200, 7, 2, 3),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_split_passes_stay_within_the_error_bound(shape):
+    N, C, H, W, K, R, st, pad = shape
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    x, w, dy = synth.gaussian((N, C, H, W), 901), synth.gaussian((K, C, R, R), 902, 0.01), synth.gaussian((N, K, P, Q), 903)
+    ax, aw, ady = np.abs(x), np.abs(w), np.abs(dy)
+    xd, wd, dyd = dev(x), dev(w), dev(dy)
+    y = hp.conv_fwd(xd, wd, st, pad, y=nan_like((N, K, P, Q)))
+    within(y, oracle.conv_fwd(x, w, st, pad), oracle.conv_fwd(ax, aw, st, pad), C * R * R)
+    if st == 1:
+        dx = hp.conv_bwd_data(dyd, wd, H, W, st, pad, dx=nan_like((N, C, H, W)))
+        within(dx, oracle.conv_bwd_data(dy, w, H, W, st, pad), oracle.conv_bwd_data(ady, aw, H, W, st, pad), K * R * R)
+
+
+def same_pattern(got, ref):
+    """Where the 64-bit result, as fp32, is infinite or NaN; the rest close to it."""
+    g, r = got.cpu().numpy(), ref.astype(np.float32)
+    assert np.array_equal(np.isnan(g), np.isnan(r)) and np.array_equal(np.isinf(g), np.isinf(r))
+    assert np.array_equal(g[np.isinf(r)], r[np.isinf(r)])
+    fin = np.isfinite(r)
+    assert np.abs(g[fin].astype(np.float64) - ref[fin]).max() <= 1e-5 * max(np.abs(ref[fin]).max(), 1e-300)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, -3.4e38])
+def test_split_passes_give_infinities_and_nan_as_fp32_does(value):
+    # one such value in a mini-batch: the windows that read it, and only they, show it.  It meets positive filters, so
+    # that no infinity of the other sign and no zero arises beside it.
+    x, w = synth.gaussian((3, 64, 13, 13), 911), np.abs(synth.gaussian((64, 64, 3, 3), 912)) + np.float32(0.5)
+    x[1, 37, 6, 12] = value
+    with np.errstate(all="ignore"):
+        same_pattern(hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1))
+        same_pattern(hp.conv_bwd_data(dev(x), dev(w), 13, 13, 1, 1), oracle.conv_bwd_data(x, w, 13, 13, 1, 1))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-34, 1e-37])
+def test_split_passes_keep_fp32_precision_for_tiny_values(scale):
+    x, w = synth.gaussian((3, 64, 13, 13), 921) * np.float32(scale), synth.gaussian((64, 64, 3, 3), 922)
+    y, ref = hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1)
+    assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 576 * 2.0 ** -24 * oracle.conv_fwd(np.abs(x), np.abs(w), 1, 1).max()
