@@ -43,6 +43,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 #include "conv_colgemm_kernels.h"
 #include "conv_bf16_dma_kernels.h"
 #include "conv_split_kernels.h"
+#include "conv_wgrad_split_kernels.h"
 #include "conv_wgrad_rows_kernels.h"
 #include "conv_wgrad_kernels.h"
 #include "fc_kernels.h"
@@ -396,6 +397,43 @@ int launch_finish_wgrad(const float *part, float *dw, int K, int C, int RS, int 
     return check_launch();
 }
 
+// fp32 backward-filter in three bfloat16 parts (wgrad_split_kernel); groups columns in one launch
+int run_wgrad_split(const float *x, const float *dy, float *dw, const Problem &pb, const Plan &pl, void *ws, hipStream_t st)
+{
+    const int GF = pl.fused_groups ? pb.groups : 1;
+    WgradSplitArgs a;
+    a.dy = dy; a.x = x; a.part = reinterpret_cast<float *>(static_cast<char *>(ws) + pl.part_off);
+    a.K = pb.K; a.C = pb.C; a.S = pb.S; a.CB = pl.sp_cb; a.ncols = pl.Kg; a.nblocks = pb.R * pb.S * pl.sp_cb;
+    a.P = pb.P; a.Q = pb.Q; a.H = pb.H; a.W = pb.W; a.stride = pb.stride; a.pad = pb.pad;
+    a.dy_bs = (int)pb.y_bs; a.x_bs = (int)pb.x_bs;
+    a.J = pb.N * pb.P * pb.Q; a.steps_per_split = pl.chunks_per_split / 2;
+    a.mtiles = ceil_div(pb.K, pl.sp_bm); a.ntiles = ceil_div(a.nblocks * 16, pl.sp_bn);
+    a.nsplit = pl.nsplit;
+    a.nunits = a.mtiles * a.ntiles * a.nsplit * GF;
+    a.units_per_xcd = ceil_div(a.nunits, 8);
+    a.dy_bytes = (unsigned)(((int64_t)(pb.N - 1) * pb.y_bs + (int64_t)pb.K * pb.P * pb.Q) * 4);
+    a.x_bytes = (unsigned)(((int64_t)(pb.N - 1) * pb.x_bs + (int64_t)pb.C * pb.H * pb.W) * 4);
+    a.dy_gs = pb.y_gs; a.x_gs = pb.x_gs; a.part_gs = (int64_t)(pl.part_bytes / 4);
+    a.div_plane = make_fastdiv((uint32_t)(pb.P * pb.Q));
+    a.div_q = make_fastdiv((uint32_t)pb.Q);
+    a.div_cb = make_fastdiv((uint32_t)a.CB);
+    a.div_s = make_fastdiv((uint32_t)pb.S);
+    const int grid = 8 * a.units_per_xcd, lds = 2 * (pl.sp_bm + pl.sp_bn) * 192;
+    const bool tail = pb.K % 16 != 0 || pb.C % 16 != 0;
+    auto go = [&](auto whole, auto ragged) {
+        auto kern = tail ? ragged : whole;
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
+    };
+    if (pl.sp_bm == 128) go(wgrad_split_kernel<2, 2, 2, 4, false>, wgrad_split_kernel<2, 2, 2, 4, true>);
+    else if (pl.sp_bm == 96) go(wgrad_split_kernel<3, 1, 1, 8, false>, wgrad_split_kernel<3, 1, 1, 8, true>);
+    else if (pl.sp_bm == 64) go(wgrad_split_kernel<2, 1, 1, 8, false>, wgrad_split_kernel<2, 1, 1, 8, true>);
+    else go(wgrad_split_kernel<1, 1, 1, 8, false>, wgrad_split_kernel<1, 1, 1, 8, true>);
+    const int rc = check_launch();
+    if (rc != kStatusOk) return rc;
+    return launch_finish_wgrad(a.part, dw, pb.K, pb.C, pb.R * pb.S, pl.nsplit, GF, st);
+}
+
 template <typename TI>
 void launch_wgrad_typed(const TileShape &t, const WgradArgs &a, int grid, hipStream_t st)
 {
@@ -705,6 +743,9 @@ int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb,
     const int RS = pb.R * pb.S;
     // bf16 MFMA kernel: reads the caller's bf16 tensors directly (128-column tiles only)
     const bool bf = pb.dtype == kDtypeBf16 && !pl.widen && pb.C % kChunk == 0;     // bf16 MFMA kernel
+    if (pl.sp)
+        return run_wgrad_split(static_cast<const float *>(x), static_cast<const float *>(dy), static_cast<float *>(dw), pb,
+                               pl, ws, st);
     if (pl.lin) {
         // same-extent stride-1 layer: pack both tensors, then every operand is a 16-byte load
         unsigned short *dyp = reinterpret_cast<unsigned short *>(wsb + pl.lin_dy_off);

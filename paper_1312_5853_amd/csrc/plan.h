@@ -233,6 +233,34 @@ inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &
     return best;
 }
 
+constexpr int64_t kWgradPartLimit = (int64_t)48 << 20;    // bytes of partial sums: what the library's own scratch holds
+
+// Row tile, split count and time estimate (us, returned) of the three-part fp32 backward-filter kernel: `nblocks` blocks
+// of 16 columns, J positions, `groups` columns in one launch.  One work-group per CU and step of 32 positions: the matrix
+// time of a BM x 256 tile (six products), about 0.7 of it reached, and 4 us a round for what nothing hides.  Splits that
+// fill one to four rounds of 256 work-groups, of at least four steps; their partial sums are written and read once.
+inline double pick_wgrad_split(int K, int nblocks, int64_t J, int groups, int64_t out_bytes, int &bm, int &ksplit)
+{
+    const int rows[4] = {128, 96, 64, 32};
+    bm = rows[0];
+    for (int i = 1; i < 4; ++i)
+        if (round_up(K, rows[i]) < round_up(K, bm)) bm = rows[i];
+    const int steps = (int)((J + 31) / 32);
+    const int64_t tiles = (int64_t)ceil_div(K, bm) * ceil_div(nblocks, 16);
+    const double step_us = (double)bm * 256 * 32 * 12 / 4096.0 / 0.7 / 2100.0;
+    double best = 1e30;
+    ksplit = 1;
+    for (int r = 1; r <= 4; ++r) {
+        int64_t ks = std::min<int64_t>(256 * r / (tiles * groups), steps / 4);
+        ks = std::max<int64_t>(1, std::min<int64_t>(ks, kWgradPartLimit / (out_bytes * groups)));
+        const int sps = ceil_div(steps, (int)ks), n = ceil_div(steps, sps);
+        const double us = (double)((tiles * n * groups + 255) / 256) * (sps * step_us + 4.0) +
+                          (2.0 * n + 1.0) * groups * out_bytes / 4.5e6;
+        if (us < best * 0.97) { best = us; ksplit = n; }
+    }
+    return best;
+}
+
 inline Plan make_plan(int op, const Problem &pb)
 {
     Plan pl = {};
@@ -487,6 +515,33 @@ inline Plan make_plan(int op, const Problem &pb)
             pl.part_off = pl.sp_x_off + round_up64(x_bytes, 256);
             pl.part_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * ncols * pl.M * 4 : 0;
             pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
+        }
+    }
+    // fp32 backward-filter through the bf16 matrix instruction, where that is estimated to be faster than the fp32 kernels
+    // (few-channel layers pad 16 / C times) and its partial sums fit where theirs do.
+    if (pb.dtype == kDtypeF32 && op == kOpBwdFilter && pb.K >= 8 && pb.C >= 8 &&
+        std::max((int64_t)pb.H * pb.W, (int64_t)pb.P * pb.Q) * 32 < kMaxSpanBytes) {
+        const int GF = pl.fused_groups ? G : 1;
+        const int64_t J = (int64_t)pb.N * pb.P * pb.Q, out_bytes = (int64_t)pb.K * pl.Kg * 4;
+        const int cb = ceil_div(pb.C, 16);
+        // fp32 kernels: matrix time of their 16-deep steps, of which the staged kernel reaches about 0.8 with two
+        // work-groups per CU, the tap-table kernel 0.5 (and two launches more); few-channel rows 104 TFLOP/s
+        const double step_us = pl.tile.bm() * (double)pl.tile.bn() * 32.0 / 256.0 / 2100.0;
+        const int64_t units = (int64_t)(pl.Mpad / pl.tile.bm()) * ceil_div(pl.Kg, pl.tile.bn()) * pl.nsplit * GF;
+        fp32_us = (double)((units + 255) / 256) * pl.chunks_per_split * step_us / (pb.C % kChunk == 0 ? 0.8 : 0.5) + 4.0 +
+                  (2.0 * pl.nsplit + 1.0) * GF * out_bytes / 4.5e6 + (pb.C % kChunk == 0 ? 0.0 : 4.0);
+        if (pl.rows_f32) fp32_us = 2.0 * J * pb.K * pl.Kg / 104e6;
+        int bm, ks;
+        const double us = pick_wgrad_split(pb.K, RS * cb, J, GF, out_bytes, bm, ks);
+        const int64_t part = (int64_t)ks * out_bytes;
+        const int steps = (int)((J + 31) / 32);
+        if (us * 1.05 < fp32_us && (part * GF <= kWgradPartLimit || part * GF <= (int64_t)pl.total)) {
+            pl.sp = true;
+            pl.sp_bm = bm; pl.sp_bn = 256; pl.sp_cb = cb;
+            pl.chunks_per_split = 2 * ceil_div(steps, ks);       // chunks of 16 positions, two to a step
+            pl.nsplit = ceil_div(2 * steps, pl.chunks_per_split);
+            pl.part_off = 0; pl.part_bytes = (size_t)pl.nsplit * out_bytes;
+            pl.total = round_up64(pl.part_bytes * GF, 256);
         }
     }
     return pl;

@@ -87,3 +87,54 @@ def test_split_passes_keep_fp32_precision_for_tiny_values(scale):
     x, w = synth.gaussian((3, 64, 13, 13), 921) * np.float32(scale), synth.gaussian((64, 64, 3, 3), 922)
     y, ref = hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1)
     assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 576 * 2.0 ** -24 * oracle.conv_fwd(np.abs(x), np.abs(w), 1, 1).max()
+
+
+# Backward-filter: rows at and above the tile heights, filter and channel counts that are no multiple of 16, fewer than 32
+# positions in a split's last step, strides 2 and 3 with windows that leave input rows unread, padding, an even filter,
+# two row tiles, columns past the last block of a tile
+WGRAD_SHAPES = [
+    (16, 64, 16, 16, 128, 3, 1, 1),
+    (3, 16, 16, 17, 129, 3, 1, 1),
+    (5, 65, 15, 17, 64, 3, 1, 1),
+    (9, 32, 31, 33, 33, 5, 1, 2),
+    (24, 40, 31, 45, 72, 3, 2, 1),
+    (6, 9, 30, 31, 10, 3, 3, 0),
+    (37, 48, 11, 9, 96, 4, 1, 2),
+    (33, 128, 13, 13, 144, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("shape", WGRAD_SHAPES)
+def test_split_backward_filter_stays_within_the_error_bound(shape):
+    N, C, H, W, K, R, st, pad = shape
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    x, dy = synth.gaussian((N, C, H, W), 904), synth.gaussian((N, K, P, Q), 905)
+    dw = hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad, dw=nan_like((K, C, R, R)))
+    within(dw, oracle.conv_bwd_filter(x, dy, R, R, st, pad),
+           oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad), N * P * Q)
+
+
+def test_split_backward_filter_of_two_columns_equals_the_columns_alone():
+    N, C, K, R = 6, 96, 256, 5
+    x, dy = synth.gaussian((N, C, 27, 27), 906), synth.gaussian((N, K, 27, 27), 907)
+    dw = hp.conv_bwd_filter_grouped(dev(x), dev(dy), R, R, 1, 2, 2, dw=nan_like((K, C // 2, R, R)))
+    for g in range(2):
+        xs, ys = x[:, 48 * g:48 * g + 48], dy[:, 128 * g:128 * g + 128]
+        within(dw[128 * g:128 * g + 128], oracle.conv_bwd_filter(xs, ys, R, R, 1, 2),
+               oracle.conv_bwd_filter(np.abs(xs), np.abs(ys), R, R, 1, 2), N * 27 * 27)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, -3.4e38])
+def test_split_backward_filter_gives_infinities_and_nan_as_fp32_does(value):
+    x, dy = synth.gaussian((16, 64, 16, 16), 913), np.abs(synth.gaussian((16, 64, 16, 16), 914)) + np.float32(0.5)
+    x[1, 37, 6, 15] = value
+    with np.errstate(all="ignore"):
+        same_pattern(hp.conv_bwd_filter(dev(x), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(x, dy, 3, 3, 1, 1))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-37])
+def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale):
+    x, dy = synth.gaussian((16, 64, 16, 16), 922), synth.gaussian((16, 64, 16, 16), 923) * np.float32(scale)
+    dw, ref = hp.conv_bwd_filter(dev(x), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(x, dy, 3, 3, 1, 1)
+    top = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), 3, 3, 1, 1).max()
+    assert np.abs(dw.cpu().numpy().astype(np.float64) - ref).max() <= 4096 * 2.0 ** -24 * top
