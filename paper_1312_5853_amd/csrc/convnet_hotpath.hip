@@ -1398,12 +1398,17 @@ static int run_fc(int op, const void *a, const void *b, void *out, const void *b
     g.mtiles = pl.mtiles; g.ntiles = pl.ntiles; g.ksplit = pl.ksplit; g.steps_per_split = pl.steps_per_split;
     g.bias = static_cast<const float *>(bias); g.relu = relu;
     const dim3 grid(pl.mtiles * pl.ntiles * pl.ksplit), block(kThreads);
-    if (pl.at) hipLaunchKernelGGL((fc_gemm_kernel<true, true>), grid, block, 0, st, g);
+    // 32-bit byte offsets: tensors of 2^31 bytes and more stay on the fp32 kernel
+    const bool split = (int64_t)std::max(N, O) * I < ((int64_t)1 << 29) && (int64_t)N * O < ((int64_t)1 << 29);
+    if (split && pl.at) hipLaunchKernelGGL((fc_split_kernel<true, true>), grid, block, 0, st, g);
+    else if (split && pl.bt) hipLaunchKernelGGL((fc_split_kernel<false, true>), grid, block, 0, st, g);
+    else if (split) hipLaunchKernelGGL((fc_split_kernel<false, false>), grid, block, 0, st, g);
+    else if (pl.at) hipLaunchKernelGGL((fc_gemm_kernel<true, true>), grid, block, 0, st, g);
     else if (pl.bt) hipLaunchKernelGGL((fc_gemm_kernel<false, true>), grid, block, 0, st, g);
     else hipLaunchKernelGGL((fc_gemm_kernel<false, false>), grid, block, 0, st, g);
     rc = check_launch();
     if (rc != kStatusOk || pl.ksplit == 1) return rc;
-    hipLaunchKernelGGL(fc_reduce_kernel, dim3(std::min<int64_t>(2048, ((int64_t)pl.M * pl.Nc + 255) / 256)), dim3(256),
+    hipLaunchKernelGGL(fc_reduce_kernel, dim3(std::min<int64_t>(2048, ((int64_t)pl.M * pl.Nc / 4 + 255) / 256)), dim3(256),
                        0, st, g.part, g.D, pl.ksplit, pl.M, pl.Nc, pl.ldd, g.bias, relu);
     return check_launch();
 }

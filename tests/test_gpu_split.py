@@ -138,3 +138,32 @@ def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale):
     dw, ref = hp.conv_bwd_filter(dev(x), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(x, dy, 3, 3, 1, 1)
     top = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), 3, 3, 1, 1).max()
     assert np.abs(dw.cpu().numpy().astype(np.float64) - ref).max() <= 4096 * 2.0 ** -24 * top
+
+
+# Fully connected: a column or row more and less than a tile, reductions that end inside a step or a split range, one sample
+@pytest.mark.parametrize("N,I,O", [(1, 36, 20), (5, 132, 124), (127, 260, 132), (129, 1000, 128), (33, 4100, 68)])
+def test_split_fully_connected_stays_within_the_error_bound(N, I, O):
+    x, w, dy = synth.gaussian((N, I), 931), synth.gaussian((O, I), 932, 0.01), synth.gaussian((N, O), 933)
+    ax, aw, ady = np.abs(x), np.abs(w), np.abs(dy)
+    within(hp.fc_fwd(dev(x), dev(w), y=nan_like((N, O))), oracle.fc_fwd(x, w), oracle.fc_fwd(ax, aw), I)
+    within(hp.fc_bwd_data(dev(dy), dev(w), dx=nan_like((N, I))), oracle.fc_bwd_data(dy, w), oracle.fc_bwd_data(ady, aw), O)
+    within(hp.fc_bwd_filter(dev(x), dev(dy), dw=nan_like((O, I))), oracle.fc_bwd_filter(x, dy),
+           oracle.fc_bwd_filter(ax, ady), N)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, -3.4e38])
+def test_split_fully_connected_gives_infinities_and_nan_as_fp32_does(value):
+    x, w = synth.gaussian((9, 260), 934), np.abs(synth.gaussian((132, 260), 935)) + np.float32(0.5)
+    x[3, 259] = value
+    with np.errstate(all="ignore"):
+        same_pattern(hp.fc_fwd(dev(x), dev(w)), oracle.fc_fwd(x, w))
+        wt = np.ascontiguousarray(w.T)                                      # a reduction over 260 outputs
+        same_pattern(hp.fc_bwd_data(dev(x), dev(wt)), oracle.fc_bwd_data(x, wt))
+        dy = np.abs(synth.gaussian((9, 132), 936)) + np.float32(0.5)
+        same_pattern(hp.fc_bwd_filter(dev(x), dev(dy)), oracle.fc_bwd_filter(x, dy))
+
+
+def test_split_fully_connected_keeps_fp32_precision_for_tiny_values():
+    x, w = synth.gaussian((9, 260), 937) * np.float32(1e-36), synth.gaussian((132, 260), 938)
+    y, ref = hp.fc_fwd(dev(x), dev(w)), oracle.fc_fwd(x, w)
+    assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 260 * 2.0 ** -24 * oracle.fc_fwd(np.abs(x), np.abs(w)).max()
