@@ -150,28 +150,47 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 // has been read, so the barrier that frees its buffer comes here; m h', m m' cover the barrier and the reads of the next
 // step's h and h' (each into the registers that held this step's).
 // ---------------------------------------------------------------------------
+// A strided backward-data is one launch over stride x stride residue classes of (h + pad, w + pad): class (a, b) meets only the
+// taps r = a, a + stride, ... and s = b, b + stride, ..., and over its own grid of positions it is a stride-1 pass over dy.
+// (24 x 40 x 31 x 45, 72 filters 3x3 stride 2, whole call:
+// 95 us with all taps and masks in fp32 -> 26 us.)  Forward and stride-1
+// backward-data are the one-class case.
+constexpr int kMaxClasses = 16;
+struct SplitClass {
+    int R, S;                  // taps
+    int OH, OW, ncols;         // grid of positions, over all samples
+    int ty, tx;                // sign -1: tap (r, s) of grid position (oh, ow) reads padded (oh + ty - r, ow + tx - s)
+    int add_h, add_w;          // position (0, 0) reads src row add_h, column add_w under tap (0, 0)
+    int tap0;                  // filter tap of (0, 0)
+    int h0, w0;                // output row, column of grid position (0, 0)
+    int first, ntiles, steps_per_split;      // first unit of the class, column tiles
+    FastDiv div_plane, div_ow, div_rs, div_s;
+};
+
 struct ColGemmSplitArgs {
     const void *At;            // wt (see above)
     const void *xs;            // split, blocked, padded activations
     float *dst;                // y or dx
     float *part;               // ksplit > 1: partial outputs [ksplit][N][M][OH*OW] per column
-    int M, Mpad, ncols;
-    int OH, OW, mul;
+    int M, Mpad;
+    int mul;                   // input rows (columns) between grid positions
+    int out_w, out_plane, out_step;          // output row and plane; rows (columns) between grid positions
+    int tap_r, tap_s, RS;      // filter taps between rows, columns of a class's taps; taps of a filter
     int Wp;
     unsigned plane_bytes;      // one part of one channel block: Hp * Wp * 32
     unsigned n_bytes;          // one sample: channel blocks of all columns * 3 * plane_bytes
-    int R, S, sign;            // sign +1: tap (r, s) reads padded (oh*mul + r, ow*mul + s); -1: (oh + R-1-r, ow + S-1-s)
+    int N, sign;               // sign +1: tap (r, s) reads padded (oh*mul + r, ow*mul + s); -1: see SplitClass
     int cblocks;               // channel blocks per column
     int dst_bs;
-    int mtiles, ntiles, tiles_per_xcd, ksplit, steps_per_split, groups;
+    int mtiles, tiles_per_xcd, ksplit, groups, nclass, units;      // units: of one column of a grouped layer
     int64_t dst_gs, part_gs;   // floats between the columns
     // the fp32 tensors, for a tile that has to be computed in fp32
     const float *w, *src;
     int64_t w_gs, src_gs;
-    int src_bs, LH, LW, add, Cg, C, transposed;
+    int src_bs, LH, LW, Cg, C, transposed;
     int epi_on;
     Epilogue epi;
-    FastDiv div_plane, div_ow, div_rs, div_s;
+    SplitClass cls[kMaxClasses];
 };
 
 template <int TM, int TN, int WM, int WN>
@@ -193,10 +212,14 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
     const int bid = blockIdx.x;
     const int idx = bid >> 3;
     const int unit = (bid & 7) * p.tiles_per_xcd + idx;
-    const int ntile = p.mtiles * p.ntiles;
-    if (idx >= p.tiles_per_xcd || unit >= ntile * p.ksplit * p.groups) return;
-    const int gcol = unit / (ntile * p.ksplit);
-    const int unit_c = unit - gcol * (ntile * p.ksplit);
+    if (idx >= p.tiles_per_xcd || unit >= p.units * p.groups) return;
+    const int gcol = unit / p.units;
+    int unit_c = unit - gcol * p.units;
+    int ci = 0;
+    while (ci + 1 < p.nclass && unit_c >= p.cls[ci + 1].first) ++ci;
+    const SplitClass &q = p.cls[ci];
+    unit_c -= q.first;
+    const int ntile = p.mtiles * q.ntiles;
     const int ks = unit_c / ntile;
     const int tile = unit_c - ks * ntile;
     const int mt = tile % p.mtiles, nt = tile / p.mtiles;
@@ -211,55 +234,56 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
     bool isa[NL];
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        int q = i * NW + wave;
-        if (q >= QA + QB) q -= NW;                               // repeats this wave's previous load
-        lq[i] = (unsigned)q * 1024u;
-        isa[i] = q < QA;
+        int lb = i * NW + wave;
+        if (lb >= QA + QB) lb -= NW;                             // repeats this wave's previous load
+        lq[i] = (unsigned)lb * 1024u;
+        isa[i] = lb < QA;
         if (isa[i]) {
-            const int c = q / (BM / 32), b = q - c * (BM / 32);
+            const int c = lb / (BM / 32), b = lb - c * (BM / 32);
             voff[i] = (unsigned)((c * p.Mpad + b * 32) * 32 + lane * 16);
         } else {
-            const int qb = q - QA;
+            const int qb = lb - QA;
             const int c = qb / (BN / 32), b = qb - c * (BN / 32);
             const int row = b * 32 + (lane >> 1);
             const int chunk = (lane & 1) ^ ((row >> 3) & 1);
             int j = n0 + row;
-            j = j < p.ncols ? j : 0;                             // columns past the end: computed, never stored
-            const int n = (int)fastdiv((uint32_t)j, p.div_plane);
-            const int rem = j - n * (p.OH * p.OW);
-            const int oh = (int)fastdiv((uint32_t)rem, p.div_ow);
-            const int ow = rem - oh * p.OW;
+            j = j < q.ncols ? j : 0;                             // columns past the end: computed, never stored
+            const int n = (int)fastdiv((uint32_t)j, q.div_plane);
+            const int rem = j - n * (q.OH * q.OW);
+            const int oh = (int)fastdiv((uint32_t)rem, q.div_ow);
+            const int ow = rem - oh * q.OW;
             voff[i] = (unsigned)n * p.n_bytes + (unsigned)c * p.plane_bytes +
                       (unsigned)((oh * p.mul * p.Wp + ow * p.mul) * 32 + chunk * 16);
         }
     }
 
-    const int step_begin = ks * p.steps_per_split;
-    const int nsteps = min(p.cblocks * p.R * p.S - step_begin, p.steps_per_split);
+    const int step_begin = ks * q.steps_per_split;
+    const int nsteps = max(0, min(p.cblocks * q.R * q.S - step_begin, q.steps_per_split));
     const size_t a_step_bytes = (size_t)p.Mpad * 96;
-    const char *a_base = static_cast<const char *>(p.At) +
-                         ((size_t)gcol * p.cblocks * p.R * p.S + step_begin) * a_step_bytes + (size_t)m0 * 32;
+    const char *const a_first = static_cast<const char *>(p.At) +
+                                ((size_t)gcol * p.cblocks * p.RS + q.tap0) * a_step_bytes + (size_t)m0 * 32;
+    const char *a_base = a_first;
     const char *const x_base = static_cast<const char *>(p.xs) + (size_t)gcol * p.cblocks * 3 * p.plane_bytes;
     int r, s, cb;                                                // next step to load
     {
-        cb = (int)fastdiv((uint32_t)step_begin, p.div_rs);
-        const int rs = step_begin - cb * (p.R * p.S);
-        r = (int)fastdiv((uint32_t)rs, p.div_s);
-        s = rs - r * p.S;
+        cb = (int)fastdiv((uint32_t)step_begin, q.div_rs);
+        const int rs = step_begin - cb * (q.R * q.S);
+        r = (int)fastdiv((uint32_t)rs, q.div_s);
+        s = rs - r * q.S;
     }
     const char *xs = nullptr;
     unsigned lbuf = 0;
     auto begin_step_loads = [&](int buf) {
-        const int ar = p.sign > 0 ? r : p.R - 1 - r, as = p.sign > 0 ? s : p.S - 1 - s;
+        const int ar = p.sign > 0 ? r : q.ty - r, as = p.sign > 0 ? s : q.tx - s;
+        a_base = a_first + (size_t)(cb * p.RS + r * p.tap_r + s * p.tap_s) * a_step_bytes;
         xs = x_base + (size_t)cb * 3 * p.plane_bytes + (ar * p.Wp + as) * 32;
         lbuf = lds_base + buf * BUF;
     };
     auto load_one = [&](int i) { dma16(isa[i] ? a_base : xs, voff[i], lbuf + lq[i]); };
     auto end_step_loads = [&]() {
-        a_base += a_step_bytes;
         s += 1;
-        if (s == p.S) { s = 0; r += 1; }
-        if (r == p.R) { r = 0; cb += 1; }
+        if (s == q.S) { s = 0; r += 1; }
+        if (r == q.R) { r = 0; cb += 1; }
     };
     auto load_step = [&](int buf) {
         begin_step_loads(buf);
@@ -380,12 +404,12 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
 #pragma unroll
             for (int jn = 0; jn < TN; ++jn) {
                 int j = n0 + (wn * TN + jn) * 32 + l32;
-                j = j < p.ncols ? j : 0;
-                const int n = (int)fastdiv((uint32_t)j, p.div_plane);
-                const int rem = j - n * (p.OH * p.OW);
-                const int oh = (int)fastdiv((uint32_t)rem, p.div_ow);
-                hb[jn] = oh * p.mul + p.add;
-                wb[jn] = (rem - oh * p.OW) * p.mul + p.add;
+                j = j < q.ncols ? j : 0;
+                const int n = (int)fastdiv((uint32_t)j, q.div_plane);
+                const int rem = j - n * (q.OH * q.OW);
+                const int oh = (int)fastdiv((uint32_t)rem, q.div_ow);
+                hb[jn] = oh * p.mul + q.add_h;
+                wb[jn] = (rem - oh * q.OW) * p.mul + q.add_w;
                 base[jn] = (int64_t)n * p.src_bs;
             }
 #pragma unroll
@@ -396,9 +420,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
                     for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
 #pragma unroll 1
             for (int st = step_begin; st < step_begin + nsteps; ++st) {
-                const int cbk = (int)fastdiv((uint32_t)st, p.div_rs);
-                const int rs = st - cbk * (p.R * p.S);
-                const int rr = (int)fastdiv((uint32_t)rs, p.div_s), ss = rs - rr * p.S;
+                const int cbk = (int)fastdiv((uint32_t)st, q.div_rs);
+                const int rs = st - cbk * (q.R * q.S);
+                const int rr = (int)fastdiv((uint32_t)rs, q.div_s), ss = rs - rr * q.S;
+                const int tap = q.tap0 + rr * p.tap_r + ss * p.tap_s;
 #pragma unroll 1
                 for (int t = 0; t < 8; ++t) {
                     const int ch = cbk * 16 + half * 8 + t;
@@ -406,8 +431,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
                         const bool ok = rowm[i] < p.M && ch < p.Cg;
-                        const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * (p.R * p.S) + rs
-                                                       : ((int64_t)rowm[i] * p.C + ch) * (p.R * p.S) + rs;
+                        const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * p.RS + tap
+                                                       : ((int64_t)rowm[i] * p.C + ch) * p.RS + tap;
                         a[i] = ok ? wg[o] : 0.f;
                     }
 #pragma unroll
@@ -428,14 +453,18 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
 
     float *const dst_c = p.dst + (size_t)gcol * p.dst_gs;
     float *const part_c = p.part + (size_t)gcol * p.part_gs;
-    const int plane = p.OH * p.OW;
+    const int plane = p.out_plane;
 #pragma unroll
     for (int jn = 0; jn < TN; ++jn) {
         const int col = n0 + (wn * TN + jn) * 32 + l32;
-        if (col >= p.ncols) continue;
-        const int n = (int)fastdiv((uint32_t)col, p.div_plane);
-        const int rem = col - n * plane;
-        float *out = p.ksplit > 1 ? part_c + ((size_t)ks * (p.ncols / plane) + n) * ((size_t)p.M * plane) + rem
+        if (col >= q.ncols) continue;
+        const int n = (int)fastdiv((uint32_t)col, q.div_plane);
+        int rem = col - n * (q.OH * q.OW);
+        if (p.out_step > 1) {
+            const int oh = (int)fastdiv((uint32_t)rem, q.div_ow);
+            rem = (oh * p.out_step + q.h0) * p.out_w + (rem - oh * q.OW) * p.out_step + q.w0;
+        }
+        float *out = p.ksplit > 1 ? part_c + ((size_t)ks * p.N + n) * ((size_t)p.M * plane) + rem
                                   : dst_c + (size_t)n * p.dst_bs + rem;
         if (p.epi_on && p.ksplit == 1)            // one column only; split sums get it in reduce_split_outputs
             epi_tile<TM, TN>(p.epi, acc, jn, m0 + wm * TM * 32 + half * 4, p.M, plane,

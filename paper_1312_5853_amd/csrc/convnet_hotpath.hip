@@ -274,28 +274,44 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
 
     ColGemmSplitArgs a;
     a.At = q.wt; a.xs = q.xs; a.dst = out; a.part = reinterpret_cast<float *>(wsb + pl.part_off);
-    a.M = pl.M; a.Mpad = pl.sp_mpad;
-    a.OH = fwd ? pb.P : pb.H; a.OW = fwd ? pb.Q : pb.W; a.mul = fwd ? pb.stride : 1;
-    a.ncols = pb.N * a.OH * a.OW;
+    a.M = pl.M; a.Mpad = pl.sp_mpad; a.N = pb.N;
+    const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W;
+    a.mul = fwd ? pb.stride : 1;
+    a.out_w = OW; a.out_plane = OH * OW; a.out_step = fwd ? 1 : pb.stride;
+    a.RS = RS; a.tap_r = a.out_step * pb.S; a.tap_s = a.out_step;
     a.Wp = q.Wp; a.plane_bytes = (unsigned)q.Hp * (unsigned)q.Wp * 32u; a.n_bytes = (unsigned)q.CBt * 3u * a.plane_bytes;
-    a.R = pb.R; a.S = pb.S; a.sign = fwd ? 1 : -1;
+    a.sign = fwd ? 1 : -1;
     a.cblocks = pl.sp_cb;
     a.dst_bs = (int)(fwd ? pb.y_bs : pb.x_bs);
     a.mtiles = pl.sp_mpad / pl.sp_bm;
-    a.ntiles = ceil_div(a.ncols, pl.sp_bn);
-    a.ksplit = pl.nsplit; a.steps_per_split = pl.chunks_per_split; a.groups = GF;
+    a.ksplit = pl.nsplit; a.groups = GF;
+    a.nclass = 0; a.units = 0;
+    for (int ch = 0; ch < a.out_step; ++ch)
+        for (int cw = 0; cw < a.out_step; ++cw) {
+            const ClassGrid gh = class_grid(fwd, OH, pb.R, pb.stride, pb.pad, ch), gw = class_grid(fwd, OW, pb.S, pb.stride, pb.pad, cw);
+            if (gh.count == 0 || gw.count == 0) continue;
+            SplitClass &c = a.cls[a.nclass++];
+            c.R = gh.taps; c.S = gw.taps; c.OH = gh.count; c.OW = gw.count; c.ncols = pb.N * gh.count * gw.count;
+            c.add_h = gh.first; c.add_w = gw.first;
+            c.ty = gh.first + pl.sp_ph; c.tx = gw.first + pl.sp_pw;
+            c.tap0 = ch * pb.S + cw; c.h0 = gh.out0; c.w0 = gw.out0;
+            c.first = a.units; c.ntiles = ceil_div(c.ncols, pl.sp_bn);
+            const int steps = pl.sp_cb * c.R * c.S;
+            c.steps_per_split = a.out_step == 1 ? pl.chunks_per_split : ceil_div(steps, a.ksplit);
+            a.units += a.mtiles * c.ntiles * a.ksplit;
+            c.div_plane = make_fastdiv((uint32_t)(c.OH * c.OW));
+            c.div_ow = make_fastdiv((uint32_t)c.OW);
+            c.div_rs = make_fastdiv((uint32_t)std::max(c.R * c.S, 1));
+            c.div_s = make_fastdiv((uint32_t)std::max(c.S, 1));
+        }
     a.dst_gs = fwd ? pb.y_gs : pb.x_gs; a.part_gs = (int64_t)(pl.part_bytes / 4);
     a.w = w; a.src = act; a.w_gs = pb.w_gs; a.src_gs = fwd ? pb.x_gs : pb.y_gs;
-    a.src_bs = (int)q.src_bs; a.LH = q.LH; a.LW = q.LW; a.add = fwd ? -pb.pad : pb.pad;
+    a.src_bs = (int)q.src_bs; a.LH = q.LH; a.LW = q.LW;
     a.Cg = Cr; a.C = pb.C; a.transposed = q.transposed;
     a.epi_on = ep && GF == 1;
     a.epi = ep ? *ep : Epilogue{};
     *ep_applied = a.epi_on;
-    a.div_plane = make_fastdiv((uint32_t)(a.OH * a.OW));
-    a.div_ow = make_fastdiv((uint32_t)a.OW);
-    a.div_rs = make_fastdiv((uint32_t)RS);
-    a.div_s = make_fastdiv((uint32_t)pb.S);
-    a.tiles_per_xcd = ceil_div(a.mtiles * a.ntiles * a.ksplit * GF, 8);
+    a.tiles_per_xcd = ceil_div(a.units * GF, 8);
     const int grid = 8 * a.tiles_per_xcd, lds = 3 * (pl.sp_bm + pl.sp_bn) * 96;
     auto go = [&](auto kern) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -309,11 +325,11 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     else go(colgemm_split_kernel<1, 2, 1, 8>);
     rc = check_launch();
     if (rc != kStatusOk || a.ksplit == 1) return rc;
-    const int per_sample = a.M * a.OH * a.OW;
+    const int per_sample = a.M * a.out_plane;
     for (int gc = 0; gc < GF; ++gc)
         hipLaunchKernelGGL(reduce_split_outputs<float>, dim3(2048), dim3(256), 0, st, a.part + gc * a.part_gs,
                            a.dst + gc * a.dst_gs, a.ksplit, per_sample, pb.N, a.dst_bs,
-                           make_fastdiv((uint32_t)per_sample), a.epi_on, a.epi, a.div_plane);
+                           make_fastdiv((uint32_t)per_sample), a.epi_on, a.epi, make_fastdiv((uint32_t)a.out_plane));
     return check_launch();
 }
 

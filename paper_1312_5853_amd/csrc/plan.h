@@ -194,6 +194,24 @@ inline void pick_dma_tile(int channels, int mtiles, int64_t ncols, TileShape &ti
     else { kc = 64; occ = 1; }
 }
 
+// One axis of a residue class of a strided backward-data: input positions h with (h + pad) % stride == cls meet the taps
+// r = cls, cls + stride, ... only; h = stride * a + cls - pad reads dy at a - (r - cls) / stride.  Forward: the one class of
+// all output positions.
+struct ClassGrid {
+    int taps, count;           // taps of the class; positions a = first, first + 1, ...
+    int first, out0;           // dy (input) position of the first under the class's first tap; its output position
+};
+inline ClassGrid class_grid(bool fwd, int out, int taps, int stride, int pad, int cls)
+{
+    if (fwd) return {taps, out, -pad, 0};
+    ClassGrid g;
+    g.taps = taps > cls ? (taps - cls + stride - 1) / stride : 0;
+    g.first = pad > cls ? (pad - cls + stride - 1) / stride : 0;
+    g.out0 = stride * g.first + cls - pad;
+    g.count = g.out0 < out ? (out - 1 - g.out0) / stride + 1 : 0;
+    return g;
+}
+
 // Tile, split count and time estimate (us, returned) of the three-part fp32 kernel for one column of `steps` steps;
 // `groups` columns share the launch.  The split count decides the order of the sums, so it must not depend on how many
 // columns run together: it is chosen for one column, the tile width (which changes no sum) for all of them.
@@ -482,16 +500,19 @@ inline Plan make_plan(int op, const Problem &pb)
     // than the fp32 kernels: it needs a pass over the input (4 bytes read, 6 written per padded position and channel)
     // that layers with little work per input element do not earn back.  The estimate is per column, so that a grouped
     // layer takes the route its columns would take alone.
-    if (pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride == 1)) && Cr >= 16) {
-        const bool fwd = op == kOpFwd;
+    if (pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) && Cr >= 16) {
+        const bool fwd = op == kOpFwd, strided = !fwd && pb.stride > 1;
         const int GF = pl.fused_groups ? G : 1;
         const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W, mul = fwd ? pb.stride : 1;
-        pl.sp_ph = fwd ? pb.pad : pb.R - 1 - pb.pad;
-        pl.sp_pw = fwd ? pb.pad : pb.S - 1 - pb.pad;
-        const int64_t hp = (int64_t)(OH - 1) * mul + pb.R, wp = (int64_t)(OW - 1) * mul + pb.S;
+        // zero rows before the data, rows of the padded planes; strided: dy rows -(taps - 1) .. (H - 1 + pad) / stride
+        const int rtaps = ceil_div(pb.R, pb.stride), staps = ceil_div(pb.S, pb.stride);
+        pl.sp_ph = fwd ? pb.pad : strided ? rtaps - 1 : pb.R - 1 - pb.pad;
+        pl.sp_pw = fwd ? pb.pad : strided ? staps - 1 : pb.S - 1 - pb.pad;
+        const int64_t hp = strided ? (pb.H - 1 + pb.pad) / pb.stride + rtaps : (int64_t)(OH - 1) * mul + pb.R;
+        const int64_t wp = strided ? (pb.W - 1 + pb.pad) / pb.stride + staps : (int64_t)(OW - 1) * mul + pb.S;
         const int cb = ceil_div(Cr, 16);
         const int64_t ncols = (int64_t)pb.N * OH * OW;
-        const int steps = cb * RS;
+        const int steps = strided ? ceil_div(cb * RS, pb.stride * pb.stride) : cb * RS;      // strided: mean over the classes
         int bm, bn, ks;
         double us = pick_split_tile(pl.M, ncols, steps, GF, bm, bn, ks);
         us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 4.5e6;
@@ -500,10 +521,12 @@ inline Plan make_plan(int op, const Problem &pb)
         const double gflop = 2.0 * ncols * Cr * RS / 1e9;          // per row
         if (pl.patch)
             fp32_us = std::max(gflop * round_up(pl.M, 32) / 90.0 * 1e3, 1.0 * ceil_div(Cr * RS, kChunk)) + 3.0;
+        else if (strided)              // all taps at every position, masked: 20 TFLOP/s of them
+            fp32_us = std::max(gflop * pl.M / 20.0 * 1e3, 1.7 * ceil_div(Cr * RS, kChunk));
         else if (Cr % kChunk != 0)
             fp32_us = std::max(gflop * pl.M / 55.0 * 1e3, 1.7 * ceil_div(Cr * RS, kChunk));
         const int mpad = round_up(pl.M, bm);
-        const int64_t x_bytes = (int64_t)pb.N * GF * cb * hp * wp * 96, w_bytes = (int64_t)GF * steps * mpad * 96;
+        const int64_t x_bytes = (int64_t)pb.N * GF * cb * hp * wp * 96, w_bytes = (int64_t)GF * cb * RS * mpad * 96;
         const int64_t limit = (int64_t)1 << 32;      // 32-bit byte offsets
         if (us * 1.1 < fp32_us && pl.sp_ph >= 0 && pl.sp_pw >= 0 && x_bytes < limit && w_bytes < limit / 2) {
             pl.sp = true;

@@ -167,3 +167,28 @@ def test_split_fully_connected_keeps_fp32_precision_for_tiny_values():
     x, w = synth.gaussian((9, 260), 937) * np.float32(1e-36), synth.gaussian((132, 260), 938)
     y, ref = hp.fc_fwd(dev(x), dev(w)), oracle.fc_fwd(x, w)
     assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 260 * 2.0 ** -24 * oracle.fc_fwd(np.abs(x), np.abs(w)).max()
+
+
+# Strided backward-data as stride-1 passes over the residue classes: one of each stride, extents that leave input rows
+# unread, a filter smaller than the stride (classes without taps), padding of half a filter and more, odd channel counts
+@pytest.mark.parametrize("shape", [
+    (24, 40, 31, 45, 72, 3, 2, 1),
+    (9, 24, 30, 31, 33, 3, 2, 1),
+    (5, 17, 29, 28, 48, 5, 3, 2),
+    (6, 65, 17, 19, 64, 2, 3, 0),
+    (3, 130, 31, 33, 100, 7, 4, 3),
+    (2, 48, 23, 25, 40, 3, 2, 3),
+])
+def test_split_strided_backward_data_stays_within_the_error_bound(shape):
+    N, C, H, W, K, R, st, pad = shape
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    w, dy = synth.gaussian((K, C, R, R), 941, 0.01), synth.gaussian((N, K, P, Q), 942)
+    ref, refabs = oracle.conv_bwd_data(dy, w, H, W, st, pad), oracle.conv_bwd_data(np.abs(dy), np.abs(w), H, W, st, pad)
+    within(hp.conv_bwd_data(dev(dy), dev(w), H, W, st, pad, dx=nan_like((N, C, H, W))), ref, refabs, K * R * R)
+    act = synth.gaussian((N, C, H, W), 943)
+    got = hp.conv_bwd_data_relu(dev(dy), dev(w), dev(act), st, pad, dx=nan_like((N, C, H, W)))
+    within(got, np.where(act > 0, ref, 0.0), refabs, K * R * R)
+    dy[0, 3, 1, 1] = np.inf                                  # positive filters: only the windows' positions show it
+    with np.errstate(all="ignore"):
+        aw = np.abs(w) + np.float32(0.5)
+        same_pattern(hp.conv_bwd_data(dev(dy), dev(aw), H, W, st, pad), oracle.conv_bwd_data(dy, aw, H, W, st, pad))
