@@ -46,6 +46,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 #include "conv_wgrad_split_kernels.h"
 #include "conv_wgrad_rows_kernels.h"
 #include "conv_wgrad_kernels.h"
+#include "conv_direct_kernels.h"
 #include "fc_kernels.h"
 #include "glue_kernels.h"
 
@@ -333,6 +334,54 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     return check_launch();
 }
 
+// Small problems on the vector units: one launch, tensors as they lie
+int run_direct(int op, const void *act, const void *w, void *out, const Problem &pb, hipStream_t st, const Epilogue *ep)
+{
+    const bool fwd = op == kOpFwd;
+    DirectArgs a;
+    a.w = w; a.src = act; a.dst = out;
+    a.M = fwd ? pb.K : pb.C; a.red = (fwd ? pb.C : pb.K) * pb.R * pb.S;
+    a.S = pb.S; a.RS = pb.R * pb.S; a.C = pb.C; a.transposed = fwd ? 0 : 1;
+    a.OH = fwd ? pb.P : pb.H; a.OW = fwd ? pb.Q : pb.W; a.LH = fwd ? pb.H : pb.P; a.LW = fwd ? pb.W : pb.Q;
+    a.stride = pb.stride; a.pad = pb.pad;
+    a.src_bs = (int)(fwd ? pb.x_bs : pb.y_bs); a.dst_bs = (int)(fwd ? pb.y_bs : pb.x_bs);
+    a.ncols = pb.N * a.OH * a.OW;
+    a.epi_on = ep != nullptr;
+    a.epi = ep ? *ep : Epilogue{};
+    a.div_plane = make_fastdiv((uint32_t)(a.OH * a.OW));
+    a.div_ow = make_fastdiv((uint32_t)a.OW);
+    a.div_rs = make_fastdiv((uint32_t)a.RS);
+    a.div_s = make_fastdiv((uint32_t)a.S);
+    a.div_stride = make_fastdiv((uint32_t)a.stride);
+    const int rows = ceil_div(a.M, kDirectRows);
+    auto go = [&](auto wide, auto narrow) {
+        const bool few = ceil_div(a.ncols, 64) * rows < 128;
+        hipLaunchKernelGGL(few ? narrow : wide, dim3(ceil_div(a.ncols, few ? 16 : 64), rows), dim3(kDirectWaves * 64), 0, st, a);
+    };
+    if (pb.dtype == kDtypeF32) go(direct_colgemm_kernel<float, float, 64>, direct_colgemm_kernel<float, float, 16>);
+    else if (pb.out_bf16)
+        go(direct_colgemm_kernel<unsigned short, unsigned short, 64>, direct_colgemm_kernel<unsigned short, unsigned short, 16>);
+    else go(direct_colgemm_kernel<unsigned short, float, 64>, direct_colgemm_kernel<unsigned short, float, 16>);
+    return check_launch();
+}
+
+int run_direct_wgrad(const void *x, const void *dy, void *dw, const Problem &pb, hipStream_t st)
+{
+    DirectWgradArgs a;
+    a.dy = dy; a.x = x; a.dw = static_cast<float *>(dw);
+    a.K = pb.K; a.RS = pb.R * pb.S; a.CRS = pb.C * a.RS; a.S = pb.S;
+    a.P = pb.P; a.Q = pb.Q; a.H = pb.H; a.W = pb.W; a.stride = pb.stride; a.pad = pb.pad;
+    a.dy_bs = (int)pb.y_bs; a.x_bs = (int)pb.x_bs; a.J = pb.N * pb.P * pb.Q;
+    a.div_plane = make_fastdiv((uint32_t)(pb.P * pb.Q));
+    a.div_q = make_fastdiv((uint32_t)pb.Q);
+    a.div_rs = make_fastdiv((uint32_t)a.RS);
+    a.div_s = make_fastdiv((uint32_t)a.S);
+    const dim3 grid(a.CRS, ceil_div(a.K, kWgradFilters)), block(kWgradWaves * 64);
+    if (pb.dtype == kDtypeF32) hipLaunchKernelGGL(direct_wgrad_kernel<float>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(direct_wgrad_kernel<unsigned short>, grid, block, 0, st, a);
+    return check_launch();
+}
+
 constexpr int kNotTaken = 1;          // a specialised path declined the shape: the caller goes on to the general one
 
 // Few-channel forward with bf16 inputs on the bf16 matrix instruction (conv_patch_bf16_kernel); kNotTaken where its
@@ -549,6 +598,7 @@ int run_colgemm(int op, const void *act, const void *w, void *out, const Problem
     const int rows = op == kOpFwd ? pb.K : pb.C;
     const int plane = op == kOpFwd ? pb.P * pb.Q : pb.H * pb.W;
     bool applied = false;
+    if (pl.direct) return run_direct(op, act, w, out, pb, st, ep);
     if (!pb.out_bf16 || pl.stage_bytes == 0) {
         int rc = run_colgemm_f32out(op, act, w, out, pb, pl, ws, st, ep, &applied);
         if (rc != kStatusOk || !ep || applied) return rc;
@@ -759,6 +809,7 @@ int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb,
     const int RS = pb.R * pb.S;
     // bf16 MFMA kernel: reads the caller's bf16 tensors directly (128-column tiles only)
     const bool bf = pb.dtype == kDtypeBf16 && !pl.widen && pb.C % kChunk == 0;     // bf16 MFMA kernel
+    if (pl.direct) return run_direct_wgrad(x, dy, dw, pb, st);
     if (pl.sp)
         return run_wgrad_split(static_cast<const float *>(x), static_cast<const float *>(dy), static_cast<float *>(dw), pb,
                                pl, ws, st);
@@ -1134,9 +1185,10 @@ static int run_grouped(int op, const void *a, const void *b, void *out, int N, i
         if (!aligned(ws, 256)) return kErrMisaligned;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (groups == 1 || pl.fused_groups)
+    if (groups == 1 || (pl.fused_groups && !pl.direct))
         return op == kOpBwdFilter ? run_wgrad(a, b, out, pb, pl, ws, st) : run_colgemm(op, a, b, out, pb, pl, ws, st);
-    // one column after the other: element sizes of the three tensors of this pass
+    // one column after the other (also where one launch could take them all but a column is small enough for the vector
+    // units, so that columns give the same bits together and alone): element sizes of the three tensors of this pass
     const int in_b = pb.dtype == kDtypeBf16 ? 2 : 4;
     const int out_b = (pb.out_bf16 && op != kOpBwdFilter) ? 2 : 4;
     Problem one = pb;
@@ -1146,9 +1198,10 @@ static int run_grouped(int op, const void *a, const void *b, void *out, int N, i
     if (op == kOpFwd) { sa = pb.x_gs * in_b; sb = pb.w_gs * in_b; so = pb.y_gs * out_b; }
     else if (op == kOpBwdData) { sa = pb.y_gs * in_b; sb = pb.w_gs * in_b; so = pb.x_gs * out_b; }
     else { sa = pb.x_gs * in_b; sb = pb.y_gs * in_b; so = pb.w_gs * 4; }
-    // every column's base must keep the alignment the kernels rely on: checked for all columns before the first
+    // every column's base must keep the alignment the kernels rely on (the fused ones rely on none): checked for all
+    // columns before the first
     // one is enqueued
-    for (int g = 1; g < groups; ++g)
+    for (int g = 1; g < groups && !pl.fused_groups; ++g)
         if ((g * sa) % 16 != 0 || (g * sb) % 16 != 0 || (g * so) % 16 != 0) return kErrMisaligned;
     for (int g = 0; g < groups; ++g) {
         const char *pa = static_cast<const char *>(a) + g * sa, *pbp = static_cast<const char *>(b) + g * sb;

@@ -170,6 +170,7 @@ struct Plan {
     bool sp;
     int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
+    bool direct;                      // small problem: one launch on the vector units, no workspace read or written
     size_t total;
 };
 
@@ -249,6 +250,19 @@ inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &
     }
     best_width(ksplit, groups, bn);
     return best;
+}
+
+constexpr int kDirectMaxRed = 800;
+// Small problems go to the vector units (conv_direct_kernels.h): at most 2^24 multiplications, and chains short enough that
+// the pass is bound by launches and latency: reduction elements per wavefront (forward / backward-data, one load each),
+// positions per thread (backward-filter, five loads each).
+inline bool pick_direct(int op, const Problem &pb)
+{
+    const int64_t J = (int64_t)pb.N * pb.P * pb.Q, crs = (int64_t)pb.C * pb.R * pb.S;
+    if (op == kOpBwdFilter) return J * pb.K * crs <= (1 << 24) && J <= 8192 && crs * ceil_div(pb.K, 4) <= 2048;
+    const int64_t cols = op == kOpFwd ? J : (int64_t)pb.N * pb.H * pb.W;
+    const int64_t red = (int64_t)(op == kOpFwd ? pb.C : pb.K) * pb.R * pb.S, rows = op == kOpFwd ? pb.K : pb.C;
+    return cols * rows * red <= (1 << 24) && red <= kDirectMaxRed && pb.R < (1 << 15) && pb.S < (1 << 15) && ((cols + 63) / 64) * ((rows + 3) / 4) <= 1024;
 }
 
 constexpr int64_t kWgradPartLimit = (int64_t)48 << 20;    // bytes of partial sums: what the library's own scratch holds
@@ -567,6 +581,7 @@ inline Plan make_plan(int op, const Problem &pb)
             pl.total = round_up64(pl.part_bytes * GF, 256);
         }
     }
+    pl.direct = pick_direct(op, pb);
     return pl;
 }
 
