@@ -7,6 +7,7 @@ Python.  If the library has not been built this module raises -- there is no
 fallback path.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -117,18 +118,25 @@ def status_string(status):
     return lib().conv_status_string(int(status)).decode()
 
 
+# The two questions below have answers that depend on their arguments alone and cost as much host time as a launch: a
+# training loop asks them for the same few layers on every step.  Bounded; lru_cache is safe between threads.
+@functools.lru_cache(maxsize=1024, typed=True)
 def workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype=DTYPE_F32):
     return int(lib().conv_workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype))
 
 
 def _stream_handle(stream):
+    """Handle of `stream`, or of the current device's current stream, as an integer (a Stream object per call would cost
+    more than the rest of the marshalling)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dtype_of(t):
@@ -139,6 +147,7 @@ def _dtype_of(t):
     raise TypeError("unsupported tensor dtype %s" % t.dtype)
 
 
+@functools.lru_cache(maxsize=1024, typed=True)
 def out_extent(size, filt, stride, pad):
     """P or Q of a layer, asked of the library (conv_output_extent)."""
     return int(lib().conv_output_extent(size, filt, stride, pad))
@@ -174,7 +183,7 @@ def _ws(ws):
 def _run(name, op, a, b, out, dims, x_bs, y_bs, dtype, ws, stream):
     need = workspace_bytes(op, *dims, dtype)
     buf, nbytes = _ws(ws).get(need)
-    wsp = ctypes.c_void_p(buf.data_ptr()) if buf is not None else ctypes.c_void_p(0)
+    wsp = buf.data_ptr() if buf is not None else 0
     if x_bs or y_bs:
         rc = getattr(lib(), name + "_ex")(_ptr(a), _ptr(b), _ptr(out), *dims, int(x_bs), int(y_bs), dtype,
                                           wsp, nbytes, _stream_handle(stream))
@@ -189,9 +198,10 @@ def _batch_stride(t):
     """Batch stride in elements of an NCHW tensor whose samples are dense (a
     channel slice of a wider tensor qualifies); 0 when the whole tensor is."""
     n, c, h, w = t.shape
-    if t.stride(3) != 1 or t.stride(2) != w or t.stride(1) != h * w:
+    sn, sc, sh, sw = t.stride()
+    if sw != 1 or sh != w or sc != h * w:
         raise ValueError("the [channel][row][col] block of every sample must be dense")
-    return 0 if (n == 1 or t.stride(0) == c * h * w) else t.stride(0)
+    return 0 if (n == 1 or sn == c * h * w) else sn
 
 
 def _io_dtype(src, out):
@@ -254,8 +264,8 @@ def conv_fwd_bias_relu(x, w, bias, stride, pad, relu=True, y=None, ws=None, stre
     dims = (N, C, H, W, K, R, S, stride, pad)
     dtype = _io_dtype(x, y)
     buf, nbytes = _ws(ws).get(workspace_bytes(OP_FWD, *dims, dtype))
-    wsp = ctypes.c_void_p(buf.data_ptr()) if buf is not None else ctypes.c_void_p(0)
-    bp = _ptr(bias) if bias is not None else ctypes.c_void_p(0)
+    wsp = buf.data_ptr() if buf is not None else 0
+    bp = _ptr(bias) if bias is not None else 0
     rc = lib().conv_fwd_bias_relu(_ptr(x), _ptr(w), bp, _ptr(y), *dims, 1 if relu else 0, dtype, wsp, nbytes,
                                   _stream_handle(stream))
     if rc != OK:
@@ -278,7 +288,7 @@ def conv_bwd_data_relu(dy, w, act, stride, pad, dx=None, ws=None, stream=None):
     dims = (N, C, H, W, K, R, S, stride, pad)
     dtype = _io_dtype(dy, dx)
     buf, nbytes = _ws(ws).get(workspace_bytes(OP_BWD_DATA, *dims, dtype))
-    wsp = ctypes.c_void_p(buf.data_ptr()) if buf is not None else ctypes.c_void_p(0)
+    wsp = buf.data_ptr() if buf is not None else 0
     rc = lib().conv_bwd_data_relu(_ptr(dy), _ptr(w), _ptr(act), _ptr(dx), *dims, dtype, wsp, nbytes,
                                   _stream_handle(stream))
     if rc != OK:
@@ -318,7 +328,7 @@ def _run_grouped(name, op, a, b, out, dims, groups, dtype, ws, stream):
             raise ValueError("grouped calls take dense tensors")
     need = int(lib().conv_workspace_bytes_grouped(op, *dims, groups, dtype))
     buf, nbytes = _ws(ws).get(need)
-    wsp = ctypes.c_void_p(buf.data_ptr()) if buf is not None else ctypes.c_void_p(0)
+    wsp = buf.data_ptr() if buf is not None else 0
     rc = getattr(lib(), name)(_ptr(a), _ptr(b), _ptr(out), *dims, groups, dtype, wsp, nbytes, _stream_handle(stream))
     if rc != OK:
         raise ConvError(rc, name)
@@ -457,7 +467,7 @@ def convert_f32_to_bf16(src, dst=None, stream=None):
 
 def _fc_ws(op, N, I, O, ws):
     buf, nbytes = _ws(ws).get(int(lib().fc_workspace_bytes(op, N, I, O, DTYPE_F32)))
-    return (ctypes.c_void_p(buf.data_ptr()) if buf is not None else ctypes.c_void_p(0)), nbytes
+    return (buf.data_ptr() if buf is not None else 0), nbytes
 
 
 def fc_fwd(x, w, bias=None, relu=False, y=None, ws=None, stream=None):
@@ -470,7 +480,7 @@ def fc_fwd(x, w, bias=None, relu=False, y=None, ws=None, stream=None):
         y = torch.empty((N, O), dtype=torch.float32, device=x.device)
     _dense(x, w, bias, y)
     wsp, nbytes = _fc_ws(OP_FWD, N, I, O, ws)
-    bp = _ptr(bias) if bias is not None else ctypes.c_void_p(0)
+    bp = _ptr(bias) if bias is not None else 0
     _check(lib().fc_fwd(_ptr(x), _ptr(w), bp, _ptr(y), N, I, O, 1 if relu else 0, _dtype_of(x), wsp, nbytes,
                         _stream_handle(stream)), "fc_fwd")
     return y
