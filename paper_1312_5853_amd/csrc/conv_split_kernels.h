@@ -65,6 +65,10 @@ __device__ __forceinline__ bool split_redo(int flags) { return (flags & 1) || ((
 //   the rest: wt[step = (channel block, r, s)][part][Mpad][16] from KCRS filters, the two 8-channel halves of a row
 //       swapped where (row >> 3) & 1: a linear copy into LDS then lets the 16 lanes of a fragment read cover all banks;
 //       one thread per 8 channels
+// fold > 1 (forward of few-channel layers): the stride x stride input positions that one output position moves past become
+//       channels, v = (c * fold + a) * fold + b of input row h * fold + a and column w * fold + b, so that a 3-channel 11x11
+//       stride-4 layer is a 48-channel 3x3 stride-1 one: 27 steps instead of 121 of which 13 of 16 channels are zero (128 x 3 x 224 x 224, 96 filters: 296 us in fp32 with
+//       the input rows in LDS -> 238 us, 37 of them this launch).
 // A grouped layer's columns follow each other in both (CBg channel blocks per column, filters one column after another).
 // Bound: HBM, 4 bytes read and 6 * Hp*Wp / (LH*LW) written per activation.
 // ---------------------------------------------------------------------------
@@ -82,9 +86,13 @@ struct SplitPrepArgs {
     int transposed;            // backward-data: rows are the filter's channels, reduction runs over the filters
     unsigned wt_chunks;        // groups * CBg * RS * Mpad * 2
     int64_t w_gs;              // floats between the columns' filters
-    FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs;
+    int Cin, R, S, rows, cols;               // fold > 1: input channels, the filter's and the input's extents
+    int pairs;                 // fold > 1: two columns b, b + 1 are inside or outside together and 8-byte aligned
+    FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs, div_sv;
 };
 
+// FOLD: the stride, or 1
+template <int FOLD>
 __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {
     float v[8];
@@ -104,8 +112,26 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
         const bool in = (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
         const int LHW = p.LH * p.LW;
         const float *s = p.src + (int64_t)n * p.src_bs + (int64_t)((int)g * p.Cg + c0) * LHW + h * p.LW + w;
+        if constexpr (FOLD > 1) {
+            const float *const x = p.src + (int64_t)n * p.src_bs;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = in && c0 + k < p.Cg ? s[(int64_t)k * LHW] : 0.f;
+            for (int k = 0; k < 8; ++k) {
+                const int ch = c0 + k, c = ch / (FOLD * FOLD), a = ch / FOLD % FOLD, b = ch % FOLD;
+                const int hh = hp * FOLD + a - p.pad_h, ww = wp * FOLD + b - p.pad_w;
+                const bool ok = c < p.Cin && (unsigned)hh < (unsigned)p.rows && (unsigned)ww < (unsigned)p.cols;
+                const float *e = x + (int64_t)c * p.rows * p.cols + hh * p.cols + ww;
+                if (FOLD % 2 == 0 && p.pairs) {
+                    if (k & 1) continue;
+                    const float2 t = ok ? *reinterpret_cast<const float2 *>(e) : float2{0.f, 0.f};
+                    v[k] = t.x; v[k + 1] = t.y;
+                } else {
+                    v[k] = ok ? *e : 0.f;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = in && c0 + k < p.Cg ? s[(int64_t)k * LHW] : 0.f;
+        }
         split_eight(v, o);
         const unsigned plane = (unsigned)p.Hp * (unsigned)p.Wp;
         u32x4 *dst = p.xs + ((size_t)t2 * 3 * plane + (i - t2 * plane)) * 2 + half;
@@ -127,6 +153,12 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const int ch = ch0 + k;
+        if constexpr (FOLD > 1) {
+            const int rv = (int)fastdiv((uint32_t)rs, p.div_sv), sv = rs - rv * (int)p.div_sv.d;
+            const int c = ch / (FOLD * FOLD), r = rv * FOLD + ch / FOLD % FOLD, sx = sv * FOLD + ch % FOLD;
+            v[k] = m < p.M && c < p.Cin && r < p.R && sx < p.S ? w[((int64_t)(m * p.Cin + c) * p.R + r) * p.S + sx] : 0.f;
+            continue;
+        }
         v[k] = m < p.M && ch < p.Cg ? (p.transposed ? w[((int64_t)ch * p.C + m) * p.RS + rs] : w[((int64_t)m * p.C + ch) * p.RS + rs])
                                     : 0.f;
     }
@@ -188,6 +220,7 @@ struct ColGemmSplitArgs {
     const float *w, *src;
     int64_t w_gs, src_gs;
     int src_bs, LH, LW, Cg, C, transposed;
+    int src_mul, fold, fR, fS; // rows of src between grid positions; fold and the filter's extents (see split_prepare)
     int epi_on;
     Epilogue epi;
     SplitClass cls[kMaxClasses];
@@ -408,8 +441,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
                 const int n = (int)fastdiv((uint32_t)j, q.div_plane);
                 const int rem = j - n * (q.OH * q.OW);
                 const int oh = (int)fastdiv((uint32_t)rem, q.div_ow);
-                hb[jn] = oh * p.mul + q.add_h;
-                wb[jn] = (rem - oh * q.OW) * p.mul + q.add_w;
+                hb[jn] = oh * p.src_mul + q.add_h;
+                wb[jn] = (rem - oh * q.OW) * p.src_mul + q.add_w;
                 base[jn] = (int64_t)n * p.src_bs;
             }
 #pragma unroll
@@ -426,19 +459,28 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
                 const int tap = q.tap0 + rr * p.tap_r + ss * p.tap_s;
 #pragma unroll 1
                 for (int t = 0; t < 8; ++t) {
-                    const int ch = cbk * 16 + half * 8 + t;
+                    int ch = cbk * 16 + half * 8 + t, dh = p.sign * rr, dw = p.sign * ss, tap_e = tap;
+                    bool real = true;                            // a tap of the filter (folded filters are padded)
+                    if (p.fold > 1) {
+                        const int ab = ch % (p.fold * p.fold);
+                        ch /= p.fold * p.fold;
+                        dh = rr * p.fold + ab / p.fold; dw = ss * p.fold + ab % p.fold;
+                        real = dh < p.fR && dw < p.fS;
+                        tap_e = dh * p.fS + dw;
+                    }
+                    const int taps = p.fold > 1 ? p.fR * p.fS : p.RS;
                     float a[TM], b[TN];
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
-                        const bool ok = rowm[i] < p.M && ch < p.Cg;
-                        const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * p.RS + tap
-                                                       : ((int64_t)rowm[i] * p.C + ch) * p.RS + tap;
+                        const bool ok = real && rowm[i] < p.M && ch < p.Cg;
+                        const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * taps + tap_e
+                                                       : ((int64_t)rowm[i] * p.C + ch) * taps + tap_e;
                         a[i] = ok ? wg[o] : 0.f;
                     }
 #pragma unroll
                     for (int jn = 0; jn < TN; ++jn) {
-                        const int h = hb[jn] + p.sign * rr, w = wb[jn] + p.sign * ss;
-                        const bool ok = ch < p.Cg && (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
+                        const int h = hb[jn] + dh, w = wb[jn] + dw;
+                        const bool ok = real && ch < p.Cg && (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
                         b[jn] = ok ? sg[base[jn] + (int64_t)ch * (p.LH * p.LW) + h * p.LW + w] : 0.f;
                     }
 #pragma unroll

@@ -252,12 +252,17 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
 {
     char *wsb = static_cast<char *>(ws);
     const bool fwd = op == kOpFwd;
-    const int Cr = fwd ? pb.C : pb.K, RS = pb.R * pb.S;
+    // a folded forward is a stride-1 pass over pl.sp_fold^2 times the channels with a filter of as many times fewer taps
+    const int fold = pl.sp_fold, R = ceil_div(pb.R, fold), S = ceil_div(pb.S, fold), stride = fold > 1 ? 1 : pb.stride;
+    const int Cr = fwd ? pb.C : pb.K, RS = R * S;
     const int GF = pl.fused_groups ? pb.groups : 1;              // columns of a grouped layer in these launches
     SplitPrepArgs q;
     q.src = act; q.xs = reinterpret_cast<u32x4 *>(wsb + pl.sp_x_off);
     q.src_bs = fwd ? pb.x_bs : pb.y_bs;
-    q.Cg = Cr; q.CBg = pl.sp_cb; q.CBt = GF * pl.sp_cb;
+    q.Cg = Cr * fold * fold; q.CBg = pl.sp_cb; q.CBt = GF * pl.sp_cb;
+    q.Cin = Cr; q.R = pb.R; q.S = pb.S; q.rows = pb.H; q.cols = pb.W;
+    q.pairs = pb.pad % 2 == 0 && pb.W % 2 == 0 && q.src_bs % 2 == 0;
+    q.div_sv = make_fastdiv((uint32_t)S);
     q.LH = fwd ? pb.H : pb.P; q.LW = fwd ? pb.W : pb.Q;
     q.Hp = pl.sp_hp; q.Wp = pl.sp_wp; q.pad_h = pl.sp_ph; q.pad_w = pl.sp_pw;
     q.positions = (unsigned)((int64_t)pb.N * q.CBt * q.Hp * q.Wp);
@@ -269,7 +274,11 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     q.div_wp = make_fastdiv((uint32_t)q.Wp); q.div_hp = make_fastdiv((uint32_t)q.Hp);
     q.div_cbt = make_fastdiv((uint32_t)q.CBt); q.div_cbg = make_fastdiv((uint32_t)q.CBg);
     q.div_mpad = make_fastdiv((uint32_t)q.Mpad); q.div_rs = make_fastdiv((uint32_t)RS);
-    hipLaunchKernelGGL(split_prepare, dim3(q.xb_blocks + grid1d(q.wt_chunks, 256)), dim3(256), 0, st, q);
+    const dim3 prep_grid(q.xb_blocks + grid1d(q.wt_chunks, 256));
+    if (fold == 4) hipLaunchKernelGGL(split_prepare<4>, prep_grid, dim3(256), 0, st, q);
+    else if (fold == 3) hipLaunchKernelGGL(split_prepare<3>, prep_grid, dim3(256), 0, st, q);
+    else if (fold == 2) hipLaunchKernelGGL(split_prepare<2>, prep_grid, dim3(256), 0, st, q);
+    else hipLaunchKernelGGL(split_prepare<1>, prep_grid, dim3(256), 0, st, q);
     int rc = check_launch();
     if (rc != kStatusOk) return rc;
 
@@ -277,9 +286,10 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     a.At = q.wt; a.xs = q.xs; a.dst = out; a.part = reinterpret_cast<float *>(wsb + pl.part_off);
     a.M = pl.M; a.Mpad = pl.sp_mpad; a.N = pb.N;
     const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W;
-    a.mul = fwd ? pb.stride : 1;
+    a.mul = fwd ? stride : 1;
+    a.src_mul = fwd ? pb.stride : 1; a.fold = fold; a.fR = pb.R; a.fS = pb.S;
     a.out_w = OW; a.out_plane = OH * OW; a.out_step = fwd ? 1 : pb.stride;
-    a.RS = RS; a.tap_r = a.out_step * pb.S; a.tap_s = a.out_step;
+    a.RS = RS; a.tap_r = a.out_step * S; a.tap_s = a.out_step;
     a.Wp = q.Wp; a.plane_bytes = (unsigned)q.Hp * (unsigned)q.Wp * 32u; a.n_bytes = (unsigned)q.CBt * 3u * a.plane_bytes;
     a.sign = fwd ? 1 : -1;
     a.cblocks = pl.sp_cb;
@@ -289,13 +299,13 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     a.nclass = 0; a.units = 0;
     for (int ch = 0; ch < a.out_step; ++ch)
         for (int cw = 0; cw < a.out_step; ++cw) {
-            const ClassGrid gh = class_grid(fwd, OH, pb.R, pb.stride, pb.pad, ch), gw = class_grid(fwd, OW, pb.S, pb.stride, pb.pad, cw);
+            const ClassGrid gh = class_grid(fwd, OH, R, pb.stride, pb.pad, ch), gw = class_grid(fwd, OW, S, pb.stride, pb.pad, cw);
             if (gh.count == 0 || gw.count == 0) continue;
             SplitClass &c = a.cls[a.nclass++];
             c.R = gh.taps; c.S = gw.taps; c.OH = gh.count; c.OW = gw.count; c.ncols = pb.N * gh.count * gw.count;
             c.add_h = gh.first; c.add_w = gw.first;
             c.ty = gh.first + pl.sp_ph; c.tx = gw.first + pl.sp_pw;
-            c.tap0 = ch * pb.S + cw; c.h0 = gh.out0; c.w0 = gw.out0;
+            c.tap0 = ch * S + cw; c.h0 = gh.out0; c.w0 = gw.out0;
             c.first = a.units; c.ntiles = ceil_div(c.ncols, pl.sp_bn);
             const int steps = pl.sp_cb * c.R * c.S;
             c.steps_per_split = a.out_step == 1 ? pl.chunks_per_split : ceil_div(steps, a.ksplit);

@@ -168,7 +168,8 @@ struct Plan {
     // sp_hp x sp_wp positions with sp_ph / sp_pw rows / columns of zeros before the data.  The workspace then holds
     // only the regions below (nsplit, chunks_per_split as above).
     bool sp;
-    int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad;
+    // sp_fold > 1: the stride x stride input positions under an output position are channels (forward of few channels)
+    int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad, sp_fold;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
     bool direct;                      // small problem: one launch on the vector units, no workspace read or written
     size_t total;
@@ -514,19 +515,25 @@ inline Plan make_plan(int op, const Problem &pb)
     // than the fp32 kernels: it needs a pass over the input (4 bytes read, 6 written per padded position and channel)
     // that layers with little work per input element do not earn back.  The estimate is per column, so that a grouped
     // layer takes the route its columns would take alone.
-    if (pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) && Cr >= 16) {
+    if (pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) &&
+        (Cr >= 16 || (op == kOpFwd && pb.stride <= 4 && Cr * pb.stride * pb.stride >= 16))) {
         const bool fwd = op == kOpFwd, strided = !fwd && pb.stride > 1;
         const int GF = pl.fused_groups ? G : 1;
-        const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W, mul = fwd ? pb.stride : 1;
+        // forward: folding pads the filter to whole strides but leaves fewer channels to pad to blocks of 16
+        const int f = pb.stride;
+        const bool shorter = f > 1 && f <= 4 && ceil_div(Cr * f * f, 16) * ceil_div(pb.R, f) * ceil_div(pb.S, f) < ceil_div(Cr, 16) * RS;
+        const int fold = pl.sp_fold = fwd && shorter && !pl.fused_groups ? f : 1;
+        const int R = ceil_div(pb.R, fold), S = ceil_div(pb.S, fold), RS_ = R * S;
+        const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W, mul = fwd && fold == 1 ? pb.stride : 1;
         // zero rows before the data, rows of the padded planes; strided: dy rows -(taps - 1) .. (H - 1 + pad) / stride
         const int rtaps = ceil_div(pb.R, pb.stride), staps = ceil_div(pb.S, pb.stride);
         pl.sp_ph = fwd ? pb.pad : strided ? rtaps - 1 : pb.R - 1 - pb.pad;
         pl.sp_pw = fwd ? pb.pad : strided ? staps - 1 : pb.S - 1 - pb.pad;
-        const int64_t hp = strided ? (pb.H - 1 + pb.pad) / pb.stride + rtaps : (int64_t)(OH - 1) * mul + pb.R;
-        const int64_t wp = strided ? (pb.W - 1 + pb.pad) / pb.stride + staps : (int64_t)(OW - 1) * mul + pb.S;
-        const int cb = ceil_div(Cr, 16);
+        const int64_t hp = strided ? (pb.H - 1 + pb.pad) / pb.stride + rtaps : (int64_t)(OH - 1) * mul + R;
+        const int64_t wp = strided ? (pb.W - 1 + pb.pad) / pb.stride + staps : (int64_t)(OW - 1) * mul + S;
+        const int cb = ceil_div(Cr * fold * fold, 16);
         const int64_t ncols = (int64_t)pb.N * OH * OW;
-        const int steps = strided ? ceil_div(cb * RS, pb.stride * pb.stride) : cb * RS;      // strided: mean over the classes
+        const int steps = strided ? ceil_div(cb * RS, pb.stride * pb.stride) : cb * RS_;      // strided: mean over the classes
         int bm, bn, ks;
         double us = pick_split_tile(pl.M, ncols, steps, GF, bm, bn, ks);
         us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 4.5e6;
@@ -540,7 +547,7 @@ inline Plan make_plan(int op, const Problem &pb)
         else if (Cr % kChunk != 0)
             fp32_us = std::max(gflop * pl.M / 55.0 * 1e3, 1.7 * ceil_div(Cr * RS, kChunk));
         const int mpad = round_up(pl.M, bm);
-        const int64_t x_bytes = (int64_t)pb.N * GF * cb * hp * wp * 96, w_bytes = (int64_t)GF * cb * RS * mpad * 96;
+        const int64_t x_bytes = (int64_t)pb.N * GF * cb * hp * wp * 96, w_bytes = (int64_t)GF * cb * RS_ * mpad * 96;
         const int64_t limit = (int64_t)1 << 32;      // 32-bit byte offsets
         if (us * 1.1 < fp32_us && pl.sp_ph >= 0 && pl.sp_pw >= 0 && x_bytes < limit && w_bytes < limit / 2) {
             pl.sp = true;

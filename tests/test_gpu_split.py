@@ -192,3 +192,32 @@ def test_split_strided_backward_data_stays_within_the_error_bound(shape):
     with np.errstate(all="ignore"):
         aw = np.abs(w) + np.float32(0.5)
         same_pattern(hp.conv_bwd_data(dev(dy), dev(aw), H, W, st, pad), oracle.conv_bwd_data(dy, aw, H, W, st, pad))
+
+
+# Few channels, stride > 1: the input positions under an output position become channels.  Strides 2, 3 and 4, filters that
+# are no multiple of the stride, odd extents and padding (no pairs of columns), a split reduction, rows of two tiles
+@pytest.mark.parametrize("shape", [
+    (12, 3, 40, 44, 96, 11, 4, 2),
+    (30, 3, 47, 51, 48, 11, 4, 1),
+    (20, 8, 33, 36, 64, 7, 2, 3),
+    (33, 20, 23, 22, 40, 7, 2, 3),
+    (40, 9, 50, 53, 130, 7, 3, 1),
+    (25, 2, 61, 64, 33, 8, 4, 4),
+])
+def test_split_folded_passes_stay_within_the_error_bound(shape):
+    N, C, H, W, K, R, st, pad = shape
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    x, w = synth.gaussian((N, C, H, W), 961), synth.gaussian((K, C, R, R), 962, 0.01)
+    dy, b = synth.gaussian((N, K, P, Q), 963), synth.gaussian((K,), 964)
+    y, yabs = oracle.conv_fwd(x, w, st, pad), oracle.conv_fwd(np.abs(x), np.abs(w), st, pad)
+    within(hp.conv_fwd(dev(x), dev(w), st, pad, y=nan_like((N, K, P, Q))), y, yabs, C * R * R)
+    b4 = b.reshape(1, -1, 1, 1)
+    within(hp.conv_fwd_bias_relu(dev(x), dev(w), dev(b), st, pad, y=nan_like((N, K, P, Q))), np.maximum(y + b4, 0.0),
+           yabs + np.abs(b4), C * R * R)
+    within(hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad, dw=nan_like((K, C, R, R))),
+           oracle.conv_bwd_filter(x, dy, R, R, st, pad), oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad), N * P * Q)
+    x[1, 1, 6, 7] = np.inf
+    with np.errstate(all="ignore"):
+        aw, ady = np.abs(w) + np.float32(0.5), np.abs(dy) + np.float32(0.5)
+        same_pattern(hp.conv_fwd(dev(x), dev(aw), st, pad), oracle.conv_fwd(x, aw, st, pad))
+        same_pattern(hp.conv_bwd_filter(dev(x), dev(ady), R, R, st, pad), oracle.conv_bwd_filter(x, ady, R, R, st, pad))
