@@ -459,7 +459,15 @@ int run_patch_bf16(const void *x, const void *w, void *out, const Problem &pb, c
 int launch_finish_wgrad(const float *part, float *dw, int K, int C, int RS, int nsplit, int groups, hipStream_t st)
 {
     const int ncols = RS * C;
-    if (C % 4 == 0 && reinterpret_cast<uintptr_t>(part) % 16 == 0) {
+    const bool quads = C % 4 == 0 && reinterpret_cast<uintptr_t>(part) % 16 == 0;
+    // few splits: bound by how dw is written, so turned through LDS; many: by the chain of partial sums of a thread, which
+    // wants every thread of the chip (two columns of 48 channels 5x5, 49 splits: 6.8 us flat, 8.6 turned)
+    const int cblocks = ceil_div(C, kFinishChannels);
+    const size_t lds = (size_t)std::min(C, kFinishChannels) * RS * 4;
+    if (quads && nsplit <= 12 && lds <= 64 * 1024 && groups * K * cblocks >= 512) {
+        hipLaunchKernelGGL(finish_wgrad_turn, dim3(groups * K * cblocks), dim3(256), lds, st, part, dw, K, C, RS, nsplit,
+                           cblocks, make_fastdiv((uint32_t)(K * cblocks)), make_fastdiv((uint32_t)cblocks));
+    } else if (quads) {
         const int count = groups * K * (ncols / 4);
         hipLaunchKernelGGL(finish_wgrad_x4, dim3(grid1d(count, 256)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
                            make_fastdiv((uint32_t)(K * (ncols / 4))), make_fastdiv((uint32_t)(ncols / 4)),
