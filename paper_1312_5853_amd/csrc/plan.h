@@ -438,7 +438,7 @@ inline Plan make_plan(int op, const Problem &pb)
                 const double step_us = pl.tile.bm() * pl.tile.bn() * 2.0 * kChunk / 64.0 / 4.0 / 2100.0;   // MFMA time
                 double best = 1e30;
                 for (int ks = 1; ks <= 4; ++ks) {
-                    if (steps * kChunk / ks < 256) break;
+                    if (ks > 1 && steps * kChunk / ks < 256) break;
                     const int sps = ceil_div(steps, ks);
                     const int units = tiles * ceil_div(steps, sps);
                     const int per_cu = ceil_div(ceil_div(units, 8), 32);
@@ -536,7 +536,7 @@ inline Plan make_plan(int op, const Problem &pb)
         const int steps = strided ? ceil_div(cb * RS, pb.stride * pb.stride) : cb * RS_;      // strided: mean over the classes
         int bm, bn, ks;
         double us = pick_split_tile(pl.M, ncols, steps, GF, bm, bn, ks);
-        us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 4.5e6;
+        us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 3.8e6;
         // the few-channel kernel reaches about 90 TFLOP/s on its padded rows, at 1 us or more per 16-deep step; the
         // tap-table kernel 55 and 1.7 us
         const double gflop = 2.0 * ncols * Cr * RS / 1e9;          // per row
@@ -579,7 +579,7 @@ inline Plan make_plan(int op, const Problem &pb)
         const double us = pick_wgrad_split(pb.K, RS * cb, J, GF, out_bytes, bm, ks);
         const int64_t part = (int64_t)ks * out_bytes;
         const int steps = (int)((J + 31) / 32);
-        if (us * 1.05 < fp32_us && (part * GF <= kWgradPartLimit || part * GF <= (int64_t)pl.total)) {
+        if (us * 1.05 + 1.5 < fp32_us && (part * GF <= kWgradPartLimit || part * GF <= (int64_t)pl.total)) {
             pl.sp = true;
             pl.sp_bm = bm; pl.sp_bn = 256; pl.sp_cb = cb;
             pl.chunks_per_split = 2 * ceil_div(steps, ks);       // chunks of 16 positions, two to a step
