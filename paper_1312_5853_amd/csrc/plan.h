@@ -298,6 +298,7 @@ inline Plan make_plan(int op, const Problem &pb)
 {
     Plan pl = {};
     pl.op = op;
+    pl.direct = pick_direct(op, pb);
     const int G = pb.groups > 1 ? pb.groups : 1;
     const int RS = pb.R * pb.S;
     if (op == kOpFwd) { pl.M = pb.K; pl.Kg = pb.C * RS; }
@@ -515,7 +516,7 @@ inline Plan make_plan(int op, const Problem &pb)
     // than the fp32 kernels: it needs a pass over the input (4 bytes read, 6 written per padded position and channel)
     // that layers with little work per input element do not earn back.  The estimate is per column, so that a grouped
     // layer takes the route its columns would take alone.
-    if (pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) &&
+    if (!pl.direct && pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) &&
         (Cr >= 16 || (op == kOpFwd && pb.stride <= 4 && Cr * pb.stride * pb.stride >= 16))) {
         const bool fwd = op == kOpFwd, strided = !fwd && pb.stride > 1;
         const int GF = pl.fused_groups ? G : 1;
@@ -563,7 +564,7 @@ inline Plan make_plan(int op, const Problem &pb)
     }
     // fp32 backward-filter through the bf16 matrix instruction, where that is estimated to be faster than the fp32 kernels
     // (few-channel layers pad 16 / C times) and its partial sums fit where theirs do.
-    if (pb.dtype == kDtypeF32 && op == kOpBwdFilter && pb.K >= 8 && pb.C >= 8 &&
+    if (!pl.direct && pb.dtype == kDtypeF32 && op == kOpBwdFilter && pb.K >= 8 && pb.C >= 8 &&
         std::max((int64_t)pb.H * pb.W, (int64_t)pb.P * pb.Q) * 32 < kMaxSpanBytes) {
         const int GF = pl.fused_groups ? G : 1;
         const int64_t J = (int64_t)pb.N * pb.P * pb.Q, out_bytes = (int64_t)pb.K * pl.Kg * 4;
@@ -588,7 +589,6 @@ inline Plan make_plan(int op, const Problem &pb)
             pl.total = round_up64(pl.part_bytes * GF, 256);
         }
     }
-    pl.direct = pick_direct(op, pb);
     return pl;
 }
 
