@@ -571,13 +571,17 @@ inline Plan make_plan(int op, const Problem &pb)
         const int cb = ceil_div(pb.C, 16);
         // fp32 kernels: matrix time of their 16-deep steps, of which the staged kernel reaches about 0.8 with two
         // work-groups per CU, the tap-table kernel 0.5 (and two launches more); few-channel rows 104 TFLOP/s
+        // (both estimates are for one column alone, so that a column takes the same route in a grouped layer)
         const double step_us = pl.tile.bm() * (double)pl.tile.bn() * 32.0 / 256.0 / 2100.0;
-        const int64_t units = (int64_t)(pl.Mpad / pl.tile.bm()) * ceil_div(pl.Kg, pl.tile.bn()) * pl.nsplit * GF;
-        fp32_us = (double)((units + 255) / 256) * pl.chunks_per_split * step_us / (pb.C % kChunk == 0 ? 0.8 : 0.5) + 4.0 +
-                  (2.0 * pl.nsplit + 1.0) * GF * out_bytes / 4.5e6 + (pb.C % kChunk == 0 ? 0.0 : 4.0);
+        const int tiles = (pl.Mpad / pl.tile.bm()) * ceil_div(pl.Kg, pl.tile.bn()), jchunks = (int)((J + kChunk - 1) / kChunk);
+        const int per_split = ceil_div(jchunks, std::max(1, std::min(kTargetGroups / tiles, jchunks / 8)));
+        const int ns = ceil_div(jchunks, per_split);
+        fp32_us = (double)(((int64_t)tiles * ns + 255) / 256) * per_split * step_us / (pb.C % kChunk == 0 ? 0.8 : 0.5) + 4.0 +
+                  (2.0 * ns + 1.0) * out_bytes / 4.5e6 + (pb.C % kChunk == 0 ? 0.0 : 4.0);
         if (pl.rows_f32) fp32_us = 2.0 * J * pb.K * pl.Kg / 104e6;
         int bm, ks;
-        const double us = pick_wgrad_split(pb.K, RS * cb, J, GF, out_bytes, bm, ks);
+        const double us = pick_wgrad_split(pb.K, RS * cb, J, 1, out_bytes, bm, ks);
+        pick_wgrad_split(pb.K, RS * cb, J, GF, out_bytes, bm, ks);
         const int64_t part = (int64_t)ks * out_bytes;
         const int steps = (int)((J + 31) / 32);
         if (us * 1.05 + 1.5 < fp32_us && (part * GF <= kWgradPartLimit || part * GF <= (int64_t)pl.total)) {
