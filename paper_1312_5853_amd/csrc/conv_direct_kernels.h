@@ -5,7 +5,7 @@
 // filters in a launch of their own, pad few rows to 32 and run one serial chain of steps on a handful of work-groups.  Here
 // the sixteen wavefronts of a work-group share the reduction, so that a chain is a sixteenth as long, read the tensors as
 // they lie, and add their sums through LDS in a fixed order.  4 x 3 x 32 x 32, 16 filters 5x5: forward 9.8 -> 4.7 us,
-// backward-data 25.3 -> 5.2, backward-filter 19.4 -> 7.5 (kernel times, launches of the old passes added up).
+// backward-data 25.3 -> 5.1, backward-filter 19.4 -> 6.0 (kernel times, launches of the old passes added up).
 
 constexpr int kDirectWaves = 16, kDirectRows = 4;
 constexpr int kWgradWaves = 8, kWgradFilters = 4;      // 75 work-groups of 16 wavefronts x 16 filters: 12.4 us

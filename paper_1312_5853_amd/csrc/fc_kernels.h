@@ -320,10 +320,13 @@ __global__ __launch_bounds__(kThreads, 2) void fc_split_kernel(const FcArgs p)
     int kload = k_begin;                        // first k of the next step to load
     unsigned moved[2] = {0u, 0u};               // bytes since step 0
     auto load_quad = [&](int set, int op, int h) {
-        unsigned v = pc[op].off[h];
-        if (kload + KC > k_end) v = kload + pc[op].k[h] < k_end ? v : kOutside;       // the range ends in this step (uniform)
-        st[set][op][h] = __builtin_bit_cast(f32x4, op == 0 ? __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, v, moved[0], 0)
-                                                           : __builtin_amdgcn_raw_buffer_load_b128(rsrc_b, v, moved[1], 0));
+        unsigned v = pc[op].off[h], moved_op = moved[op];
+        if (kload + KC > k_end) {                // (uniform) the range ends in this step, or has ended: nothing is read then
+            v = kload + pc[op].k[h] < k_end ? v : kOutside;
+            moved_op = kload < k_end ? moved_op : 0u;
+        }
+        st[set][op][h] = __builtin_bit_cast(f32x4, op == 0 ? __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, v, moved_op, 0)
+                                                           : __builtin_amdgcn_raw_buffer_load_b128(rsrc_b, v, moved_op, 0));
     };
     auto next_load_step = [&]() { kload += KC; moved[0] += adv[0]; moved[1] += adv[1]; };
     u32x4 sp[3];
