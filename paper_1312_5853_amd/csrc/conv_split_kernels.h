@@ -11,8 +11,8 @@
 // error (2-norm) against 64-bit sums, 384 channels 3x3 forward: 2.7e-7; fp32 kernel 6.7e-7; with one accumulator for all
 // six products 8.1e-7.
 //
-// Range: the split is exact for |x| >= 2^-110 and for 0.  A tile whose sums are not finite (infinities, NaN or an
-// overflow in its inputs), or all tiny (below 2^-80, where the parts of the inputs may have been flushed), is computed
+// Range: the split is exact for |x| >= 2^-110 and for 0.  A tile with infinite sums (infinities in its inputs or an
+// overflow), or whose sums are all tiny (below 2^-80, where the parts of the inputs may have been flushed), is computed
 // again by its work-group from the fp32 tensors with the fp32 matrix instruction, so that infinities, NaN and tiny values
 // come out as fp32 arithmetic gives them.
 
@@ -29,6 +29,13 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned &h, unsign
     l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a2, b2}, bf16x2));
 }
 
+// An input whose h part is infinite: an infinity, or a finite value that rounds to one.  Its m part is NaN.
+__device__ __forceinline__ bool split_overflows(float v)
+{
+    const unsigned u = __float_as_uint(v) & 0x7fffffffu;
+    return u >= 0x7f7f8000u && u <= 0x7f800000u;
+}
+
 // eight consecutive reduction elements -> one 16-byte piece of each part
 __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
 {
@@ -38,22 +45,47 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
         split_pair(v[2 * t], v[2 * t + 1], h, m, l);
         o[0][t] = h; o[1][t] = m; o[2][t] = l;
     }
+    // h stays finite where the value is (and takes an infinity alone), so that the sums of h h' are NaN only where fp32's are
+    bool over = false;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) over |= split_overflows(v[k]);
+    if (over) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (!split_overflows(v[k])) continue;
+            const unsigned u = __float_as_uint(v[k]), sign = u & 0x80000000u;
+            const bool inf = (u & 0x7fffffffu) == 0x7f800000u;
+            const unsigned hb = sign | (inf ? 0x7f800000u : 0x7f7f0000u);
+            const float rest = inf ? 0.f : v[k] - __uint_as_float(hb);
+            const unsigned mb = __float_as_uint(rest) & 0xffff0000u;             // at most 16 bits are left: two parts hold them
+            const unsigned lb = __float_as_uint(rest - __uint_as_float(mb));
+            const int sh = (k & 1) * 16;
+            o[0][k >> 1] = (o[0][k >> 1] & ~(0xffffu << sh)) | (hb >> 16) << sh;
+            o[1][k >> 1] = (o[1][k >> 1] & ~(0xffffu << sh)) | (mb >> 16) << sh;
+            o[2][k >> 1] = (o[2][k >> 1] & ~(0xffffu << sh)) | (lb >> 16) << sh;
+        }
+    }
 }
 
-// Whether a wave's sums call for the fp32 computation: bit 0 some sum is not finite, bit 1 some sum is at least 2^-80,
-// bit 2 some sum is not zero.
+// What a wave's sums (hh: of h h'; low: of the smaller products) say: bit 0 some sum is infinite, bit 1 some sum is at least
+// 2^-80, bit 2 some sum is not zero, bit 3 some sum is NaN.
 template <int TM, int TN>
-__device__ __forceinline__ int split_sum_flags(const f32x16 (&acc)[TM][TN])
+__device__ __forceinline__ int split_sum_flags(const f32x16 (&hh)[TM][TN], const f32x16 (&low)[TM][TN])
 {
     unsigned top = 0;
+    bool inf = false;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int jn = 0; jn < TN; ++jn)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) top = max(top, __float_as_uint(acc[i][jn][v]) & 0x7fffffffu);
-    return (__ballot(top >= 0x7f800000u) ? 1 : 0) | (__ballot(top >= (unsigned)(127 - 80) << 23) ? 2 : 0) |
-           (__ballot(top > 0u) ? 4 : 0);
+            for (int v = 0; v < 16; ++v) {
+                const unsigned sum = __float_as_uint(hh[i][jn][v] + low[i][jn][v]) & 0x7fffffffu;
+                top = max(top, sum);
+                inf |= sum == 0x7f800000u || (__float_as_uint(hh[i][jn][v]) & 0x7fffffffu) == 0x7f800000u;
+            }
+    return (__ballot(inf) ? 1 : 0) | (__ballot(top >= (unsigned)(127 - 80) << 23) ? 2 : 0) | (__ballot(top > 0u) ? 4 : 0) |
+           (__ballot(top > 0x7f800000u) ? 8 : 0);
 }
 __device__ __forceinline__ bool split_redo(int flags) { return (flags & 1) || ((flags & 4) && !(flags & 2)); }
 
@@ -412,16 +444,15 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
     while (step + 2 < nsteps) do_step(std::true_type{});
     while (step < nsteps) do_step(std::false_type{});
 
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
-
     // sums that call for fp32 arithmetic: the whole work-group computes its tile again
     {
         __syncthreads();                                        // the LDS buffers are free
         int *const flags = reinterpret_cast<int *>(lds_fast);
-        const int f = split_sum_flags<TM, TN>(acc);
+        const int f = split_sum_flags<TM, TN>(acc, low);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
         if (lane == 0) flags[wave] = f;
         __syncthreads();
         int all = 0;
@@ -458,36 +489,43 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
                 const int rr = (int)fastdiv((uint32_t)rs, q.div_s), ss = rs - rr * q.S;
                 const int tap = q.tap0 + rr * p.tap_r + ss * p.tap_s;
 #pragma unroll 1
-                for (int t = 0; t < 8; ++t) {
-                    int ch = cbk * 16 + half * 8 + t, dh = p.sign * rr, dw = p.sign * ss, tap_e = tap;
-                    bool real = true;                            // a tap of the filter (folded filters are padded)
-                    if (p.fold > 1) {
-                        const int ab = ch % (p.fold * p.fold);
-                        ch /= p.fold * p.fold;
-                        dh = rr * p.fold + ab / p.fold; dw = ss * p.fold + ab % p.fold;
-                        real = dh < p.fR && dw < p.fS;
-                        tap_e = dh * p.fS + dw;
+                for (int t0 = 0; t0 < 8; t0 += 4) {              // the loads of four elements in flight, unconditional
+                    float a[4][TM], b[4][TN];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        int ch = cbk * 16 + half * 8 + t0 + t, dh = p.sign * rr, dw = p.sign * ss, tap_e = tap;
+                        bool real = true;                        // a tap of the filter (folded filters are padded)
+                        if (p.fold > 1) {
+                            const int ab = ch % (p.fold * p.fold);
+                            ch /= p.fold * p.fold;
+                            dh = rr * p.fold + ab / p.fold; dw = ss * p.fold + ab % p.fold;
+                            real = dh < p.fR && dw < p.fS;
+                            tap_e = dh * p.fS + dw;
+                        }
+                        const int taps = p.fold > 1 ? p.fR * p.fS : p.RS;
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) {
+                            const bool ok = real && rowm[i] < p.M && ch < p.Cg;
+                            const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * taps + tap_e
+                                                           : ((int64_t)rowm[i] * p.C + ch) * taps + tap_e;
+                            const float e = wg[ok ? o : 0];
+                            a[t][i] = ok ? e : 0.f;
+                        }
+#pragma unroll
+                        for (int jn = 0; jn < TN; ++jn) {
+                            const int h = hb[jn] + dh, w = wb[jn] + dw;
+                            const bool ok = real && ch < p.Cg && (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
+                            const float e = sg[ok ? base[jn] + (int64_t)ch * (p.LH * p.LW) + h * p.LW + w : 0];
+                            b[t][jn] = ok ? e : 0.f;
+                        }
                     }
-                    const int taps = p.fold > 1 ? p.fR * p.fS : p.RS;
-                    float a[TM], b[TN];
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        const bool ok = real && rowm[i] < p.M && ch < p.Cg;
-                        const int64_t o = p.transposed ? ((int64_t)ch * p.C + rowm[i]) * taps + tap_e
-                                                       : ((int64_t)rowm[i] * p.C + ch) * taps + tap_e;
-                        a[i] = ok ? wg[o] : 0.f;
-                    }
+                    for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int jn = 0; jn < TN; ++jn) {
-                        const int h = hb[jn] + dh, w = wb[jn] + dw;
-                        const bool ok = real && ch < p.Cg && (unsigned)h < (unsigned)p.LH && (unsigned)w < (unsigned)p.LW;
-                        b[jn] = ok ? sg[base[jn] + (int64_t)ch * (p.LH * p.LW) + h * p.LW + w] : 0.f;
-                    }
+                        for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int jn = 0; jn < TN; ++jn)
-                            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[jn], acc[i][jn], 0, 0, 0);
+                            for (int jn = 0; jn < TN; ++jn)
+                                acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][i], b[t][jn], acc[i][jn], 0, 0, 0);
                 }
             }
         }

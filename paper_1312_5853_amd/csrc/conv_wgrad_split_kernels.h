@@ -287,11 +287,6 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
         half_step(I<1>{});
     }
 
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
-
     // column of this lane in block column jn of the wave: (r, s) tap and channel
     auto column = [&](int jn, int &rs, int &ch) {
         const int blk = n0 / 16 + (wn * TN + jn) * 2 + (l32 >> 4);
@@ -304,13 +299,47 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
     {
         __syncthreads();
         int *const flags = reinterpret_cast<int *>(lds_fast);
-        const int f = split_sum_flags<TM, TN>(acc);
+        const int f = split_sum_flags<TM, TN>(acc, low);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
         if (lane == 0) flags[wave] = f;
         __syncthreads();
         int all = 0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) all |= flags[i];
-        if (split_redo(uniform(all))) {
+        // NaN sums are right unless an infinity, or a value whose h part is one, took part (its m part is NaN): look for it
+        bool redo = split_redo(uniform(all));
+        if (!redo && (uniform(all) & 8)) {
+            bool over = false;
+            jnext = jbeg + pos;
+            for (int step = 0; step < nsteps; ++step) {
+                next_position();
+#pragma unroll
+                for (int u = 0; u < NT; ++u) {
+                    if (none[u]) continue;
+                    const int plane = (isa[u] ? PQ : p.H * p.W) * 4;
+                    const auto rsrc = isa[u] ? rsrc_dy : rsrc_x;
+                    const bool in = (unsigned)(hb + tap_r[u]) < (unsigned)p.H && (unsigned)(wb + tap_s[u]) < (unsigned)p.W;
+                    const unsigned v = isa[u] ? (ybase == kOutside ? kOutside : ybase + row_off[u])
+                                              : in ? xbase + (unsigned)(tap_r[u] * p.W + tap_s[u]) * 4u + row_off[u] : kOutside;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        over |= split_overflows(__builtin_bit_cast(
+                            float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, TAIL ? v + (unsigned)(k * plane) : v, TAIL ? 0 : k * plane, 0)));
+                }
+            }
+            const int any = __ballot(over) ? 1 : 0;
+            __syncthreads();
+            if (lane == 0) flags[wave] = any;
+            __syncthreads();
+            int seen = 0;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) seen |= flags[i];
+            redo = uniform(seen) != 0;
+        }
+        if (redo) {
             int tr[TN], ts[TN];
             int64_t boff[TN];
             bool bok[TN];
@@ -329,31 +358,38 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
 #pragma unroll 1
-            for (int j0 = jbeg; j0 < jend; j0 += 2) {
-                const int j = j0 + half;
-                const bool jok = j < jend;
-                const int js = jok ? j : jbeg;
-                const int n = (int)fastdiv((uint32_t)js, p.div_plane);
-                const int pq = js - n * PQ;
-                const int pp = (int)fastdiv((uint32_t)pq, p.div_q);
-                const int h0 = pp * p.stride - p.pad, w0 = (pq - pp * p.Q) * p.stride - p.pad;
-                float a[TM], b[TN];
+            for (int j0 = jbeg; j0 < jend; j0 += 8) {            // the loads of eight positions in flight, unconditional
+                float a[4][TM], b[4][TN];
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const int k = m0 + (wm * TM + i) * 32 + l32;
-                    a[i] = jok && k < p.K ? dyg[(int64_t)n * p.dy_bs + (int64_t)k * PQ + pq] : 0.f;
+                for (int t = 0; t < 4; ++t) {
+                    const int j = j0 + t * 2 + half;
+                    const bool jok = j < jend;
+                    const int js = jok ? j : jbeg;
+                    const int n = (int)fastdiv((uint32_t)js, p.div_plane);
+                    const int pq = js - n * PQ;
+                    const int pp = (int)fastdiv((uint32_t)pq, p.div_q);
+                    const int h0 = pp * p.stride - p.pad, w0 = (pq - pp * p.Q) * p.stride - p.pad;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int k = m0 + (wm * TM + i) * 32 + l32;
+                        const float e = dyg[(int64_t)n * p.dy_bs + (int64_t)min(k, p.K - 1) * PQ + pq];
+                        a[t][i] = jok && k < p.K ? e : 0.f;
+                    }
+#pragma unroll
+                    for (int jn = 0; jn < TN; ++jn) {
+                        const int h = h0 + tr[jn], w = w0 + ts[jn];
+                        const bool ok = jok && bok[jn] && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
+                        const float e = xg[ok ? (int64_t)n * p.x_bs + boff[jn] + h * p.W + w : 0];
+                        b[t][jn] = ok ? e : 0.f;
+                    }
                 }
 #pragma unroll
-                for (int jn = 0; jn < TN; ++jn) {
-                    const int h = h0 + tr[jn], w = w0 + ts[jn];
-                    const bool ok = jok && bok[jn] && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
-                    b[jn] = ok ? xg[(int64_t)n * p.x_bs + boff[jn] + h * p.W + w] : 0.f;
-                }
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                    for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int jn = 0; jn < TN; ++jn)
-                        acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[jn], acc[i][jn], 0, 0, 0);
+                        for (int jn = 0; jn < TN; ++jn)
+                            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][i], b[t][jn], acc[i][jn], 0, 0, 0);
             }
         }
     }

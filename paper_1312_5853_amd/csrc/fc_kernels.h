@@ -449,19 +449,40 @@ __global__ __launch_bounds__(kThreads, 2) void fc_split_kernel(const FcArgs p)
         if (step + 1 < nsteps) do_step(I<1>{});
     }
 
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
-
     // sums that call for fp32 arithmetic: the whole work-group computes its tile again
     {
         __syncthreads();
         int *const flags = reinterpret_cast<int *>(tiles);
-        const int f = split_sum_flags<TM, TN>(acc);
+        const int f = split_sum_flags<TM, TN>(acc, low);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
         if (lane == 0) flags[wave] = f;
         __syncthreads();
-        if (split_redo(uniform(flags[0] | flags[1] | flags[2] | flags[3]))) {
+        // NaN sums are right unless an infinity, or a value whose h part is one, took part (its m part is NaN): look for it
+        const int all = uniform(flags[0] | flags[1] | flags[2] | flags[3]);
+        bool redo = split_redo(all);
+        if (!redo && (all & 8)) {
+            bool over = false;
+            kload = k_begin;
+            moved[0] = moved[1] = 0u;
+            for (int step = 0; step < nsteps; ++step) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    load_quad(0, q >> 1, q & 1);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) over |= split_overflows(st[0][q >> 1][q & 1][t]);
+                }
+                next_load_step();
+            }
+            const int any = __ballot(over) ? 1 : 0;
+            __syncthreads();
+            if (lane == 0) flags[wave] = any;
+            __syncthreads();
+            redo = uniform(flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+        }
+        if (redo) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -469,24 +490,31 @@ __global__ __launch_bounds__(kThreads, 2) void fc_split_kernel(const FcArgs p)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
 #pragma unroll 1
-            for (int k0 = k_begin; k0 < k_end; k0 += 2) {
-                const int k = k0 + half;
-                float a[TM], b[TN];
+            for (int k0 = k_begin; k0 < k_end; k0 += 8) {        // the loads of eight elements in flight, unconditional
+                float a[4][TM], b[4][TN];
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const int r = m0 + (wm * TM + i) * 32 + l32;
-                    a[i] = k < k_end && r < p.M ? p.A[AT ? (size_t)k * p.lda + r : (size_t)r * p.lda + k] : 0.f;
+                for (int t = 0; t < 4; ++t) {
+                    const int k = k0 + t * 2 + half, kc = min(k, k_end - 1);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int r = m0 + (wm * TM + i) * 32 + l32, rc = min(r, p.M - 1);
+                        const float e = p.A[AT ? (size_t)kc * p.lda + rc : (size_t)rc * p.lda + kc];
+                        a[t][i] = k < k_end && r < p.M ? e : 0.f;
+                    }
+#pragma unroll
+                    for (int jn = 0; jn < TN; ++jn) {
+                        const int r = n0 + (wn * TN + jn) * 32 + l32, rc = min(r, p.Nc - 1);
+                        const float e = p.B[BT ? (size_t)kc * p.ldb + rc : (size_t)rc * p.ldb + kc];
+                        b[t][jn] = k < k_end && r < p.Nc ? e : 0.f;
+                    }
                 }
 #pragma unroll
-                for (int jn = 0; jn < TN; ++jn) {
-                    const int r = n0 + (wn * TN + jn) * 32 + l32;
-                    b[jn] = k < k_end && r < p.Nc ? p.B[BT ? (size_t)k * p.ldb + r : (size_t)r * p.ldb + k] : 0.f;
-                }
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                    for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int jn = 0; jn < TN; ++jn)
-                        acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[jn], acc[i][jn], 0, 0, 0);
+                        for (int jn = 0; jn < TN; ++jn)
+                            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][i], b[t][jn], acc[i][jn], 0, 0, 0);
             }
         }
     }

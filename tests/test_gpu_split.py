@@ -221,3 +221,23 @@ def test_split_folded_passes_stay_within_the_error_bound(shape):
         aw, ady = np.abs(w) + np.float32(0.5), np.abs(dy) + np.float32(0.5)
         same_pattern(hp.conv_fwd(dev(x), dev(aw), st, pad), oracle.conv_fwd(x, aw, st, pad))
         same_pattern(hp.conv_bwd_filter(dev(x), dev(ady), R, R, st, pad), oracle.conv_bwd_filter(x, ady, R, R, st, pad))
+
+
+def test_split_passes_tell_nan_from_values_that_only_their_first_part_makes_infinite():
+    # a NaN, and in the same sums a finite value above the largest bfloat16 beside a zero: the NaN shows where fp32 has it,
+    # and the zero times the large value stays zero
+    x, w = synth.gaussian((3, 64, 13, 13), 971), np.abs(synth.gaussian((64, 64, 3, 3), 972)) + np.float32(0.5)
+    x[1, 5, 6, 7] = np.nan
+    x[2, 9, 3, 3] = np.float32(3.4e38)
+    w[:, 9] = 0.0
+    dy = np.abs(synth.gaussian((16, 64, 16, 16), 973)) + np.float32(0.5)
+    xb = synth.gaussian((16, 64, 16, 16), 974)
+    xb[3, 2, 8, 8], xb[4, 7, 1, 1] = np.nan, np.float32(3.4e38)
+    dy[4] = 0.0
+    a, b = synth.gaussian((9, 260), 975), np.abs(synth.gaussian((132, 260), 976)) + np.float32(0.5)
+    a[3, 7], a[4, 9] = np.nan, np.float32(-3.4e38)
+    b[:, 9] = 0.0
+    with np.errstate(all="ignore"):
+        same_pattern(hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1))
+        same_pattern(hp.conv_bwd_filter(dev(xb), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(xb, dy, 3, 3, 1, 1))
+        same_pattern(hp.fc_fwd(dev(a), dev(b)), oracle.fc_fwd(a, b))
