@@ -1,4 +1,7 @@
+import collections
+import ctypes
 import os
+import subprocess
 import sys
 
 import pytest
@@ -27,6 +30,25 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+Route = collections.namedtuple("Route", "kernels fold nsplit rows columns workspace")
+
+
+@pytest.fixture(scope="session")
+def route(tmp_path_factory):
+    """route(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0): what the planner does with such a pass, so that a test
+    written for one set of kernels ("fp32", "split" or "direct") can assert that it reaches them."""
+    so = str(tmp_path_factory.mktemp("plan") / "plan_query.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "plan_query.cpp")],
+                   check=True)
+    query = ctypes.CDLL(so).plan_query
+
+    def ask(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0):
+        out = (ctypes.c_longlong * 6)()
+        assert query(op, N, C, H, W, K, R, R, stride, pad, groups, dtype, out) == 0
+        return Route(("fp32", "split", "direct")[out[0]], *list(out)[1:])
+    return ask
 
 
 # Normalised max errors the parity tests measured, printed once at the end of the run (also under -q).

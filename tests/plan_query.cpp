@@ -1,0 +1,27 @@
+// Which kernels the planner sends a convolution pass to, for tests that have to reach one of them (built by
+// conftest.py as a shared library; host code only).
+#include "../paper_1312_5853_amd/csrc/plan.h"
+
+using namespace convnet;
+
+// out: 0 fp32 kernels, 1 three-part kernels, 2 vector units; fold; splits of the reduction; rows, columns of a tile; workspace
+extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups, int dtype,
+                          long long *out)
+{
+    Problem pb;
+    const int rc = make_problem(pb, N, C / groups, H, W, K / groups, R, S, stride, pad, 0, 0, dtype);
+    if (rc != kStatusOk) return rc;
+    if (groups > 1) {
+        pb.groups = groups;
+        pb.x_bs = (int64_t)C * H * W; pb.y_bs = (int64_t)K * pb.P * pb.Q;
+        pb.x_gs = pb.x_bs / groups; pb.y_gs = pb.y_bs / groups; pb.w_gs = (int64_t)(K / groups) * (C / groups) * R * S;
+    }
+    const Plan pl = make_plan(op, pb);
+    out[0] = pl.direct ? 2 : pl.sp ? 1 : 0;
+    out[1] = pl.sp ? (pl.sp_fold > 1 ? pl.sp_fold : 1) : 1;
+    out[2] = pl.nsplit;
+    out[3] = pl.sp ? pl.sp_bm : pl.tile.bm();
+    out[4] = pl.sp ? pl.sp_bn : pl.tile.bn();
+    out[5] = (long long)pl.total;
+    return kStatusOk;
+}

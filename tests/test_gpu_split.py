@@ -241,3 +241,34 @@ def test_split_passes_tell_nan_from_values_that_only_their_first_part_makes_infi
         same_pattern(hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1))
         same_pattern(hp.conv_bwd_filter(dev(xb), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(xb, dy, 3, 3, 1, 1))
         same_pattern(hp.fc_fwd(dev(a), dev(b)), oracle.fc_fwd(a, b))
+
+
+def near_where_finite(got, ref, refabs, length):
+    """NaN and infinities where the 64-bit result has them; elsewhere the error bound of a finite input."""
+    g = got.cpu().numpy().astype(np.float64)
+    assert np.array_equal(np.isnan(g), np.isnan(ref)) and np.array_equal(g[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert (np.abs(g - ref)[fin] <= ((length / 16.0 + 24.0) * 2.0 ** -24 * refabs)[fin]).all()
+
+
+# A folded filter is padded to whole strides with zeros, under which real input lies: row 37 = 4 * 7 - 2 + 11 is under the
+# padded row of output row 7 and inside the windows of rows 8 and 9 (and 15 likewise for columns).  In sample 2 output row 7
+# ends the first tile of 256 positions, the true windows lie in the next; in sample 5 they share one.
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf, 3.4e38])
+def test_folded_forward_keeps_nan_and_infinities_inside_their_windows(value, route):
+    shape = N, C, H, W, K, R, st, pad = 12, 3, 40, 44, 96, 11, 4, 2
+    r = route(0, *shape)
+    assert r.kernels == "split" and r.fold == 4 and r.columns == 256 and 2 * 90 + 7 * 10 + 4 < 256 <= 2 * 90 + 8 * 10
+    x, w = np.abs(synth.gaussian((N, C, H, W), 981)), np.abs(synth.gaussian((K, C, R, R), 982)) + np.float32(0.5)
+    b = synth.gaussian((K,), 983)
+    refabs = oracle.conv_fwd(x, w, st, pad)
+    x[2, 1, 37, 15] = value
+    x[5, 0, 9, 9] = value
+    with np.errstate(all="ignore"):
+        ref = oracle.conv_fwd(x, w, st, pad)
+        ref = np.where(np.isinf(ref.astype(np.float32)), np.copysign(np.inf, ref), ref)
+        refabs = np.where(np.isfinite(ref), np.maximum(refabs, np.abs(ref)), refabs)
+        near_where_finite(hp.conv_fwd(dev(x), dev(w), st, pad, y=nan_like(ref.shape)), ref, refabs, C * R * R)
+        rb = ref + b.reshape(1, -1, 1, 1)
+        near_where_finite(hp.conv_fwd_bias_relu(dev(x), dev(w), dev(b), st, pad, y=nan_like(ref.shape)),
+                          np.where(rb > 0, rb, 0.0), refabs + np.abs(b).reshape(1, -1, 1, 1), C * R * R)
