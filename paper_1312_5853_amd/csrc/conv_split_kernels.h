@@ -11,29 +11,27 @@
 // error (2-norm) against 64-bit sums, 384 channels 3x3 forward: 2.7e-7; fp32 kernel 6.7e-7; with one accumulator for all
 // six products 8.1e-7.
 //
-// Range: the split is exact for |x| >= 2^-110 and for 0.  A tile with infinite sums (infinities in its inputs or an
-// overflow), or whose sums are all tiny (below 2^-80, where the parts of the inputs may have been flushed), is computed
-// again by its work-group from the fp32 tensors with the fp32 matrix instruction, so that infinities, NaN and tiny values
-// come out as fp32 arithmetic gives them.
+// Range: each operand is split as 2^24 times itself and a sum is multiplied by 2^-48 at the end, both exact, so that the parts
+// of every finite fp32 value below 2^104, subnormal ones included, are zero or normal bfloat16 numbers: small operands keep
+// all their bits, whatever lies beside them or multiplies them.  What no longer fits, operands from 2^104 and sums from 2^80
+// on, makes its sum infinite or NaN, and the work-group computes such a tile again from the fp32 tensors with the fp32 matrix
+// instruction (split_finish), so that large values, infinities and NaN come out as fp32 arithmetic gives them.
+
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// two fp32 values -> their bfloat16 parts, two to a word
+// two fp32 values -> the bfloat16 parts of 2^24 times them, two to a word
 __device__ __forceinline__ void split_pair(float a, float b, unsigned &h, unsigned &m, unsigned &l)
 {
+    a *= kSplitScale;
+    b *= kSplitScale;
     h = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
     const float a1 = a - __uint_as_float(h << 16), b1 = b - __uint_as_float(h & 0xffff0000u);
     m = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a1, b1}, bf16x2));
     const float a2 = a1 - __uint_as_float(m << 16), b2 = b1 - __uint_as_float(m & 0xffff0000u);
     l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a2, b2}, bf16x2));
-}
-
-// An input whose h part is infinite: an infinity, or a finite value that rounds to one.  Its m part is NaN.
-__device__ __forceinline__ bool split_overflows(float v)
-{
-    const unsigned u = __float_as_uint(v) & 0x7fffffffu;
-    return u >= 0x7f7f8000u && u <= 0x7f800000u;
 }
 
 // eight consecutive reduction elements -> one 16-byte piece of each part
@@ -45,49 +43,70 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
         split_pair(v[2 * t], v[2 * t + 1], h, m, l);
         o[0][t] = h; o[1][t] = m; o[2][t] = l;
     }
-    // h stays finite where the value is (and takes an infinity alone), so that the sums of h h' are NaN only where fp32's are
-    bool over = false;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) over |= split_overflows(v[k]);
-    if (over) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (!split_overflows(v[k])) continue;
-            const unsigned u = __float_as_uint(v[k]), sign = u & 0x80000000u;
-            const bool inf = (u & 0x7fffffffu) == 0x7f800000u;
-            const unsigned hb = sign | (inf ? 0x7f800000u : 0x7f7f0000u);
-            const float rest = inf ? 0.f : v[k] - __uint_as_float(hb);
-            const unsigned mb = __float_as_uint(rest) & 0xffff0000u;             // at most 16 bits are left: two parts hold them
-            const unsigned lb = __float_as_uint(rest - __uint_as_float(mb));
-            const int sh = (k & 1) * 16;
-            o[0][k >> 1] = (o[0][k >> 1] & ~(0xffffu << sh)) | (hb >> 16) << sh;
-            o[1][k >> 1] = (o[1][k >> 1] & ~(0xffffu << sh)) | (mb >> 16) << sh;
-            o[2][k >> 1] = (o[2][k >> 1] & ~(0xffffu << sh)) | (lb >> 16) << sh;
-        }
-    }
 }
 
-// What a wave's sums (hh: of h h'; low: of the smaller products) say: bit 0 some sum is infinite, bit 1 some sum is at least
-// 2^-80, bit 2 some sum is not zero, bit 3 some sum is NaN.
-template <int TM, int TN>
-__device__ __forceinline__ int split_sum_flags(const f32x16 (&hh)[TM][TN], const f32x16 (&low)[TM][TN])
+// Operands that may take part in an overflow: of fewer than 2^29 products of factors below 2^25 (2^49 as split) no sum
+// reaches 2^127.  The second: the same of an h part.
+__device__ __forceinline__ bool split_large(float v)
 {
-    unsigned top = 0;
-    bool inf = false;
+    const unsigned u = __float_as_uint(v) & 0x7fffffffu;
+    return u >= 0x4c000000u && u <= 0x7f800000u;
+}
+__device__ __forceinline__ bool split_large_part(unsigned bf16) { return bf16 >= 0x5800u && bf16 <= 0x7f80u; }
+
+// OR of the waves' flags f in every wave; `words` is LDS that nothing else is in after the first barrier
+template <int NW>
+__device__ __forceinline__ int split_group_or(int *words, int wave, int lane, int f)
+{
+    __syncthreads();
+    if (lane == 0) words[wave] = f;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) all |= words[i];
+    return uniform(all);
+}
+
+// The end of every split kernel: acc becomes the sums (in: of h h'; low: of the smaller products), and the result says
+// whether the work-group has to compute its tile again in fp32.  That is so where a sum to be stored is infinite; and where
+// one is NaN, unless a NaN operand alone made it: where scan(), which looks through this wave's share of the tile's operands,
+// finds one that may have overflowed (an overflow to both sides is NaN, and so is an operand from 2^104 on times zero).
+// Row v of block i is row0 + 32 i + 8 (v / 4) + v % 4 of `rows`.
+template <int TM, int TN, int NW, typename Scan>
+__device__ __forceinline__ bool split_finish(f32x16 (&acc)[TM][TN], const f32x16 (&low)[TM][TN], int row0, int rows,
+                                             const bool (&col_ok)[TN], int *words, int wave, int lane, Scan scan)
+{
+    float probe = 0.f;                  // NaN where some sum is not finite
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int jn = 0; jn < TN; ++jn)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const unsigned sum = __float_as_uint(hh[i][jn][v] + low[i][jn][v]) & 0x7fffffffu;
-                top = max(top, sum);
-                inf |= sum == 0x7f800000u || (__float_as_uint(hh[i][jn][v]) & 0x7fffffffu) == 0x7f800000u;
+                acc[i][jn][v] = (acc[i][jn][v] + low[i][jn][v]) * kSplitUnscale;
+                probe = fmaf(acc[i][jn][v], 0.f, probe);
             }
-    return (__ballot(inf) ? 1 : 0) | (__ballot(top >= (unsigned)(127 - 80) << 23) ? 2 : 0) | (__ballot(top > 0u) ? 4 : 0) |
-           (__ballot(top > 0x7f800000u) ? 8 : 0);
+    bool inf = false, nan = false;
+    if (__ballot(probe != 0.f)) {
+        int left = rows - row0;
+        asm("" : "+v"(left));          // or the compiler keeps the rows' numbers and masks in registers from here to the stores
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const unsigned s = __float_as_uint(acc[i][jn][v]) & 0x7fffffffu;
+                    const bool stored = col_ok[jn] && i * 32 + (v >> 2) * 8 + (v & 3) < left;
+                    inf |= stored && s == 0x7f800000u;
+                    nan |= stored && s > 0x7f800000u;
+                }
+    }
+    const int f = split_group_or<NW>(words, wave, lane, (__ballot(inf) ? 1 : 0) | (__ballot(nan) ? 2 : 0));
+    if (f & 1) return true;
+    if (!(f & 2)) return false;
+    return split_group_or<NW>(words, wave, lane, __ballot(scan()) ? 1 : 0) != 0;
 }
-__device__ __forceinline__ bool split_redo(int flags) { return (flags & 1) || ((flags & 4) && !(flags & 2)); }
 
 // ---------------------------------------------------------------------------
 // Preparation, one launch:
@@ -446,22 +465,37 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
 
     // sums that call for fp32 arithmetic: the whole work-group computes its tile again
     {
-        __syncthreads();                                        // the LDS buffers are free
-        int *const flags = reinterpret_cast<int *>(lds_fast);
-        const int f = split_sum_flags<TM, TN>(acc, low);
+        bool col_ok[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int jn = 0; jn < TN; ++jn) col_ok[jn] = n0 + (wn * TN + jn) * 32 + l32 < q.ncols;
+        auto scan = [&]() {
+            // A filter padded to whole strides has zeros over real input: there a NaN input makes a sum NaN that its window
+            // does not call for.
+            const bool padded = p.fold > 1 && (p.fR % p.fold != 0 || p.fS % p.fold != 0);
+            bool large = false;
+#pragma unroll 1
+            for (int st = step_begin; st < step_begin + nsteps; ++st) {
+                cb = (int)fastdiv((uint32_t)st, q.div_rs);
+                const int rs = st - cb * (q.R * q.S);
+                r = (int)fastdiv((uint32_t)rs, q.div_s);
+                s = rs - r * q.S;
+                begin_step_loads(0);
 #pragma unroll
-            for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
-        if (lane == 0) flags[wave] = f;
-        __syncthreads();
-        int all = 0;
+                for (int i = 0; i < NL; ++i) {
+                    const unsigned lb = lq[i] / 1024u;
+                    if (isa[i] ? lb >= BM / 32 : lb - QA >= BN / 32) continue;               // not an h part
+                    const u32x4 e = *reinterpret_cast<const u32x4 *>((isa[i] ? a_base : xs) + voff[i]);
 #pragma unroll
-        for (int i = 0; i < NW; ++i) all |= flags[i];
-        // A filter padded to whole strides has zeros over real input: a NaN or an infinity under them makes a sum NaN that its
-        // window does not call for.
-        const bool padded = p.fold > 1 && (p.fR % p.fold != 0 || p.fS % p.fold != 0);
-        if (split_redo(uniform(all)) || (padded && (uniform(all) & 8))) {
+                    for (int t = 0; t < 8; ++t) {
+                        const unsigned h = (e[t >> 1] >> (16 * (t & 1))) & 0x7fffu;
+                        large |= split_large_part(h) || (padded && !isa[i] && h > 0x7f80u);
+                    }
+                }
+            }
+            return large;
+        };
+        if (split_finish<TM, TN, NW>(acc, low, m0 + wm * TM * 32 + half * 4, p.M, col_ok, reinterpret_cast<int *>(lds_fast), wave,
+                                     lane, scan)) {
             const float *const wg = p.w + (size_t)gcol * p.w_gs;
             const float *const sg = p.src + (size_t)gcol * p.src_gs;
             int rowm[TM], hb[TN], wb[TN];

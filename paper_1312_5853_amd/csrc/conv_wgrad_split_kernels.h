@@ -297,22 +297,14 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
 
     // sums that call for fp32 arithmetic: the whole work-group computes its tile again
     {
-        __syncthreads();
-        int *const flags = reinterpret_cast<int *>(lds_fast);
-        const int f = split_sum_flags<TM, TN>(acc, low);
+        bool col_ok[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
-        if (lane == 0) flags[wave] = f;
-        __syncthreads();
-        int all = 0;
-#pragma unroll
-        for (int i = 0; i < NW; ++i) all |= flags[i];
-        // NaN sums are right unless an infinity, or a value whose h part is one, took part (its m part is NaN): look for it
-        bool redo = split_redo(uniform(all));
-        if (!redo && (uniform(all) & 8)) {
-            bool over = false;
+        for (int jn = 0; jn < TN; ++jn) {
+            int rs, ch;
+            col_ok[jn] = column(jn, rs, ch);
+        }
+        auto scan = [&]() {
+            bool large = false;
             jnext = jbeg + pos;
             for (int step = 0; step < nsteps; ++step) {
                 next_position();
@@ -321,25 +313,17 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
                     if (none[u]) continue;
                     const int plane = (isa[u] ? PQ : p.H * p.W) * 4;
                     const auto rsrc = isa[u] ? rsrc_dy : rsrc_x;
-                    const bool in = (unsigned)(hb + tap_r[u]) < (unsigned)p.H && (unsigned)(wb + tap_s[u]) < (unsigned)p.W;
-                    const unsigned v = isa[u] ? (ybase == kOutside ? kOutside : ybase + row_off[u])
-                                              : in ? xbase + (unsigned)(tap_r[u] * p.W + tap_s[u]) * 4u + row_off[u] : kOutside;
+                    piece_offset(u);
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
-                        over |= split_overflows(__builtin_bit_cast(
-                            float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, TAIL ? v + (unsigned)(k * plane) : v, TAIL ? 0 : k * plane, 0)));
+                        large |= split_large(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                 rsrc, TAIL ? voff[u] + (unsigned)(k * plane) : voff[u], TAIL ? 0 : k * plane, 0)));
                 }
             }
-            const int any = __ballot(over) ? 1 : 0;
-            __syncthreads();
-            if (lane == 0) flags[wave] = any;
-            __syncthreads();
-            int seen = 0;
-#pragma unroll
-            for (int i = 0; i < NW; ++i) seen |= flags[i];
-            redo = uniform(seen) != 0;
-        }
-        if (redo) {
+            return large;
+        };
+        if (split_finish<TM, TN, NW>(acc, low, m0 + wm * TM * 32 + half * 4, p.K, col_ok, reinterpret_cast<int *>(lds_fast), wave,
+                                     lane, scan)) {
             int tr[TN], ts[TN];
             int64_t boff[TN];
             bool bok[TN];

@@ -451,38 +451,27 @@ __global__ __launch_bounds__(kThreads, 2) void fc_split_kernel(const FcArgs p)
 
     // sums that call for fp32 arithmetic: the whole work-group computes its tile again
     {
-        __syncthreads();
-        int *const flags = reinterpret_cast<int *>(tiles);
-        const int f = split_sum_flags<TM, TN>(acc, low);
+        bool col_ok[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int jn = 0; jn < TN; ++jn) acc[i][jn] += low[i][jn];
-        if (lane == 0) flags[wave] = f;
-        __syncthreads();
-        // NaN sums are right unless an infinity, or a value whose h part is one, took part (its m part is NaN): look for it
-        const int all = uniform(flags[0] | flags[1] | flags[2] | flags[3]);
-        bool redo = split_redo(all);
-        if (!redo && (all & 8)) {
-            bool over = false;
+        for (int jn = 0; jn < TN; ++jn) col_ok[jn] = n0 + (wn * TN + jn) * 32 + l32 < p.Nc;
+        auto scan = [&]() {
+            bool large = false;
             kload = k_begin;
             moved[0] = moved[1] = 0u;
+#pragma unroll 1
             for (int step = 0; step < nsteps; ++step) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     load_quad(0, q >> 1, q & 1);
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) over |= split_overflows(st[0][q >> 1][q & 1][t]);
+                    for (int t = 0; t < 4; ++t) large |= split_large(st[0][q >> 1][q & 1][t]);
                 }
                 next_load_step();
             }
-            const int any = __ballot(over) ? 1 : 0;
-            __syncthreads();
-            if (lane == 0) flags[wave] = any;
-            __syncthreads();
-            redo = uniform(flags[0] | flags[1] | flags[2] | flags[3]) != 0;
-        }
-        if (redo) {
+            return large;
+        };
+        if (split_finish<TM, TN, 4>(acc, low, m0 + wm * TM * 32 + half * 4, p.M, col_ok, reinterpret_cast<int *>(tiles), wave,
+                                    lane, scan)) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll

@@ -272,3 +272,102 @@ def test_folded_forward_keeps_nan_and_infinities_inside_their_windows(value, rou
         rb = ref + b.reshape(1, -1, 1, 1)
         near_where_finite(hp.conv_fwd_bias_relu(dev(x), dev(w), dev(b), st, pad, y=nan_like(ref.shape)),
                           np.where(rb > 0, rb, 0.0), refabs + np.abs(b).reshape(1, -1, 1, 1), C * R * R)
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# Operands of every magnitude.  Pass: extents N, C, H, W, K, R, stride, pad (fully connected: N, I, O), the axis of each
+# operand that does not run along the reduction.  Both operands are N(0, 1) before they are scaled.
+# ---------------------------------------------------------------------------------------------------------------
+PASSES = {
+    "fwd": ((3, 96, 13, 13, 96, 3, 1, 1), 0, 0),
+    "fwd_folded": ((12, 3, 40, 44, 96, 11, 4, 2), 0, 0),
+    "bwd_data": ((3, 96, 13, 13, 96, 3, 1, 1), 0, 1),
+    "bwd_data_strided": ((6, 65, 17, 19, 64, 2, 3, 0), 0, 1),
+    "bwd_filter": ((8, 32, 13, 13, 32, 3, 1, 1), 1, 1),
+    "bwd_filter_tail": ((5, 65, 15, 17, 64, 3, 1, 1), 1, 1),
+    "fc_fwd": ((9, 260, 132), 0, 0),
+    "fc_bwd_data": ((9, 132, 260), 0, 1),
+    "fc_bwd_filter": ((70, 132, 124), 1, 1),
+}
+
+
+def pass_operands(name, route):
+    """The two operands, and a function of them: (GPU result, 64-bit result, 64-bit sum of magnitudes, reduction length)."""
+    shape = PASSES[name][0]
+    if name.startswith("fc_"):
+        N, I, O = shape
+        a, b = {"fc_fwd": ((N, I), (O, I)), "fc_bwd_data": ((N, O), (O, I)), "fc_bwd_filter": ((N, I), (N, O))}[name]
+        gpu, ref = getattr(hp, name), getattr(oracle, name)
+        length = {"fc_fwd": I, "fc_bwd_data": O, "fc_bwd_filter": N}[name]
+        more = ()
+    else:
+        N, C, H, W, K, R, st, pad = shape
+        P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+        x, w, dy = (N, C, H, W), (K, C, R, R), (N, K, P, Q)
+        op = 0 if name.startswith("fwd") else 1 if name.startswith("bwd_data") else 2
+        assert route(op, *shape).kernels == "split" and (route(op, *shape).fold > 1) == (name == "fwd_folded")
+        (a, b), more = (((x, w), (st, pad)), ((dy, w), (H, W, st, pad)), ((x, dy), (R, R, st, pad)))[op]
+        gpu, ref = ((hp.conv_fwd, oracle.conv_fwd), (hp.conv_bwd_data, oracle.conv_bwd_data),
+                    (hp.conv_bwd_filter, oracle.conv_bwd_filter))[op]
+        length = (C * R * R, K * R * R, N * P * Q)[op]
+
+    def run(a, b):
+        return gpu(dev(a), dev(b), *more), ref(a, b, *more), ref(np.abs(a), np.abs(b), *more), length
+    return synth.gaussian(a, 991), synth.gaussian(b, 992), run
+
+
+def along(t, axis, index):
+    return tuple([slice(None)] * axis + [index] + [slice(None)] * (t.ndim - axis - 1))
+
+
+def rescale(a, axis_a, b, axis_b, kind):
+    f = np.float32
+    if kind == "tiny x large":
+        return a * f(1e-37), b * f(1e18)
+    if kind == "large x tiny":
+        return a * f(1e15), b * f(1e-36)
+    if kind == "subnormal x large":
+        return a * f(1e-40), b * f(1e14)
+    if kind == "tiny beside ordinary":          # one sample, filter or channel, of both operands
+        a[along(a, axis_a, 1)] *= f(1e-37)
+        b[along(b, axis_b, 2)] *= f(1e-37)
+        a[along(a, axis_a, 2)] *= f(1e30)       # times 1e-37: sums around 1e-7
+        return a, b
+    if kind == "overflow of the accumulators":  # sums of both signs beyond 2^80
+        return a * f(1e20), b * f(1e8)
+    if kind == "large beside ordinary":
+        a[along(a, axis_a, 1)] *= f(1e34)
+        return a, b
+    raise ValueError(kind)
+
+
+KINDS = ["tiny x large", "large x tiny", "subnormal x large", "tiny beside ordinary", "overflow of the accumulators",
+         "large beside ordinary"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("name", sorted(PASSES))
+def test_split_passes_keep_fp32_precision_at_every_magnitude(name, kind, route):
+    a, b, run = pass_operands(name, route)
+    a, b = rescale(a, PASSES[name][1], b, PASSES[name][2], kind)
+    got, ref, absref, length = run(a, b)
+    # results below 2^-126 are subnormal: one rounding of at most 2^-150 per split range and one of their sum, and the fp32
+    # kernels' products on top of that (`length` of them)
+    bound = (length / 16.0 + 24.0) * 2.0 ** -24 * absref + (length + 16) * 2.0 ** -150
+    err = np.abs(got.cpu().numpy().astype(np.float64) - ref)
+    worst = float((err / bound).max())
+    assert worst <= 1.0
+
+
+@pytest.mark.parametrize("name", sorted(PASSES))
+def test_split_passes_show_nan_beside_overflowing_accumulators(name, route):
+    # everything overflows the accumulators, in one place there is a NaN: it shows where fp32 has it and nowhere else
+    a, b, run = pass_operands(name, route)
+    a, b = a * np.float32(1e20), b * np.float32(1e8)
+    a.reshape(-1)[a.size // 2 + 1] = np.nan
+    with np.errstate(all="ignore"):
+        got, ref, absref, length = run(a, b)
+    got = got.cpu().numpy().astype(np.float64)
+    nan_as_it_should, fin = np.array_equal(np.isnan(got), np.isnan(ref)), np.isfinite(ref)
+    bound = (length / 16.0 + 24.0) * 2.0 ** -24 * absref
+    assert nan_as_it_should and fin.any() and (np.abs(got - ref)[fin] <= bound[fin]).all()
