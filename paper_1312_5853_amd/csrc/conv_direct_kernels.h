@@ -32,8 +32,9 @@ template <typename TI, typename TO, int POS>
 __global__ __launch_bounds__(kDirectWaves * 64) void direct_colgemm_kernel(const DirectArgs p)
 {
     constexpr int U = 8, PER_WAVE = 64 / POS, SLICES = kDirectWaves * PER_WAVE;
-    __shared__ __attribute__((aligned(16))) float filt[kDirectMaxRed * kDirectRows];
-    __shared__ int2 taps[kDirectMaxRed];                     // source plane, r << 16 | s
+    // the element after the last is zero: what a group reads past its share, so that no infinity of another group's meets a zero
+    __shared__ __attribute__((aligned(16))) float filt[(kDirectMaxRed + 1) * kDirectRows];
+    __shared__ int2 taps[kDirectMaxRed + 1];                 // source plane, r << 16 | s
     __shared__ float sums[kDirectWaves][kDirectRows][POS];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int pos = lane % POS;
@@ -57,19 +58,23 @@ __global__ __launch_bounds__(kDirectWaves * 64) void direct_colgemm_kernel(const
         const int a = (int)fastdiv((uint32_t)g, p.div_rs), rs = g - a * p.RS;
         filt[i] = ld_elem(w, p.transposed ? (int64_t)(a * p.C + m) * p.RS + rs : (int64_t)m * p.red + g);
     }
+    if (threadIdx.x < kDirectRows) filt[p.red * kDirectRows + threadIdx.x] = 0.f;
+    if (threadIdx.x == 0) taps[p.red] = make_int2(0, 0);
     __syncthreads();
 
     const int per = (p.red + SLICES - 1) / SLICES;
     const int g0 = (wave * PER_WAVE + lane / POS) * per;
     const int base = n * p.src_bs;
     float acc[kDirectRows] = {};
+    const int g1 = min(g0 + per, p.red);
     for (int t = 0; t < per; t += U) {
         float v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int2 tap = taps[min(g0 + t + u, p.red - 1)];
+            const int g = g0 + t + u;
+            const int2 tap = taps[g < g1 ? g : p.red];
             int h = hb + (tap.y >> 16), x = wb + (int)(short)tap.y;
-            bool ok = t + u < per && g0 + t + u < p.red;
+            bool ok = g < g1;
             if (p.transposed && p.stride > 1) {
                 const int hq = (int)fastdiv((uint32_t)max(h, 0), p.div_stride), xq = (int)fastdiv((uint32_t)max(x, 0), p.div_stride);
                 ok = ok && hq * p.stride == h && xq * p.stride == x;
@@ -81,7 +86,8 @@ __global__ __launch_bounds__(kDirectWaves * 64) void direct_colgemm_kernel(const
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const f32x4 f = *reinterpret_cast<const f32x4 *>(&filt[min(g0 + t + u, p.red - 1) * kDirectRows]);
+            const int g = g0 + t + u;
+            const f32x4 f = *reinterpret_cast<const f32x4 *>(&filt[(g < g1 ? g : p.red) * kDirectRows]);
 #pragma unroll
             for (int i = 0; i < kDirectRows; ++i) acc[i] = fmaf(f[i], v[u], acc[i]);
         }

@@ -73,3 +73,23 @@ def test_direct_passes_of_two_columns_equal_the_columns_alone():
         assert torch.equal(part(y, g), hp.conv_fwd(part(x, g), wg, 1, 1))
         assert torch.equal(part(dx, g), hp.conv_bwd_data(part(dy, g), wg, 9, 9, 1, 1))
         assert torch.equal(dw[4 * g:4 * g + 4], hp.conv_bwd_filter(part(x, g), part(dy, g), 3, 3, 1, 1))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(4, 3, 32, 32, 16, 5, 1, 0), (2, 3, 9, 9, 17, 3, 1, 0), (1, 1, 11, 11, 2, 3, 1, 0)])
+def test_direct_passes_give_an_infinite_filter_value_as_an_infinity(shape, dtype, route):
+    # positive operands, one filter with one infinity, no padding: infinite wherever that value takes part, as long as no group
+    # of lanes multiplies it by the zero of an element that is not its own
+    N, C, H, W, K, R, st, pad = shape
+    for op in (0, 1):
+        assert route(op, *shape, dtype=0 if dtype == "f32" else 1).kernels == "direct"
+    P = H - R + 1
+    x, dy = np.abs(synth.gaussian((N, C, H, W), 958)) + np.float32(0.5), np.abs(synth.gaussian((N, K, P, P), 959)) + np.float32(0.5)
+    w = np.abs(synth.gaussian((K, C, R, R), 960)) + np.float32(0.5)
+    w[1, 0, R - 1, 1] = np.inf
+    y = hp.conv_fwd(dev(x, dtype), dev(w, dtype), st, pad).float().cpu().numpy()
+    filters = np.isinf(y).all(axis=(0, 2, 3))
+    assert filters[1] and filters.sum() == 1 and np.isfinite(np.delete(y, 1, 1)).all()
+    dx = hp.conv_bwd_data(dev(dy, dtype), dev(w, dtype), H, W, st, pad).float().cpu().numpy()
+    inner = dx[:, :, R - 1:P, R - 1:P]                         # positions that every tap reaches
+    assert np.isinf(inner[:, 0]).all() and np.isfinite(inner[:, 1:]).all()
