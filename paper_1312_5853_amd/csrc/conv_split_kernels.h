@@ -45,15 +45,6 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
     }
 }
 
-// Operands that may take part in an overflow: of fewer than 2^29 products of factors below 2^25 (2^49 as split) no sum
-// reaches 2^127.  The second: the same of an h part.
-__device__ __forceinline__ bool split_large(float v)
-{
-    const unsigned u = __float_as_uint(v) & 0x7fffffffu;
-    return u >= 0x4c000000u && u <= 0x7f800000u;
-}
-__device__ __forceinline__ bool split_large_part(unsigned bf16) { return bf16 >= 0x5800u && bf16 <= 0x7f80u; }
-
 // OR of the waves' flags f in every wave; `words` is LDS that nothing else is in after the first barrier
 template <int NW>
 __device__ __forceinline__ int split_group_or(int *words, int wave, int lane, int f)
@@ -67,13 +58,16 @@ __device__ __forceinline__ int split_group_or(int *words, int wave, int lane, in
     return uniform(all);
 }
 
+__device__ __forceinline__ bool is_nan_bits(unsigned u) { return (u & 0x7fffffffu) > 0x7f800000u; }
+
 // The end of every split kernel: acc becomes the sums (in: of h h'; low: of the smaller products), and the result says
 // whether the work-group has to compute its tile again in fp32.  That is so where a sum to be stored is infinite; and where
-// one is NaN, unless a NaN operand alone made it: where scan(), which looks through this wave's share of the tile's operands,
-// finds one that may have overflowed (an overflow to both sides is NaN, and so is an operand from 2^104 on times zero).
-// Row v of block i is row0 + 32 i + 8 (v / 4) + v % 4 of `rows`.
-template <int TM, int TN, int NW, typename Scan>
-__device__ __forceinline__ bool split_finish(f32x16 (&acc)[TM][TN], const f32x16 (&low)[TM][TN], int row0, int rows,
+// one is NaN without a NaN among the operands of its row or its column (sums that overflow to both sides, an operand from
+// 2^104 on times zero).  scan(rows, columns) marks those that have one, from this wave's share of the tile's operands.
+// Value v of block (i, jn) is row `row` + 32 i + 8 (v / 4) + v % 4 and column `col` + 32 jn of the tile of BM x BN; rows
+// from `rows` on are not stored.  `words`: 16 + BM + BN words of LDS that nothing is in after a barrier.
+template <int TM, int TN, int NW, int BM, int BN, typename Scan>
+__device__ __forceinline__ bool split_finish(f32x16 (&acc)[TM][TN], const f32x16 (&low)[TM][TN], int row, int rows, int col,
                                              const bool (&col_ok)[TN], int *words, int wave, int lane, Scan scan)
 {
     float probe = 0.f;                  // NaN where some sum is not finite
@@ -87,25 +81,42 @@ __device__ __forceinline__ bool split_finish(f32x16 (&acc)[TM][TN], const f32x16
                 probe = fmaf(acc[i][jn][v], 0.f, probe);
             }
     bool inf = false, nan = false;
+    int left = rows - row;
+    asm("" : "+v"(left));              // or the compiler keeps the rows' numbers and masks in registers from here to the stores
     if (__ballot(probe != 0.f)) {
-        int left = rows - row0;
-        asm("" : "+v"(left));          // or the compiler keeps the rows' numbers and masks in registers from here to the stores
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int jn = 0; jn < TN; ++jn)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const unsigned s = __float_as_uint(acc[i][jn][v]) & 0x7fffffffu;
+                    const unsigned s = __float_as_uint(acc[i][jn][v]);
                     const bool stored = col_ok[jn] && i * 32 + (v >> 2) * 8 + (v & 3) < left;
-                    inf |= stored && s == 0x7f800000u;
-                    nan |= stored && s > 0x7f800000u;
+                    inf |= stored && (s & 0x7fffffffu) == 0x7f800000u;
+                    nan |= stored && is_nan_bits(s);
                 }
     }
     const int f = split_group_or<NW>(words, wave, lane, (__ballot(inf) ? 1 : 0) | (__ballot(nan) ? 2 : 0));
     if (f & 1) return true;
     if (!(f & 2)) return false;
-    return split_group_or<NW>(words, wave, lane, __ballot(scan()) ? 1 : 0) != 0;
+    int *const marks = words + 16;
+    for (int i = wave * 64 + lane; i < BM + BN; i += NW * 64) marks[i] = 0;
+    __syncthreads();
+    scan(marks, marks + BM);
+    __syncthreads();
+    bool open = false;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) {
+            const bool here = col_ok[jn] && !marks[BM + col + jn * 32];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int d = i * 32 + (v >> 2) * 8 + (v & 3);
+                open |= here && d < left && is_nan_bits(__float_as_uint(acc[i][jn][v])) && !marks[row + d];
+            }
+        }
+    return split_group_or<NW>(words, wave, lane, __ballot(open) ? 1 : 0) != 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -468,11 +479,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
         bool col_ok[TN];
 #pragma unroll
         for (int jn = 0; jn < TN; ++jn) col_ok[jn] = n0 + (wn * TN + jn) * 32 + l32 < q.ncols;
-        auto scan = [&]() {
+        auto scan = [&](int *nan_rows, int *nan_cols) {
             // A filter padded to whole strides has zeros over real input: there a NaN input makes a sum NaN that its window
             // does not call for.
             const bool padded = p.fold > 1 && (p.fR % p.fold != 0 || p.fS % p.fold != 0);
-            bool large = false;
 #pragma unroll 1
             for (int st = step_begin; st < step_begin + nsteps; ++st) {
                 cb = (int)fastdiv((uint32_t)st, q.div_rs);
@@ -481,21 +491,19 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
                 s = rs - r * q.S;
                 begin_step_loads(0);
 #pragma unroll
-                for (int i = 0; i < NL; ++i) {
-                    const unsigned lb = lq[i] / 1024u;
-                    if (isa[i] ? lb >= BM / 32 : lb - QA >= BN / 32) continue;               // not an h part
+                for (int i = 0; i < NL; ++i) {                   // the blocks of h parts: rows b * 32 + lane / 2
+                    const int lb = (int)(lq[i] / 1024u), b = isa[i] ? lb : lb - QA;
+                    if (isa[i] ? b >= BM / 32 : b >= BN / 32 || padded) continue;
                     const u32x4 e = *reinterpret_cast<const u32x4 *>((isa[i] ? a_base : xs) + voff[i]);
+                    bool nan = false;
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        const unsigned h = (e[t >> 1] >> (16 * (t & 1))) & 0x7fffu;
-                        large |= split_large_part(h) || (padded && !isa[i] && h > 0x7f80u);
-                    }
+                    for (int t = 0; t < 4; ++t) nan |= is_nan_bits(e[t] & 0xffff0000u) || is_nan_bits(e[t] << 16);
+                    if (nan) (isa[i] ? nan_rows : nan_cols)[b * 32 + (lane >> 1)] = 1;
                 }
             }
-            return large;
         };
-        if (split_finish<TM, TN, NW>(acc, low, m0 + wm * TM * 32 + half * 4, p.M, col_ok, reinterpret_cast<int *>(lds_fast), wave,
-                                     lane, scan)) {
+        if (split_finish<TM, TN, NW, BM, BN>(acc, low, wm * TM * 32 + half * 4, p.M - m0, wn * TN * 32 + l32, col_ok,
+                                             reinterpret_cast<int *>(lds_fast), wave, lane, scan)) {
             const float *const wg = p.w + (size_t)gcol * p.w_gs;
             const float *const sg = p.src + (size_t)gcol * p.src_gs;
             int rowm[TM], hb[TN], wb[TN];

@@ -92,6 +92,10 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
     const float *const xg = p.x + (size_t)gcol * p.x_gs;
     const auto rsrc_dy = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(dyg), 0, (int)p.dy_bytes, 0x00020000);
     const auto rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(xg), 0, (int)p.x_bytes, 0x00020000);
+    auto rsrc_of = [&](bool a) {           // by value: a conditional of the two names would keep both in memory
+        if (a) return rsrc_dy;
+        return rsrc_x;
+    };
 
     // Piece u of this wave: block q = u * 8 + wave of the step (filters first), position lane % 32, rows
     // (lane / 32) * 8 .. + 7 of the block.
@@ -150,7 +154,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
     auto load_one = [&](int u, int k) {
         if (none[u]) return;
         const int plane = (isa[u] ? PQ : p.H * p.W) * 4;
-        const auto rsrc = isa[u] ? rsrc_dy : rsrc_x;
+        const auto rsrc = rsrc_of(isa[u]);
         // outside: 0x80000000 + 7 * plane stays past the extent (tensors and planes are shorter than 2^31 bytes together)
         const unsigned v = TAIL ? voff[u] + (unsigned)(k * plane) : voff[u];
         st[u][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, TAIL ? 0 : k * plane, 0));
@@ -303,27 +307,29 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
             int rs, ch;
             col_ok[jn] = column(jn, rs, ch);
         }
-        auto scan = [&]() {
-            bool large = false;
+        auto scan = [&](int *nan_rows, int *nan_cols) {
             jnext = jbeg + pos;
             for (int step = 0; step < nsteps; ++step) {
                 next_position();
 #pragma unroll
                 for (int u = 0; u < NT; ++u) {
                     if (none[u]) continue;
-                    const int plane = (isa[u] ? PQ : p.H * p.W) * 4;
-                    const auto rsrc = isa[u] ? rsrc_dy : rsrc_x;
+                    const int plane = (isa[u] ? PQ : p.H * p.W) * 4, b = u * NW + wave;
+                    const auto rsrc = rsrc_of(isa[u]);
+                    int *const mark = (isa[u] ? nan_rows + b * 16 : nan_cols + (b - QA) * 16) + oct * 8;
                     piece_offset(u);
+                    unsigned nans = 0;
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
-                        large |= split_large(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                 rsrc, TAIL ? voff[u] + (unsigned)(k * plane) : voff[u], TAIL ? 0 : k * plane, 0)));
+                        nans |= is_nan_bits(__builtin_amdgcn_raw_buffer_load_b32(rsrc, TAIL ? voff[u] + (unsigned)(k * plane) : voff[u],
+                                                                                 TAIL ? 0 : k * plane, 0)) ? 1u << k : 0u;
+                    for (int k = 0; k < 8; ++k)
+                        if (nans >> k & 1) mark[k] = 1;
                 }
             }
-            return large;
         };
-        if (split_finish<TM, TN, NW>(acc, low, m0 + wm * TM * 32 + half * 4, p.K, col_ok, reinterpret_cast<int *>(lds_fast), wave,
-                                     lane, scan)) {
+        if (split_finish<TM, TN, NW, BM, BN>(acc, low, wm * TM * 32 + half * 4, p.K - m0, wn * TN * 32 + l32, col_ok,
+                                             reinterpret_cast<int *>(lds_fast), wave, lane, scan)) {
             int tr[TN], ts[TN];
             int64_t boff[TN];
             bool bok[TN];

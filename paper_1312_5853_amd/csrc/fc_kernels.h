@@ -454,24 +454,26 @@ __global__ __launch_bounds__(kThreads, 2) void fc_split_kernel(const FcArgs p)
         bool col_ok[TN];
 #pragma unroll
         for (int jn = 0; jn < TN; ++jn) col_ok[jn] = n0 + (wn * TN + jn) * 32 + l32 < p.Nc;
-        auto scan = [&]() {
-            bool large = false;
+        auto scan = [&](int *nan_rows, int *nan_cols) {
             kload = k_begin;
             moved[0] = moved[1] = 0u;
 #pragma unroll 1
             for (int step = 0; step < nsteps; ++step) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
+                    const bool across_k = q < 2 ? AT : BT;           // four rows at one k, or four k of one row
+                    int *const mark = (q < 2 ? nan_rows : nan_cols) +
+                                      (across_k ? (lane >> 3) * 16 + (lane & 1) * 8 + (q & 1) * 4 : wave * 32 + (lane >> 1));
                     load_quad(0, q >> 1, q & 1);
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) large |= split_large(st[0][q >> 1][q & 1][t]);
+                    for (int t = 0; t < 4; ++t)
+                        if (is_nan_bits(__float_as_uint(st[0][q >> 1][q & 1][t]))) mark[across_k ? t : 0] = 1;
                 }
                 next_load_step();
             }
-            return large;
         };
-        if (split_finish<TM, TN, 4>(acc, low, m0 + wm * TM * 32 + half * 4, p.M, col_ok, reinterpret_cast<int *>(tiles), wave,
-                                    lane, scan)) {
+        if (split_finish<TM, TN, 4, BM, BN>(acc, low, wm * TM * 32 + half * 4, p.M - m0, wn * TN * 32 + l32, col_ok,
+                                            reinterpret_cast<int *>(tiles), wave, lane, scan)) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll

@@ -338,11 +338,16 @@ def rescale(a, axis_a, b, axis_b, kind):
     if kind == "large beside ordinary":
         a[along(a, axis_a, 1)] *= f(1e34)
         return a, b
+    if kind == "large x zero":
+        keep = b[along(b, axis_b, 1)] * f(1e-3)
+        b = np.zeros_like(b)
+        b[along(b, axis_b, 1)] = keep
+        return a * f(1e34), b
     raise ValueError(kind)
 
 
 KINDS = ["tiny x large", "large x tiny", "subnormal x large", "tiny beside ordinary", "overflow of the accumulators",
-         "large beside ordinary"]
+         "large beside ordinary", "large x zero"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
