@@ -22,7 +22,11 @@
  *  - All tensor pointers are DEVICE pointers owned by the caller.  The library
  *    never allocates, frees or keeps them.  Scratch memory comes from the `ws`
  *    argument (device pointer, 256-byte aligned, at least
- *    conv_workspace_bytes() bytes); its contents are undefined afterwards.
+ *    conv_workspace_bytes() bytes); its contents are undefined afterwards.  An fp32
+ *    convolution pass also takes less, down to what its kernels on the fp32
+ *    matrix instruction need (re-laid-out filters and partial sums, no copy of
+ *    the activations), and then runs on those: other kernels, so other bits, but
+ *    the same for the same workspace size.
  *  - Outputs are fully overwritten (no accumulation into the destination, every
  *    element written -- dx positions that no window touches receive 0).
  *  - dtype: CONV_DTYPE_F32  = fp32 tensors, fp32 MFMA arithmetic.
@@ -62,7 +66,7 @@ typedef enum conv_status {
                                           batch stride smaller than one sample */
     CONV_ERR_TOO_LARGE = -2,           /* a tensor span reaches 2^31 bytes */
     CONV_ERR_BAD_DTYPE = -3,
-    CONV_ERR_WORKSPACE_TOO_SMALL = -4, /* ws is NULL or ws_bytes < conv_workspace_bytes() while scratch is needed */
+    CONV_ERR_WORKSPACE_TOO_SMALL = -4, /* ws is NULL or ws_bytes too small while scratch is needed */
     CONV_ERR_MISALIGNED = -5,          /* tensor base not 16-byte aligned, or ws not 256-byte aligned */
     CONV_ERR_HIP = -6,                 /* the HIP runtime refused a launch; hipGetLastError() text via conv_last_hip_error() */
     CONV_ERR_SCRATCH_LIMIT = -7        /* conv_bwd_filter_noalloc: the pass needs more than CONV_NOALLOC_SCRATCH_BYTES */
@@ -209,7 +213,7 @@ int conv_bwd_data_relu(const void *dy, const void *w, const void *act, void *dx,
                        int dtype, void *ws, size_t ws_bytes, void *stream);
 
 /*
- * Scratch bytes the given pass needs for these extents (op = CONV_OP_*).
+ * Scratch bytes the fastest kernels of the given pass need for these extents (op = CONV_OP_*).
  * Pure host arithmetic; returns 0 for invalid arguments.  The figure depends
  * only on the arguments, never on the device or on earlier calls.
  */

@@ -566,7 +566,7 @@ int prepare(int op, const void *a, const void *b, void *out, int N, int C, int H
     int rc = make_problem(pb, N, C, H, W, K, R, S, stride, pad, x_bs, y_bs, dtype);
     if (rc != kStatusOk) return rc;
     if (!aligned(a, 16) || !aligned(b, 16) || !aligned(out, 16)) return kErrMisaligned;
-    pl = make_plan(op, pb);
+    pl = plan_for_workspace(op, pb, ws_bytes);
     if (pl.total > 0) {
         if (!ws || ws_bytes < pl.total) return kErrWorkspace;
         if (!aligned(ws, 256)) return kErrMisaligned;
@@ -1197,7 +1197,7 @@ static int run_grouped(int op, const void *a, const void *b, void *out, int N, i
     int rc = grouped_problem(pb, N, C, H, W, K, R, S, stride, pad, groups, dtype);
     if (rc != kStatusOk) return rc;
     if (!aligned(a, 16) || !aligned(b, 16) || !aligned(out, 16)) return kErrMisaligned;
-    const Plan pl = make_plan(op, pb);
+    const Plan pl = plan_for_workspace(op, pb, ws_bytes);
     if (pl.total > 0) {
         if (!ws || ws_bytes < pl.total) return kErrWorkspace;
         if (!aligned(ws, 256)) return kErrMisaligned;

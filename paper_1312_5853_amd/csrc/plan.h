@@ -294,7 +294,8 @@ inline double pick_wgrad_split(int K, int nblocks, int64_t J, int groups, int64_
     return best;
 }
 
-inline Plan make_plan(int op, const Problem &pb)
+// three_part = false: fp32 passes stay on the fp32 kernels
+inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
 {
     Plan pl = {};
     pl.op = op;
@@ -516,7 +517,7 @@ inline Plan make_plan(int op, const Problem &pb)
     // than the fp32 kernels: it needs a pass over the input (4 bytes read, 6 written per padded position and channel)
     // that layers with little work per input element do not earn back.  The estimate is per column, so that a grouped
     // layer takes the route its columns would take alone.
-    if (!pl.direct && pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) &&
+    if (three_part && !pl.direct && pb.dtype == kDtypeF32 && (op == kOpFwd || (op == kOpBwdData && pb.stride <= 4)) &&
         (Cr >= 16 || (op == kOpFwd && pb.stride <= 4 && Cr * pb.stride * pb.stride >= 16))) {
         const bool fwd = op == kOpFwd, strided = !fwd && pb.stride > 1;
         const int GF = pl.fused_groups ? G : 1;
@@ -564,7 +565,7 @@ inline Plan make_plan(int op, const Problem &pb)
     }
     // fp32 backward-filter through the bf16 matrix instruction, where that is estimated to be faster than the fp32 kernels
     // (few-channel layers pad 16 / C times) and its partial sums fit where theirs do.
-    if (!pl.direct && pb.dtype == kDtypeF32 && op == kOpBwdFilter && pb.K >= 8 && pb.C >= 8 &&
+    if (three_part && !pl.direct && pb.dtype == kDtypeF32 && op == kOpBwdFilter && pb.K >= 8 && pb.C >= 8 &&
         std::max((int64_t)pb.H * pb.W, (int64_t)pb.P * pb.Q) * 32 < kMaxSpanBytes) {
         const int GF = pl.fused_groups ? G : 1;
         const int64_t J = (int64_t)pb.N * pb.P * pb.Q, out_bytes = (int64_t)pb.K * pl.Kg * 4;
@@ -594,6 +595,16 @@ inline Plan make_plan(int op, const Problem &pb)
         }
     }
     return pl;
+}
+
+// The plan of a call that brings ws_bytes of workspace.  The three-part kernels want up to six bytes per padded input element;
+// a caller that has less, but as much as the fp32 kernels take, gets those.
+inline Plan plan_for_workspace(int op, const Problem &pb, size_t ws_bytes)
+{
+    const Plan pl = make_plan(op, pb);
+    if (!pl.sp || ws_bytes >= pl.total) return pl;
+    const Plan fp32 = make_plan(op, pb, false);
+    return ws_bytes >= fp32.total ? fp32 : pl;
 }
 
 // ---------------------------------------------------------------------------

@@ -76,6 +76,16 @@ int main()
             CHECK(make_plan(op, dense).total == make_plan(op, wide).total);
             CHECK(!make_plan(op, dense).widen && !make_plan(op, dense).widen_w && !make_plan(op, dense).patch);
         }
+    // a workspace too small for the three-part kernels but large enough for the fp32 kernels gets these, one byte less is too small
+    for (int op = kOpFwd; op <= kOpBwdFilter; ++op) {
+        if (op == kOpBwdFilter) CHECK(make_problem(pb, 7, 14, 53, 12, 63, 5, 5, 1, 2, 0, 0, 0) == kStatusOk);
+        else CHECK(make_problem(pb, 3, 96, 13, 13, 96, 3, 3, 1, 1, 0, 0, 0) == kStatusOk);
+        const Plan want = make_plan(op, pb), fp32 = make_plan(op, pb, false);
+        CHECK(want.sp && !fp32.sp && fp32.total < want.total);
+        CHECK(plan_for_workspace(op, pb, want.total).sp && !plan_for_workspace(op, pb, want.total - 1).sp);
+        CHECK(plan_for_workspace(op, pb, fp32.total).total == fp32.total);
+        CHECK(plan_for_workspace(op, pb, fp32.total - 1).total == want.total);
+    }
     // fully connected plans: GEMM views, ranges that cover the reduction exactly, argument checks
     FcPlan fp;
     CHECK(make_fc_plan(fp, kOpFwd, 128, 9216, 4096, 0) == kStatusOk);

@@ -4,9 +4,9 @@
 
 using namespace convnet;
 
-// out: 0 fp32 kernels, 1 three-part kernels, 2 vector units; fold; splits of the reduction; rows, columns of a tile; workspace
+// ws_bytes: what the call brings, or -1: as much as it wants.  out: 0 fp32 kernels, 1 three-part kernels, 2 vector units; fold; splits of the reduction; rows, columns of a tile; workspace
 extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups, int dtype,
-                          long long *out)
+                          long long ws_bytes, long long *out)
 {
     Problem pb;
     const int rc = make_problem(pb, N, C / groups, H, W, K / groups, R, S, stride, pad, 0, 0, dtype);
@@ -16,7 +16,7 @@ extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int 
         pb.x_bs = (int64_t)C * H * W; pb.y_bs = (int64_t)K * pb.P * pb.Q;
         pb.x_gs = pb.x_bs / groups; pb.y_gs = pb.y_bs / groups; pb.w_gs = (int64_t)(K / groups) * (C / groups) * R * S;
     }
-    const Plan pl = make_plan(op, pb);
+    const Plan pl = ws_bytes < 0 ? make_plan(op, pb) : plan_for_workspace(op, pb, (size_t)ws_bytes);
     out[0] = pl.direct ? 2 : pl.sp ? 1 : 0;
     out[1] = pl.sp ? (pl.sp_fold > 1 ? pl.sp_fold : 1) : 1;
     out[2] = pl.nsplit;

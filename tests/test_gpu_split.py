@@ -274,6 +274,43 @@ def test_folded_forward_keeps_nan_and_infinities_inside_their_windows(value, rou
                           np.where(rb > 0, rb, 0.0), refabs + np.abs(b).reshape(1, -1, 1, 1), C * R * R)
 
 
+# A caller that brings the workspace of the fp32 kernels, as sized before there were others, is served by them; nothing past it
+# is written.  Dense, strided, folded and grouped calls.
+@pytest.mark.parametrize("op,shape,groups", [
+    (0, (3, 96, 13, 13, 96, 3, 1, 1), 1), (0, (12, 3, 40, 44, 96, 11, 4, 2), 1), (0, (4, 192, 13, 13, 256, 3, 1, 1), 2),
+    (1, (3, 96, 13, 13, 96, 3, 1, 1), 1), (1, (6, 65, 17, 19, 64, 2, 3, 0), 1),
+    (2, (2, 75, 19, 10, 204, 3, 3, 1), 1), (2, (7, 14, 53, 12, 63, 5, 1, 2), 1),
+])
+def test_a_workspace_of_the_fp32_kernels_size_is_accepted(op, shape, groups, route):
+    N, C, H, W, K, R, st, pad = shape
+    want = route(op, *shape, groups=groups)
+    assert want.kernels == "split"
+    sizes = [b for b in range(0, want.workspace, 256) if route(op, *shape, groups=groups, workspace=b).kernels == "fp32"]
+    assert sizes, "the fp32 kernels need less here"
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    x, w, dy = (dev(synth.gaussian(s, 985 + i)) for i, s in enumerate([(N, C, H, W), (K, C // groups, R, R), (N, K, P, Q)]))
+    a, b, out = ((x, w, nan_like(dy.shape)), (dy, w, nan_like(x.shape)), (x, dy, nan_like(w.shape)))[op]
+    buf = torch.full((sizes[0] + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    name = ("conv_fwd", "conv_bwd_data", "conv_bwd_filter")[op] + ("_grouped" if groups > 1 else "")
+    more = (groups,) if groups > 1 else ()
+    call = lambda nbytes: getattr(hp.lib(), name)(a.data_ptr(), b.data_ptr(), out.data_ptr(), N, C, H, W, K, R, R, st, pad,
+                                                  *more, hp.DTYPE_F32, buf.data_ptr(), nbytes,
+                                                  torch.cuda.current_stream().cuda_stream)
+    assert call(sizes[0] - 1) == hp.ERR_WORKSPACE
+    assert call(sizes[0]) == hp.OK
+    assert bool((buf[sizes[0]:] == 0x5A).all())
+    ax, aw, ady = (t.cpu().numpy() for t in (x, w, dy))
+    cut = lambda t, g, axis: np.ascontiguousarray(np.split(t, groups, axis)[g])
+    length = (C // groups * R * R, K // groups * R * R, N * P * Q)[op]
+    for g in range(groups):
+        gx, gw, gdy = cut(ax, g, 1), cut(aw, g, 0), cut(ady, g, 1)
+        one = lambda f: ((lambda: oracle.conv_fwd(f(gx), f(gw), st, pad)), (lambda: oracle.conv_bwd_data(f(gdy), f(gw), H, W, st, pad)),
+                         (lambda: oracle.conv_bwd_filter(f(gx), f(gdy), R, R, st, pad)))[op]()
+        ref, absref = one(lambda t: t), one(np.abs)
+        err = np.abs(cut(out.cpu().numpy(), g, 0 if op == 2 else 1).astype(np.float64) - ref)
+        assert (err <= (length + 8) * 2.0 ** -24 * absref).all()                     # an fp32 sum of that length
+
+
 # ---------------------------------------------------------------------------------------------------------------
 # Operands of every magnitude.  Pass: extents N, C, H, W, K, R, stride, pad (fully connected: N, I, O), the axis of each
 # operand that does not run along the reduction.  Both operands are N(0, 1) before they are scaled.
