@@ -1485,8 +1485,7 @@ static int run_fc(int op, const void *a, const void *b, void *out, const void *b
     g.mtiles = pl.mtiles; g.ntiles = pl.ntiles; g.ksplit = pl.ksplit; g.steps_per_split = pl.steps_per_split;
     g.bias = static_cast<const float *>(bias); g.relu = relu;
     const dim3 grid(pl.mtiles * pl.ntiles * pl.ksplit), block(kThreads);
-    // 32-bit byte offsets: tensors of 2^31 bytes and more stay on the fp32 kernel
-    const bool split = (int64_t)std::max(N, O) * I < ((int64_t)1 << 29) && (int64_t)N * O < ((int64_t)1 << 29);
+    const bool split = pl.three_part;
     if (split && pl.at) hipLaunchKernelGGL((fc_split_kernel<true, true>), grid, block, 0, st, g);
     else if (split && pl.bt) hipLaunchKernelGGL((fc_split_kernel<false, true>), grid, block, 0, st, g);
     else if (split) hipLaunchKernelGGL((fc_split_kernel<false, false>), grid, block, 0, st, g);

@@ -551,7 +551,9 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
         const int mpad = round_up(pl.M, bm);
         const int64_t x_bytes = (int64_t)pb.N * GF * cb * hp * wp * 96, w_bytes = (int64_t)GF * cb * RS_ * mpad * 96;
         const int64_t limit = (int64_t)1 << 32;      // 32-bit byte offsets
-        if (us * 1.1 < fp32_us && pl.sp_ph >= 0 && pl.sp_pw >= 0 && x_bytes < limit && w_bytes < limit / 2) {
+        // (one product: the fp32 kernels round it once, the six products leave out up to 2^-23 of it; from two on the error of
+        // the fp32 kernels is the larger one)
+        if (us * 1.1 < fp32_us && (int64_t)Cr * RS > 1 && pl.sp_ph >= 0 && pl.sp_pw >= 0 && x_bytes < limit && w_bytes < limit / 2) {
             pl.sp = true;
             pl.sp_bm = bm; pl.sp_bn = bn; pl.sp_cb = cb; pl.sp_hp = (int)hp; pl.sp_wp = (int)wp; pl.sp_mpad = mpad;
             pl.chunks_per_split = ceil_div(steps, ks);
@@ -585,7 +587,7 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
         pick_wgrad_split(pb.K, RS * cb, J, GF, out_bytes, bm, ks);
         const int64_t part = (int64_t)ks * out_bytes;
         const int steps = (int)((J + 31) / 32);
-        if (us * 1.05 + 1.5 < fp32_us && (part * GF <= kWgradPartLimit || part * GF <= (int64_t)pl.total)) {
+        if (us * 1.05 + 1.5 < fp32_us && J > 1 && (part * GF <= kWgradPartLimit || part * GF <= (int64_t)pl.total)) {
             pl.sp = true;
             pl.sp_bm = bm; pl.sp_bn = 256; pl.sp_cb = cb;
             pl.chunks_per_split = 2 * ceil_div(steps, ks);       // chunks of 16 positions, two to a step
@@ -618,6 +620,7 @@ struct FcPlan {
     bool at, bt;                  // operand A / B has its rows (columns) contiguous rather than k
     int mtiles, ntiles, ksplit, steps_per_split;
     size_t part_bytes;            // ksplit > 1: partial sums [ksplit][M][Nc], the whole workspace
+    bool three_part;              // fc_split_kernel, else fc_gemm_kernel
 };
 
 inline int make_fc_plan(FcPlan &pl, int op, int N, int I, int O, int dtype)
@@ -642,6 +645,10 @@ inline int make_fc_plan(FcPlan &pl, int op, int N, int I, int O, int dtype)
     pl.ksplit = ceil_div(steps, pl.steps_per_split);
     pl.part_bytes = pl.ksplit > 1 ? (size_t)pl.ksplit * pl.M * pl.Nc * 4 : 0;
     if (tiles * pl.ksplit >= lim) return kErrTooLarge;
+    // Three parts: 32-bit byte offsets, so tensors below 2^31 bytes; and reductions of two and more.  A sum of one product is
+    // rounded once in fp32, while the six products leave out up to 2^-23 of it (2-norm error of 1024 x 768 such values 2.53e-8
+    // against 2.60e-8; of two products 2.83e-8 against 2.61e-8, of sixteen 5.5e-8 against 2.9e-8).
+    pl.three_part = pl.K > 1 && (int64_t)std::max(N, O) * I < lim / 4 && (int64_t)N * O < lim / 4;
     return kStatusOk;
 }
 

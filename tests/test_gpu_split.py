@@ -169,6 +169,17 @@ def test_split_fully_connected_keeps_fp32_precision_for_tiny_values():
     assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 260 * 2.0 ** -24 * oracle.fc_fwd(np.abs(x), np.abs(w)).max()
 
 
+# A sum of one product is that product rounded once, whichever way the extents would send it
+def test_a_single_product_is_correctly_rounded(route):
+    x, dy = synth.gaussian((1, 1000), 945), synth.gaussian((1, 252), 946)
+    assert np.array_equal(hp.fc_bwd_filter(dev(x), dev(dy)).cpu().numpy(), dy.T * x)
+    shape = 1, 397, 1, 1, 21, 1, 1, 0
+    assert route(2, *shape).kernels != "split" and route(2, 2, *shape[1:]).kernels == "split"
+    x, dy = synth.gaussian((1, 397, 1, 1), 947), synth.gaussian((1, 21, 1, 1), 948)
+    dw = hp.conv_bwd_filter(dev(x), dev(dy), 1, 1, 1, 0).cpu().numpy()
+    assert np.array_equal(dw.reshape(21, 397), dy.reshape(21, 1) * x.reshape(1, 397))
+
+
 # Strided backward-data as stride-1 passes over the residue classes: one of each stride, extents that leave input rows
 # unread, a filter smaller than the stride (classes without taps), padding of half a filter and more, odd channel counts
 @pytest.mark.parametrize("shape", [
