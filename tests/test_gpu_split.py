@@ -424,3 +424,25 @@ def test_split_passes_show_nan_beside_overflowing_accumulators(name, route):
     nan_as_it_should, fin = np.array_equal(np.isnan(got), np.isnan(ref)), np.isfinite(ref)
     bound = (length / 16.0 + 24.0) * 2.0 ** -24 * absref
     assert nan_as_it_should and fin.any() and (np.abs(got - ref)[fin] <= bound[fin]).all()
+
+
+def test_fully_connected_tensors_of_two_gib_run_on_the_fp32_kernel():
+    # 4096 x 131072 weights are 2^31 bytes: past the 32-bit offsets of the three-part kernel, all three passes
+    N, I, O = 3, 131072, 4096
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(949)
+    draw = lambda *shape: torch.empty(shape, device="cuda").normal_(0.0, 1.0, generator=gen)
+    x, w, dy, b = draw(N, I), draw(O, I), draw(N, O), draw(O)
+    ws = hp.Workspace("cuda")
+    y, dx, dw = hp.fc_fwd(x, w, b, ws=ws), hp.fc_bwd_data(dy, w, ws=ws), hp.fc_bwd_filter(x, dy, ws=ws)
+    worst = lambda got, ref, absref, length: float(((got.double() - ref).abs() / ((length + 8) * 2.0 ** -24 * absref)).max())
+    x64, dy64 = x.double(), dy.double()
+    dx_ref, dx_abs = torch.zeros_like(x64), torch.zeros_like(x64)
+    for o in range(0, O, 256):
+        wc, dyc = w[o:o + 256].double(), dy64[:, o:o + 256]
+        ref, absref = x64 @ wc.t() + b[o:o + 256].double(), x64.abs() @ wc.abs().t() + b[o:o + 256].double().abs()
+        assert worst(y[:, o:o + 256], ref, absref, I) <= 1.0
+        assert worst(dw[o:o + 256], dyc.t() @ x64, dyc.abs().t() @ x64.abs(), N) <= 1.0
+        dx_ref += dyc @ wc
+        dx_abs += dyc.abs() @ wc.abs()
+    assert worst(dx, dx_ref, dx_abs, O) <= 1.0
