@@ -8,6 +8,7 @@ fallback path.
 """
 import ctypes
 import functools
+import operator
 import os
 
 import torch
@@ -119,10 +120,30 @@ def status_string(status):
 
 
 # The two questions below have answers that depend on their arguments alone and cost as much host time as a launch: a
-# training loop asks them for the same few layers on every step.  Bounded; lru_cache is safe between threads.
+# training loop asks them for the same few layers on every step.  Bounded; lru_cache is safe between threads.  The keys are
+# plain ints: whatever else stands for a whole number (a 0-d array, which has no hash, or a 0-d tensor, whose hash is its
+# identity) is turned into one first, in the public functions here and for the scalars of a call in `_whole`.
 @functools.lru_cache(maxsize=1024, typed=True)
-def workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype=DTYPE_F32):
+def _workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype):
     return int(lib().conv_workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype))
+
+
+@functools.lru_cache(maxsize=1024, typed=True)
+def _out_extent(size, filt, stride, pad):
+    return int(lib().conv_output_extent(size, filt, stride, pad))
+
+
+def _whole(*values):
+    return tuple(map(operator.index, values))
+
+
+def workspace_bytes(op, N, C, H, W, K, R, S, stride, pad, dtype=DTYPE_F32):
+    return _workspace_bytes(*_whole(op, N, C, H, W, K, R, S, stride, pad, dtype))
+
+
+def out_extent(size, filt, stride, pad):
+    """P or Q of a layer, asked of the library (conv_output_extent)."""
+    return _out_extent(*_whole(size, filt, stride, pad))
 
 
 def _stream_handle(stream):
@@ -145,12 +166,6 @@ def _dtype_of(t):
     if t.dtype == torch.bfloat16:
         return DTYPE_BF16
     raise TypeError("unsupported tensor dtype %s" % t.dtype)
-
-
-@functools.lru_cache(maxsize=1024, typed=True)
-def out_extent(size, filt, stride, pad):
-    """P or Q of a layer, asked of the library (conv_output_extent)."""
-    return int(lib().conv_output_extent(size, filt, stride, pad))
 
 
 class Workspace:
@@ -181,7 +196,7 @@ def _ws(ws):
 
 
 def _run(name, op, a, b, out, dims, x_bs, y_bs, dtype, ws, stream):
-    need = workspace_bytes(op, *dims, dtype)
+    need = _workspace_bytes(op, *dims, dtype)
     buf, nbytes = _ws(ws).get(need)
     wsp = buf.data_ptr() if buf is not None else 0
     if x_bs or y_bs:
@@ -219,11 +234,13 @@ def _io_dtype(src, out):
 def conv_fwd(x, w, stride, pad, y=None, ws=None, stream=None, out_bf16=False):
     """x [N,C,H,W], w [K,C,R,S] -> y [N,K,P,Q], fp32 (or bfloat16: pass a bfloat16 y, or out_bf16=True, with
     bfloat16 inputs).  x and y may be channel slices of wider NCHW tensors (their batch strides are passed on)."""
+    if not (type(stride) is type(pad) is int):
+        stride, pad = _whole(stride, pad)
     N, C, H, W = x.shape
     K, Cw, R, S = w.shape
     if C != Cw or not w.is_contiguous():
         raise ValueError("filter tensor does not match the input")
-    P, Q = out_extent(H, R, stride, pad), out_extent(W, S, stride, pad)
+    P, Q = _out_extent(H, R, stride, pad), _out_extent(W, S, stride, pad)
     if y is None:
         y = torch.empty((N, K, P, Q), dtype=torch.bfloat16 if out_bf16 else torch.float32, device=x.device)
     dims = (N, C, H, W, K, R, S, stride, pad)
@@ -232,6 +249,8 @@ def conv_fwd(x, w, stride, pad, y=None, ws=None, stream=None, out_bf16=False):
 
 def conv_bwd_data(dy, w, H, W, stride, pad, dx=None, ws=None, stream=None, out_bf16=False):
     """dy [N,K,P,Q], w [K,C,R,S] -> dx [N,C,H,W] fp32 or bfloat16 (H, W: the layer's input extent)."""
+    if not (type(H) is type(W) is type(stride) is type(pad) is int):
+        H, W, stride, pad = _whole(H, W, stride, pad)
     N = dy.shape[0]
     K, C, R, S = w.shape
     if dy.shape[1] != K or not w.is_contiguous():
@@ -251,19 +270,21 @@ def _dense(*ts):
 
 def conv_fwd_bias_relu(x, w, bias, stride, pad, relu=True, y=None, ws=None, stream=None, out_bf16=False):
     """y = relu(conv_fwd(x, w) + bias[k]) in one call (bias: fp32 [K] or None; relu=False leaves the sum as it is)."""
+    if not (type(stride) is type(pad) is int):
+        stride, pad = _whole(stride, pad)
     N, C, H, W = x.shape
     K, Cw, R, S = w.shape
     if C != Cw:
         raise ValueError("filter tensor does not match the input")
     if bias is not None and (bias.dtype != torch.float32 or bias.numel() != K):
         raise ValueError("bias must hold one fp32 value per filter")
-    P, Q = out_extent(H, R, stride, pad), out_extent(W, S, stride, pad)
+    P, Q = _out_extent(H, R, stride, pad), _out_extent(W, S, stride, pad)
     if y is None:
         y = torch.empty((N, K, P, Q), dtype=torch.bfloat16 if out_bf16 else torch.float32, device=x.device)
     _dense(x, w, bias, y)
     dims = (N, C, H, W, K, R, S, stride, pad)
     dtype = _io_dtype(x, y)
-    buf, nbytes = _ws(ws).get(workspace_bytes(OP_FWD, *dims, dtype))
+    buf, nbytes = _ws(ws).get(_workspace_bytes(OP_FWD, *dims, dtype))
     wsp = buf.data_ptr() if buf is not None else 0
     bp = _ptr(bias) if bias is not None else 0
     rc = lib().conv_fwd_bias_relu(_ptr(x), _ptr(w), bp, _ptr(y), *dims, 1 if relu else 0, dtype, wsp, nbytes,
@@ -276,6 +297,8 @@ def conv_fwd_bias_relu(x, w, bias, stride, pad, relu=True, y=None, ws=None, stre
 def conv_bwd_data_relu(dy, w, act, stride, pad, dx=None, ws=None, stream=None):
     """dx = conv_bwd_data(dy, w) where act > 0, else 0 (act [N,C,H,W]: output or input of the ReLU that feeds this
     layer, element type of dx)."""
+    if not (type(stride) is type(pad) is int):
+        stride, pad = _whole(stride, pad)
     N, C, H, W = act.shape
     K, Cw, R, S = w.shape
     if dy.shape[1] != K or Cw != C:
@@ -287,7 +310,7 @@ def conv_bwd_data_relu(dy, w, act, stride, pad, dx=None, ws=None, stream=None):
     _dense(dy, w, act, dx)
     dims = (N, C, H, W, K, R, S, stride, pad)
     dtype = _io_dtype(dy, dx)
-    buf, nbytes = _ws(ws).get(workspace_bytes(OP_BWD_DATA, *dims, dtype))
+    buf, nbytes = _ws(ws).get(_workspace_bytes(OP_BWD_DATA, *dims, dtype))
     wsp = buf.data_ptr() if buf is not None else 0
     rc = lib().conv_bwd_data_relu(_ptr(dy), _ptr(w), _ptr(act), _ptr(dx), *dims, dtype, wsp, nbytes,
                                   _stream_handle(stream))
@@ -298,6 +321,8 @@ def conv_bwd_data_relu(dy, w, act, stride, pad, dx=None, ws=None, stream=None):
 
 def conv_bwd_filter(x, dy, R, S, stride, pad, dw=None, ws=None, stream=None):
     """x [N,C,H,W], dy [N,K,P,Q] -> dw [K,C,R,S] fp32."""
+    if not (type(R) is type(S) is type(stride) is type(pad) is int):
+        R, S, stride, pad = _whole(R, S, stride, pad)
     N, C, H, W = x.shape
     K = dy.shape[1]
     if dw is None:
@@ -337,11 +362,13 @@ def _run_grouped(name, op, a, b, out, dims, groups, dtype, ws, stream):
 
 def conv_fwd_grouped(x, w, stride, pad, groups, y=None, ws=None, stream=None, out_bf16=False):
     """x [N,C,H,W], w [K,C/groups,R,S] -> y [N,K,P,Q]: column g's filters read column g's channels only."""
+    if not (type(stride) is type(pad) is int):
+        stride, pad = _whole(stride, pad)
     N, C, H, W = x.shape
     K, Cg, R, S = w.shape
     if Cg * groups != C or K % groups:
         raise ValueError("filter tensor does not match the input and the group count")
-    P, Q = out_extent(H, R, stride, pad), out_extent(W, S, stride, pad)
+    P, Q = _out_extent(H, R, stride, pad), _out_extent(W, S, stride, pad)
     if y is None:
         y = torch.empty((N, K, P, Q), dtype=torch.bfloat16 if out_bf16 else torch.float32, device=x.device)
     return _run_grouped("conv_fwd_grouped", OP_FWD, x, w, y, (N, C, H, W, K, R, S, stride, pad), groups,

@@ -93,3 +93,20 @@ def test_direct_passes_give_an_infinite_filter_value_as_an_infinity(shape, dtype
     dx = hp.conv_bwd_data(dev(dy, dtype), dev(w, dtype), H, W, st, pad).float().cpu().numpy()
     inner = dx[:, :, R - 1:P, R - 1:P]                         # positions that every tap reaches
     assert np.isinf(inner[:, 0]).all() and np.isfinite(inner[:, 1:]).all()
+
+
+def test_calls_take_whole_number_objects_and_read_them_anew():
+    x, w, dy = (dev(synth.gaussian(s, 963 + i), "f32") for i, s in enumerate([(2, 3, 9, 9), (4, 3, 3, 3), (2, 4, 9, 9)]))
+    st, pad, nine = torch.tensor(2), np.array(1), np.array(9)
+    assert torch.equal(hp.conv_fwd(x, w, st, pad), hp.conv_fwd(x, w, 2, 1))
+    st.fill_(1)
+    assert torch.equal(hp.conv_fwd(x, w, st, pad), hp.conv_fwd(x, w, 1, 1))
+    assert torch.equal(hp.conv_fwd_bias_relu(x, w, None, st, pad), hp.conv_fwd_bias_relu(x, w, None, 1, 1))
+    assert torch.equal(hp.conv_bwd_data(dy, w, nine, nine, st, pad), hp.conv_bwd_data(dy, w, 9, 9, 1, 1))
+    assert torch.equal(hp.conv_bwd_data_relu(dy, w, x, st, pad), hp.conv_bwd_data_relu(dy, w, x, 1, 1))
+    three = np.array(3)
+    assert torch.equal(hp.conv_bwd_filter(x, dy, three, three, st, pad), hp.conv_bwd_filter(x, dy, 3, 3, 1, 1))
+    with pytest.raises(TypeError):
+        hp.conv_fwd(x, w, 1.0, 1)
+    x, w = dev(synth.gaussian((2, 4, 8, 8), 966), "f32"), dev(synth.gaussian((4, 2, 3, 3), 967), "f32")
+    assert torch.equal(hp.conv_fwd_grouped(x, w, st, pad, 2), hp.conv_fwd_grouped(x, w, 1, 1, 2))

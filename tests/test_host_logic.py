@@ -316,3 +316,19 @@ def test_fc_and_sgd_argument_checks(lib):
     assert lib.sgd_update_multi(ptrs, ptrs, ptrs, neg, 2, f(0.1), f(0), f(0), f(1), None) == b.ERR_INVALID_ARG
     assert lib.sgd_update_multi(ptrs, odd, ptrs, cnt, 2, f(0.1), f(0), f(0), f(1), None) == b.ERR_MISALIGNED
     assert lib.sgd_update_multi(None, None, None, None, 0, f(0.1), f(0), f(0), f(1), None) == b.OK
+
+
+def test_extents_given_as_whole_number_objects(lib):
+    """A 0-d array has no hash and a 0-d tensor hashes by its identity: both are read anew on every call."""
+    import numpy as np
+    import torch
+    from paper_1312_5853_amd import binding as b
+    assert b.out_extent(np.array(32), 5, np.int64(1), 2) == 32
+    size = torch.tensor(32)
+    assert b.out_extent(size, 5, 1, 2) == 32
+    size.fill_(10)
+    assert b.out_extent(size, 5, 1, 2) == 10
+    dims = [2, 16, 8, 8, 16, 3, 3, 1]
+    assert b.workspace_bytes(0, *dims, np.array(1)) == b.workspace_bytes(0, *dims, 1) == b.workspace_bytes(0, *dims, pad=1, dtype=0)
+    with pytest.raises(TypeError):
+        b.out_extent(32.0, 5, 1, 2)
