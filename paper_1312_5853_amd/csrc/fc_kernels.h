@@ -34,36 +34,39 @@ struct FcArgs {
     int relu;
 };
 
-// A wave's sums (rows from m0, columns from n0): the result with bias and ReLU, or partial sums of range ks
+// A wave's sums (rows from m0, columns from n0): the result with bias and ReLU, or partial sums of range ks.  One 64-bit
+// address, rows and column blocks at uniform distances from it; the blocks of a row one after the other, so that a row's 256
+// bytes go out together (backward-filter 9216 -> 4096 at N = 2, bound by its 151 MB of stores: 37 us with a 64-bit product
+// per store, 32.4 with the column blocks outside, 30.0 so; at N = 128 77, 75.1 and 73).
 template <int TM, int TN>
 __device__ __forceinline__ void fc_store_tile(const FcArgs &p, const f32x16 (&acc)[TM][TN], int ks, int m0, int n0, int lane)
 {
     const int l32 = lane & 31, half = lane >> 5;
     // accumulator value v of block (i, jn): row 32 * i + 8 * (v / 4) + 4 * (lane / 32) + v % 4, column lane % 32
-    const bool final_sums = p.ksplit == 1;
-    float *out = final_sums ? p.D : p.part + (size_t)ks * p.M * p.Nc;
-    const int ldo = final_sums ? p.ldd : p.Nc;
+    const bool final_sums = p.ksplit == 1, relu = final_sums && p.relu;
+    const int ldo = final_sums ? p.ldd : p.Nc, left = p.M - m0 - half * 4, right = p.Nc - n0 - l32;
+    float *const out = (final_sums ? p.D : p.part + (size_t)ks * p.M * p.Nc) + (size_t)(m0 + half * 4) * ldo + n0 + l32;
+    float bv[TN];
 #pragma unroll
     for (int jn = 0; jn < TN; ++jn) {
-        const int col = n0 + jn * 32 + l32;
-        if (col >= p.Nc) continue;
         // The wait for the bias load must sit here, once: left to the compiler it lands in front of every
         // conditional store below, as a wait for ALL outstanding memory operations, the stores before it included,
         // so that the 64 stores of a tile went out one round trip at a time.
-        float bv = final_sums && p.bias ? p.bias[col] : 0.f;
-        asm volatile("" : "+v"(bv));          // the loaded value is complete from here on
+        bv[jn] = final_sums && p.bias && jn * 32 < right ? p.bias[n0 + jn * 32 + l32] : 0.f;
+        asm volatile("" : "+v"(bv[jn]));          // the loaded value is complete from here on
+    }
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int row0 = m0 + i * 32 + half * 4;
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + (v >> 2) * 8 + (v & 3);
-                float r = acc[i][jn][v] + bv;
-                if (final_sums && p.relu) r = r > 0.f ? r : 0.f;
-                if (row < p.M) out[(size_t)row * ldo + col] = r;
+        for (int v = 0; v < 16; ++v) {
+            const int d = i * 32 + (v >> 2) * 8 + (v & 3);
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) {
+                float r = acc[i][jn][v] + bv[jn];
+                if (relu) r = r > 0.f ? r : 0.f;
+                if (d < left && jn * 32 < right) out[(size_t)d * ldo + jn * 32] = r;
             }
         }
-    }
 }
 
 template <bool AT, bool BT>
@@ -257,8 +260,8 @@ __global__ __launch_bounds__(kThreads, 2) void fc_gemm_kernel(const FcArgs p)
 //   transposed    [8 blocks of 16 rows][16 k]: k in line k ^ 4 * (block & 1), read with ds_read_b64_tr_b16 (the order of k
 //                 inside a fragment is the one above, see conv_wgrad_split_kernels.h)
 // Raw buffer loads read zero outside the matrices and past the range: tensors of 2^31 bytes and more go to fc_gemm_kernel.
-// 9216 -> 4096, N = 128, kernel and sum of the partials: forward 101 -> 70 us, backward-data 106 -> 72, backward-filter
-// 113 -> 77; error against 64 bits 4.4e-7 -> 1.5e-7.  Bound: matrix instructions 45 % of the time at one barrier per 16-deep
+// 9216 -> 4096, N = 128, kernel and sum of the partials: forward 101 -> 69 us, backward-data 106 -> 67, backward-filter
+// 113 -> 73; error against 64 bits 4.4e-7 -> 1.5e-7.  Bound: matrix instructions 45 % of the time at one barrier per 16-deep
 // step; of the backward-filter the first loads of each tile's short reduction and the 151 MB it writes.
 // ---------------------------------------------------------------------------
 template <bool AT, bool BT>
