@@ -947,30 +947,41 @@ __global__ __launch_bounds__(256) void pack_lin(const PackLinArgs a)
                    a.Jx, a.x_bs, a.div_jx, a.div_wq);
 }
 
-// dw[k][c][rs] = part[0][k][rs*C + c] + part[1][k][rs*C + c] + ...  (fixed order)
+// dw[k][c][rs] = sum over the splits of part[t][k][rs*C + c], in a fixed order: 64 outputs per work-group, lane group g of
+// four adds the splits g, g + 4, g + 8, ... in ascending order, eight loads in flight, then the groups' sums are added in order.
+// (One chain per output was bound by its latency where many splits meet few outputs: 356 x 61 1x1, 74 splits, 18.6 -> 4.0 us.)
 // groups > 1: K filters per column; the partials of column g follow those of column g - 1, dw holds the columns'
 // filters one after the other
-// (one thread per output word: a thread per (k, c) plane that loops over the taps and splits reads and writes
-// better-shaped runs but has 54 dependent loads in a row and was 4-10 times slower)
-__global__ void finish_wgrad(const float *__restrict__ part, float *__restrict__ dw, int K, int C, int RS,
-                             int nsplit, int groups, FastDiv div_kcols, FastDiv div_cols, FastDiv div_c)
+__global__ __launch_bounds__(256) void finish_wgrad(const float *__restrict__ part, float *__restrict__ dw, int K, int C, int RS,
+                                                   int nsplit, int groups, FastDiv div_kcols, FastDiv div_cols, FastDiv div_c)
 {
+    __shared__ float sums[4][64];
     const int ncols = RS * C;
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= groups * K * ncols) return;
+    const int o = threadIdx.x & 63, g = threadIdx.x >> 6;
+    int i = blockIdx.x * 64 + o;
+    const bool in = i < groups * K * ncols;
+    if (!in) i = 0;
     const int gcol = (int)fastdiv((uint32_t)i, div_kcols);
     i -= gcol * (K * ncols);
     part += (size_t)gcol * nsplit * K * ncols;
+    float s = 0.f;
+    if (g < nsplit) {
+        s = part[(size_t)g * K * ncols + i];
+#pragma unroll 8
+        for (int t = g + 4; t < nsplit; t += 4) s += part[(size_t)t * K * ncols + i];
+    }
+    sums[g][o] = s;
+    __syncthreads();
+    if (g != 0 || !in) return;
+    for (int t = 1; t < min(nsplit, 4); ++t) s += sums[t][o];
     dw += (size_t)gcol * K * ncols;
     const int k = (int)fastdiv((uint32_t)i, div_cols), col = i - k * ncols;
     const int rs = (int)fastdiv((uint32_t)col, div_c), c = col - rs * C;
-    float s = part[i];
-    for (int t = 1; t < nsplit; ++t) s += part[(size_t)t * K * ncols + i];
     dw[((size_t)k * C + c) * RS + rs] = s;
 }
 
 // The same for a channel count that is a multiple of four: a thread adds four consecutive columns (one tap, four
-// channels) of all splits with 16-byte loads, in the same order as above, and stores the four words.
+// channels) of all splits with 16-byte loads, in ascending order, and stores the four words.
 __global__ __launch_bounds__(256) void finish_wgrad_x4(const float *__restrict__ part, float *__restrict__ dw, int K,
                                                         int C, int RS, int nsplit, int groups, FastDiv div_kquads,
                                                         FastDiv div_quads, FastDiv div_c)
@@ -994,7 +1005,7 @@ __global__ __launch_bounds__(256) void finish_wgrad_x4(const float *__restrict__
 }
 
 // The same for few splits: a work-group adds up to 64 channels of one filter under all taps, four consecutive columns per
-// thread with 16-byte loads, eight splits in flight, in the same order as above, and turns them through LDS, so that dw is
+// thread with 16-byte loads, eight splits in flight, in the same order, and turns them through LDS, so that dw is
 // written in runs of 64 * R*S words (above: one word per channel, R*S words apart).  384 x 384 3x3, six splits: 15.7 -> 9.0 us;
 // 256 x 384, nine splits: 11.9 -> 6.8 us.  Bound: the partial sums it reads.
 constexpr int kFinishChannels = 64;

@@ -474,7 +474,7 @@ int launch_finish_wgrad(const float *part, float *dw, int K, int C, int RS, int 
                            make_fastdiv((uint32_t)C));
     } else {
         const int count = groups * K * ncols;
-        hipLaunchKernelGGL(finish_wgrad, dim3(grid1d(count, 256)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
+        hipLaunchKernelGGL(finish_wgrad, dim3(grid1d(count, 64)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
                            make_fastdiv((uint32_t)(K * ncols)), make_fastdiv((uint32_t)ncols), make_fastdiv((uint32_t)C));
     }
     return check_launch();

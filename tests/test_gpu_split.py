@@ -101,6 +101,13 @@ WGRAD_SHAPES = [
     (6, 9, 30, 31, 10, 3, 3, 0),
     (37, 48, 11, 9, 96, 4, 1, 2),
     (33, 128, 13, 13, 144, 3, 1, 1),
+    # partial sums of channel counts that are no multiple of four: 1, 2, 3, 4, 5 and 74 splits
+    (2, 113, 6, 4, 56, 3, 1, 1),
+    (9, 113, 6, 20, 187, 1, 2, 0),
+    (6, 49, 16, 19, 105, 3, 2, 1),
+    (10, 45, 18, 3, 94, 3, 1, 1),
+    (2, 61, 19, 17, 106, 3, 1, 1),
+    (28, 61, 30, 14, 356, 1, 1, 0),
 ]
 
 
