@@ -1004,33 +1004,36 @@ __global__ __launch_bounds__(256) void finish_wgrad_x4(const float *__restrict__
     out[0] = s[0]; out[RS] = s[1]; out[2 * RS] = s[2]; out[3 * RS] = s[3];
 }
 
-// The same for few splits: a work-group adds up to 64 channels of one filter under all taps, four consecutive columns per
-// thread with 16-byte loads, eight splits in flight, in the same order, and turns them through LDS, so that dw is
-// written in runs of 64 * R*S words (above: one word per channel, R*S words apart).  384 x 384 3x3, six splits: 15.7 -> 9.0 us;
-// 256 x 384, nine splits: 11.9 -> 6.8 us.  Bound: the partial sums it reads.
+// The same for few splits: a work-group adds up to 64 channels of one filter under all taps, V consecutive columns per
+// thread (4, with 16-byte loads, where the channel count allows; else 1), eight splits in flight, in ascending order, and turns
+// them through LDS, so that dw is written in runs of 64 * R*S words (above: one word per channel, R*S words apart).  384 x 384
+// 3x3, six splits: 15.7 -> 9.0 us; 256 x 384, nine splits: 11.9 -> 6.8 us; 304 x 201 7x7, one split: 17 -> 10 us.  Bound: the
+// partial sums it reads.
 constexpr int kFinishChannels = 64;
+template <int V>
 __global__ __launch_bounds__(256) void finish_wgrad_turn(const float *__restrict__ part, float *__restrict__ dw, int K,
                                                         int C, int RS, int nsplit, int cblocks, FastDiv div_kblocks,
                                                         FastDiv div_cblocks)
 {
+    typedef float vec __attribute__((ext_vector_type(V)));
     extern __shared__ float turned[];                      // [channel][R*S]
     const int ncols = RS * C;
     int b = blockIdx.x;
     const int gcol = (int)fastdiv((uint32_t)b, div_kblocks);
     b -= gcol * (K * cblocks);
     const int k = (int)fastdiv((uint32_t)b, div_cblocks), c0 = (b - k * cblocks) * kFinishChannels;
-    const int nc = min(C - c0, kFinishChannels), quads = nc / 4;
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(part + (size_t)gcol * nsplit * K * ncols + (size_t)k * ncols + c0);
-    const size_t split_quads = (size_t)K * (ncols / 4);
-    for (int i = threadIdx.x; i < RS * (kFinishChannels / 4); i += 256) {
-        const int rs = i / (kFinishChannels / 4), q = i % (kFinishChannels / 4);
-        if (q >= quads) continue;
-        const f32x4 *e = src + (size_t)rs * (C / 4) + q;
-        f32x4 s = e[0];
+    const int nc = min(C - c0, kFinishChannels), pieces = nc / V;
+    const vec *src = reinterpret_cast<const vec *>(part + (size_t)gcol * nsplit * K * ncols + (size_t)k * ncols + c0);
+    const size_t split_pieces = (size_t)K * (ncols / V);
+    for (int i = threadIdx.x; i < RS * (kFinishChannels / V); i += 256) {
+        const int rs = i / (kFinishChannels / V), q = i % (kFinishChannels / V);
+        if (q >= pieces) continue;
+        const vec *e = src + (size_t)rs * (C / V) + q;
+        vec s = e[0];
 #pragma unroll 8
-        for (int t = 1; t < nsplit; ++t) s += e[t * split_quads];
+        for (int t = 1; t < nsplit; ++t) s += e[t * split_pieces];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) turned[(q * 4 + t) * RS + rs] = s[t];
+        for (int t = 0; t < V; ++t) turned[(q * V + t) * RS + rs] = s[t];
     }
     __syncthreads();
     float *out = dw + ((size_t)gcol * K + k) * ncols + (size_t)c0 * RS;

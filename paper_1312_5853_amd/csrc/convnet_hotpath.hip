@@ -464,9 +464,10 @@ int launch_finish_wgrad(const float *part, float *dw, int K, int C, int RS, int 
     // wants every thread of the chip (two columns of 48 channels 5x5, 49 splits: 6.8 us flat, 8.6 turned)
     const int cblocks = ceil_div(C, kFinishChannels);
     const size_t lds = (size_t)std::min(C, kFinishChannels) * RS * 4;
-    if (quads && nsplit <= 12 && lds <= 64 * 1024 && groups * K * cblocks >= 512) {
-        hipLaunchKernelGGL(finish_wgrad_turn, dim3(groups * K * cblocks), dim3(256), lds, st, part, dw, K, C, RS, nsplit,
-                           cblocks, make_fastdiv((uint32_t)(K * cblocks)), make_fastdiv((uint32_t)cblocks));
+    if (nsplit <= 12 && lds <= 64 * 1024 && groups * K * cblocks >= 512) {
+        hipLaunchKernelGGL(quads ? finish_wgrad_turn<4> : finish_wgrad_turn<1>, dim3(groups * K * cblocks), dim3(256), lds, st,
+                           part, dw, K, C, RS, nsplit, cblocks, make_fastdiv((uint32_t)(K * cblocks)),
+                           make_fastdiv((uint32_t)cblocks));
     } else if (quads) {
         const int count = groups * K * (ncols / 4);
         hipLaunchKernelGGL(finish_wgrad_x4, dim3(grid1d(count, 256)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
