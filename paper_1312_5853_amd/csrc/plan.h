@@ -214,20 +214,24 @@ inline ClassGrid class_grid(bool fwd, int out, int taps, int stride, int pad, in
     return g;
 }
 
-// Tile, split count and time estimate (us, returned) of the three-part fp32 kernel for one column of `steps` steps;
-// `groups` columns share the launch.  The split count decides the order of the sums, so it must not depend on how many
-// columns run together: it is chosen for one column, the tile width (which changes no sum) for all of them.
-//   Rows per tile: what pads M least, ties to the taller tile.
+// Rows of a tile: what pads `rows` least, ties to the taller tile
+inline int least_padding(int rows)
+{
+    int bm = 128;
+    for (int b : {96, 64, 32})
+        if (round_up(rows, b) < round_up(rows, bm)) bm = b;
+    return bm;
+}
+
+// Width, split count and time estimate (us, returned) of the three-part fp32 kernel on tiles of bm rows for one column of
+// `steps` steps; `groups` columns share the launch.  The split count decides the order of the sums, so it must not depend on
+// how many columns run together: it is chosen for one column, the tile width (which changes no sum) for all of them.
 //   Time of a round: steps x matrix time of a tile (six products, 4096 FLOP per clock and CU, about 0.75 of it reached)
-//   plus 3 us for the first loads and the stores, which nothing hides with one work-group per CU.
+//   plus 3 us for the first loads and the stores, which nothing hides with one work-group per CU; `weight` times the former.
 //   Splits are powers of two (a coarse grid: small shards of a mini-batch then take the same split and give the same
 //   bits), of at least 12 steps.  A split adds the launch that sums the partial outputs and their traffic (about 4.5 MB per us).
-inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &bm, int &bn, int &ksplit)
+inline double split_tile_time(int M, int64_t ncols, int steps, int groups, int bm, double weight, int &bn, int &ksplit)
 {
-    const int rows[4] = {128, 96, 64, 32};
-    bm = rows[0];
-    for (int i = 1; i < 4; ++i)
-        if (round_up(M, rows[i]) < round_up(M, bm)) bm = rows[i];
     const int64_t mtiles = ceil_div(M, bm);
     const double out_mb = (double)ncols * M * 4.0 / 1e6;
     // best width for a split count: its time, rounds of 256 work-groups
@@ -237,7 +241,7 @@ inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &
         for (int w : {512, 256, 192, 128}) {
             if ((w == 512) != (bm == 32) || (w < 256 && bm != 128)) continue;
             const int64_t units = mtiles * ((ncols + w - 1) / w) * ceil_div(steps, sps) * cols;
-            const double us = (double)((units + 255) / 256) * (sps * (double)bm * w * 16 * 12 / 4096.0 / 0.75 / 2200.0 + 3.0);
+            const double us = (double)((units + 255) / 256) * (sps * weight * bm * w * 16 * 12 / 4096.0 / 0.75 / 2200.0 + 3.0);
             if (us < best) { best = us; width = w; }
         }
         return best;
@@ -251,6 +255,24 @@ inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &
     }
     best_width(ksplit, groups, bn);
     return best;
+}
+
+// The same with the rows of the tile: what pads M least, but many tiles of 32 x 512 compete with the taller ones by time, in
+// which they count half again: they move more per matrix instruction (0.72 us a step; 64 x 256 with as much work 0.60).
+// 224 filters 1x1 on 116x133x54x45: 7 x 32 rows 334 us a call, 2 x 128 rows 263.  The estimate is that of the least padding,
+// to which the rules that compare it with the fp32 kernels are fitted.
+inline double pick_split_tile(int M, int64_t ncols, int steps, int groups, int &bm, int &bn, int &ksplit)
+{
+    bm = least_padding(M);
+    const double us = split_tile_time(M, ncols, steps, groups, bm, 1.0, bn, ksplit);
+    if (bm > 32 || M <= 32) return us;
+    double best = split_tile_time(M, ncols, steps, groups, 32, 1.5, bn, ksplit);
+    for (int b : {64, 96, 128}) {
+        int bn_b, ks_b;
+        const double t = split_tile_time(M, ncols, steps, groups, b, 1.0, bn_b, ks_b);
+        if (t < best) { best = t; bm = b; bn = bn_b; ksplit = ks_b; }
+    }
+    return us;
 }
 
 constexpr int kDirectMaxRed = 800;
@@ -268,19 +290,14 @@ inline bool pick_direct(int op, const Problem &pb)
 
 constexpr int64_t kWgradPartLimit = (int64_t)48 << 20;    // bytes of partial sums: what the library's own scratch holds
 
-// Row tile, split count and time estimate (us, returned) of the three-part fp32 backward-filter kernel: `nblocks` blocks
-// of 16 columns, J positions, `groups` columns in one launch.  One work-group per CU and step of 32 positions: the matrix
-// time of a BM x 256 tile (six products), about 0.7 of it reached, and 4 us a round for what nothing hides.  Splits that
-// fill one to four rounds of 256 work-groups, of at least four steps; their partial sums are written and read once.
-inline double pick_wgrad_split(int K, int nblocks, int64_t J, int groups, int64_t out_bytes, int &bm, int &ksplit)
+// Split count and time estimate (us, returned) of the three-part fp32 backward-filter kernel on tiles of bm rows: `nblocks`
+// blocks of 16 columns, J positions, `groups` columns in one launch.  One work-group per CU, step_us a step of 32 positions and
+// 4 us a round for what nothing hides.  Splits that fill one to four rounds of 256 work-groups, of at least four steps; their
+// partial sums are written and read once.
+inline double wgrad_split_time(int K, int nblocks, int64_t J, int groups, int64_t out_bytes, int bm, double step_us, int &ksplit)
 {
-    const int rows[4] = {128, 96, 64, 32};
-    bm = rows[0];
-    for (int i = 1; i < 4; ++i)
-        if (round_up(K, rows[i]) < round_up(K, bm)) bm = rows[i];
     const int steps = (int)((J + 31) / 32);
     const int64_t tiles = (int64_t)ceil_div(K, bm) * ceil_div(nblocks, 16);
-    const double step_us = (double)bm * 256 * 32 * 12 / 4096.0 / 0.7 / 2100.0;
     double best = 1e30;
     ksplit = 1;
     for (int r = 1; r <= 4; ++r) {
@@ -292,6 +309,25 @@ inline double pick_wgrad_split(int K, int nblocks, int64_t J, int groups, int64_
         if (us < best * 0.97) { best = us; ksplit = n; }
     }
     return best;
+}
+
+// The same with the rows of the tile: what pads K least, but many tiles of 32 rows compete with the taller ones by time, in
+// which a step counts 0.95 + 0.0132 BM us (measured 1.37, 1.79, 2.22 and 2.64 for 32 to 128 rows: the 256 columns are loaded
+// and split whatever the rows).  352 filters, 194 channels 3x3 stride 2, 68 x 8 x 24: 11 x 32 rows 105 us a call, 3 x 128 rows
+// or 4 x 96 (chosen) 52.  The estimate is that of the least padding and of the matrix time of a step (six products, about 0.7 of it reached), to
+// which the rule that compares it with the fp32 kernels is fitted.
+inline double pick_wgrad_split(int K, int nblocks, int64_t J, int groups, int64_t out_bytes, int &bm, int &ksplit)
+{
+    bm = least_padding(K);
+    const double us = wgrad_split_time(K, nblocks, J, groups, out_bytes, bm, bm * 256.0 * 32 * 12 / 4096.0 / 0.7 / 2100.0, ksplit);
+    if (bm > 32 || K <= 32) return us;
+    double best = 1e30;
+    for (int b : {32, 64, 96, 128}) {
+        int ks_b;
+        const double t = wgrad_split_time(K, nblocks, J, groups, out_bytes, b, 0.95 + 0.0132 * b, ks_b);
+        if (t < best) { best = t; bm = b; ksplit = ks_b; }
+    }
+    return us;
 }
 
 // three_part = false: fp32 passes stay on the fp32 kernels
@@ -539,11 +575,17 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
         int bm, bn, ks;
         double us = pick_split_tile(pl.M, ncols, steps, GF, bm, bn, ks);
         us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 3.8e6;
+        // a stride beyond the filter: most positions get a zero, and the stores, every stride-th word of a row, decide
+        // (192 channels at 89x35x31, 51 filters 1x1 stride 3: 71 us, fp32 44; 224 at 100x29x39, 96 filters stride 2: 88, 120)
+        const bool gaps = strided && (pb.R < pb.stride || pb.S < pb.stride);
+        if (gaps) us = std::max(us, 14.5 + 0.64 * ncols * pl.M * 4.0 / 1e6);
         // the few-channel kernel reaches about 90 TFLOP/s on its padded rows, at 1 us or more per 16-deep step; the
         // tap-table kernel 55 and 1.7 us
         const double gflop = 2.0 * ncols * Cr * RS / 1e9;          // per row
         if (pl.patch)
             fp32_us = std::max(gflop * round_up(pl.M, 32) / 90.0 * 1e3, 1.0 * ceil_div(Cr * RS, kChunk)) + 3.0;
+        else if (gaps)
+            fp32_us = std::max(gflop * pl.M / 38.0 * 1e3 + 8.0, 15.0 + 1.2 * ceil_div(Cr * RS, kChunk));
         else if (strided)              // all taps at every position, masked: 20 TFLOP/s of them
             fp32_us = std::max(gflop * pl.M / 20.0 * 1e3, 1.7 * ceil_div(Cr * RS, kChunk));
         else if (Cr % kChunk != 0)
