@@ -32,8 +32,9 @@ def dev(a, dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", SHAPES)
-def test_direct_passes_stay_within_the_error_bound(shape, dtype):
+def test_direct_passes_stay_within_the_error_bound(shape, dtype, route):
     N, C, H, W, K, R, st, pad = shape
+    assert all(route(op, *shape, dtype=0 if dtype == "f32" else 1).kernels == "direct" for op in range(3))
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     x, w = synth.gaussian((N, C, H, W), 951), synth.gaussian((K, C, R, R), 952)
     dy, b = synth.gaussian((N, K, P, Q), 953), synth.gaussian((K,), 954)
@@ -62,7 +63,8 @@ def test_direct_passes_stay_within_the_error_bound(shape, dtype):
            oracle.conv_bwd_filter(ax, ady, R, R, st, pad), N * P * Q, False)
 
 
-def test_direct_passes_of_two_columns_equal_the_columns_alone():
+def test_direct_passes_of_two_columns_equal_the_columns_alone(route):
+    assert all(route(op, 2, 32, 9, 9, 8, 3, 1, 1, groups=2).kernels == "direct" for op in range(3))
     x, w, dy = (torch.from_numpy(synth.gaussian(s, 955 + i)).cuda()
                 for i, s in enumerate([(2, 32, 9, 9), (8, 16, 3, 3), (2, 8, 9, 9)]))
     part = lambda t, g: t.chunk(2, 1)[g].contiguous()

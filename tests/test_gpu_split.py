@@ -31,33 +31,44 @@ def within(got, ref, absref, length):
     assert np.isfinite(err).all() and (err <= bound).all(), float((err / np.maximum(bound, 1e-300)).max())
 
 
-# N, C, H, W, K, R, stride, pad: rows 1 above and at a tile height (32, 64, 96, 128), a column more and less than a
-# tile (256, 512), channel counts that are no multiple of 16, one position, split reductions (few columns), an even
-# filter, padding beyond half the filter
+# N, C, H, W, K, R, stride, pad, and which of forward (f) and backward-data (d) run on the three-part kernels: rows 1 above
+# and at a tile height (32, 64, 96, 128), a column more and less than a tile (256, 512), channel counts that are no multiple
+# of 16, one position, split reductions (few columns), an even filter, padding beyond half the filter, 224 rows (four tiles of
+# 64, not seven of 32), each tile of the kernel
 SHAPES = [
-    (16, 64, 16, 16, 128, 3, 1, 1),
-    (1, 128, 16, 17, 129, 3, 1, 1),
-    (7, 96, 13, 13, 97, 3, 1, 1),
-    (3, 65, 15, 17, 64, 3, 1, 1),
-    (5, 64, 21, 21, 33, 3, 1, 1),
-    (9, 32, 31, 33, 32, 5, 1, 2),
-    (1, 256, 1, 1, 160, 1, 1, 0),
-    (2, 384, 13, 13, 384, 3, 1, 1),
-    (2, 112, 12, 10, 100, 4, 1, 3),
-    (4, 100, 24, 19, 200, 7, 2, 3),
+    ((16, 64, 16, 16, 128, 3, 1, 1), "f"),
+    ((1, 128, 16, 17, 129, 3, 1, 1), "d"),
+    ((7, 96, 13, 13, 97, 3, 1, 1), "fd"),
+    ((3, 65, 15, 17, 64, 3, 1, 1), "f"),
+    ((5, 64, 21, 21, 33, 3, 1, 1), "fd"),
+    ((16, 64, 27, 27, 32, 5, 1, 2), "fd"),
+    ((1, 1024, 1, 1, 1024, 1, 1, 0), "fd"),
+    ((2, 384, 13, 13, 384, 3, 1, 1), "fd"),
+    ((2, 112, 12, 10, 100, 4, 1, 3), "fd"),
+    ((4, 100, 24, 19, 200, 7, 2, 3), "f"),
+    ((6, 19, 25, 28, 229, 5, 1, 2), "fd"),
+    ((28, 61, 29, 24, 384, 1, 1, 0), "f"),
+    ((4, 70, 27, 27, 224, 3, 1, 1), "f"),
 ]
 
 
-@pytest.mark.parametrize("shape", SHAPES)
-def test_split_passes_stay_within_the_error_bound(shape):
+def test_these_shapes_take_every_tile_of_the_forward_kernel(route):
+    tiles = {(r.rows, r.columns) for shape, passes in SHAPES for p in passes for r in [route("fd".index(p), *shape)]}
+    assert tiles == {(128, 256), (128, 192), (128, 128), (96, 256), (64, 256), (32, 512)}
+
+
+@pytest.mark.parametrize("shape,passes", SHAPES)
+def test_split_passes_stay_within_the_error_bound(shape, passes, route):
     N, C, H, W, K, R, st, pad = shape
+    assert all(route("fd".index(p), *shape).kernels == "split" for p in passes)
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     x, w, dy = synth.gaussian((N, C, H, W), 901), synth.gaussian((K, C, R, R), 902, 0.01), synth.gaussian((N, K, P, Q), 903)
     ax, aw, ady = np.abs(x), np.abs(w), np.abs(dy)
     xd, wd, dyd = dev(x), dev(w), dev(dy)
-    y = hp.conv_fwd(xd, wd, st, pad, y=nan_like((N, K, P, Q)))
-    within(y, oracle.conv_fwd(x, w, st, pad), oracle.conv_fwd(ax, aw, st, pad), C * R * R)
-    if st == 1:
+    if "f" in passes:
+        y = hp.conv_fwd(xd, wd, st, pad, y=nan_like((N, K, P, Q)))
+        within(y, oracle.conv_fwd(x, w, st, pad), oracle.conv_fwd(ax, aw, st, pad), C * R * R)
+    if "d" in passes:
         dx = hp.conv_bwd_data(dyd, wd, H, W, st, pad, dx=nan_like((N, C, H, W)))
         within(dx, oracle.conv_bwd_data(dy, w, H, W, st, pad), oracle.conv_bwd_data(ady, aw, H, W, st, pad), K * R * R)
 
@@ -71,11 +82,15 @@ def same_pattern(got, ref):
     assert np.abs(g[fin].astype(np.float64) - ref[fin]).max() <= 1e-5 * max(np.abs(ref[fin]).max(), 1e-300)
 
 
+STRIDE1 = 3, 96, 13, 13, 96, 3, 1, 1         # both passes on the three-part kernels
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, -3.4e38])
-def test_split_passes_give_infinities_and_nan_as_fp32_does(value):
+def test_split_passes_give_infinities_and_nan_as_fp32_does(value, route):
     # one such value in a mini-batch: the windows that read it, and only they, show it.  It meets positive filters, so
     # that no infinity of the other sign and no zero arises beside it.
-    x, w = synth.gaussian((3, 64, 13, 13), 911), np.abs(synth.gaussian((64, 64, 3, 3), 912)) + np.float32(0.5)
+    assert route(0, *STRIDE1).kernels == route(1, *STRIDE1).kernels == "split"
+    x, w = synth.gaussian((3, 96, 13, 13), 911), np.abs(synth.gaussian((96, 96, 3, 3), 912)) + np.float32(0.5)
     x[1, 37, 6, 12] = value
     with np.errstate(all="ignore"):
         same_pattern(hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1))
@@ -83,23 +98,29 @@ def test_split_passes_give_infinities_and_nan_as_fp32_does(value):
 
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-34, 1e-37])
-def test_split_passes_keep_fp32_precision_for_tiny_values(scale):
-    x, w = synth.gaussian((3, 64, 13, 13), 921) * np.float32(scale), synth.gaussian((64, 64, 3, 3), 922)
+def test_split_passes_keep_fp32_precision_for_tiny_values(scale, route):
+    assert route(0, *STRIDE1).kernels == "split"
+    x, w = synth.gaussian((3, 96, 13, 13), 921) * np.float32(scale), synth.gaussian((96, 96, 3, 3), 922)
     y, ref = hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1)
-    assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 576 * 2.0 ** -24 * oracle.conv_fwd(np.abs(x), np.abs(w), 1, 1).max()
+    assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() <= 864 * 2.0 ** -24 * oracle.conv_fwd(np.abs(x), np.abs(w), 1, 1).max()
 
 
 # Backward-filter: rows at and above the tile heights, filter and channel counts that are no multiple of 16, fewer than 32
 # positions in a split's last step, strides 2 and 3 with windows that leave input rows unread, padding, an even filter,
 # two row tiles, columns past the last block of a tile
 WGRAD_SHAPES = [
-    (16, 64, 16, 16, 128, 3, 1, 1),
+    (28, 80, 16, 2, 128, 1, 2, 0),
+    (59, 144, 2, 7, 64, 1, 2, 0),
+    (64, 48, 13, 13, 96, 3, 1, 1),
+    (8, 32, 13, 13, 32, 3, 1, 1),
+    (6, 19, 25, 28, 229, 5, 1, 2),
     (3, 16, 16, 17, 129, 3, 1, 1),
     (5, 65, 15, 17, 64, 3, 1, 1),
     (9, 32, 31, 33, 33, 5, 1, 2),
     (24, 40, 31, 45, 72, 3, 2, 1),
-    (6, 9, 30, 31, 10, 3, 3, 0),
-    (37, 48, 11, 9, 96, 4, 1, 2),
+    (16, 9, 64, 60, 24, 3, 2, 0),
+    (6, 13, 40, 41, 40, 5, 3, 0),
+    (36, 41, 8, 9, 28, 2, 1, 2),
     (33, 128, 13, 13, 144, 3, 1, 1),
     # partial sums of channel counts that are no multiple of four: 1, 2, 3, 4, 5 and 74 splits
     (2, 113, 6, 4, 56, 3, 1, 1),
@@ -111,9 +132,16 @@ WGRAD_SHAPES = [
 ]
 
 
+def test_these_shapes_take_every_tile_of_the_backward_filter_kernel(route):
+    # whole and ragged counts of channels and filters are kernels of their own
+    tiles = {(route(2, *s).rows, s[1] % 16 != 0 or s[4] % 16 != 0) for s in WGRAD_SHAPES}
+    assert tiles == {(rows, ragged) for rows in (32, 64, 96, 128) for ragged in (False, True)}
+
+
 @pytest.mark.parametrize("shape", WGRAD_SHAPES)
-def test_split_backward_filter_stays_within_the_error_bound(shape):
+def test_split_backward_filter_stays_within_the_error_bound(shape, route):
     N, C, H, W, K, R, st, pad = shape
+    assert route(2, *shape).kernels == "split"
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     x, dy = synth.gaussian((N, C, H, W), 904), synth.gaussian((N, K, P, Q), 905)
     dw = hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad, dw=nan_like((K, C, R, R)))
@@ -121,8 +149,10 @@ def test_split_backward_filter_stays_within_the_error_bound(shape):
            oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad), N * P * Q)
 
 
-def test_split_backward_filter_of_two_columns_equals_the_columns_alone():
+def test_split_backward_filter_of_two_columns_stays_within_the_error_bound(route):
+    # (not the bits of the columns alone: the splits are chosen for the columns of a launch together, as the fp32 kernels do)
     N, C, K, R = 6, 96, 256, 5
+    assert route(2, N, C, 27, 27, K, R, 1, 2, groups=2).kernels == "split"
     x, dy = synth.gaussian((N, C, 27, 27), 906), synth.gaussian((N, K, 27, 27), 907)
     dw = hp.conv_bwd_filter_grouped(dev(x), dev(dy), R, R, 1, 2, 2, dw=nan_like((K, C // 2, R, R)))
     for g in range(2):
@@ -131,20 +161,29 @@ def test_split_backward_filter_of_two_columns_equals_the_columns_alone():
                oracle.conv_bwd_filter(np.abs(xs), np.abs(ys), R, R, 1, 2), N * 27 * 27)
 
 
+WHOLE, RAGGED = (8, 32, 13, 13, 32, 3, 1, 1), (5, 65, 15, 17, 64, 3, 1, 1)
+
+
+@pytest.mark.parametrize("shape", [WHOLE, RAGGED])
 @pytest.mark.parametrize("value", [np.inf, np.nan, -3.4e38])
-def test_split_backward_filter_gives_infinities_and_nan_as_fp32_does(value):
-    x, dy = synth.gaussian((16, 64, 16, 16), 913), np.abs(synth.gaussian((16, 64, 16, 16), 914)) + np.float32(0.5)
-    x[1, 37, 6, 15] = value
+def test_split_backward_filter_gives_infinities_and_nan_as_fp32_does(value, shape, route):
+    N, C, H, W, K, R, st, pad = shape
+    assert route(2, *shape).kernels == "split"
+    x, dy = synth.gaussian((N, C, H, W), 913), np.abs(synth.gaussian((N, K, H, W), 914)) + np.float32(0.5)
+    x[1, 27, 6, W - 1] = value
     with np.errstate(all="ignore"):
-        same_pattern(hp.conv_bwd_filter(dev(x), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(x, dy, 3, 3, 1, 1))
+        same_pattern(hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad), oracle.conv_bwd_filter(x, dy, R, R, st, pad))
 
 
+@pytest.mark.parametrize("shape", [WHOLE, RAGGED])
 @pytest.mark.parametrize("scale", [1e-30, 1e-37])
-def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale):
-    x, dy = synth.gaussian((16, 64, 16, 16), 922), synth.gaussian((16, 64, 16, 16), 923) * np.float32(scale)
-    dw, ref = hp.conv_bwd_filter(dev(x), dev(dy), 3, 3, 1, 1), oracle.conv_bwd_filter(x, dy, 3, 3, 1, 1)
-    top = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), 3, 3, 1, 1).max()
-    assert np.abs(dw.cpu().numpy().astype(np.float64) - ref).max() <= 4096 * 2.0 ** -24 * top
+def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale, shape, route):
+    N, C, H, W, K, R, st, pad = shape
+    assert route(2, *shape).kernels == "split"
+    x, dy = synth.gaussian((N, C, H, W), 922), synth.gaussian((N, K, H, W), 923) * np.float32(scale)
+    dw, ref = hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad), oracle.conv_bwd_filter(x, dy, R, R, st, pad)
+    top = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad).max()
+    assert np.abs(dw.cpu().numpy().astype(np.float64) - ref).max() <= N * H * W * 2.0 ** -24 * top
 
 
 # Fully connected: a column or row more and less than a tile, reductions that end inside a step or a split range, one sample
@@ -197,8 +236,9 @@ def test_a_single_product_is_correctly_rounded(route):
     (3, 130, 31, 33, 100, 7, 4, 3),
     (2, 48, 23, 25, 40, 3, 2, 3),
 ])
-def test_split_strided_backward_data_stays_within_the_error_bound(shape):
+def test_split_strided_backward_data_stays_within_the_error_bound(shape, route):
     N, C, H, W, K, R, st, pad = shape
+    assert route(1, *shape).kernels == "split"
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     w, dy = synth.gaussian((K, C, R, R), 941, 0.01), synth.gaussian((N, K, P, Q), 942)
     ref, refabs = oracle.conv_bwd_data(dy, w, H, W, st, pad), oracle.conv_bwd_data(np.abs(dy), np.abs(w), H, W, st, pad)
@@ -219,11 +259,12 @@ def test_split_strided_backward_data_stays_within_the_error_bound(shape):
     (30, 3, 47, 51, 48, 11, 4, 1),
     (20, 8, 33, 36, 64, 7, 2, 3),
     (33, 20, 23, 22, 40, 7, 2, 3),
-    (40, 9, 50, 53, 130, 7, 3, 1),
+    (1, 9, 29, 27, 20, 10, 3, 1),
     (25, 2, 61, 64, 33, 8, 4, 4),
 ])
-def test_split_folded_passes_stay_within_the_error_bound(shape):
+def test_split_folded_passes_stay_within_the_error_bound(shape, route):
     N, C, H, W, K, R, st, pad = shape
+    assert route(0, *shape).fold == st
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     x, w = synth.gaussian((N, C, H, W), 961), synth.gaussian((K, C, R, R), 962, 0.01)
     dy, b = synth.gaussian((N, K, P, Q), 963), synth.gaussian((K,), 964)
@@ -234,22 +275,23 @@ def test_split_folded_passes_stay_within_the_error_bound(shape):
            yabs + np.abs(b4), C * R * R)
     within(hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad, dw=nan_like((K, C, R, R))),
            oracle.conv_bwd_filter(x, dy, R, R, st, pad), oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad), N * P * Q)
-    x[1, 1, 6, 7] = np.inf
+    x[N - 1, 1, 6, 7] = np.inf
     with np.errstate(all="ignore"):
         aw, ady = np.abs(w) + np.float32(0.5), np.abs(dy) + np.float32(0.5)
         same_pattern(hp.conv_fwd(dev(x), dev(aw), st, pad), oracle.conv_fwd(x, aw, st, pad))
         same_pattern(hp.conv_bwd_filter(dev(x), dev(ady), R, R, st, pad), oracle.conv_bwd_filter(x, ady, R, R, st, pad))
 
 
-def test_split_passes_tell_nan_from_values_that_only_their_first_part_makes_infinite():
+def test_split_passes_tell_nan_from_values_that_only_their_first_part_makes_infinite(route):
     # a NaN, and in the same sums a finite value above the largest bfloat16 beside a zero: the NaN shows where fp32 has it,
     # and the zero times the large value stays zero
-    x, w = synth.gaussian((3, 64, 13, 13), 971), np.abs(synth.gaussian((64, 64, 3, 3), 972)) + np.float32(0.5)
+    assert route(0, *STRIDE1).kernels == route(2, *WHOLE).kernels == "split"
+    x, w = synth.gaussian((3, 96, 13, 13), 971), np.abs(synth.gaussian((96, 96, 3, 3), 972)) + np.float32(0.5)
     x[1, 5, 6, 7] = np.nan
     x[2, 9, 3, 3] = np.float32(3.4e38)
     w[:, 9] = 0.0
-    dy = np.abs(synth.gaussian((16, 64, 16, 16), 973)) + np.float32(0.5)
-    xb = synth.gaussian((16, 64, 16, 16), 974)
+    dy = np.abs(synth.gaussian((8, 32, 13, 13), 973)) + np.float32(0.5)
+    xb = synth.gaussian((8, 32, 13, 13), 974)
     xb[3, 2, 8, 8], xb[4, 7, 1, 1] = np.nan, np.float32(3.4e38)
     dy[4] = 0.0
     a, b = synth.gaussian((9, 260), 975), np.abs(synth.gaussian((132, 260), 976)) + np.float32(0.5)
