@@ -29,7 +29,9 @@
  *    the same for the same workspace size.
  *  - Outputs are fully overwritten (no accumulation into the destination, every
  *    element written -- dx positions that no window touches receive 0).
- *  - dtype: CONV_DTYPE_F32  = fp32 tensors, fp32 MFMA arithmetic.
+ *  - dtype: CONV_DTYPE_F32  = fp32 tensors, fp32 accumulation; products on the
+ *           fp32 matrix instruction or as six products of bfloat16 parts of the
+ *           operands, at an error no larger.
  *           CONV_DTYPE_BF16 = x, w, dy hold bfloat16 (2 bytes, already rounded
  *           by the caller); products accumulate in fp32; outputs (y, dx, dw)
  *           are fp32.
