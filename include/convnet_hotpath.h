@@ -127,9 +127,8 @@ int conv_bwd_filter(const void *x, const void *dy, void *dw,
  * and frees nothing, on the device or through any library.
  *   - A pass whose conv_workspace_bytes(CONV_OP_BWD_FILTER, ...) exceeds
  *     CONV_NOALLOC_SCRATCH_BYTES returns CONV_ERR_SCRATCH_LIMIT before anything
- *     is enqueued.  fp32: the partial sums do not grow with N (at most 36 MB,
- *     the first layer's 256 partial results), and all five layers of the stack
- *     fit at any batch size.  bf16: the packed copies grow with N (the third
+ *     is enqueued.  fp32: the partial sums do not grow with N beyond what
+ *     the array holds, and all five layers of the stack fit at any batch size.  bf16: the packed copies grow with N (the third
  *     layer needs 31 MB at N = 16, 46 MB at N = 64).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time
  *     on one GPU (different streams or threads) race.  Calls on one stream are
