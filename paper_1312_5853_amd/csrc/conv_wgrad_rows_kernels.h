@@ -591,3 +591,401 @@ __global__ __launch_bounds__(kRowsF32Threads, 1) void wgrad_rows_f32_kernel(cons
             if (row < p.K && col < p.Kg) out[(size_t)row * p.Kg + col] = acc[i][v];
         }
 }
+
+// ---------------------------------------------------------------------------
+// fp32 tensors on the bf16 matrix instruction, operands split into three bfloat16 parts (six products, two accumulators:
+// arithmetic, error and range as in conv_split_kernels.h), for stride 4.  The same decomposition: a work-group owns the whole
+// K x (C*R*S) result for its (image, output-row range) units.
+//
+// Columns come in quads, four consecutive taps s = 4 sg .. 4 sg + 3 of one (c, r): at output column q they are the input
+// columns 4 (q + sg) .. + 3 of the padded row, eight aligned bytes of a staged part.  That is the piece that
+// ds_read_b64_tr_b16 takes from a lane, so the transposed operand (eight consecutive q of a tap per lane) comes straight from
+// the input row as it lies in memory: no shifted copies, which in three parts would not fit the LDS.  S = 11 costs one unused
+// column in twelve.
+//   dy   [buffer][part][96 filters][144 bytes]: 64 positions, zero from Q on
+//   x    [c][ring row][part][456 bytes]: padded input columns 0 .. 4 Q + 7; 456 = 200 mod 256 keeps the two filter rows that a
+//        read meets in different banks
+// The result is 3 x 13 blocks of 32 x 32, five to each of eight waves (two per SIMD, so that one's splitting and LDS stores
+// pass under the other's matrix instructions): the three rows of column block `wave`, and two of the fifteen blocks of
+// columns 8..12 (rows_split_extra).  An output row is 4 x 30 matrix instructions per wave; the next row's values are loaded at
+// its start and split and stored between its 16-position blocks.
+// From position Q on dy is zero and the input holds values of other windows, or of other rows: where one of those is not
+// finite the sum becomes NaN, and the rule below computes it again unless a NaN of its own explains it.
+// Bound: matrix instructions (128 x 3 x 224 x 224, 96 filters 11 x 11: 30 x 110 x 32 clocks x 2 waves = 106 us at 2 GHz).
+// MEASURED_PLACEHOLDER
+// ---------------------------------------------------------------------------
+constexpr int kRowsSplitThreads = 512;
+constexpr int kRowsSplitPitch = 456;                              // bytes of a part of a staged input row
+constexpr int kRowsSplitRow = 3 * kRowsSplitPitch;
+constexpr int kRowsSplitDyPart = kRowsM * kRowsPitch;
+constexpr int kRowsSplitDyBuf = 3 * kRowsSplitDyPart;
+// (LDS behind the input rows: the reads of positions from Q on, cleared afterwards, reach 72 bytes past the last row)
+
+struct WgradRowsSplitArgs {
+    const float *x, *dy;
+    float *part;                 // [work-group][K][Kg]
+    int C, H, W, K, R, S, P, Q, Kg, pad;       // stride 4
+    int x_bs, y_bs;              // elements between images
+    unsigned x_bytes, dy_bytes;  // from the first element to the last
+    int splits, units;
+    int SG, quads;               // ceil(S / 4); C * R * SG <= 104
+    int nnew;                    // input rows a step adds per channel: min(R, 4)
+    int xg, dyg;                 // groups of four: padded input columns, output columns
+    FastDiv div_splits, div_xg, div_dyg, div_nnew;
+};
+
+// Blocks of column blocks 8..12 that a wave computes beside its own: (row block, column block) twice, the row blocks different.
+// The last of the sixteen repeats a block, which is not stored.
+struct RowsSplitExtra { int row0, col0, row1, col1; };
+__device__ __forceinline__ RowsSplitExtra rows_split_extra(int wave)
+{
+    constexpr unsigned table[8] = {0x0818, 0x1929, 0x2A0A, 0x091A, 0x0B1B, 0x1C2C, 0x2B0C, 0x280F};
+    const unsigned t = table[wave & 7];
+    return RowsSplitExtra{(int)(t >> 12), (int)(t >> 8 & 15), (int)(t >> 4 & 15), (int)(t & 15)};
+}
+
+// NKB: blocks of 16 positions per output row
+template <int NKB>
+__global__ __launch_bounds__(kRowsSplitThreads, 1) void wgrad_rows_split_kernel(const WgradRowsSplitArgs p)
+{
+    constexpr unsigned kOutside = 0x80000000u;
+    constexpr int NW = kRowsSplitThreads / 64;
+    extern __shared__ __attribute__((aligned(16))) float lds_fast[];
+    char *const lds = reinterpret_cast<char *>(lds_fast);
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int echan = kRowsRing * kRowsSplitRow;
+
+    // zero: dy's positions from Q on, and whatever the input's positions from there on may read before it is staged
+    for (int o = tid * 16; o < 2 * kRowsSplitDyBuf + p.C * echan + 128; o += kRowsSplitThreads * 16)
+        *reinterpret_cast<u32x4 *>(lds + o) = u32x4{0u, 0u, 0u, 0u};
+
+    const auto rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.x), 0, (int)p.x_bytes, 0x00020000);
+    const auto rsrc_dy = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.dy), 0, (int)p.dy_bytes, 0x00020000);
+
+    // row blocks in the order slot 0, 1 (which serve the two extra blocks), 2; column blocks: own, of slot 0, of slot 1
+    const RowsSplitExtra ex = rows_split_extra(wave);
+    const int slot_row[3] = {ex.row0, ex.row1, 3 - ex.row0 - ex.row1};
+    const int blk_col[3] = {wave, ex.col0, min(ex.col1, 12)};
+    const bool stored4 = ex.col1 < 13;
+
+    // this lane's address in a column block, position (lane % 16) / 4 of its half and quad lane % 4 of sixteen columns, and
+    // the quad's filter row from bit 24 on
+    unsigned tap[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const int quad = blk_col[b] * 8 + ((lane >> 4) & 1) * 4 + (lane & 3);
+        const int qq = quad < p.quads ? quad : 0;                 // quads past the last: computed, never stored
+        const int cr = qq / p.SG, sg = qq - cr * p.SG;
+        const int c = cr / p.R;
+        tap[b] = (unsigned)(2 * kRowsSplitDyBuf + c * echan + (half * 8 + ((lane & 15) >> 2) + sg) * 8) |
+                 (unsigned)(cr - c * p.R) << 24;
+    }
+
+    f32x16 acc[5], low[5];
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { acc[t][v] = 0.f; low[t][v] = 0.f; }
+
+    // Staging items of four values: two of x (c, new row i, group of padded columns) and three of dy (filter, group of
+    // positions) per thread.  Kept per item: byte offset in its tensor from the row of an output row on (kOutside: no item),
+    // byte offset in LDS (of x: of ring row 0, i from bit 24 on), and four bits that say which values are inside the row.
+    unsigned x_off[2], x_lds[2], dy_off[3], dy_lds[3], inside = 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int it = tid + kRowsSplitThreads * u;
+        const int t = (int)fastdiv((uint32_t)it, p.div_xg), g = it - t * p.xg;
+        const int c = (int)fastdiv((uint32_t)t, p.div_nnew), i = t - c * p.nnew, w = 4 * g - p.pad;
+        x_off[u] = c < p.C ? (unsigned)((c * p.H + i) * p.W + w) * 4u : kOutside;
+        x_lds[u] = c < p.C ? (unsigned)(2 * kRowsSplitDyBuf + c * echan + g * 8) | (unsigned)i << 24 : kOutside;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) inside |= (unsigned)(w + e) < (unsigned)p.W ? 1u << (4 * u + e) : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        const int it = tid + kRowsSplitThreads * u;
+        const int m = (int)fastdiv((uint32_t)it, p.div_dyg), g = it - m * p.dyg;
+        dy_off[u] = m < p.K ? (unsigned)(m * p.P * p.Q + 4 * g) * 4u : kOutside;
+        dy_lds[u] = m < p.K ? (unsigned)(m * kRowsPitch + g * 8) : kOutside;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) inside |= 4 * g + e < p.Q ? 1u << (8 + 4 * u + e) : 0u;
+    }
+    // rows outside the image read as zero; a row past the unit's last one reads what is there and is not used
+    auto load_x = [&](float (&v)[4], int u, int n, int first_hh) {
+        const int h0 = first_hh - p.pad;
+        const bool ok = (unsigned)(h0 + (int)(x_lds[u] >> 24)) < (unsigned)p.H;       // (no item: row 128 and up)
+        const unsigned base = x_off[u] + (unsigned)(n * p.x_bs + h0 * p.W) * 4u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_x, ok ? base + 4u * e : kOutside, 0, 0));
+    };
+    auto load_dy = [&](float (&v)[4], int u, int n, int prow) {
+        const unsigned base = dy_off[u] + (unsigned)(n * p.y_bs + prow * p.Q) * 4u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_dy, base + 4u * e, 0, 0));
+    };
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 sp[3];
+    auto split_two = [&](const float (&v)[4], int t, int bit) {   // values 2t, 2t + 1 of the item whose bits start at `bit`
+        auto in = [&](int e) {
+            return __uint_as_float(__float_as_uint(v[e]) & (unsigned)__builtin_amdgcn_sbfe((int)inside, bit + e, 1));
+        };
+        unsigned h, m, l;
+        split_pair(in(2 * t), in(2 * t + 1), h, m, l);
+        sp[0][t] = h; sp[1][t] = m; sp[2][t] = l;
+    };
+    auto put = [&](char *dst, int part_bytes) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x2 *>(dst + c * part_bytes) = sp[c];
+    };
+    auto put_x = [&](int u, int first_hh, int rows) {
+        const int i = (int)x_lds[u] >> 24;
+        if ((i >= 0) & (i < rows))
+            put(lds + (x_lds[u] & 0xffffffu) + ((unsigned)(first_hh + i) & (kRowsRing - 1)) * kRowsSplitRow, kRowsSplitPitch);
+    };
+    auto store_x = [&](const float (&v)[4], int u, int first_hh, int rows) {
+        split_two(v, 0, 4 * u); split_two(v, 1, 4 * u);
+        put_x(u, first_hh, rows);
+    };
+    auto put_dy = [&](int u, int buf) {
+        if ((int)dy_lds[u] >= 0) put(lds + buf * kRowsSplitDyBuf + dy_lds[u], kRowsSplitDyPart);
+    };
+    auto store_dy = [&](const float (&v)[4], int u, int buf) {
+        split_two(v, 0, 8 + 4 * u); split_two(v, 1, 8 + 4 * u);
+        put_dy(u, buf);
+    };
+
+    typedef __attribute__((address_space(3))) char *lds_bytes;
+    typedef __attribute__((address_space(3))) s16x4 *lds_quad;
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    s16x8 fa[2][3], fb[2][3];                                     // [set][part]
+    unsigned a_off[3], b_off[3];
+    auto read_a = [&](int set, int slot, int kb) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            fa[set][c] = *reinterpret_cast<const s16x8 *>(lds + a_off[slot] + c * kRowsSplitDyPart + kb * 32);
+    };
+    auto read_b = [&](int set, int b, int kb) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const lds_bytes a = (lds_bytes)lds + b_off[b] + c * kRowsSplitPitch + kb * 128;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad)a);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad)(a + 32));
+            fb[set][c] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
+    auto product = [&](int tile, int a, int b, int ca, int cb) {
+        f32x16 &sum = ca + cb == 0 ? acc[tile] : low[tile];
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[a][ca]),
+                                                      __builtin_bit_cast(bf16x8, fb[b][cb]), sum, 0, 0, 0);
+    };
+
+    for (int unit = blockIdx.x; unit < p.units; unit += gridDim.x) {
+        const int n = (int)fastdiv((uint32_t)unit, p.div_splits);
+        const int sp = unit - n * p.splits;
+        const int p_begin = (int)((int64_t)p.P * sp / p.splits), p_end = (int)((int64_t)p.P * (sp + 1) / p.splits);
+        if (p_begin >= p_end) continue;
+        __syncthreads();                                          // zero fill / the previous unit's reads are done
+        {
+            float d0[4], d1[4], d2[4], x0[4], x1[4];
+            load_dy(d0, 0, n, p_begin); load_dy(d1, 1, n, p_begin); load_dy(d2, 2, n, p_begin);
+#pragma unroll 1
+            for (int r0 = 0; r0 < p.R; r0 += p.nnew) {            // every input row of the first output row
+                const int hh = 4 * p_begin + r0, rows = min(p.nnew, p.R - r0);
+                load_x(x0, 0, n, hh); load_x(x1, 1, n, hh);
+                store_x(x0, 0, hh, rows); store_x(x1, 1, hh, rows);
+            }
+            store_dy(d0, 0, 0); store_dy(d1, 1, 0); store_dy(d2, 2, 0);
+        }
+        __syncthreads();
+        int buf = 0;
+        for (int prow = p_begin; prow < p_end; ++prow) {
+            const int hh_new = 4 * (prow + 1) + p.R - p.nnew;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                a_off[i] = (unsigned)(buf * kRowsSplitDyBuf + (slot_row[i] * 32 + l32) * kRowsPitch + half * 16);
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                b_off[b] = (tap[b] & 0xffffffu) + ((4u * prow + (tap[b] >> 24)) & (kRowsRing - 1)) * kRowsSplitRow;
+            read_b(0, 0, 0);
+            read_a(0, 2, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            float v0[4], v1[4], v2[4];                            // values of the next row: two items of dy, then the others
+            load_dy(v0, 0, n, prow + 1); load_dy(v1, 1, n, prow + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            // One block of 16 positions.  The filters' fragments of a slot alternate between two sets, the own column block stays
+            // in set 0 of the inputs and the extra ones pass through set 1: 48 registers of operands beside 160 of sums.  The
+            // next row's values are split and stored between matrix instructions, one pair of a thread's four at a time: dy's
+            // first two items in block 1, the others, loaded at the end of that block, in the last (after the row's last
+            // loads in rows of one or two blocks).  Past the unit's last row that writes where nothing is read.
+            constexpr int KA = NKB > 2 ? 1 : NKB - 1, KB = NKB > 2 ? NKB - 1 : NKB;
+            auto work = [&](auto kb_c, auto m_c) {
+                constexpr int kb = decltype(kb_c)::value, i = decltype(m_c)::value - (kb == KA ? 20 : 16);
+                if constexpr ((kb == KA || kb == KB) && i >= 0) {
+                    constexpr int u = i / 3, s = i % 3;
+                    if constexpr (kb == KA && u < 2) {
+                        if constexpr (s < 2) split_two(u == 0 ? v0 : v1, s, 8 + 4 * u); else put_dy(u, buf ^ 1);
+                    } else if constexpr (kb == KB && u < 3) {
+                        if constexpr (s < 2) split_two(u == 0 ? v0 : u == 1 ? v1 : v2, s, u == 0 ? 16 : 4 * (u - 1));
+                        else if constexpr (u == 0) put_dy(2, buf ^ 1);
+                        else put_x(u - 1, hh_new, p.nnew);
+                    }
+                }
+            };
+            auto second_loads = [&]() {
+                load_dy(v0, 2, n, prow + 1); load_x(v1, 0, n, hh_new); load_x(v2, 1, n, hh_new);
+            };
+            auto block = [&](auto kb_c) {
+                constexpr int kb = decltype(kb_c)::value, U = kb & 1, V = U ^ 1;
+                constexpr bool last = kb + 1 == NKB;
+                static_for<30>([&](auto m_c) {
+                    constexpr int m = decltype(m_c)::value;
+                    if constexpr (m == 0) { read_a(V, 0, kb); read_b(1, 1, kb); }
+                    if constexpr (m == 6) read_a(U, 1, kb);
+                    if constexpr (m == 18) read_b(1, 2, kb);
+                    if constexpr (m == 24 && !last) { read_b(0, 0, kb + 1); read_a(V, 2, kb + 1); }
+                    __builtin_amdgcn_sched_barrier(0);
+                    constexpr int ca[6] = {2, 0, 0, 1, 0, 1}, cb[6] = {0, 0, 2, 0, 1, 1};
+                    constexpr int g = m < 6 ? m : m < 18 ? (m - 6) / 2 : m < 24 ? m - 18 : m - 24;
+                    constexpr int tile = m < 6 ? 2 : m < 18 ? (m & 1) * 3 : m < 24 ? 1 : 4;
+                    product(tile, m < 6 || m >= 18 ? U : V, tile < 3 ? 0 : 1, ca[g], cb[g]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    work(kb_c, m_c);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (kb == KA) second_loads();
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            block(I<0>{});
+            if constexpr (NKB > 1) block(I<1>{});
+            if constexpr (NKB > 2) block(I<2>{});
+            if constexpr (NKB > 3) block(I<3>{});
+            if constexpr (KB == NKB) { store_dy(v0, 2, buf ^ 1); store_x(v1, 0, hh_new, p.nnew); store_x(v2, 1, hh_new, p.nnew); }
+            __syncthreads();
+            buf ^= 1;
+        }
+    }
+
+    // ---- sums that call for fp32 arithmetic: the work-group computes its share again (rule of split_finish) ----
+    int col_j[3];                                                 // (c, r, s) of this lane's column, -1 where there is none
+    int col_c[3], col_r[3], col_s[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const int quad = blk_col[b] * 8 + (l32 >> 2);
+        const int cr = quad / p.SG, s = (quad - cr * p.SG) * 4 + (l32 & 3);
+        const bool ok = quad < p.quads && s < p.S;
+        col_j[b] = ok ? cr * p.S + s : -1;
+        col_c[b] = ok ? cr / p.R : 0;
+        col_r[b] = ok ? cr - cr / p.R * p.R : 0;
+        col_s[b] = ok ? s : 0;
+    }
+    if (!stored4) col_j[2] = -1;
+    auto tile_slot = [](int t) { return t < 3 ? t : t - 3; };
+    auto tile_col = [](int t) { return t < 3 ? 0 : t - 2; };
+    int *const words = reinterpret_cast<int *>(lds_fast);
+    bool inf = false, nan = false;
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            acc[t][v] = (acc[t][v] + low[t][v]) * kSplitUnscale;
+            const unsigned s = __float_as_uint(acc[t][v]);
+            const bool here = col_j[tile_col(t)] >= 0 && slot_row[tile_slot(t)] * 32 + (v >> 2) * 8 + half * 4 + (v & 3) < p.K;
+            inf |= here && (s & 0x7fffffffu) == 0x7f800000u;
+            nan |= here && is_nan_bits(s);
+        }
+    const int f = split_group_or<NW>(words, wave, lane, (__ballot(inf) ? 1 : 0) | (__ballot(nan) ? 2 : 0));
+    bool again = f & 1;
+    // f(a, b) over this lane's operands: four pairs of positions at a time, this half's of each pair
+    auto sweep = [&](auto use) {
+#pragma unroll 1
+        for (int unit = blockIdx.x; unit < p.units; unit += gridDim.x) {
+            const int n = (int)fastdiv((uint32_t)unit, p.div_splits);
+            const int sp = unit - n * p.splits;
+            const int p_begin = (int)((int64_t)p.P * sp / p.splits), p_end = (int)((int64_t)p.P * (sp + 1) / p.splits);
+#pragma unroll 1
+            for (int prow = p_begin; prow < p_end; ++prow)
+#pragma unroll 1
+                for (int q0 = 0; q0 < p.Q; q0 += 8) {
+                    float a[4][3], b[4][3];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int q = q0 + 2 * t + half;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            const int m = slot_row[i] * 32 + l32;
+                            const bool ok = q < p.Q && m < p.K;
+                            a[t][i] = load_or_zero(p.dy, (int64_t)n * p.y_bs + ((int64_t)m * p.P + prow) * p.Q + q, ok);
+                        }
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            const int h = 4 * prow + col_r[c] - p.pad, w = 4 * q + col_s[c] - p.pad;
+                            const bool ok = q < p.Q && col_j[c] >= 0 && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
+                            b[t][c] = load_or_zero(p.x, (int64_t)n * p.x_bs + ((int64_t)col_c[c] * p.H + h) * p.W + w, ok);
+                        }
+                    }
+                    if (!use(a, b)) return;
+                }
+        }
+    };
+    if (!again && (f & 2)) {
+        int *const marks = words + 16;                            // rows with a NaN operand
+        for (int i = tid; i < kRowsM; i += kRowsSplitThreads) marks[i] = 0;
+        __syncthreads();
+        int rows = 0, cols = 0;                                   // this lane's rows and columns with one, by slot
+#pragma unroll
+        for (int c = 0; c < 3; ++c) cols |= col_j[c] < 0 ? 1 << c : 0;
+        sweep([&](const float (&a)[4][3], const float (&b)[4][3]) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    rows |= is_nan_bits(__float_as_uint(a[t][i])) ? 1 << i : 0;
+                    cols |= is_nan_bits(__float_as_uint(b[t][i])) ? 1 << i : 0;
+                }
+            const int all_cols = cols | __shfl_xor(cols, 32);
+            return !__all(all_cols == 7);                         // every column of the wave explains its sums
+        });
+        cols |= __shfl_xor(cols, 32);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (rows >> i & 1) marks[slot_row[i] * 32 + l32] = 1;
+        __syncthreads();
+        bool open = false;
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = slot_row[tile_slot(t)] * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+                open |= !(cols >> tile_col(t) & 1) && row < p.K && is_nan_bits(__float_as_uint(acc[t][v])) && !marks[row];
+            }
+        again = split_group_or<NW>(words, wave, lane, __ballot(open) ? 1 : 0) != 0;
+    }
+    if (again) {
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+        sweep([&](const float (&a)[4][3], const float (&b)[4][3]) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 5; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][tile_slot(i)], b[t][tile_col(i)], acc[i], 0, 0, 0);
+            return true;
+        });
+    }
+
+    float *const out = p.part + (size_t)blockIdx.x * p.K * p.Kg;
+#pragma unroll
+    for (int t = 0; t < 5; ++t) {
+        const int j = col_j[tile_col(t)];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = slot_row[tile_slot(t)] * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+            if (j >= 0 && row < p.K) out[(size_t)row * p.Kg + j] = acc[t][v];
+        }
+    }
+}

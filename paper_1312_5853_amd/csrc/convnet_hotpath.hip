@@ -819,6 +819,45 @@ int run_colgemm_f32out(int op, const void *act, const void *w, void *out, const 
     return check_launch();
 }
 
+void launch_rows_f32(const float *x, const float *dy, float *part, const Problem &pb, const Plan &pl, hipStream_t st)
+{
+    WgradRowsF32Args a;
+    a.x = x; a.dy = dy; a.part = part;
+    a.N = pb.N; a.C = pb.C; a.H = pb.H; a.W = pb.W; a.K = pb.K; a.R = pb.R; a.S = pb.S; a.P = pb.P; a.Q = pb.Q;
+    a.Kg = pl.Kg; a.stride = pb.stride; a.pad = pb.pad;
+    a.x_bs = (int)pb.x_bs; a.y_bs = (int)pb.y_bs;
+    a.splits = pl.rows_splits; a.units = pb.N * pl.rows_splits;
+    a.WP = pl.rows_wp; a.nnew = pb.R < pb.stride ? pb.R : pb.stride;
+    a.div_splits = make_fastdiv((uint32_t)a.splits);
+    if (pl.rows_lds > 64 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(wgrad_rows_f32_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    hipLaunchKernelGGL(wgrad_rows_f32_kernel, dim3(pl.rows_wgs), dim3(kRowsF32Threads), pl.rows_lds, st, a);
+}
+
+void launch_rows_split(const float *x, const float *dy, float *part, const Problem &pb, const Plan &pl, hipStream_t st)
+{
+    WgradRowsSplitArgs a;
+    a.x = x; a.dy = dy; a.part = part;
+    a.C = pb.C; a.H = pb.H; a.W = pb.W; a.K = pb.K; a.R = pb.R; a.S = pb.S; a.P = pb.P; a.Q = pb.Q;
+    a.Kg = pl.Kg; a.pad = pb.pad;
+    a.x_bs = (int)pb.x_bs; a.y_bs = (int)pb.y_bs;
+    a.x_bytes = (unsigned)(4 * ((pb.N - 1) * pb.x_bs + (int64_t)pb.C * pb.H * pb.W));
+    a.dy_bytes = (unsigned)(4 * ((pb.N - 1) * pb.y_bs + (int64_t)pb.K * pb.P * pb.Q));
+    a.splits = pl.rows_splits; a.units = pb.N * pl.rows_splits;
+    a.SG = ceil_div(pb.S, 4); a.quads = pb.C * pb.R * a.SG;
+    a.nnew = pb.R < 4 ? pb.R : 4;
+    a.xg = pb.Q - 1 + a.SG; a.dyg = ceil_div(pb.Q, 4);       // at most 58 and 14: 928 items of x, 1344 of dy
+    a.div_splits = make_fastdiv((uint32_t)a.splits);
+    a.div_xg = make_fastdiv((uint32_t)a.xg);
+    a.div_dyg = make_fastdiv((uint32_t)a.dyg);
+    a.div_nnew = make_fastdiv((uint32_t)a.nnew);
+    void (*const kern)(WgradRowsSplitArgs) = pb.Q > 48 ? wgrad_rows_split_kernel<4> : pb.Q > 32 ? wgrad_rows_split_kernel<3>
+                                            : pb.Q > 16 ? wgrad_rows_split_kernel<2> : wgrad_rows_split_kernel<1>;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    hipLaunchKernelGGL(kern, dim3(pl.rows_wgs), dim3(kRowsSplitThreads), pl.rows_lds, st, a);
+}
+
 int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb, const Plan &pl, void *ws,
               hipStream_t st)
 {
@@ -907,27 +946,17 @@ int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb,
     }
     if (pl.rows_f32) {
         // few channels, fp32: the input rows of an output row in LDS, one partial result per work-group
-        WgradRowsF32Args a;
-        a.x = static_cast<const float *>(x); a.dy = static_cast<const float *>(dy);
-        a.part = reinterpret_cast<float *>(wsb + pl.part_off);
-        a.N = pb.N; a.C = pb.C; a.H = pb.H; a.W = pb.W; a.K = pb.K; a.R = pb.R; a.S = pb.S; a.P = pb.P; a.Q = pb.Q;
-        a.Kg = pl.Kg; a.stride = pb.stride; a.pad = pb.pad;
-        a.x_bs = (int)pb.x_bs; a.y_bs = (int)pb.y_bs;
-        a.splits = pl.rows_splits; a.units = pb.N * pl.rows_splits;
-        a.WP = pl.rows_wp; a.nnew = pb.R < pb.stride ? pb.R : pb.stride;
-        a.div_splits = make_fastdiv((uint32_t)a.splits);
-        if (pl.rows_lds > 64 * 1024)
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(wgrad_rows_f32_kernel),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        hipLaunchKernelGGL(wgrad_rows_f32_kernel, dim3(pl.rows_wgs), dim3(kRowsF32Threads), pl.rows_lds, st, a);
+        float *const part = reinterpret_cast<float *>(wsb + pl.part_off);
+        if (pl.rows_split) launch_rows_split(static_cast<const float *>(x), static_cast<const float *>(dy), part, pb, pl, st);
+        else launch_rows_f32(static_cast<const float *>(x), static_cast<const float *>(dy), part, pb, pl, st);
         int rc = check_launch();
         if (rc != kStatusOk) return rc;
         const int count = pb.K * pl.Kg;
         if (count % 4 == 0 && reinterpret_cast<uintptr_t>(dw) % 16 == 0)
-            hipLaunchKernelGGL(reduce_partials_x4, dim3(grid1d(count, 64)), dim3(256), 0, st, a.part,
+            hipLaunchKernelGGL(reduce_partials_x4, dim3(grid1d(count, 64)), dim3(256), 0, st, part,
                                static_cast<float *>(dw), count, pl.rows_wgs);
         else
-            hipLaunchKernelGGL(reduce_partials, dim3(grid1d(count, 64)), dim3(256), 0, st, a.part,
+            hipLaunchKernelGGL(reduce_partials, dim3(grid1d(count, 64)), dim3(256), 0, st, part,
                                static_cast<float *>(dw), count, pl.rows_wgs);
         return check_launch();
     }

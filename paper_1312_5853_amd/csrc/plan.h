@@ -163,6 +163,7 @@ struct Plan {
     // the same decomposition for fp32 tensors (any stride up to 4): rows_wp = LDS pitch of a staged input row
     bool rows_f32;
     int rows_wp;
+    bool rows_split;     // ... on three bfloat16 parts (stride 4): rows_lds is then its
     // fp32 forward / stride-1 backward-data on the bf16 matrix instruction, operands split into three bfloat16 parts
     // (colgemm_split_kernel): tile sp_bm x sp_bn, sp_cb blocks of 16 channels per column, zero-padded planes of
     // sp_hp x sp_wp positions with sp_ph / sp_pw rows / columns of zeros before the data.  The workspace then holds
@@ -445,6 +446,16 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 const int64_t units = (int64_t)pb.N * splits;
                 pl.rows_wgs = units < 256 ? (int)units : 256;
                 pl.part_bytes = (size_t)pl.rows_wgs * pb.K * pl.Kg * 4;
+                // Three parts: stride 4 (a quad of taps is then eight aligned bytes of a staged row), 13 blocks of 32 columns,
+                // rows of 228 staged columns.  Its 15 matrix instructions of 32 clocks per SIMD stand against 72 of 64 in fp32
+                // whatever the extents, so it is taken wherever it fits.  Sums of one product stay in fp32.
+                const int quads = pb.C * pb.R * ceil_div(pb.S, 4);
+                const int64_t split_lds = 2 * 3 * 96 * 144 + (int64_t)pb.C * 16 * 3 * 456 + 128;     // + slack
+                if (three_part && pb.stride == 4 && pb.S <= 12 && quads <= 104 && pb.Q <= 55 && split_lds <= 150 * 1024 &&
+                    (int64_t)pb.N * pb.P * pb.Q > 1) {
+                    pl.rows_split = true;
+                    pl.rows_lds = (int)split_lds;
+                }
             }
         }
         off += round_up64(pl.part_bytes * (pl.fused_groups ? G : 1), 256);

@@ -17,7 +17,7 @@ extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int 
         pb.x_gs = pb.x_bs / groups; pb.y_gs = pb.y_bs / groups; pb.w_gs = (int64_t)(K / groups) * (C / groups) * R * S;
     }
     const Plan pl = ws_bytes < 0 ? make_plan(op, pb) : plan_for_workspace(op, pb, (size_t)ws_bytes);
-    out[0] = pl.direct ? 2 : pl.sp ? 1 : 0;
+    out[0] = pl.direct ? 2 : pl.sp || pl.rows_split ? 1 : 0;
     out[1] = pl.sp ? (pl.sp_fold > 1 ? pl.sp_fold : 1) : 1;
     out[2] = pl.nsplit;
     out[3] = pl.sp ? pl.sp_bm : pl.tile.bm();

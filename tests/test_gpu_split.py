@@ -186,6 +186,58 @@ def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale, shape
     assert np.abs(dw.cpu().numpy().astype(np.float64) - ref).max() <= N * H * W * 2.0 ** -24 * top
 
 
+# Few-channel stride-4 backward-filter with the input rows in LDS: one to four blocks of 16 positions, the last full, nearly
+# full and with one position; 104 and fewer quads of taps, an unused column in a quad; 49, 65 and 96 filters; odd padding;
+# more (image, row range) units than work-groups; rows of the longest extent
+ROW_SHAPES = [
+    (3, 3, 40, 120, 96, 11, 4, 2),
+    (300, 3, 19, 15, 50, 11, 4, 2),
+    (2, 3, 30, 226, 96, 11, 4, 2),
+    (5, 2, 33, 160, 65, 12, 4, 0),
+    (40, 3, 24, 200, 49, 7, 4, 1),
+    (7, 3, 43, 69, 96, 11, 4, 2),
+    (19, 3, 15, 73, 96, 11, 4, 3),
+]
+
+
+@pytest.mark.parametrize("shape", ROW_SHAPES)
+def test_split_row_kernel_stays_within_the_error_bound(shape, route):
+    N, C, H, W, K, R, st, pad = shape
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    assert route(2, *shape).kernels == "split"
+    x, dy = synth.gaussian((N, C, H, W), 951), synth.gaussian((N, K, P, Q), 952)
+    dw = hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad, dw=nan_like((K, C, R, R)))
+    within(dw, oracle.conv_bwd_filter(x, dy, R, R, st, pad),
+           oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad), N * P * Q)
+
+
+# Special values in the input, in dy, and one of each in different places; Q = 29: column 200 lies under taps 0..8 of the
+# last three positions and, of the columns that are staged, under no window of the positions past Q
+@pytest.mark.parametrize("where", ["x", "dy", "both"])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
+def test_split_row_kernel_gives_infinities_and_nan_as_fp32_does(value, where, route):
+    shape = N, C, H, W, K, R, st, pad = 3, 3, 40, 120, 96, 11, 4, 2
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    assert route(2, *shape).kernels == "split"
+    x, dy = np.abs(synth.gaussian((N, C, H, W), 953)) + np.float32(0.5), np.abs(synth.gaussian((N, K, P, Q), 954)) + np.float32(0.5)
+    if where != "dy":
+        x[1, 2, 17, W - 1] = value
+    if where != "x":
+        dy[2, 41, 3, 7] = np.nan if where == "both" else value
+    with np.errstate(all="ignore"):
+        same_pattern(hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad), oracle.conv_bwd_filter(x, dy, R, R, st, pad))
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-37])
+def test_split_row_kernel_keeps_fp32_precision_for_tiny_values(scale, route):
+    shape = N, C, H, W, K, R, st, pad = 3, 3, 40, 120, 96, 11, 4, 2
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    x, dy = synth.gaussian((N, C, H, W), 955), synth.gaussian((N, K, P, Q), 956) * np.float32(scale)
+    dw, ref = hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad), oracle.conv_bwd_filter(x, dy, R, R, st, pad)
+    top = oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad).max()
+    assert np.abs(dw.cpu().numpy().astype(np.float64) - ref).max() <= N * P * Q * 2.0 ** -24 * top
+
+
 # Fully connected: a column or row more and less than a tile, reductions that end inside a step or a split range, one sample
 @pytest.mark.parametrize("N,I,O", [(1, 36, 20), (5, 132, 124), (127, 260, 132), (129, 1000, 128), (33, 4100, 68)])
 def test_split_fully_connected_stays_within_the_error_bound(N, I, O):
