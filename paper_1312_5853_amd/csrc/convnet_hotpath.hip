@@ -42,6 +42,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 #include "device_common.h"
 #include "conv_colgemm_kernels.h"
 #include "conv_bf16_dma_kernels.h"
+#include "conv_bf16_window_kernels.h"
 #include "conv_split_kernels.h"
 #include "conv_wgrad_split_kernels.h"
 #include "conv_wgrad_rows_kernels.h"
@@ -169,8 +170,8 @@ void launch_colgemm_bf16(const TileShape &t, int kc, const ColGemmFastArgs &a, c
 
 int grid1d(int64_t n, int block) { return (int)((n + block - 1) / block); }
 
-template <typename Kern>
-void launch_dma(Kern kern, const ColGemmDmaArgs &a, int grid, int lds, hipStream_t st, int threads = kThreads)
+template <typename Kern, typename Args>
+void launch_dma(Kern kern, const Args &a, int grid, int lds, hipStream_t st, int threads = kThreads)
 {
     if (lds > 64 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -242,6 +243,80 @@ int run_colgemm_dma(int op, const void *act, const void *w, void *out, const Pro
     else if (tn == 3) launch_dma(colgemm_bf16_dma_kernel<2, 3, 2, 2, 32, 2>, a, grid, lds, st);
     else if (kc == 64) launch_dma(colgemm_bf16_dma_kernel<2, 2, 2, 2, 64, 1>, a, grid, lds, st);
     else launch_dma(colgemm_bf16_dma_kernel<2, 2, 2, 2, 32, 2>, a, grid, lds, st);
+    return check_launch();
+}
+
+// bf16 stride-1 forward / backward-data with the window in LDS: one preparation launch, then the contraction of all columns
+int run_colgemm_window(int op, const void *act, const void *w, void *out, const Problem &pb, const Plan &pl, void *ws,
+                       hipStream_t st, const Epilogue *ep, bool *ep_applied)
+{
+    char *wsb = static_cast<char *>(ws);
+    const bool fwd = op == kOpFwd;
+    const int Cr = fwd ? pb.C : pb.K, RS = pb.R * pb.S, GF = pl.fused_groups ? pb.groups : 1;
+    const int bm = pl.win_bm, bn = pl.win_tn * 32 * (bm == 64 ? 4 : 2), mtiles = ceil_div(pl.M, bm);
+    WindowPrepArgs q;
+    q.src = static_cast<const unsigned short *>(act);
+    q.xb = reinterpret_cast<u32x4 *>(wsb + pl.xb_off);
+    q.src_bs = fwd ? pb.x_bs : pb.y_bs;
+    q.Cg = Cr; q.CBp = pl.win_cb;
+    q.LH = fwd ? pb.H : pb.P; q.LW = fwd ? pb.W : pb.Q;
+    q.Hp = pl.win_hp; q.Wp = pl.win_wp; q.pad_h = pl.win_ph; q.pad_w = pl.win_pw;
+    q.positions = (unsigned)(pb.N * q.Hp * q.Wp);
+    q.total = (unsigned)GF * (unsigned)q.CBp * q.positions;           // 32 bytes each, together below 2^31
+    q.xb_blocks = grid1d(q.total, 256);
+    q.w = static_cast<const unsigned short *>(w);
+    q.wt = reinterpret_cast<u32x4 *>(wsb + pl.wt_off);
+    q.M = pl.M; q.Mpad = mtiles * bm; q.R = pb.R; q.S = pb.S; q.C = pb.C; q.ncb = pl.win_ncb;
+    q.transposed = fwd ? 0 : 1;
+    q.wt_halves = (unsigned)(pl.wt_bytes / 16);
+    q.w_gs = pb.w_gs;
+    q.div_pos = make_fastdiv(q.positions);
+    q.div_hpwp = make_fastdiv((uint32_t)(q.Hp * q.Wp));
+    q.div_wp = make_fastdiv((uint32_t)q.Wp);
+    q.div_cbp = make_fastdiv((uint32_t)q.CBp);
+    q.div_mpad = make_fastdiv((uint32_t)q.Mpad);
+    q.div_ncb = make_fastdiv((uint32_t)q.ncb);
+    q.div_taps = make_fastdiv((uint32_t)RS);
+    hipLaunchKernelGGL(window_prepare, dim3(q.xb_blocks + grid1d(q.wt_halves, 256)), dim3(256), 0, st, q);
+    int rc = check_launch();
+    if (rc != kStatusOk) return rc;
+
+    ColGemmWindowArgs a;
+    a.At = reinterpret_cast<const char *>(q.wt); a.xb = reinterpret_cast<const char *>(q.xb); a.dst = out;
+    a.M = pl.M; a.Mpad = q.Mpad;
+    a.OH = fwd ? pb.P : pb.H; a.OW = fwd ? pb.Q : pb.W;
+    a.ncols = pb.N * a.OH * a.OW;
+    a.Hp = q.Hp; a.Wp = q.Wp; a.R = pb.R; a.S = pb.S;
+    a.chunks = pl.win_cb / pl.win_ncb;
+    a.cb_bytes = q.positions * 32u;
+    a.win_bytes = pl.win_bytes;
+    a.mtiles = mtiles; a.ntiles = ceil_div(a.ncols, bn); a.groups = GF;
+    a.tiles_per_xcd = ceil_div(a.mtiles * a.ntiles * GF, 8);
+    a.at_gb = (int64_t)(pl.wt_bytes / GF);
+    a.dst_gs = fwd ? pb.y_gs : pb.x_gs;
+    a.dst_bs = (int)(fwd ? pb.y_bs : pb.x_bs); a.out_bf16 = pb.out_bf16;
+    a.epi_on = ep && GF == 1;
+    a.epi = ep ? *ep : Epilogue{};
+    *ep_applied = a.epi_on;
+    a.div_plane = make_fastdiv((uint32_t)(a.OH * a.OW));
+    a.div_ow = make_fastdiv((uint32_t)a.OW);
+    const int grid = 8 * a.tiles_per_xcd, lds = pl.win_lds;
+    const bool multi = a.chunks > 1, wide = pl.win_tn == 3;
+    auto go = [&](auto rows_c, auto ncb_c) {
+        constexpr int WM = decltype(rows_c)::value / 64, WN = 4 / WM, NCB = decltype(ncb_c)::value;
+        if (multi && wide) launch_dma(colgemm_bf16_window_kernel<2, 3, WM, WN, NCB, true>, a, grid, lds, st);
+        else if (multi) launch_dma(colgemm_bf16_window_kernel<2, 2, WM, WN, NCB, true>, a, grid, lds, st);
+        else if (wide) launch_dma(colgemm_bf16_window_kernel<2, 3, WM, WN, NCB, false>, a, grid, lds, st);
+        else launch_dma(colgemm_bf16_window_kernel<2, 2, WM, WN, NCB, false>, a, grid, lds, st);
+    };
+    using I64 = std::integral_constant<int, 64>;
+    using I128 = std::integral_constant<int, 128>;
+    using C2 = std::integral_constant<int, 2>;
+    using C3 = std::integral_constant<int, 3>;
+    if (bm == 64 && pl.win_ncb == 2) go(I64{}, C2{});
+    else if (bm == 64) go(I64{}, C3{});
+    else if (pl.win_ncb == 2) go(I128{}, C2{});
+    else go(I128{}, C3{});
     return check_launch();
 }
 
@@ -656,6 +731,7 @@ int run_colgemm_f32out(int op, const void *act, const void *w, void *out, const 
     const bool bf = pb.dtype == kDtypeBf16 && !pl.widen_w;   // bf16 MFMA kernel reads the caller's tensors directly
     int64_t w_bs = (int64_t)pb.K * pb.C * RS;
     if (pl.dma) return run_colgemm_dma(op, act, w, out, pb, pl, ws, st, ep, ep_applied);
+    if (pl.win) return run_colgemm_window(op, act, w, out, pb, pl, ws, st, ep, ep_applied);
     if (pl.sp)
         return run_colgemm_split(op, static_cast<const float *>(act), static_cast<const float *>(w),
                                  static_cast<float *>(out), pb, pl, ws, st, ep, ep_applied);

@@ -172,6 +172,11 @@ struct Plan {
     // sp_fold > 1: the stride x stride input positions under an output position are channels (forward of few channels)
     int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad, sp_fold;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
+    // bf16 stride-1 forward / backward-data with the input window of a tile in LDS (colgemm_bf16_window_kernel): 64 or 128 rows,
+    // win_tn blocks of 32 positions per wave, win_ncb channel blocks per step of win_cb (padded) in a column, planes of
+    // win_hp x win_wp positions, win_bytes of LDS per block's window, win_lds in all
+    bool win;
+    int win_bm, win_tn, win_ncb, win_cb, win_hp, win_wp, win_ph, win_pw, win_bytes, win_lds;
     bool direct;                      // small problem: one launch on the vector units, no workspace read or written
     size_t total;
 };
@@ -329,6 +334,59 @@ inline double pick_wgrad_split(int K, int nblocks, int64_t J, int groups, int64_
         if (t < best) { best = t; bm = b; ksplit = ks_b; }
     }
     return us;
+}
+
+// LDS bytes of one channel block's window under `bn` consecutive positions (n, oh, ow): their padded rows, plus R - 1 more for
+// each sample that begins among them, from a multiple of 16 positions on
+inline int64_t window_bytes(int N, int OH, int OW, int R, int hp, int wp, int bn, int unit)
+{
+    const int64_t rows = (bn + OW - 2) / OW + 1, begins = (rows + OH - 2) / OH;
+    const int64_t span = std::min<int64_t>(rows + (R - 1) * (begins + 1), (int64_t)N * hp);
+    return round_up64((span * wp + 15) * 32, unit);
+}
+
+// bf16, stride 1, what the direct-to-LDS kernel does not take: more than 32 rows, more than one block of 16 channels, enough
+// taps that the window is worth loading, and a window that fits.
+inline void plan_window(int op, const Problem &pb, Plan &pl)
+{
+    const bool fwd = op == kOpFwd;
+    const int Cr = fwd ? pb.C : pb.K, RS = pb.R * pb.S;
+    if (pb.dtype != kDtypeBf16 || op == kOpBwdFilter || pb.stride != 1 || pl.dma || Cr % kChunk != 0 || Cr < 32 || pl.M <= 32 ||
+        RS < 9 || (pb.groups > 1 && !pl.fused_groups))
+        return;
+    const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W;
+    const int ph = fwd ? pb.pad : pb.R - 1 - pb.pad, pw = fwd ? pb.pad : pb.S - 1 - pb.pad;
+    if (ph < 0 || pw < 0) return;
+    const int64_t hp = (int64_t)OH + pb.R - 1, wp = (int64_t)OW + pb.S - 1;
+    const int G = pb.groups > 1 ? pb.groups : 1;
+    const int cb = Cr / 16, ncb = round_up(cb, 3) <= round_up(cb, 2) ? 3 : 2, cbp = round_up(cb, ncb);
+    const bool multi = cbp > ncb;
+    const int bm = pl.M <= 64 ? 64 : 128, mtiles = ceil_div(pl.M, bm);
+    const int64_t ncols = (int64_t)pb.N * OH * OW, xb_bytes = (int64_t)G * cbp * pb.N * hp * wp * 32;
+    const int64_t wt_bytes = (int64_t)G * cbp * RS * mtiles * bm * 32;
+    if (xb_bytes + (1 << 20) >= kMaxSpanBytes || wt_bytes >= kMaxSpanBytes) return;
+    int64_t best = -1;
+    for (int tn = 3; tn >= 2; --tn) {
+        const int bn = tn * 32 * (bm == 64 ? 4 : 2);
+        const int64_t win = window_bytes(pb.N, OH, OW, pb.R, (int)hp, (int)wp, bn, multi ? 4096 : 1024);     // (rounds of four waves' loads)
+        const int64_t lds = (multi ? 3 : 2) * (int64_t)ncb * bm * 32 + (multi ? 2 : 1) * ncb * win;
+        // (a round of every block per step, none in a chunk's last two steps)
+        if (lds > 160 * 1024 || (multi && win / 4096 > RS - 2)) continue;
+        const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, per_round = lds <= 80 * 1024 ? 512 : 256;
+        const int64_t cost = (tiles + per_round - 1) / per_round * bn;
+        if (best >= 0 && cost >= best) continue;
+        best = cost;
+        pl.win_tn = tn; pl.win_bytes = (int)win; pl.win_lds = (int)lds;
+    }
+    if (best < 0) return;
+    pl.win = true;
+    pl.win_bm = bm; pl.win_ncb = ncb; pl.win_cb = cbp; pl.win_hp = (int)hp; pl.win_wp = (int)wp; pl.win_ph = ph; pl.win_pw = pw;
+    pl.nsplit = 1;
+    pl.wt_off = 0; pl.wt_bytes = (size_t)wt_bytes;
+    pl.xb_off = round_up64(wt_bytes, 256);
+    // the last tiles' windows and the filters past the last step reach behind the tensors
+    pl.xb_bytes = (size_t)xb_bytes + 2 * (size_t)pl.win_bytes + 2 * (size_t)ncb * mtiles * bm * 32;
+    pl.total = pl.xb_off + round_up64(pl.xb_bytes, 256);
 }
 
 // three_part = false: fp32 passes stay on the fp32 kernels
@@ -649,6 +707,7 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.total = round_up64(pl.part_bytes * GF, 256);
         }
     }
+    if (three_part && !pl.direct) plan_window(op, pb, pl);
     return pl;
 }
 
@@ -657,7 +716,7 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
 inline Plan plan_for_workspace(int op, const Problem &pb, size_t ws_bytes)
 {
     const Plan pl = make_plan(op, pb);
-    if (!pl.sp || ws_bytes >= pl.total) return pl;
+    if (!(pl.sp || pl.win) || ws_bytes >= pl.total) return pl;
     const Plan fp32 = make_plan(op, pb, false);
     return ws_bytes >= fp32.total ? fp32 : pl;
 }
