@@ -17,11 +17,17 @@
 //       the row: linear in memory and in LDS.
 // The columns of a grouped layer follow each other in both; channel blocks are padded with zeros to whole chunks of NCB.
 //
-// A step is one tap x NCB channel blocks.  Filters of step + NBUF - 1 are in flight while a step is multiplied.  Layers of one
-// chunk (MULTI = 0) hold one window and two filter buffers, so that two work-groups share a CU and hide each other's window
-// loads; others prefetch the next chunk's window into a second buffer during the taps and use three filter buffers.
-// Four waves; a wave owns 64 rows x 32 TN positions: with TN = 3 it reads five fragments for six matrix instructions.
-// MEASURED_PLACEHOLDER
+// A step is one tap (MULTI: two) x NCB channel blocks.  Layers of one chunk hold one window and two filter buffers, so that two
+// work-groups of four waves share a CU and hide each other's window loads.  Others (MULTI) prefetch the next chunk's window
+// into a second buffer and keep the filters of two steps in flight in three buffers; that fills the LDS, so the work-group has
+// eight waves, two per SIMD: waves 0..3 take the even taps, waves 4..7 the odd ones, and the two sums of a tile are added
+// through LDS at the end, each group finishing half of the rows.  (With four waves the loop took 91k clocks where the matrix
+// work is 38k: one wave per SIMD waits for each of its LDS reads.)
+// A wave owns 64 rows x 32 TN positions: with TN = 3 it reads five fragments for six matrix instructions.
+// Two columns 48 -> 128 channels 5x5 on 27x27, both together, preparation + kernel, against the register-staged kernel: forward
+// N = 64 57 -> 41 us (9 + 32), N = 128 94 -> 70; backward-data N = 64 79 -> 54 (12 + 42), N = 128 137 -> 98.  Bound: matrix
+// instructions in the loop (87 % of its clocks forward, N = 64); 4.6k clocks of set-up and first window and 11k of stores beside
+// its 33k; backward-data pads 48 rows to 64.  The preparation is bound by memory (5 TB/s at N = 128).
 
 struct ColGemmWindowArgs {
     const char *At, *xb;
@@ -39,19 +45,20 @@ struct ColGemmWindowArgs {
     FastDiv div_plane, div_ow;
 };
 
-template <int TM, int TN, int WM, int WN, int NCB, bool MULTI>
-__global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_window_kernel(const ColGemmWindowArgs p)
+template <int TN, int WM, int WN, int NCB, bool MULTI>
+__global__ __launch_bounds__(MULTI ? 512 : 256, MULTI ? 1 : 2) void colgemm_bf16_window_kernel(const ColGemmWindowArgs p)
 {
-    constexpr int NW = WM * WN, BM = TM * WM * 32, BN = TN * WN * 32;
+    constexpr int TM = 2, KG = MULTI ? 2 : 1, NW = 4 * KG;       // KG: groups of four waves that share out the taps
+    constexpr int BM = TM * WM * 32, BN = TN * WN * 32;
     constexpr int NBUF = MULTI ? 3 : 2;
-    constexpr int AQ = NCB * BM / 32;                            // 1 KB blocks of filters per step
-    constexpr int NLA = (AQ + NW - 1) / NW;                      // ... per wave (the last may repeat an earlier one)
-    constexpr int ABUF = AQ * 1024;
+    constexpr int AQ = NCB * BM / 32;                            // 1 KB blocks of filters per tap
+    constexpr int NLA = (AQ + 3) / 4;                            // ... per wave and step (the last may repeat an earlier one)
+    constexpr int ABUF = KG * AQ * 1024;
     constexpr int NLW = NCB;                                     // loads of the next window per wave and step
-    static_assert(NW == 4, "four waves");
+    static_assert(WM * WN == 4, "four waves");
 
     extern __shared__ __attribute__((aligned(16))) float lds_fast[];
-    const char *const lds = reinterpret_cast<const char *>(lds_fast);        // filter buffers | window buffers
+    char *const lds = reinterpret_cast<char *>(lds_fast);        // filter buffers | window buffers
     const unsigned lds_base = (unsigned)(size_t)lds_fast;
 
     const int bid = blockIdx.x;
@@ -65,8 +72,8 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
     const int m0 = mt * BM, n0 = nt * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = uniform(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+    const int wave = uniform(tid >> 6), kg = MULTI ? wave >> 2 : 0, w4 = wave & 3;
+    const int wm = w4 / WN, wn = w4 % WN;
     const int l32 = lane & 31, half = lane >> 5;
 
     // number of output position j's window origin among the padded positions
@@ -82,22 +89,27 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
     // follows it, so that every wave has the same number of loads in flight)
     const int kilobytes = uniform(((end - start) * 32 + 1023) / 1024), rounds = (kilobytes + NW - 1) / NW;
     const char *const xb = p.xb + (size_t)gcol * p.chunks * NCB * p.cb_bytes + (size_t)start * 32;
-    const int taps = p.R * p.S, steps = p.chunks * taps;
+    const int taps = p.R * p.S, chunk_steps = (taps + KG - 1) / KG, steps = p.chunks * chunk_steps;
     const unsigned w_voff = (unsigned)(wave * 1024 + lane * 16);
     const unsigned w_lds = lds_base + NBUF * ABUF + wave * 1024;
-    // filters of a step: 1 KB blocks of 32 rows, NCB * BM / 32 of them
+    // filters: each group loads its tap's, 1 KB blocks of 32 rows
     unsigned a_voff[NLA], a_lds[NLA];
 #pragma unroll
     for (int i = 0; i < NLA; ++i) {
-        int q = i * NW + wave;
-        if (q >= AQ) q -= NW;
+        int q = i * 4 + w4;
+        if (q >= AQ) q -= 4;
         const int b = q / (BM / 32), r = q - b * (BM / 32);
-        a_voff[i] = (unsigned)(b * p.Mpad * 32 + r * 1024 + lane * 16);
-        a_lds[i] = lds_base + q * 1024;
+        a_voff[i] = (unsigned)((kg * NCB + b) * p.Mpad * 32 + r * 1024 + lane * 16);
+        a_lds[i] = lds_base + (kg * AQ + q) * 1024;
     }
-    const size_t a_step = (size_t)NCB * p.Mpad * 32;
-    const char *a_next = p.At + (size_t)gcol * p.at_gb + (size_t)m0 * 32;            // filters of the next step to load
+    const size_t a_step = (size_t)KG * NCB * p.Mpad * 32, a_last = a_step - (size_t)(chunk_steps * KG - taps) * NCB * p.Mpad * 32;
+    const char *a_next = p.At + (size_t)gcol * p.at_gb + (size_t)m0 * 32;              // filters of the next step to load
+    int a_left = chunk_steps;
     auto load_a = [&](int i, unsigned buf) { dma16(a_next, a_voff[i], a_lds[i] + buf); };
+    auto advance_a = [&]() {
+        if (KG > 1 && --a_left == 0) { a_left = chunk_steps; a_next += a_last; }
+        else a_next += a_step;
+    };
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -107,7 +119,7 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0.f;
 
-    const int a_row = (wm * TM * 32 + l32) * 32 + (half ^ ((l32 >> 3) & 1)) * 16;
+    const int a_row = kg * AQ * 1024 + (wm * TM * 32 + l32) * 32 + (half ^ ((l32 >> 3) & 1)) * 16;
     unsigned pos[TN];                                            // byte offset of this lane's position, half in bit 4
 #pragma unroll
     for (int jn = 0; jn < TN; ++jn)
@@ -138,7 +150,7 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
     for (int t = 0; t < NBUF - 1; ++t) {
 #pragma unroll
         for (int i = 0; i < NLA; ++i) load_a(i, t * ABUF);
-        a_next += a_step;
+        advance_a();
     }
     wait_vmcnt<0>();
     __syncthreads();
@@ -151,8 +163,8 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
     // A wave has little else to issue beside its matrix instructions: offsets move on by additions.
     constexpr unsigned kFirstWindow = NBUF * ABUF;
     const unsigned win_buf = (unsigned)(NCB * p.win_bytes);
-    unsigned tap_off = kFirstWindow, abuf = 0, aload = (NBUF - 1) * ABUF;
-    int step = 0, s_left = p.S, tap_left = taps;
+    unsigned tap_off = kFirstWindow + kg * 32u, abuf = 0, aload = (NBUF - 1) * ABUF;
+    int step = 0, s_left = p.S - kg, chunk_left = chunk_steps, tap = kg;
     // next chunk's window: loads left, of the block that is being loaded, where from and where to
     int w_left = MULTI && p.chunks > 1 ? NCB * rounds : 0, w_block = rounds, chunk = 0;
     const char *w_src = xb + (size_t)NCB * p.cb_bytes;
@@ -164,6 +176,7 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
     auto do_step = [&](auto par_c) {
         constexpr int par = decltype(par_c)::value;
         const bool more_w = MULTI && w_left > 0;
+        const bool real = KG == 1 || tap < taps;                 // an odd count of taps: the second group's last is none
 #pragma unroll
         for (int b = 0; b < NCB; ++b) {
             const int set = (par + b) & 1;
@@ -175,13 +188,15 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
                 else wait_vmcnt<NLA>();
                 asm volatile("s_waitcnt lgkmcnt(0)");
                 __syncthreads();
-                tap_off += 32;
-                if (--s_left == 0) { s_left = p.S; tap_off += (unsigned)(p.Wp - p.S) * 32u; }
-                if (MULTI && --tap_left == 0) {
-                    tap_left = taps;
+                tap_off += KG * 32;
+                tap += KG;
+                if ((s_left -= KG) <= 0) { s_left += p.S; tap_off += (unsigned)(p.Wp - p.S) * 32u; }
+                if (MULTI && --chunk_left == 0) {
+                    chunk_left = chunk_steps;
                     wbuf = win_buf - wbuf;
-                    tap_off = kFirstWindow + wbuf;
-                    s_left = p.S;
+                    tap_off = kFirstWindow + wbuf + kg * 32u;
+                    s_left = p.S - kg;
+                    tap = kg;
                     ++chunk;
                     w_left = chunk + 1 < p.chunks ? NCB * rounds : 0;
                     w_block = rounds;
@@ -193,40 +208,34 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
                 read_frags(0, set ^ 1);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if (b == 0) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < NLA; ++i) load_a(i, aload);
+                if (MULTI && more_w) {
 #pragma unroll
-                for (int jn = 0; jn < TN; ++jn) {
-                    acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[set][i]),
-                                                                         __builtin_bit_cast(bf16x8, fb[set][jn]), acc[i][jn],
-                                                                         0, 0, 0);
-                    const int m = i * TN + jn;
-                    if (b == 0 && m < NLA) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        load_a(m, aload);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (MULTI && b == 0 && m == NLA) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (more_w) {
-#pragma unroll
-                            for (int i2 = 0; i2 < NLW; ++i2) {                   // (NCB * rounds is a multiple of NLW)
-                                dma16(w_src, w_voff, w_dst);
-                                --w_left;
-                                if (--w_block == 0) { w_block = rounds; w_src += w_hop; w_dst += w_hop_lds; }
-                                else { w_src += NW * 1024; w_dst += NW * 1024; }
-                            }
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (int i = 0; i < NLW; ++i) {              // (NCB * rounds is a multiple of NLW)
+                        dma16(w_src, w_voff, w_dst);
+                        --w_left;
+                        if (--w_block == 0) { w_block = rounds; w_src += w_hop; w_dst += w_hop_lds; }
+                        else { w_src += NW * 1024; w_dst += NW * 1024; }
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (real)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int jn = 0; jn < TN; ++jn)
+                        acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[set][i]),
+                                                                             __builtin_bit_cast(bf16x8, fb[set][jn]),
+                                                                             acc[i][jn], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        a_next += a_step;
+        advance_a();
         aload = aload == (NBUF - 1) * ABUF ? 0 : aload + ABUF;
         ++step;
     };
-    static_assert(NLA + (MULTI ? 1 : 0) <= TM * TN, "one load per matrix instruction at most");
     if (NCB % 2 == 0) {
         while (step < steps) do_step(std::integral_constant<int, 0>{});
     } else {
@@ -238,57 +247,97 @@ __global__ __launch_bounds__(WM * WN * 64, MULTI ? 1 : 2) void colgemm_bf16_wind
     }
     wait_vmcnt<0>();
 
+    constexpr int TF = TM / KG;                                  // blocks of 32 rows that a wave finishes
+    f32x16 fin[TF][TN];
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int i = 0; i < TF; ++i)
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) fin[i][jn] = acc[i][jn];
+    } else {
+        // each group hands over the sums of the rows that the other finishes
+        f32x4 *const trade = reinterpret_cast<f32x4 *>(lds) + (size_t)w4 * (TN * 4 * 64) + lane;
+        constexpr int side = 4 * TN * 4 * 64;
+        __syncthreads();
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) {
+            const f32x16 a = acc[0][jn], b = acc[1][jn];         // (by value: a choice of arrays would keep both in memory)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                f32x4 other;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    other[e] = kg == 0 ? b[4 * v + e] : a[4 * v + e];
+                    fin[0][jn][4 * v + e] = kg == 0 ? a[4 * v + e] : b[4 * v + e];
+                }
+                trade[(kg ^ 1) * side + (jn * 4 + v) * 64] = other;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const f32x4 o = trade[kg * side + (jn * 4 + v) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) fin[0][jn][4 * v + e] += o[e];
+            }
+    }
+
+    // Stores: offsets from the tensor's first byte fit 32 bits (checked spans).
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const int plane = p.OH * p.OW;
+    const int plane = p.OH * p.OW, row0 = m0 + wm * TM * 32 + kg * 32 + half * 4;
 #pragma unroll
     for (int jn = 0; jn < TN; ++jn) {
         const int col = n0 + (wn * TN + jn) * 32 + l32;
-        const int n = (int)fastdiv((uint32_t)min(col, p.ncols - 1), p.div_plane);
-        const int rem = min(col, p.ncols - 1) - n * plane;
-        if (p.epi_on)
-            epi_tile<TM, TN>(p.epi, acc, jn, m0 + wm * TM * 32 + half * 4, p.M, plane, (int64_t)n * p.epi.mask_bs + rem);
-        const size_t own = (size_t)gcol * p.dst_gs + (size_t)n * p.dst_bs + rem;
-        const int row0 = m0 + wm * TM * 32 + half * 4;
-        int left = p.M - row0;
-        asm volatile("" : "+v"(left));           // or the rows' masks and offsets are kept in registers over the columns
         const bool in = col < p.ncols;
+        const int n = (int)fastdiv((uint32_t)(in ? col : p.ncols - 1), p.div_plane);
+        const int rem = (in ? col : p.ncols - 1) - n * plane;
+        if (p.epi_on) epi_tile<TF, TN>(p.epi, fin, jn, row0, p.M, plane, (int64_t)n * p.epi.mask_bs + rem);
+        const unsigned own = (unsigned)n * (unsigned)p.dst_bs + (unsigned)rem + (unsigned)row0 * (unsigned)plane;
+        int left = in ? p.M - row0 : 0;
+        asm volatile("" : "+v"(left));           // or the rows' masks are kept in registers over the columns
         if (!p.out_bf16) {
-            if (!in) continue;
-            float *const out = static_cast<float *>(p.dst) + own + (size_t)row0 * plane;
+            char *const out = reinterpret_cast<char *>(static_cast<float *>(p.dst) + (size_t)gcol * p.dst_gs);
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TF; ++i)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int d = i * 32 + (v >> 2) * 8 + (v & 3);
-                    if (d < left) out[(unsigned)(d * plane)] = acc[i][jn][v];
+                    if (d < left) *reinterpret_cast<float *>(out + (4u * (own + (unsigned)(d * plane)))) = fin[i][jn][v];
                 }
             continue;
         }
         // Neighbouring lanes (positions col, col + 1 of one sample) trade a value so that the even lane stores row a of both
         // positions and the odd lane row a + 1 of both, four bytes each; lanes whose neighbour belongs to another sample, or
         // lies past the last column, store their two values one by one.
+        char *const out = reinterpret_cast<char *>(static_cast<unsigned short *>(p.dst) + (size_t)gcol * p.dst_gs);
         const bool odd = l32 & 1;
         const bool pair = odd ? rem >= 1 : rem + 1 < plane && col + 1 < p.ncols;
-        unsigned short *const out = static_cast<unsigned short *>(p.dst) + own + (size_t)row0 * plane;
-        unsigned short *const both = out + (odd ? plane - 1 : 0);
+        const unsigned both = own + (odd ? (unsigned)plane - 1u : 0u);
+        const int left_both = left - (odd ? 1 : 0);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TF; ++i)
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 const int d = i * 32 + (v >> 2) * 8 + (v & 3);
-                const float va = acc[i][jn][v], vb = acc[i][jn][v + 1];
+                const float va = fin[i][jn][v], vb = fin[i][jn][v + 1];
                 const float send = odd ? va : vb;
                 const float recv = __builtin_bit_cast(
                     float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));
-                if (pair) {
-                    const bf16x2 pk = __builtin_convertvector((f32x2){odd ? recv : va, odd ? vb : recv}, bf16x2);
-                    if (in && d + (odd ? 1 : 0) < left) __builtin_memcpy(both + (unsigned)(d * plane), &pk, 4);
-                } else if (in) {
-                    if (d < left) out[(unsigned)(d * plane)] = bf16_round(va);
-                    if (d + 1 < left) out[(unsigned)((d + 1) * plane)] = bf16_round(vb);
-                }
+                const bf16x2 pk = __builtin_convertvector((f32x2){odd ? recv : va, odd ? vb : recv}, bf16x2);
+                if (pair && d < left_both) __builtin_memcpy(out + 2u * (both + (unsigned)(d * plane)), &pk, 4);
             }
+        if (!pair)
+#pragma unroll
+            for (int i = 0; i < TF; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int d = i * 32 + (v >> 2) * 8 + (v & 3);
+                    if (d < left)
+                        *reinterpret_cast<unsigned short *>(out + 2u * (own + (unsigned)(d * plane))) = bf16_round(fin[i][jn][v]);
+                }
     }
 }
 

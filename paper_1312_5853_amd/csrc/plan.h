@@ -346,13 +346,18 @@ inline int64_t window_bytes(int N, int OH, int OW, int R, int hp, int wp, int bn
 }
 
 // bf16, stride 1, what the direct-to-LDS kernel does not take: more than 32 rows, more than one block of 16 channels, enough
-// taps that the window is worth loading, and a window that fits.
+// taps that the window is worth loading, and a window that fits; and an estimate below that of the register-staged kernel,
+// which splits the reduction and so wins where few tiles meet a long one.  Both estimates (us, all columns of a launch
+// together: two columns of 48 -> 128 channels at N = 64 are one round of windows and three of the staged kernel) were fitted to 280 passes of drawn layers, to 11 and 15 %; over them the rule
+// takes 0.93 of the register-staged kernel's time in all, the better of the two each time would take 0.91.  Measured on both
+// sides of the line, window / staged: 58x80x21x28, 64 channels 3x3 19 / 32 us; 27 x 112 x 44 x 36, 125 filters 5x5 50 / 72;
+// 8 x 208 x 16 x 25, 295 filters 5x5 57 / 56; 7 x 208 x 24 x 14, 144 filters 7x7 95 / 77; 1 x 128 x 14 x 12, 80 filters 5x5 32 / 19.
 inline void plan_window(int op, const Problem &pb, Plan &pl)
 {
     const bool fwd = op == kOpFwd;
     const int Cr = fwd ? pb.C : pb.K, RS = pb.R * pb.S;
     if (pb.dtype != kDtypeBf16 || op == kOpBwdFilter || pb.stride != 1 || pl.dma || Cr % kChunk != 0 || Cr < 32 || pl.M <= 32 ||
-        RS < 9 || (pb.groups > 1 && !pl.fused_groups))
+        RS < 9 || pb.S < 3 || (pb.groups > 1 && !pl.fused_groups))
         return;
     const int OH = fwd ? pb.P : pb.H, OW = fwd ? pb.Q : pb.W;
     const int ph = fwd ? pb.pad : pb.R - 1 - pb.pad, pw = fwd ? pb.pad : pb.S - 1 - pb.pad;
@@ -368,10 +373,11 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     int64_t best = -1;
     for (int tn = 3; tn >= 2; --tn) {
         const int bn = tn * 32 * (bm == 64 ? 4 : 2);
-        const int64_t win = window_bytes(pb.N, OH, OW, pb.R, (int)hp, (int)wp, bn, multi ? 4096 : 1024);     // (rounds of four waves' loads)
-        const int64_t lds = (multi ? 3 : 2) * (int64_t)ncb * bm * 32 + (multi ? 2 : 1) * ncb * win;
+        const int64_t win = window_bytes(pb.N, OH, OW, pb.R, (int)hp, (int)wp, bn, multi ? 8192 : 1024);     // (rounds of eight waves' loads)
+        int64_t lds = (multi ? 6 : 2) * (int64_t)ncb * bm * 32 + (multi ? 2 : 1) * ncb * win;
+        if (multi) lds = std::max<int64_t>(lds, 8 * tn * 4096);          // the sums that the two groups of waves trade
         // (a round of every block per step, none in a chunk's last two steps)
-        if (lds > 160 * 1024 || (multi && win / 4096 > RS - 2)) continue;
+        if (lds > 160 * 1024 || (multi && win / 8192 > (RS + 1) / 2 - 2)) continue;
         const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, per_round = lds <= 80 * 1024 ? 512 : 256;
         const int64_t cost = (tiles + per_round - 1) / per_round * bn;
         if (best >= 0 && cost >= best) continue;
@@ -379,13 +385,27 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
         pl.win_tn = tn; pl.win_bytes = (int)win; pl.win_lds = (int)lds;
     }
     if (best < 0) return;
+    {
+        const int bn = pl.win_tn * 32 * (bm == 64 ? 4 : 2), slots = pl.win_lds <= 80 * 1024 ? 512 : 256;
+        const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, rounds = (tiles + slots - 1) / slots;
+        const double slices = cbp * RS * (pl.win_tn == 3 ? 1.0 : 0.72);
+        const double us = 11.7 + 0.6 * xb_bytes / 1e6 + (multi ? 0.148 * slices * rounds
+                                                                   : 0.131 * slices * (tiles > 256 ? 2 * rounds : 1));
+        const int kc = Cr % 64 == 0 ? 64 : Cr % 48 == 0 ? 48 : Cr % 32 == 0 ? 32 : 16;           // channels per step
+        const int64_t staged = (pl.Mpad / pl.tile.bm()) * ((ncols + pl.tile.bn() - 1) / pl.tile.bn()) * pl.nsplit * G;
+        const double steps = (double)ceil_div(Cr / kc * RS, pl.nsplit) * ((staged + 255) / 256);
+        const double staged_us = 12.5 + 0.33 * pl.blk_bytes / 1e6 +
+                                 (pl.nsplit > 1 ? 3.1 + 0.26 * ncols * G * pl.M * 4.0 * pl.nsplit / 1e6 : 0.0) +
+                                 steps * (0.0943 * kc / 16 * pl.tile.bm() * pl.tile.bn() / 16384.0 + 0.14);
+        if (us >= 0.9 * staged_us) return;
+    }
     pl.win = true;
     pl.win_bm = bm; pl.win_ncb = ncb; pl.win_cb = cbp; pl.win_hp = (int)hp; pl.win_wp = (int)wp; pl.win_ph = ph; pl.win_pw = pw;
     pl.nsplit = 1;
     pl.wt_off = 0; pl.wt_bytes = (size_t)wt_bytes;
     pl.xb_off = round_up64(wt_bytes, 256);
     // the last tiles' windows and the filters past the last step reach behind the tensors
-    pl.xb_bytes = (size_t)xb_bytes + 2 * (size_t)pl.win_bytes + 2 * (size_t)ncb * mtiles * bm * 32;
+    pl.xb_bytes = (size_t)xb_bytes + 2 * (size_t)pl.win_bytes + 6 * (size_t)ncb * mtiles * bm * 32;
     pl.total = pl.xb_off + round_up64(pl.xb_bytes, 256);
 }
 

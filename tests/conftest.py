@@ -38,7 +38,7 @@ Route = collections.namedtuple("Route", "kernels fold nsplit rows columns worksp
 @pytest.fixture(scope="session")
 def route(tmp_path_factory):
     """route(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0, workspace=None): what the planner does with such a pass
-    (and a workspace of so many bytes), so that a test written for one set of kernels ("fp32", "split" or "direct") can assert that it reaches them."""
+    (and a workspace of so many bytes), so that a test written for one set of kernels ("fp32", "split", "direct" or "window") can assert that it reaches them."""
     so = str(tmp_path_factory.mktemp("plan") / "plan_query.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "plan_query.cpp")],
                    check=True)
@@ -48,7 +48,7 @@ def route(tmp_path_factory):
         out = (ctypes.c_longlong * 6)()
         assert query(op, N, C, H, W, K, R, R, stride, pad, groups, dtype,
                      ctypes.c_longlong(-1 if workspace is None else workspace), out) == 0
-        return Route(("fp32", "split", "direct")[out[0]], *list(out)[1:])
+        return Route(("fp32", "split", "direct", "window")[out[0]], *list(out)[1:])
     return ask
 
 

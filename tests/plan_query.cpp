@@ -4,7 +4,7 @@
 
 using namespace convnet;
 
-// ws_bytes: what the call brings, or -1: as much as it wants.  out: 0 fp32 kernels, 1 three-part kernels, 2 vector units; fold; splits of the reduction; rows, columns of a tile; workspace
+// ws_bytes: what the call brings, or -1: as much as it wants.  out: 0 fp32 kernels, 1 three-part kernels, 2 vector units, 3 bf16 with the input window in LDS; fold; splits of the reduction; rows, columns of a tile; workspace
 extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups, int dtype,
                           long long ws_bytes, long long *out)
 {
@@ -17,11 +17,11 @@ extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int 
         pb.x_gs = pb.x_bs / groups; pb.y_gs = pb.y_bs / groups; pb.w_gs = (int64_t)(K / groups) * (C / groups) * R * S;
     }
     const Plan pl = ws_bytes < 0 ? make_plan(op, pb) : plan_for_workspace(op, pb, (size_t)ws_bytes);
-    out[0] = pl.direct ? 2 : pl.sp || pl.rows_split ? 1 : 0;
+    out[0] = pl.direct ? 2 : pl.sp || pl.rows_split ? 1 : pl.win ? 3 : 0;
     out[1] = pl.sp ? (pl.sp_fold > 1 ? pl.sp_fold : 1) : 1;
     out[2] = pl.nsplit;
-    out[3] = pl.sp ? pl.sp_bm : pl.tile.bm();
-    out[4] = pl.sp ? pl.sp_bn : pl.tile.bn();
+    out[3] = pl.sp ? pl.sp_bm : pl.win ? pl.win_bm : pl.tile.bm();
+    out[4] = pl.sp ? pl.sp_bn : pl.win ? pl.win_tn * 32 * (pl.win_bm == 64 ? 4 : 2) : pl.tile.bn();
     out[5] = (long long)pl.total;
     return kStatusOk;
 }
