@@ -678,6 +678,7 @@ struct WgradLinDmaArgs {
     const unsigned short *xp;
     float *part;
     int K, Kpad, C, ncols;
+    int Ctotal, nsplit;       // channels of all columns of a grouped layer in this launch
     int S, Wq;
     int N, G, Jx;             // G = Jy / 8 groups of 8 positions per image
     int row_x_bytes;          // bytes per xp row (N * Jx * 2)
@@ -706,8 +707,9 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
     const int unit = (bid & 7) * p.units_per_xcd + idx;
     if (idx >= p.units_per_xcd || unit >= p.nunits) return;
     const int ntile = p.mtiles * p.ntiles;
-    const int split = unit / ntile;
-    const int tile = unit - split * ntile;
+    const int gcol = unit / (ntile * p.nsplit), unit_c = unit - gcol * (ntile * p.nsplit);
+    const int split = unit_c / ntile;
+    const int tile = unit_c - split * ntile;
     const int mt = tile % p.mtiles, nt = tile / p.mtiles;
     const int m0 = mt * BM, n0 = nt * BN;
 
@@ -732,7 +734,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
         const int rs = (int)fastdiv((uint32_t)col, p.div_c), c = col - rs * p.C;
         const int r = (int)fastdiv((uint32_t)rs, p.div_s), sx = rs - r * p.S;
         const int shift = r * p.Wq + sx;                   // odd shifts read the copy that is moved up by one element
-        bbase[u] = (uint32_t)(c + (shift & 1) * p.C) * (uint32_t)p.row_x_bytes + 2u * (uint32_t)(shift & ~1);
+        bbase[u] = (uint32_t)(gcol * p.C + c + (shift & 1) * p.Ctotal) * (uint32_t)p.row_x_bytes + 2u * (uint32_t)(shift & ~1);
     }
     int pn[2], pg[2];
 #pragma unroll
@@ -744,7 +746,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
     }
     const unsigned aoff = (unsigned)((wave * NA * 64 + lane) * 16);
     const size_t a_step_bytes = (size_t)p.Kpad * RB;
-    const char *a_base = reinterpret_cast<const char *>(p.dyT) + (size_t)step_begin * a_step_bytes + (size_t)m0 * RB;
+    const char *a_base = reinterpret_cast<const char *>(p.dyT) + ((size_t)gcol * p.steps + step_begin) * a_step_bytes + (size_t)m0 * RB;
     const char *const xpb = reinterpret_cast<const char *>(p.xp);
 
     unsigned la = 0, lb = 0, pos[2] = {0u, 0u};
@@ -847,7 +849,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
     while (step + 2 < nsteps) do_step(std::true_type{});
     while (step < nsteps) do_step(std::false_type{});
 
-    float *out = p.part + (size_t)split * p.K * p.ncols;
+    float *out = p.part + ((size_t)gcol * p.nsplit + split) * p.K * p.ncols;
 #pragma unroll
     for (int jn = 0; jn < TN; ++jn) {
         const int col = n0 + (wn * TN + jn) * 32 + l32;
@@ -870,7 +872,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
 __device__ __forceinline__ void pack_dy_lin(int64_t i8, const unsigned short *__restrict__ dy,
                                             unsigned short *__restrict__ dyp, int N, int K, int P, int Q, int Wq, int Jy,
                                             int row_elems, int64_t dy_bs, FastDiv div_row, FastDiv div_jy,
-                                            FastDiv div_wq, int kpad)
+                                            FastDiv div_wq, int kpad, int Kcol, int steps, FastDiv div_kcol)
 {
     const int64_t i = i8 * 8;
     if (i >= (int64_t)K * row_elems) return;
@@ -890,8 +892,10 @@ __device__ __forceinline__ void pack_dy_lin(int64_t i8, const unsigned short *__
         reinterpret_cast<u32x4 *>(dyp)[i8] = o;
     } else {
         // dyT[step][Kpad][64]: chunk (e % 64) / 8 of row k and step e / 64 goes to position chunk ^ swz(k)
-        const uint32_t st = e >> 6, chunk = (e >> 3) & 7;
-        reinterpret_cast<u32x4 *>(dyp)[((size_t)st * kpad + k) * 8 + (chunk ^ ((k >> 1) & 7))] = o;
+        // (of a grouped layer the columns, Kcol filters each, follow each other)
+        const uint32_t g = fastdiv(k, div_kcol), kc = k - g * (uint32_t)Kcol;
+        const uint32_t st = g * (uint32_t)steps + (e >> 6), chunk = (e >> 3) & 7;
+        reinterpret_cast<u32x4 *>(dyp)[((size_t)st * kpad + kc) * 8 + (chunk ^ ((kc >> 1) & 7))] = o;
     }
 }
 
@@ -931,17 +935,18 @@ struct PackLinArgs {
     const unsigned short *dy, *x;
     unsigned short *dyp, *xp;
     int N, K, C, P, Q, H, W, pad, Wq, Jy, Jx, row_elems, dy_blocks;
+    int Kcol, steps;       // filters per column; 64-position steps
     int kpad;              // > 0: dy goes to the step-major swizzled layout dyT[step][kpad][64] (rows K..kpad-1 are not
                            // written: what the kernel computes from them is never stored)
     int64_t dy_bs, x_bs;
-    FastDiv div_row, div_jy, div_jx, div_wq;
+    FastDiv div_row, div_jy, div_jx, div_wq, div_kcol;
 };
 
 __global__ __launch_bounds__(256) void pack_lin(const PackLinArgs a)
 {
     if ((int)blockIdx.x < a.dy_blocks)
         pack_dy_lin((int64_t)blockIdx.x * 256 + threadIdx.x, a.dy, a.dyp, a.N, a.K, a.P, a.Q, a.Wq, a.Jy, a.row_elems,
-                    a.dy_bs, a.div_row, a.div_jy, a.div_wq, a.kpad);
+                    a.dy_bs, a.div_row, a.div_jy, a.div_wq, a.kpad, a.Kcol, a.steps, a.div_kcol);
     else
         pack_x_lin((int64_t)(blockIdx.x - a.dy_blocks) * 256 + threadIdx.x, a.x, a.xp, a.N, a.C, a.H, a.W, a.pad, a.Wq,
                    a.Jx, a.x_bs, a.div_jx, a.div_wq);

@@ -951,20 +951,21 @@ int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb,
         // same-extent stride-1 layer: pack both tensors, then every operand is a 16-byte load
         unsigned short *dyp = reinterpret_cast<unsigned short *>(wsb + pl.lin_dy_off);
         unsigned short *xp = reinterpret_cast<unsigned short *>(wsb + pl.lin_x_off);
-        const int row_elems = pl.lin_steps * 64;
+        const int row_elems = pl.lin_steps * 64, GF = pl.fused_groups ? pb.groups : 1;
         PackLinArgs q;
         q.dy = static_cast<const unsigned short *>(dy); q.x = static_cast<const unsigned short *>(x);
         q.dyp = dyp; q.xp = xp;
-        q.N = pb.N; q.K = pb.K; q.C = pb.C; q.P = pb.P; q.Q = pb.Q; q.H = pb.H; q.W = pb.W; q.pad = pb.pad;
+        q.N = pb.N; q.K = pb.K * GF; q.C = pb.C * GF; q.P = pb.P; q.Q = pb.Q; q.H = pb.H; q.W = pb.W; q.pad = pb.pad;
+        q.Kcol = pb.K; q.steps = pl.lin_steps; q.div_kcol = make_fastdiv((uint32_t)pb.K);
         q.Wq = pl.lin_wq; q.Jy = pl.lin_jy; q.Jx = pl.lin_jx; q.row_elems = row_elems;
-        q.dy_blocks = grid1d((int64_t)pb.K * row_elems / 8, 256);
+        q.dy_blocks = grid1d((int64_t)q.K * row_elems / 8, 256);
         q.kpad = round_up(pb.K, 128);
         q.dy_bs = pb.y_bs; q.x_bs = pb.x_bs;
         q.div_row = make_fastdiv((uint32_t)row_elems);
         q.div_jy = make_fastdiv((uint32_t)pl.lin_jy);
         q.div_jx = make_fastdiv((uint32_t)pl.lin_jx);
         q.div_wq = make_fastdiv((uint32_t)pl.lin_wq);
-        hipLaunchKernelGGL(pack_lin, dim3(q.dy_blocks + grid1d((int64_t)pb.C * pb.N * pl.lin_jx / 8, 256)), dim3(256),
+        hipLaunchKernelGGL(pack_lin, dim3(q.dy_blocks + grid1d((int64_t)q.C * pb.N * pl.lin_jx / 8, 256)), dim3(256),
                            0, st, q);
         WgradLinDmaArgs a;
         a.dyT = dyp; a.xp = xp; a.part = reinterpret_cast<float *>(wsb + pl.part_off);
@@ -974,7 +975,8 @@ int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb,
         a.steps = pl.lin_steps; a.steps_per_split = pl.chunks_per_split;
         a.mtiles = a.Kpad / 128;
         a.ntiles = ceil_div(pl.Kg, 256);
-        a.nunits = a.mtiles * a.ntiles * pl.nsplit;
+        a.Ctotal = pb.C * GF; a.nsplit = pl.nsplit;
+        a.nunits = a.mtiles * a.ntiles * pl.nsplit * GF;
         a.units_per_xcd = ceil_div(a.nunits, 8);
         a.div_c = make_fastdiv((uint32_t)pb.C);
         a.div_s = make_fastdiv((uint32_t)pb.S);
@@ -987,7 +989,7 @@ int run_wgrad(const void *x, const void *dy, void *dw, const Problem &caller_pb,
         }
         int rc = check_launch();
         if (rc != kStatusOk) return rc;
-        return launch_finish_wgrad(a.part, static_cast<float *>(dw), pb.K, pb.C, RS, pl.nsplit, 1, st);
+        return launch_finish_wgrad(a.part, static_cast<float *>(dw), pb.K, pb.C, RS, pl.nsplit, GF, st);
     }
     if (pl.rows && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(dy) % 4 == 0) {
         // few channels, stride 4, bf16: input rows as shifted copies in LDS, one partial result per work-group
@@ -1309,7 +1311,8 @@ static int run_grouped(int op, const void *a, const void *b, void *out, int N, i
         if (!aligned(ws, 256)) return kErrMisaligned;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (groups == 1 || (pl.fused_groups && !pl.direct))
+    const bool together = groups == 1 || (pl.fused_groups && !pl.direct);
+    if (together && !(pl.lin && groups > 1))
         return op == kOpBwdFilter ? run_wgrad(a, b, out, pb, pl, ws, st) : run_colgemm(op, a, b, out, pb, pl, ws, st);
     // one column after the other (also where one launch could take them all but a column is small enough for the vector
     // units, so that columns give the same bits together and alone): element sizes of the three tensors of this pass
@@ -1325,8 +1328,9 @@ static int run_grouped(int op, const void *a, const void *b, void *out, int N, i
     // every column's base must keep the alignment the kernels rely on (the fused ones rely on none): checked for all
     // columns before the first
     // one is enqueued
-    for (int g = 1; g < groups && !pl.fused_groups; ++g)
+    for (int g = 1; g < groups && (!pl.fused_groups || pl.lin); ++g)
         if ((g * sa) % 16 != 0 || (g * sb) % 16 != 0 || (g * so) % 16 != 0) return kErrMisaligned;
+    if (together) return run_wgrad(a, b, out, pb, pl, ws, st);
     for (int g = 0; g < groups; ++g) {
         const char *pa = static_cast<const char *>(a) + g * sa, *pbp = static_cast<const char *>(b) + g * sb;
         char *po = static_cast<char *>(out) + g * so;

@@ -144,7 +144,7 @@ struct Plan {
     // bf16 backward-filter of a stride-1 layer whose output has the input's extent: packed copies in which a
     // filter tap is a linear shift (row pitch lin_wq, lin_jy / lin_jx elements per image), 64 positions per step
     bool lin;
-    int lin_wq, lin_jy, lin_jx, lin_steps;
+    int lin_wq, lin_jy, lin_jx, lin_steps;      // (a grouped layer: fused_groups, both regions hold all columns)
     size_t lin_dy_off, lin_dy_bytes, lin_x_off, lin_x_bytes;
     // columns of a grouped layer run in ONE launch (fp32 kernels of the fast paths): the filter and partial-sum
     // regions then hold `groups` consecutive copies; otherwise the host runs the columns one after the other
@@ -480,15 +480,19 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             const int kpad = round_up(pb.K, 128);
             const int64_t dy_bytes = (int64_t)kpad * steps * 64 * 2, x_bytes = (int64_t)2 * pb.C * pb.N * jx * 2;
             if (jy >= 64 && dy_bytes < kMaxSpanBytes && x_bytes < kMaxSpanBytes) {
+                // the columns of a grouped layer in one launch of each kernel (two of 48 -> 128 channels 5x5, N = 64: 80 -> 60 us),
+                // where their packed copies together can still be indexed
+                pl.fused_groups = G > 1 && three_part && dy_bytes * G < kMaxSpanBytes && x_bytes * G < kMaxSpanBytes;
+                const int GF = pl.fused_groups ? G : 1;
                 pl.lin = true;
                 pl.lin_wq = wq; pl.lin_jy = jy; pl.lin_jx = jx; pl.lin_steps = (int)steps;
-                want = 256 / ((kpad / 128) * ceil_div(pl.Kg, 256));
+                want = 256 / ((kpad / 128) * ceil_div(pl.Kg, 256) * GF);
                 int ns = want < (int)(steps / 4) ? want : (int)(steps / 4);     // at least 4 steps per split
                 if (ns < 1) ns = 1;
                 pl.chunks_per_split = ceil_div((int)steps, ns);
                 pl.nsplit = ceil_div((int)steps, pl.chunks_per_split);
-                pl.lin_dy_off = off; pl.lin_dy_bytes = (size_t)dy_bytes; off += round_up64(pl.lin_dy_bytes, 256);
-                pl.lin_x_off = off; pl.lin_x_bytes = (size_t)x_bytes; off += round_up64(pl.lin_x_bytes, 256);
+                pl.lin_dy_off = off; pl.lin_dy_bytes = (size_t)dy_bytes * GF; off += round_up64(pl.lin_dy_bytes, 256);
+                pl.lin_x_off = off; pl.lin_x_bytes = (size_t)x_bytes * GF; off += round_up64(pl.lin_x_bytes, 256);
             }
         }
         pl.part_off = off;
@@ -731,12 +735,13 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
     return pl;
 }
 
-// The plan of a call that brings ws_bytes of workspace.  The three-part kernels want up to six bytes per padded input element;
-// a caller that has less, but as much as the fp32 kernels take, gets those.
+// The plan of a call that brings ws_bytes of workspace.  The three-part kernels want up to six bytes per padded input element,
+// the window kernel and the columns of a backward-filter in one launch more than the staged kernel and one column; a caller that
+// has less, but as much as those take, gets those.
 inline Plan plan_for_workspace(int op, const Problem &pb, size_t ws_bytes)
 {
     const Plan pl = make_plan(op, pb);
-    if (!(pl.sp || pl.win) || ws_bytes >= pl.total) return pl;
+    if (!(pl.sp || pl.win || (pl.lin && pl.fused_groups)) || ws_bytes >= pl.total) return pl;
     const Plan fp32 = make_plan(op, pb, false);
     return ws_bytes >= fp32.total ? fp32 : pl;
 }
