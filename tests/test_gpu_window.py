@@ -70,6 +70,18 @@ def test_window_passes_stay_within_the_error_bound(op, N, C, H, W, K, R, pad, ro
         assert torch.equal(half, dx.to(torch.bfloat16))
 
 
+# The columns of a grouped bf16 backward-filter in one launch: filters that fill no 128-row tile, three columns, one and many
+# split ranges of the reduction, odd extents
+@pytest.mark.parametrize("N,C,H,W,K,R,groups", [(6, 96, 27, 27, 256, 5, 2), (3, 48, 19, 23, 120, 3, 3), (40, 64, 13, 15, 320, 3, 2)])
+def test_grouped_backward_filter_stays_within_the_error_bound(N, C, H, W, K, R, groups):
+    xb, x = bf16((N, C, H, W), 968)
+    dyb, dy = bf16((N, K, H, W), 969)
+    dw = hp.conv_bwd_filter_grouped(xb.cuda(), dyb.cuda(), R, R, 1, R // 2, groups,
+                                    dw=torch.full((K, C // groups, R, R), float("nan"), device="cuda"))
+    within(dw, oracle.conv_bwd_filter_grouped(x, dy, R, R, 1, R // 2, groups),
+           oracle.conv_bwd_filter_grouped(np.abs(x), np.abs(dy), R, R, 1, R // 2, groups), N * H * W)
+
+
 # NaN and infinities show in the windows that read them and in no others, chunks padded with zeros included
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 @pytest.mark.parametrize("shape", [(0, 1, 80, 9, 34, 60, 3, 2), (0, 3, 48, 6, 25, 119, 4, 0), (1, 2, 64, 13, 17, 80, 3, 0)])
