@@ -545,7 +545,8 @@ int launch_finish_wgrad(const float *part, float *dw, int K, int C, int RS, int 
                            make_fastdiv((uint32_t)cblocks));
     } else if (quads) {
         const int count = groups * K * (ncols / 4);
-        hipLaunchKernelGGL(finish_wgrad_x4, dim3(grid1d(count, 256)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
+        const bool idle = grid1d(count, 256) < 128;
+        hipLaunchKernelGGL(idle ? finish_wgrad_x4<4> : finish_wgrad_x4<1>, dim3(grid1d(count, idle ? 64 : 256)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
                            make_fastdiv((uint32_t)(K * (ncols / 4))), make_fastdiv((uint32_t)(ncols / 4)),
                            make_fastdiv((uint32_t)C));
     } else {
