@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 // ---------------------------------------------------------------------------
 // The contraction.  Both operands go from global memory straight into LDS (dma16, conv_bf16_dma_kernels.h); one step is
 // one filter tap x 16 channels: BM filter rows and BN positions of 32 bytes in each of three parts, in an LDS buffer of
-// (BM + BN) * 96 bytes, three buffers.  Eight waves, one work-group per CU.  A fragment of a part serves two or three
+// (BM + BN) * 96 bytes, three buffers.  Eight waves, one work-group per CU (four and two where many rounds follow each other).  A fragment of a part serves two or three
 // products, so a 128 x 256 tile needs 24 bytes per clock through the vector memory path and 62 from LDS against the
 // 60 and ~190 they deliver: unlike the one-part bf16 kernel (48 and 96) this one is bound by its matrix instructions:
 // 71 % of its cycles, at a clock that the power limit holds to 1.94 GHz (1.38 of the 1.77 that the pipe sustains alone on
@@ -297,7 +297,7 @@ struct ColGemmSplitArgs {
 };
 
 template <int TM, int TN, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const ColGemmSplitArgs p)
+__global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_split_kernel(const ColGemmSplitArgs p)
 {
     constexpr int NW = WM * WN;
     constexpr int BM = TM * WM * 32, BN = TN * WN * 32;
@@ -305,8 +305,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void colgemm_split_kernel(const Co
     constexpr int NL = (QA + QB + NW - 1) / NW;                // ... per wave (the last may repeat an earlier one)
     constexpr int BUF = (BM + BN) * 96;
     constexpr int MPG = TM * TN;                               // matrix instructions per product
-    static_assert(NW == 8, "eight waves");
-    static_assert(3 * BUF <= 160 * 1024, "three LDS buffers");
+    static_assert(NW == 8 || NW == 4, "eight waves, or four and two work-groups per CU");
+    static_assert(3 * BUF * (8 / NW) <= 160 * 1024, "three LDS buffers");
 
     extern __shared__ __attribute__((aligned(16))) float lds_fast[];
     const char *const lds = reinterpret_cast<const char *>(lds_fast);

@@ -401,9 +401,12 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     const int grid = 8 * a.tiles_per_xcd, lds = 3 * (pl.sp_bm + pl.sp_bn) * 96;
     auto go = [&](auto kern) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(pl.sp_pair ? 256 : 512), lds, st, a);
     };
-    if (pl.sp_bm == 128 && pl.sp_bn == 256) go(colgemm_split_kernel<2, 2, 2, 4>);
+    if (pl.sp_pair && pl.sp_bm == 128) go(colgemm_split_kernel<2, 2, 2, 2>);
+    else if (pl.sp_pair && pl.sp_bm == 96) go(colgemm_split_kernel<3, 1, 1, 4>);
+    else if (pl.sp_pair) go(colgemm_split_kernel<2, 1, 1, 4>);
+    else if (pl.sp_bm == 128 && pl.sp_bn == 256) go(colgemm_split_kernel<2, 2, 2, 4>);
     else if (pl.sp_bm == 128 && pl.sp_bn == 192) go(colgemm_split_kernel<1, 3, 4, 2>);
     else if (pl.sp_bm == 128) go(colgemm_split_kernel<2, 1, 2, 4>);
     else if (pl.sp_bm == 96) go(colgemm_split_kernel<3, 1, 1, 8>);

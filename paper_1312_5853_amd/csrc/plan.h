@@ -170,6 +170,8 @@ struct Plan {
     // only the regions below (nsplit, chunks_per_split as above).
     bool sp;
     // sp_fold > 1: the stride x stride input positions under an output position are channels (forward of few channels)
+    // sp_pair: four-wave work-groups, two to a CU
+    bool sp_pair;
     int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad, sp_fold;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
     // bf16 stride-1 forward / backward-data with the input window of a tile in LDS (colgemm_bf16_window_kernel): 64 or 128 rows,
@@ -693,6 +695,14 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.sp_bm = bm; pl.sp_bn = bn; pl.sp_cb = cb; pl.sp_hp = (int)hp; pl.sp_wp = (int)wp; pl.sp_mpad = mpad;
             pl.chunks_per_split = ceil_div(steps, ks);
             pl.nsplit = ceil_div(steps, pl.chunks_per_split);
+            // More than two rounds of tiles with short reductions: half the width on four waves, two work-groups to a CU, so that
+            // one's first loads and stores pass under the other's matrix instructions (whole layers, 8 -> 4 waves: 128 x 3 x 224 x
+            // 224, 96 filters 11x11, 27 steps 404 -> 397 us; two columns 48 -> 128 5x5, 75 and 100 steps 1069 -> 1077; the line lies
+            // between them).  In one round it costs more: 384 -> 384 3x3, kernel 231 -> 241, 384 -> 256 172 -> 213.
+            if (bn == 256 && pl.chunks_per_split <= 45 && (int64_t)(mpad / bm) * ((ncols + 255) / 256) * pl.nsplit * GF > 512) {
+                pl.sp_pair = true;
+                pl.sp_bn = 128;
+            }
             pl.sp_w_off = 0; pl.sp_w_bytes = (size_t)w_bytes;
             pl.sp_x_off = round_up64(w_bytes, 256); pl.sp_x_bytes = (size_t)x_bytes;
             pl.part_off = pl.sp_x_off + round_up64(x_bytes, 256);

@@ -73,6 +73,28 @@ def test_split_passes_stay_within_the_error_bound(shape, passes, route):
         within(dx, oracle.conv_bwd_data(dy, w, H, W, st, pad), oracle.conv_bwd_data(ady, aw, H, W, st, pad), K * R * R)
 
 
+# More than two rounds of tiles: half as wide, two work-groups to a CU; each height, ragged last tiles, a strided pass, samples
+# compared at both ends of the mini-batch
+@pytest.mark.parametrize("op,shape", [
+    (0, (192, 32, 33, 31, 128, 3, 1, 1)), (0, (150, 3, 127, 119, 96, 11, 4, 2)), (0, (133, 48, 33, 31, 60, 3, 1, 1)),
+    (1, (133, 60, 33, 31, 48, 3, 1, 1)), (1, (131, 64, 33, 31, 40, 3, 2, 1)),
+])
+def test_split_passes_of_many_rounds_stay_within_the_error_bound(op, shape, route):
+    N, C, H, W, K, R, st, pad = shape
+    r = route(op, *shape)
+    assert r.kernels == "split" and r.columns == 128
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    a = synth.gaussian((N, C, H, W) if op == 0 else (N, K, P, Q), 971)
+    w = synth.gaussian((K, C, R, R), 972, 0.01)
+    got = (hp.conv_fwd(dev(a), dev(w), st, pad, y=nan_like((N, K, P, Q))) if op == 0
+           else hp.conv_bwd_data(dev(a), dev(w), H, W, st, pad, dx=nan_like((N, C, H, W))))
+    assert bool(torch.isfinite(got).all())
+    for part in (slice(0, 3), slice(N // 2, N // 2 + 3), slice(N - 3, N)):
+        s = a[part]
+        f = (lambda t, u: oracle.conv_fwd(t, u, st, pad)) if op == 0 else (lambda t, u: oracle.conv_bwd_data(t, u, H, W, st, pad))
+        within(got[part], f(s, w), f(np.abs(s), np.abs(w)), (C if op == 0 else K) * R * R)
+
+
 def same_pattern(got, ref):
     """Where the 64-bit result, as fp32, is infinite or NaN; the rest close to it."""
     g, r = got.cpu().numpy(), ref.astype(np.float32)
