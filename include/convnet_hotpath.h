@@ -26,7 +26,10 @@
  *    convolution pass also takes less, down to what its kernels on the fp32
  *    matrix instruction need (re-laid-out filters and partial sums, no copy of
  *    the activations), and then runs on those: other kernels, so other bits, but
- *    the same for the same workspace size.
+ *    the same for the same workspace size.  So does a bfloat16 forward or
+ *    backward-data pass that would keep its input window on chip (down to an
+ *    unpadded copy of the activations) and a grouped bfloat16 backward-filter
+ *    (down to what one column needs).
  *  - Outputs are fully overwritten (no accumulation into the destination, every
  *    element written -- dx positions that no window touches receive 0).
  *  - dtype: CONV_DTYPE_F32  = fp32 tensors, fp32 accumulation; products on the

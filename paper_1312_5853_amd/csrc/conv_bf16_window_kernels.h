@@ -359,7 +359,7 @@ struct WindowPrepArgs {
     int transposed;            // backward-data: rows are the filter's channels, taps run backwards
     unsigned wt_halves;        // groups * CBp * R * S * Mpad * 2
     int64_t w_gs;
-    FastDiv div_pos, div_hpwp, div_wp, div_cbp, div_mpad, div_ncb, div_taps, div_s;
+    FastDiv div_pos, div_hpwp, div_wp, div_cbp, div_mpad, div_ncb, div_taps;
 };
 
 __global__ __launch_bounds__(256) void window_prepare(const WindowPrepArgs p)

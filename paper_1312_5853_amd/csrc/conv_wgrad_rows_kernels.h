@@ -612,7 +612,7 @@ __global__ __launch_bounds__(kRowsF32Threads, 1) void wgrad_rows_f32_kernel(cons
 // From position Q on dy is zero and the input holds values of other windows, or of other rows: where one of those is not
 // finite the sum becomes NaN, and the rule below computes it again unless a NaN of its own explains it.
 // Bound: matrix instructions (128 x 3 x 224 x 224, 96 filters 11 x 11: 30 x 110 x 32 clocks x 2 waves = 106 us at 2 GHz).
-// Measured: that layer's calls (forward and this) 488 -> 397 us, kernel 324 -> 217 under the profiler's clocks; matrix unit busy
+// Measured: that layer's calls (forward and this) 488 -> 397 us; kernel in the running network 267 -> 175 us; matrix unit busy
 // 64 % of its cycles; error against 64 bits 7.0e-7 -> 2.6e-7.  What was costly on the way: bounds and indexes worked out at each
 // load (506 vector instructions per wave and row, 214 now), masks on the operand of the last block, and sums that spilled.
 // ---------------------------------------------------------------------------

@@ -411,7 +411,8 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     pl.total = pl.xb_off + round_up64(pl.xb_bytes, 256);
 }
 
-// three_part = false: fp32 passes stay on the fp32 kernels
+// three_part = false: the kernels that want the least workspace: fp32 passes on the fp32 kernels, no input windows, the columns of
+// a grouped bf16 backward-filter one after the other
 inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
 {
     Plan pl = {};
