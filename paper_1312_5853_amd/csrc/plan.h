@@ -533,11 +533,13 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 pl.part_bytes = (size_t)pl.rows_wgs * pb.K * pl.Kg * 4;
                 // Three parts: stride 4 (a quad of taps is then eight aligned bytes of a staged row), 13 blocks of 32 columns,
                 // rows of 228 staged columns.  Its 15 matrix instructions of 32 clocks per SIMD stand against 72 of 64 in fp32
-                // whatever the extents, so it is taken wherever it fits.  Sums of one product stay in fp32.
+                // whatever the extents; but its start (148 KB of LDS to clear, a wave's worth of tables) is longer, so a work-group needs
+                // about three output rows (first layer, three parts / fp32: N = 2, half a row 35 / 29 us; 8, 1.7 rows 44.6 / 40.8; 16,
+                // 3.4 rows 53.5 / 56.8; 33 107 / 141; 300 569 / 954).
                 const int quads = pb.C * pb.R * ceil_div(pb.S, 4);
                 const int64_t split_lds = 2 * 3 * 96 * 144 + (int64_t)pb.C * 16 * 3 * 456 + 128;     // + slack
                 if (three_part && pb.stride == 4 && pb.S <= 12 && quads <= 104 && pb.Q <= 55 && split_lds <= 150 * 1024 &&
-                    (int64_t)pb.N * pb.P * pb.Q > 1) {
+                    (int64_t)pb.N * pb.P >= 3 * 256) {
                     pl.rows_split = true;
                     pl.rows_lds = (int)split_lds;
                 }

@@ -212,13 +212,13 @@ def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale, shape
 # full and with one position; 104 and fewer quads of taps, an unused column in a quad; 49, 65 and 96 filters; odd padding;
 # more (image, row range) units than work-groups; rows of the longest extent
 ROW_SHAPES = [
-    (3, 3, 40, 120, 96, 11, 4, 2),
+    (86, 3, 40, 120, 96, 11, 4, 2),
     (300, 3, 19, 15, 50, 11, 4, 2),
-    (2, 3, 30, 226, 96, 11, 4, 2),
-    (5, 2, 33, 160, 65, 12, 4, 0),
-    (40, 3, 24, 200, 49, 7, 4, 1),
-    (7, 3, 43, 69, 96, 11, 4, 2),
-    (19, 3, 15, 73, 96, 11, 4, 3),
+    (128, 3, 30, 226, 96, 11, 4, 2),
+    (131, 2, 33, 160, 65, 12, 4, 0),
+    (154, 3, 24, 200, 49, 7, 4, 1),
+    (77, 3, 43, 69, 96, 11, 4, 2),
+    (259, 3, 15, 73, 96, 11, 4, 3),
 ]
 
 
@@ -238,7 +238,7 @@ def test_split_row_kernel_stays_within_the_error_bound(shape, route):
 @pytest.mark.parametrize("where", ["x", "dy", "both"])
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
 def test_split_row_kernel_gives_infinities_and_nan_as_fp32_does(value, where, route):
-    shape = N, C, H, W, K, R, st, pad = 3, 3, 40, 120, 96, 11, 4, 2
+    shape = N, C, H, W, K, R, st, pad = 86, 3, 40, 120, 96, 11, 4, 2
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     assert route(2, *shape).kernels == "split"
     x, dy = np.abs(synth.gaussian((N, C, H, W), 953)) + np.float32(0.5), np.abs(synth.gaussian((N, K, P, Q), 954)) + np.float32(0.5)
@@ -252,7 +252,7 @@ def test_split_row_kernel_gives_infinities_and_nan_as_fp32_does(value, where, ro
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-37])
 def test_split_row_kernel_keeps_fp32_precision_for_tiny_values(scale, route):
-    shape = N, C, H, W, K, R, st, pad = 3, 3, 40, 120, 96, 11, 4, 2
+    shape = N, C, H, W, K, R, st, pad = 86, 3, 40, 120, 96, 11, 4, 2
     P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
     x, dy = synth.gaussian((N, C, H, W), 955), synth.gaussian((N, K, P, Q), 956) * np.float32(scale)
     dw, ref = hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad), oracle.conv_bwd_filter(x, dy, R, R, st, pad)
