@@ -603,25 +603,25 @@ __global__ __launch_bounds__(kRowsF32Threads, 1) void wgrad_rows_f32_kernel(cons
 // the input row as it lies in memory: no shifted copies, which in three parts would not fit the LDS.  S = 11 costs one unused
 // column in twelve.
 //   dy   [buffer][part][96 filters][144 bytes]: 64 positions, zero from Q on
-//   x    [c][ring row][part][456 bytes]: padded input columns 0 .. 4 Q + 7; 456 = 200 mod 256 keeps the two filter rows that a
-//        read meets in different banks
+//   x    [c][ring row]: three parts of 456 bytes, padded input columns 0 .. 4 Q + 7, and 72 bytes of zeros; 1440 = 160 mod 256
+//        keeps the filter rows that a read meets in different banks
 // The result is 3 x 13 blocks of 32 x 32, five to each of eight waves (two per SIMD, so that one's splitting and LDS stores
 // pass under the other's matrix instructions): the three rows of column block `wave`, and two of the fifteen blocks of
 // columns 8..12 (rows_split_extra).  An output row is 4 x 30 matrix instructions per wave; the next row's values are loaded at
 // its start and split and stored between its 16-position blocks.
-// From position Q on dy is zero and the input holds values of other windows, or of other rows: where one of those is not
-// finite the sum becomes NaN, and the rule below computes it again unless a NaN of its own explains it.
+// From position Q on dy is zero and the input holds values of other windows of the same row, or zeros: where one of those is
+// not finite the sum becomes NaN, and the rule below computes it again unless a NaN of its own explains it.
 // Bound: matrix instructions (128 x 3 x 224 x 224, 96 filters 11 x 11: 30 x 110 x 32 clocks x 2 waves = 106 us at 2 GHz).
 // Measured: that layer's calls (forward and this) 488 -> 397 us; kernel in the running network 267 -> 175 us; matrix unit busy
 // 64 % of its cycles; error against 64 bits 7.0e-7 -> 2.6e-7.  What was costly on the way: bounds and indexes worked out at each
 // load (506 vector instructions per wave and row, 214 now), masks on the operand of the last block, and sums that spilled.
 // ---------------------------------------------------------------------------
 constexpr int kRowsSplitThreads = 512;
-constexpr int kRowsSplitPitch = 456;                              // bytes of a part of a staged input row
-constexpr int kRowsSplitRow = 3 * kRowsSplitPitch;
 constexpr int kRowsSplitDyPart = kRowsM * kRowsPitch;
 constexpr int kRowsSplitDyBuf = 3 * kRowsSplitDyPart;
-// (LDS behind the input rows: the reads of positions from Q on, cleared afterwards, reach 72 bytes past the last row)
+// What a row's reads reach past a part is another part of the same row or the zeros behind them, never a row that is being staged.
+static_assert(2 * kRowsSplitPitch + rows_split_read_end(4) <= kRowsSplitRow, "reads stay inside their row");
+static_assert(kRowsSplitRow % 16 == 0, "cleared 16 bytes at a time");
 
 struct WgradRowsSplitArgs {
     const float *x, *dy;
@@ -659,7 +659,7 @@ __global__ __launch_bounds__(kRowsSplitThreads, 1) void wgrad_rows_split_kernel(
     const int echan = kRowsRing * kRowsSplitRow;
 
     // zero: dy's positions from Q on, and whatever the input's positions from there on may read before it is staged
-    for (int o = tid * 16; o < 2 * kRowsSplitDyBuf + p.C * echan + 128; o += kRowsSplitThreads * 16)
+    for (int o = tid * 16; o < 2 * kRowsSplitDyBuf + p.C * echan; o += kRowsSplitThreads * 16)
         *reinterpret_cast<u32x4 *>(lds + o) = u32x4{0u, 0u, 0u, 0u};
 
     const auto rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.x), 0, (int)p.x_bytes, 0x00020000);

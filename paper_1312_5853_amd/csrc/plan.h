@@ -411,6 +411,16 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     pl.total = pl.xb_off + round_up64(pl.xb_bytes, 256);
 }
 
+// LDS layout of the first-layer backward-filter in three parts (wgrad_rows_split_kernel).  A staged input row holds its parts one
+// after the other and zeros behind them: an output row is read in whole blocks of 16 positions, and the last of four blocks
+// reaches past the third part, where the next row of the ring may be being staged.
+constexpr int kRowsSplitPitch = 456;                              // bytes of a part: 228 padded input columns
+constexpr int kRowsSplitGap = 72;
+constexpr int kRowsSplitRow = 3 * kRowsSplitPitch + kRowsSplitGap;
+// one past the last byte of a part's row that the reads of `blocks` blocks touch: two quads of eight bytes at every position, from
+// position 8 half + 0..3 and quad sg = 0..2 of a filter row on, the second 32 bytes behind the first
+constexpr int rows_split_read_end(int blocks) { return (blocks - 1) * 128 + (8 + 3 + 2) * 8 + 32 + 8; }
+
 // three_part = false: the kernels that want the least workspace: fp32 passes on the fp32 kernels, no input windows, the columns of
 // a grouped bf16 backward-filter one after the other
 inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
@@ -537,7 +547,7 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 // about three output rows (first layer, three parts / fp32: N = 2, half a row 35 / 29 us; 8, 1.7 rows 44.6 / 40.8; 16,
                 // 3.4 rows 53.5 / 56.8; 33 107 / 141; 300 569 / 954).
                 const int quads = pb.C * pb.R * ceil_div(pb.S, 4);
-                const int64_t split_lds = 2 * 3 * 96 * 144 + (int64_t)pb.C * 16 * 3 * 456 + 128;     // + slack
+                const int64_t split_lds = 2 * 3 * 96 * 144 + (int64_t)pb.C * 16 * kRowsSplitRow;
                 if (three_part && pb.stride == 4 && pb.S <= 12 && quads <= 104 && pb.Q <= 55 && split_lds <= 150 * 1024 &&
                     (int64_t)pb.N * pb.P >= 3 * 256) {
                     pl.rows_split = true;

@@ -2,6 +2,7 @@
 // division against the / operator, the tile choice and the workspace plan.
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
 #include "../paper_1312_5853_amd/csrc/plan.h"
 
@@ -86,6 +87,38 @@ int main()
         CHECK(plan_for_workspace(op, pb, fp32.total).total == fp32.total);
         CHECK(plan_for_workspace(op, pb, fp32.total - 1).total == want.total);
     }
+    // first-layer backward-filter in three parts: while the waves read an output row, others stage the rows that the next one
+    // adds; no read touches a row that is being staged, and every read lies inside the staged channels
+    for (int Q : {1, 16, 17, 48, 49, 55})
+        for (int R = 1; R <= 12; ++R)
+            for (int S : {1, 4, 9, 12})
+                for (int prow = 0; prow < 4; ++prow) {
+                    const int nnew = R < 4 ? R : 4, blocks = ceil_div(Q, 16), C = 3;
+                    std::vector<char> staged((size_t)C * 16 * kRowsSplitRow, 0);
+                    for (int c = 0; c < C; ++c)
+                        for (int i = 0; i < nnew; ++i) {
+                            const int row = (4 * (prow + 1) + R - nnew + i) & 15;
+                            for (int b = 0; b < 8 * (Q - 1 + ceil_div(S, 4)); ++b)
+                                for (int part = 0; part < 3; ++part)
+                                    staged[(size_t)(c * 16 + row) * kRowsSplitRow + part * kRowsSplitPitch + b] = 1;
+                        }
+                    int end = 0;
+                    bool apart = true;
+                    for (int c = 0; c < C; ++c)
+                        for (int r = 0; r < R; ++r)
+                            for (int sg = 0; sg < ceil_div(S, 4); ++sg)
+                                for (int at = 0; at < 16; ++at)           // eight bytes of position 8 half + 0..3, then of 4..7
+                                    for (int part = 0; part < 3; ++part)
+                                        for (int kb = 0; kb < blocks; ++kb) {
+                                            const int o = (at / 8 * 8 + at % 4 + sg) * 8 + kb * 128 + (at / 4 % 2) * 32;
+                                            end = std::max(end, o + 8);
+                                            const size_t b = (size_t)(c * 16 + ((4 * prow + r) & 15)) * kRowsSplitRow +
+                                                             part * kRowsSplitPitch + o;
+                                            for (int e = 0; e < 8; ++e) apart = apart && b + e < staged.size() && !staged[b + e];
+                                        }
+                    CHECK(apart);
+                    CHECK(end <= rows_split_read_end(blocks) && (S != 12 || end == rows_split_read_end(blocks)));
+                }
     // fully connected plans: GEMM views, ranges that cover the reduction exactly, argument checks
     FcPlan fp;
     CHECK(make_fc_plan(fp, kOpFwd, 128, 9216, 4096, 0) == kStatusOk);

@@ -250,6 +250,29 @@ def test_split_row_kernel_gives_infinities_and_nan_as_fp32_does(value, where, ro
         same_pattern(hp.conv_bwd_filter(dev(x), dev(dy), R, R, st, pad), oracle.conv_bwd_filter(x, dy, R, R, st, pad))
 
 
+# Output rows of four blocks of 16 positions: their reads reach past the staged columns.  Special values in early columns of rows
+# that are staged while others are read, of rows behind a work-group's last, and on every call the same bits
+@pytest.mark.parametrize("value", [np.nan, np.inf, 3.4e38, 2.0 ** 110])
+def test_split_row_kernel_repeats_itself_where_a_staged_row_is_not_finite(value, route):
+    shape = N, C, H, W, K, R, st, pad = 128, 3, 30, 226, 96, 11, 4, 2
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    assert route(2, *shape).kernels == "split" and Q == 55
+    x, dy = synth.gaussian((N, C, H, W), 957), synth.gaussian((N, K, P, Q), 958)
+    x[1, 0, 9, 0] = x[7, 1, 13, 11] = x[N - 1, 2, H - 1, 30] = value
+    xd, dyd = dev(x), dev(dy)
+    first = hp.conv_bwd_filter(xd, dyd, R, R, st, pad).view(torch.int32).clone()
+    for _ in range(20):
+        assert torch.equal(hp.conv_bwd_filter(xd, dyd, R, R, st, pad).view(torch.int32), first)
+    with np.errstate(all="ignore"):
+        g, ref = first.view(torch.float32).cpu().numpy(), oracle.conv_bwd_filter(x, dy, R, R, st, pad)
+        r, ref_abs = ref.astype(np.float32), oracle.conv_bwd_filter(np.abs(x), np.abs(dy), R, R, st, pad)
+    assert np.array_equal(np.isnan(g), np.isnan(r)) and np.array_equal(np.isinf(g), np.isinf(r))
+    ok = np.isfinite(r)
+    # in fp32 a product passes through the sum of its work-group's positions and that of the 256 work-groups, one rounding each
+    bound = (N * P * Q / 256 + 256 + 24) * 2.0 ** -24 * ref_abs
+    assert (np.abs(g[ok].astype(np.float64) - ref[ok]) <= bound[ok]).all()
+
+
 @pytest.mark.parametrize("scale", [1e-30, 1e-37])
 def test_split_row_kernel_keeps_fp32_precision_for_tiny_values(scale, route):
     shape = N, C, H, W, K, R, st, pad = 86, 3, 40, 120, 96, 11, 4, 2
