@@ -820,9 +820,11 @@ __global__ __launch_bounds__(kRowsSplitThreads, 1) void wgrad_rows_split_kernel(
             // One block of 16 positions.  The filters' fragments of a slot alternate between two sets, the own column block stays
             // in set 0 of the inputs and the extra ones pass through set 1: 48 registers of operands beside 160 of sums.  The
             // next row's values are split and stored between matrix instructions, one pair of a thread's four at a time: dy's
-            // first two items in block 1, the others, loaded at the end of that block, in the last (after the row's last
-            // loads in rows of one or two blocks).  Past the unit's last row that writes where nothing is read.
-            constexpr int KA = NKB > 2 ? 1 : NKB - 1, KB = NKB > 2 ? NKB - 1 : NKB;
+            // first two items in block 1, the others, loaded at the end of that block, in the last.  Rows of fewer than four blocks
+            // take the first two in the last block and the others after it: closer together they do not fit the registers
+            // (three blocks: 66 spills in the loop, 608 us where rows of 55 positions take 160).  Past the unit's last row
+            // that writes where nothing is read.
+            constexpr int KA = NKB > 3 ? 1 : NKB - 1, KB = NKB > 3 ? NKB - 1 : NKB;
             auto work = [&](auto kb_c, auto m_c) {
                 constexpr int kb = decltype(kb_c)::value, i = decltype(m_c)::value - (kb == KA ? 20 : 16);
                 if constexpr ((kb == KA || kb == KB) && i >= 0) {

@@ -273,6 +273,31 @@ def test_split_row_kernel_repeats_itself_where_a_staged_row_is_not_finite(value,
     assert (np.abs(g[ok].astype(np.float64) - ref[ok]) <= bound[ok]).all()
 
 
+# Every instance (one to four blocks of 16 positions) keeps its operands in registers: a call on shorter rows takes no longer than
+# one on the longest (with spills in the loop rows of 47 took two to four times as long)
+def test_split_row_kernel_takes_no_longer_on_shorter_rows(route):
+    def time(W):
+        shape = N, C, H, _, K, R, st, pad = 128, 3, 128, W, 96, 11, 4, 2
+        assert route(2, *shape).kernels == "split"
+        P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+        x, dy = torch.randn(N, C, H, W, device="cuda"), torch.randn(N, K, P, Q, device="cuda")
+        dw = torch.empty(K, C, R, R, device="cuda")
+        best = float("inf")
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            hp.conv_bwd_filter(x, dy, R, R, st, pad, dw=dw)
+            start.record()
+            for _ in range(10):
+                hp.conv_bwd_filter(x, dy, R, R, st, pad, dw=dw)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end))
+        return best
+    longest = time(224)
+    for W in (192, 128, 64):
+        assert time(W) <= 1.1 * longest, W
+
+
 @pytest.mark.parametrize("scale", [1e-30, 1e-37])
 def test_split_row_kernel_keeps_fp32_precision_for_tiny_values(scale, route):
     shape = N, C, H, W, K, R, st, pad = 86, 3, 40, 120, 96, 11, 4, 2
