@@ -542,14 +542,19 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 pl.rows_wgs = units < 256 ? (int)units : 256;
                 pl.part_bytes = (size_t)pl.rows_wgs * pb.K * pl.Kg * 4;
                 // Three parts: stride 4 (a quad of taps is then eight aligned bytes of a staged row), 13 blocks of 32 columns,
-                // rows of 228 staged columns.  Its 15 matrix instructions of 32 clocks per SIMD stand against 72 of 64 in fp32
-                // whatever the extents; but its start (148 KB of LDS to clear, a wave's worth of tables) is longer, so a work-group needs
-                // about three output rows (first layer, three parts / fp32: N = 2, half a row 35 / 29 us; 8, 1.7 rows 44.6 / 40.8; 16,
-                // 3.4 rows 53.5 / 56.8; 33 107 / 141; 300 569 / 954).
-                const int quads = pb.C * pb.R * ceil_div(pb.S, 4);
+                // rows of 228 staged columns.  An output row costs it 60 matrix instructions of 32 clocks per SIMD for each
+                // block of 16 positions (two waves of 30), and the fp32 kernel 9 of 64 for each pair of positions: 2.4 times
+                // as much in full blocks, less in rows of up to six.  Its start (149 KB of LDS to clear, a wave's worth of
+                // tables) is 9 us longer.  Fitted to 126 drawn layers: 28 us, 0.27 a row and 1.09 a block of it, against 19
+                // us, 1.13 a row and 0.26 a pair.  With the line at 10 us they take 1.001 times what the better of the two
+                // each time would, and none that it sends here took longer (three parts / fp32, us, rows per work-group:
+                // 1 position, 20 rows 56 / 51; 4, 26 rows 62 / 64; 7, 22 rows 55 / 60; 16, 6 rows 34 / 36; 33, 6 rows
+                // 51 / 53; 55, 10 rows 81 / 102; first layer N = 16 53.5 / 56.8, N = 300 569 / 954).
+                const int quads = pb.C * pb.R * ceil_div(pb.S, 4), blocks = ceil_div(pb.Q, 16);
+                const int rows = (int)((units + pl.rows_wgs - 1) / pl.rows_wgs) * ceil_div(pb.P, splits);    // per work-group
                 const int64_t split_lds = 2 * 3 * 96 * 144 + (int64_t)pb.C * 16 * kRowsSplitRow;
                 if (three_part && pb.stride == 4 && pb.S <= 12 && quads <= 104 && pb.Q <= 55 && split_lds <= 150 * 1024 &&
-                    (int64_t)pb.N * pb.P >= 3 * 256) {
+                    (int64_t)pb.N * pb.P >= 3 * 256 && rows * (0.85 + 0.26 * ceil_div(pb.Q, 2) - 1.09 * blocks) > 10.0) {
                     pl.rows_split = true;
                     pl.rows_lds = (int)split_lds;
                 }

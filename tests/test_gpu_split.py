@@ -209,16 +209,16 @@ def test_split_backward_filter_keeps_fp32_precision_for_tiny_values(scale, shape
 
 
 # Few-channel stride-4 backward-filter with the input rows in LDS: one to four blocks of 16 positions, the last full, nearly
-# full and with one position; 104 and fewer quads of taps, an unused column in a quad; 49, 65 and 96 filters; odd padding;
+# full, half full and with one position; 104 and fewer quads of taps, an unused column in a quad; 49, 65 and 96 filters; odd padding;
 # more (image, row range) units than work-groups; rows of the longest extent
 ROW_SHAPES = [
     (86, 3, 40, 120, 96, 11, 4, 2),
-    (300, 3, 19, 15, 50, 11, 4, 2),
+    (300, 3, 51, 31, 50, 11, 4, 2),
     (128, 3, 30, 226, 96, 11, 4, 2),
     (131, 2, 33, 160, 65, 12, 4, 0),
     (154, 3, 24, 200, 49, 7, 4, 1),
     (77, 3, 43, 69, 96, 11, 4, 2),
-    (259, 3, 15, 73, 96, 11, 4, 3),
+    (259, 3, 27, 73, 96, 11, 4, 3),
 ]
 
 

@@ -171,6 +171,19 @@ def test_host_planning_selftest(tmp_path):
     assert "0 failures" in out.stdout
 
 
+def test_route_of_the_first_layer_backward_filter(route):
+    """Three parts where they were measured to be the faster: not in rows of a few outputs, whose matrix instructions are padding
+    for the larger part, nor where a work-group has too few rows to earn back its start."""
+    kernels = lambda N, H, W, R, pad=2: route(2, N, 3, H, W, 96, R, 4, pad).kernels
+    for N in (14, 16, 33, 128, 256):
+        assert kernels(N, 224, 224, 11) == "split", N
+    assert kernels(13, 224, 224, 11) == "fp32"
+    # three parts / fp32, us: one output per row, 28 rows a work-group 60 / 54; two, 56 rows 93 / 80; six, 8 rows 40 / 35
+    assert kernels(128, 224, 7, 11) == kernels(256, 224, 11, 9) == kernels(64, 128, 23, 7) == "fp32"
+    # seven, 22 rows 55 / 60; 19, 28 rows 97 / 122; 38, 28 rows 129 / 200
+    assert kernels(128, 224, 31, 11) == kernels(128, 224, 79, 11, 3) == kernels(128, 224, 159, 11, 0) == "split"
+
+
 SAN_FLAGS = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
 # leak checking off (the OpenMP runtime keeps its thread pool); the link-order check is off because the test
 # harness may preload a library of its own ahead of the sanitizer runtime
