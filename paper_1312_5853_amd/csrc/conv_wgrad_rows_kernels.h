@@ -616,7 +616,6 @@ __global__ __launch_bounds__(kRowsF32Threads, 1) void wgrad_rows_f32_kernel(cons
 // 64 % of its cycles; error against 64 bits 7.0e-7 -> 2.6e-7.  What was costly on the way: bounds and indexes worked out at each
 // load (506 vector instructions per wave and row, 214 now), masks on the operand of the last block, and sums that spilled.
 // ---------------------------------------------------------------------------
-constexpr int kRowsSplitThreads = 512;
 constexpr int kRowsSplitDyPart = kRowsM * kRowsPitch;
 constexpr int kRowsSplitDyBuf = 3 * kRowsSplitDyPart;
 // What a row's reads reach past a part is another part of the same row or the zeros behind them, never a row that is being staged.

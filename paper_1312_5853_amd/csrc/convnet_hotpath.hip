@@ -927,7 +927,7 @@ void launch_rows_split(const float *x, const float *dy, float *part, const Probl
     a.splits = pl.rows_splits; a.units = pb.N * pl.rows_splits;
     a.SG = ceil_div(pb.S, 4); a.quads = pb.C * pb.R * a.SG;
     a.nnew = pb.R < 4 ? pb.R : 4;
-    a.xg = pb.Q - 1 + a.SG; a.dyg = ceil_div(pb.Q, 4);       // at most 58 and 14: 928 items of x, 1344 of dy
+    a.xg = pb.Q - 1 + a.SG; a.dyg = ceil_div(pb.Q, 4);
     a.div_splits = make_fastdiv((uint32_t)a.splits);
     a.div_xg = make_fastdiv((uint32_t)a.xg);
     a.div_dyg = make_fastdiv((uint32_t)a.dyg);

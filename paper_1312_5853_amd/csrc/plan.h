@@ -414,6 +414,7 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
 // LDS layout of the first-layer backward-filter in three parts (wgrad_rows_split_kernel).  A staged input row holds its parts one
 // after the other and zeros behind them: an output row is read in whole blocks of 16 positions, and the last of four blocks
 // reaches past the third part, where the next row of the ring may be being staged.
+constexpr int kRowsSplitThreads = 512;
 constexpr int kRowsSplitPitch = 456;                              // bytes of a part: 228 padded input columns
 constexpr int kRowsSplitGap = 72;
 constexpr int kRowsSplitRow = 3 * kRowsSplitPitch + kRowsSplitGap;
@@ -552,8 +553,12 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 // 51 / 53; 55, 10 rows 81 / 102; first layer N = 16 53.5 / 56.8, N = 300 569 / 954).
                 const int quads = pb.C * pb.R * ceil_div(pb.S, 4), blocks = ceil_div(pb.Q, 16);
                 const int rows = (int)((units + pl.rows_wgs - 1) / pl.rows_wgs) * ceil_div(pb.P, splits);    // per work-group
+                // staging items of four values, two of x and three of dy per thread.  (The conditions below leave at most 3 x 4 x
+                // 57 and 96 x 14 of them: with four channels the input rows would not fit the LDS.)
+                const int x_items = pb.C * std::min(pb.R, 4) * (pb.Q - 1 + ceil_div(pb.S, 4)), dy_items = pb.K * ceil_div(pb.Q, 4);
                 const int64_t split_lds = 2 * 3 * 96 * 144 + (int64_t)pb.C * 16 * kRowsSplitRow;
                 if (three_part && pb.stride == 4 && pb.S <= 12 && quads <= 104 && pb.Q <= 55 && split_lds <= 150 * 1024 &&
+                    x_items <= 2 * kRowsSplitThreads && dy_items <= 3 * kRowsSplitThreads &&
                     (int64_t)pb.N * pb.P >= 3 * 256 && rows * (0.85 + 0.26 * ceil_div(pb.Q, 2) - 1.09 * blocks) > 10.0) {
                     pl.rows_split = true;
                     pl.rows_lds = (int)split_lds;

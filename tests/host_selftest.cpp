@@ -119,6 +119,16 @@ int main()
                     CHECK(apart);
                     CHECK(end <= rows_split_read_end(blocks) && (S != 12 || end == rows_split_read_end(blocks)));
                 }
+    // ... and its threads hold all the values that a row stages, up to the largest extents it is sent
+    for (int C = 1; C <= 4; ++C)
+        for (int R = 1; R <= 12; ++R)
+            for (int W = R; W <= 256; W += 3) {
+                if (make_problem(pb, 256, C, 64, W, 96, R, R, 4, R / 4, 0, 0, 0) != kStatusOk) continue;
+                pl = make_plan(kOpBwdFilter, pb);
+                if (!pl.rows_split) continue;
+                CHECK(C * (R < 4 ? R : 4) * (pb.Q - 1 + ceil_div(R, 4)) <= 3 * 4 * 57 && 3 * 4 * 57 <= 2 * kRowsSplitThreads);
+                CHECK(96 * ceil_div(pb.Q, 4) <= 96 * 14 && 96 * 14 <= 3 * kRowsSplitThreads && pl.rows_lds <= 150 * 1024);
+            }
     // fully connected plans: GEMM views, ranges that cover the reduction exactly, argument checks
     FcPlan fp;
     CHECK(make_fc_plan(fp, kOpFwd, 128, 9216, 4096, 0) == kStatusOk);
