@@ -176,7 +176,8 @@ __global__ __launch_bounds__(MULTI ? 512 : 256, MULTI ? 1 : 2) void colgemm_bf16
     auto do_step = [&](auto par_c) {
         constexpr int par = decltype(par_c)::value;
         const bool more_w = MULTI && w_left > 0;
-        const bool real = KG == 1 || tap < taps;                 // an odd count of taps: the second group's last is none
+        const bool real = KG == 1 || tap < taps;                 // an odd count of taps: the second group's last is none (the
+                                                                 // LDS goes on a row behind the last window for its reads)
 #pragma unroll
         for (int b = 0; b < NCB; ++b) {
             const int set = (par + b) & 1;

@@ -372,6 +372,8 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     const int64_t ncols = (int64_t)pb.N * OH * OW, xb_bytes = (int64_t)G * cbp * pb.N * hp * wp * 32;
     const int64_t wt_bytes = (int64_t)G * cbp * RS * mtiles * bm * 32;
     if (xb_bytes + (1 << 20) >= kMaxSpanBytes || wt_bytes >= kMaxSpanBytes) return;
+    // an odd count of taps: the second group of waves reads a tap past the last, in the row behind the window (unused)
+    const int64_t row_behind = multi && RS % 2 ? wp * 32 : 0;
     int64_t best = -1;
     for (int tn = 3; tn >= 2; --tn) {
         const int bn = tn * 32 * (bm == 64 ? 4 : 2);
@@ -379,7 +381,7 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
         int64_t lds = (multi ? 6 : 2) * (int64_t)ncb * bm * 32 + (multi ? 2 : 1) * ncb * win;
         if (multi) lds = std::max<int64_t>(lds, 8 * tn * 4096);          // the sums that the two groups of waves trade
         // (a round of every block per step, none in a chunk's last two steps)
-        if (lds > 160 * 1024 || (multi && win / 8192 > (RS + 1) / 2 - 2)) continue;
+        if (lds + row_behind > 160 * 1024 || (multi && win / 8192 > (RS + 1) / 2 - 2)) continue;
         const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, per_round = lds <= 80 * 1024 ? 512 : 256;
         const int64_t cost = (tiles + per_round - 1) / per_round * bn;
         if (best >= 0 && cost >= best) continue;
@@ -402,6 +404,7 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
         if (us >= 0.9 * staged_us) return;
     }
     pl.win = true;
+    pl.win_lds += (int)row_behind;
     pl.win_bm = bm; pl.win_ncb = ncb; pl.win_cb = cbp; pl.win_hp = (int)hp; pl.win_wp = (int)wp; pl.win_ph = ph; pl.win_pw = pw;
     pl.nsplit = 1;
     pl.wt_off = 0; pl.wt_bytes = (size_t)wt_bytes;

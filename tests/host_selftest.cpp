@@ -129,6 +129,40 @@ int main()
                 CHECK(C * (R < 4 ? R : 4) * (pb.Q - 1 + ceil_div(R, 4)) <= 3 * 4 * 57 && 3 * 4 * 57 <= 2 * kRowsSplitThreads);
                 CHECK(96 * ceil_div(pb.Q, 4) <= 96 * 14 && 96 * 14 <= 3 * kRowsSplitThreads && pl.rows_lds <= 150 * 1024);
             }
+    // bf16 kernel with the input window in LDS: a tile's window fits its buffer, and no group of waves reads past the LDS at any
+    // step of its walk over the taps (the second of two groups reads one past the last where their count is odd)
+    struct { int op, N, C, H, W, K, R, S, pad; } windows[] = {
+        {kOpFwd, 64, 48, 27, 27, 128, 5, 5, 2}, {kOpBwdData, 64, 48, 27, 27, 128, 5, 5, 2}, {kOpBwdData, 2, 448, 3, 22, 80, 3, 3, 0},
+        {kOpFwd, 3, 80, 4, 20, 240, 3, 3, 0}, {kOpFwd, 1, 80, 4, 58, 304, 3, 3, 0}, {kOpBwdData, 1, 272, 3, 45, 80, 3, 3, 1},
+        {kOpFwd, 2, 80, 1, 37, 384, 3, 3, 1}, {kOpBwdData, 1, 192, 1, 171, 80, 1, 9, 0}, {kOpFwd, 9, 48, 32, 30, 47, 4, 4, 0},
+    };
+    int window_plans = 0;
+    for (const auto &t : windows) {
+        CHECK(make_problem(pb, t.N, t.C, t.H, t.W, t.K, t.R, t.S, 1, t.pad, 0, 0, 1) == kStatusOk);
+        pl = make_plan(t.op, pb);
+        if (!pl.win) continue;
+        ++window_plans;
+        const int OH = t.op == kOpFwd ? pb.P : pb.H, OW = t.op == kOpFwd ? pb.Q : pb.W, taps = t.R * t.S;
+        const int groups = pl.win_cb > pl.win_ncb ? 2 : 1, bn = pl.win_tn * 32 * (pl.win_bm == 64 ? 4 : 2);
+        const int64_t ncols = (int64_t)t.N * OH * OW;
+        auto origin = [&](int64_t j) {
+            return (j / (OH * OW) * pl.win_hp + j % (OH * OW) / OW) * pl.win_wp + j % OW;
+        };
+        for (int64_t n0 = 0; n0 < ncols; n0 += bn) {
+            const int64_t start = origin(n0) & ~(int64_t)15, last = origin(std::min(n0 + bn, ncols) - 1);
+            CHECK((last + (t.R - 1) * pl.win_wp + t.S - start) * 32 <= pl.win_bytes);
+            // group g reads taps g, g + groups, ... of every block of the last of two windows (or of the one)
+            const int64_t filters = (int64_t)(groups == 2 ? 6 : 2) * pl.win_ncb * pl.win_bm * 32;
+            const int64_t block = filters + (int64_t)(groups * pl.win_ncb - 1) * pl.win_bytes;
+            for (int g = 0; g < groups; ++g)
+                for (int step = 0; step < (taps + groups - 1) / groups; ++step) {
+                    const int tap = g + step * groups;
+                    CHECK(block + (last - start + tap / t.S * pl.win_wp + tap % t.S + 1) * 32 <= pl.win_lds);
+                }
+        }
+        CHECK(pl.win_lds <= 160 * 1024);
+    }
+    CHECK(window_plans >= 6);
     // fully connected plans: GEMM views, ranges that cover the reduction exactly, argument checks
     FcPlan fp;
     CHECK(make_fc_plan(fp, kOpFwd, 128, 9216, 4096, 0) == kStatusOk);
