@@ -304,8 +304,10 @@ int run_colgemm_window(int op, const void *act, const void *w, void *out, const 
     const bool multi = a.chunks > 1, wide = pl.win_tn == 3;
     auto go = [&](auto rows_c, auto ncb_c) {
         constexpr int WM = decltype(rows_c)::value / 64, WN = 4 / WM, NCB = decltype(ncb_c)::value;
-        if (multi && wide) launch_dma(colgemm_bf16_window_kernel<3, WM, WN, NCB, true>, a, grid, lds, st, 512);
-        else if (multi) launch_dma(colgemm_bf16_window_kernel<2, WM, WN, NCB, true>, a, grid, lds, st, 512);
+        if constexpr (NCB == 2) {
+            if (multi && wide) return launch_dma(colgemm_bf16_window_kernel<3, WM, WN, NCB, true>, a, grid, lds, st, 512);
+        }
+        if (multi) launch_dma(colgemm_bf16_window_kernel<2, WM, WN, NCB, true>, a, grid, lds, st, 512);
         else if (wide) launch_dma(colgemm_bf16_window_kernel<3, WM, WN, NCB, false>, a, grid, lds, st);
         else launch_dma(colgemm_bf16_window_kernel<2, WM, WN, NCB, false>, a, grid, lds, st);
     };

@@ -375,7 +375,9 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     // an odd count of taps: the second group of waves reads a tap past the last, in the row behind the window (unused)
     const int64_t row_behind = multi && RS % 2 ? wp * 32 : 0;
     int64_t best = -1;
-    for (int tn = 3; tn >= 2; --tn) {
+    // (six windows of three blocks beside the filters: 8 KB each for 128 rows, 16 for 64, which 192 or 384 positions and their
+    // borders fill only in tensors where the narrower tile takes less)
+    for (int tn = multi && ncb == 3 ? 2 : 3; tn >= 2; --tn) {
         const int bn = tn * 32 * (bm == 64 ? 4 : 2);
         const int64_t win = window_bytes(pb.N, OH, OW, pb.R, (int)hp, (int)wp, bn, multi ? 8192 : 1024);     // (rounds of eight waves' loads)
         int64_t lds = (multi ? 6 : 2) * (int64_t)ncb * bm * 32 + (multi ? 2 : 1) * ncb * win;
