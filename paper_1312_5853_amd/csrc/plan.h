@@ -350,10 +350,16 @@ inline int64_t window_bytes(int N, int OH, int OW, int R, int hp, int wp, int bn
 // bf16, stride 1, what the direct-to-LDS kernel does not take: more than 32 rows, more than one block of 16 channels, enough
 // taps that the window is worth loading, and a window that fits; and an estimate below that of the register-staged kernel,
 // which splits the reduction and so wins where few tiles meet a long one.  Both estimates (us, all columns of a launch
-// together: two columns of 48 -> 128 channels at N = 64 are one round of windows and three of the staged kernel) were fitted to 280 passes of drawn layers, to 11 and 15 %; over them the rule
-// takes 0.93 of the register-staged kernel's time in all, the better of the two each time would take 0.91.  Measured on both
-// sides of the line, window / staged: 58x80x21x28, 64 channels 3x3 19 / 32 us; 27 x 112 x 44 x 36, 125 filters 5x5 50 / 72;
-// 8 x 208 x 16 x 25, 295 filters 5x5 57 / 56; 7 x 208 x 24 x 14, 144 filters 7x7 95 / 77; 1 x 128 x 14 x 12, 80 filters 5x5 32 / 19.
+// together: two columns of 48 -> 128 channels at N = 64 are one round of windows and three of the staged kernel) were fitted to
+// 280 passes of drawn layers, and looked at again on 700 others that the kernel can take:
+//   - several chunks: one work-group of eight waves per CU, whatever its LDS (its registers);
+//   - one chunk: two of four waves in 80 KB of LDS, else one, which then has nobody beside it and takes 1.3 times as long a
+//     slice (4 x 64 x 19 x 49, two columns of 167 filters 9x9: 51 us, staged 38).
+// The rule takes 0.85 of the register-staged kernel's time over those 700, the better of the two each time would take 0.82; of
+// the 358 passes that it sends here 13 are 3 to 10 % slower, and of 394 further ones 10, by up to 21 %: where the estimate of
+// the register-staged kernel is off (it is good to 17 %).  Measured on both sides of
+// the line, window / staged: 58x80x21x28, 64 channels 3x3 19 / 32 us; 27 x 112 x 44 x 36, 125 filters 5x5 50 / 72; 8 x 208 x 16 x 25, 295 filters 5x5 57 /
+// 56; 7 x 208 x 24 x 14, 144 filters 7x7 95 / 77; 1 x 128 x 14 x 12, 80 filters 5x5 32 / 19.
 inline void plan_window(int op, const Problem &pb, Plan &pl)
 {
     const bool fwd = op == kOpFwd;
@@ -384,7 +390,7 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
         if (multi) lds = std::max<int64_t>(lds, 8 * tn * 4096);          // the sums that the two groups of waves trade
         // (a round of every block per step, none in a chunk's last two steps)
         if (lds + row_behind > 160 * 1024 || (multi && win / 8192 > (RS + 1) / 2 - 2)) continue;
-        const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, per_round = lds <= 80 * 1024 ? 512 : 256;
+        const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, per_round = !multi && lds <= 80 * 1024 ? 512 : 256;
         const int64_t cost = (tiles + per_round - 1) / per_round * bn;
         if (best >= 0 && cost >= best) continue;
         best = cost;
@@ -392,11 +398,14 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     }
     if (best < 0) return;
     {
-        const int bn = pl.win_tn * 32 * (bm == 64 ? 4 : 2), slots = pl.win_lds <= 80 * 1024 ? 512 : 256;
+        const int bn = pl.win_tn * 32 * (bm == 64 ? 4 : 2), slots = !multi && pl.win_lds <= 80 * 1024 ? 512 : 256;
         const int64_t tiles = mtiles * ((ncols + bn - 1) / bn) * G, rounds = (tiles + slots - 1) / slots;
         const double slices = cbp * RS * (pl.win_tn == 3 ? 1.0 : 0.72);
-        const double us = 11.7 + 0.6 * xb_bytes / 1e6 + (multi ? 0.148 * slices * rounds
-                                                                   : 0.131 * slices * (tiles > 256 ? 2 * rounds : 1));
+        const bool lone = !multi && slots == 256;
+        const double us = (lone ? 9.5 : 11.7) + 0.6 * xb_bytes / 1e6 +
+                          (multi  ? 0.148 * slices * rounds
+                           : lone ? 0.17 * slices * (tiles > 256 ? 1.2 * rounds : 1.0)
+                                  : 0.131 * slices * (tiles > 256 ? 2 * rounds : 1));
         const int kc = Cr % 64 == 0 ? 64 : Cr % 48 == 0 ? 48 : Cr % 32 == 0 ? 32 : 16;           // channels per step
         const int64_t staged = (pl.Mpad / pl.tile.bm()) * ((ncols + pl.tile.bn() - 1) / pl.tile.bn()) * pl.nsplit * G;
         const double steps = (double)ceil_div(Cr / kc * RS, pl.nsplit) * ((staged + 255) / 256);

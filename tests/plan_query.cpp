@@ -4,7 +4,9 @@
 
 using namespace convnet;
 
-// ws_bytes: what the call brings, or -1: as much as it wants.  out: 0 fp32 kernels, 1 three-part kernels, 2 vector units, 3 bf16 with the input window in LDS; fold; splits of the reduction; rows, columns of a tile; workspace
+// ws_bytes: what the call brings, or -1: as much as it wants.  out: 0 fp32 kernels, 1 three-part kernels, 2 vector units, 3
+// bf16 with the input window in LDS; fold; splits of the reduction; rows, columns of a tile; workspace; of the window kernel
+// channel blocks per step and chunks; whether the columns of a bf16 backward-filter run in one launch
 extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups, int dtype,
                           long long ws_bytes, long long *out)
 {
@@ -23,5 +25,8 @@ extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int 
     out[3] = pl.sp ? pl.sp_bm : pl.win ? pl.win_bm : pl.tile.bm();
     out[4] = pl.sp ? pl.sp_bn : pl.win ? pl.win_tn * 32 * (pl.win_bm == 64 ? 4 : 2) : pl.tile.bn();
     out[5] = (long long)pl.total;
+    out[6] = pl.win ? pl.win_ncb : 0;
+    out[7] = pl.win ? pl.win_cb / pl.win_ncb : 0;
+    out[8] = pl.lin && pl.fused_groups && !pl.direct;
     return kStatusOk;
 }

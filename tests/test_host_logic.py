@@ -184,6 +184,22 @@ def test_route_of_the_first_layer_backward_filter(route):
     assert kernels(128, 224, 31, 11) == kernels(128, 224, 79, 11, 3) == kernels(128, 224, 159, 11, 0) == "split"
 
 
+def test_route_of_the_bf16_window_kernel(route):
+    """One work-group per CU where several chunks fill its registers, and where one chunk's window fills more than half of the LDS:
+    neither counts on a second one beside it."""
+    # several chunks: tiles of 192 positions, not of 128 (141 -> 122, 54 -> 39 and 50 -> 43 us)
+    for shape in [(184, 152, 59, 13, 224, 3, 1, 0, 2), (93, 80, 26, 14, 256, 3, 1, 1, 1), (40, 608, 58, 6, 224, 3, 1, 1, 2)]:
+        r = route(1, *shape, dtype=1)
+        assert r.kernels == "window" and r.chunks > 1 and (r.rows, r.columns) == (128, 192), shape
+    # one chunk of 81 taps, one work-group per CU: window / staged 51 / 38 and 48 / 41 us
+    assert route(0, 4, 64, 19, 49, 334, 9, 1, 4, groups=2, dtype=1).kernels != "window"
+    assert route(1, 6, 96, 55, 52, 48, 9, 1, 0, dtype=1).kernels != "window"
+    # the network's second layer keeps it
+    for N in (64, 128, 256):
+        assert route(0, N, 96, 27, 27, 256, 5, 1, 2, groups=2, dtype=1).kernels == "window"
+        assert route(1, N, 96, 27, 27, 256, 5, 1, 2, groups=2, dtype=1).kernels == "window"
+
+
 SAN_FLAGS = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
 # leak checking off (the OpenMP runtime keeps its thread pool); the link-order check is off because the test
 # harness may preload a library of its own ahead of the sanitizer runtime
