@@ -13,11 +13,9 @@ LIB = os.path.join(_HERE, "libconvnet_hotpath.so")
 CEILING_SRC = os.path.join(_HERE, "csrc", "mfma_ceiling.hip")
 CEILING_EXE = os.path.join(_HERE, "mfma_ceiling")
 DEPS = [SRC] + [os.path.join(_HERE, "csrc", h) for h in (
-    "plan.h", "fastdiv.h", "device_common.h", "conv_colgemm_kernels.h", "conv_bf16_dma_kernels.h", "conv_bf16_window_kernels.h", "conv_split_kernels.h",
-    "conv_wgrad_split_kernels.h", "conv_direct_kernels.h",
-    "conv_wgrad_rows_kernels.h",
-    "conv_wgrad_kernels.h", "fc_kernels.h",
-    "glue_kernels.h")] + [os.path.join(os.path.dirname(_HERE), "include", "convnet_hotpath.h")]
+    "plan.h", "fastdiv.h", "device_common.h", "conv_colgemm_kernels.h", "conv_bf16_dma_kernels.h",
+    "conv_bf16_window_kernels.h", "conv_split_kernels.h", "conv_wgrad_split_kernels.h", "conv_direct_kernels.h",
+    "conv_wgrad_rows_kernels.h", "conv_wgrad_kernels.h", "fc_kernels.h", "glue_kernels.h")] + [os.path.join(os.path.dirname(_HERE), "include", "convnet_hotpath.h")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC", "-Wall",

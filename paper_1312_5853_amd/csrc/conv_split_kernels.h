@@ -241,9 +241,10 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 // ---------------------------------------------------------------------------
 // The contraction.  Both operands go from global memory straight into LDS (dma16, conv_bf16_dma_kernels.h); one step is
 // one filter tap x 16 channels: BM filter rows and BN positions of 32 bytes in each of three parts, in an LDS buffer of
-// (BM + BN) * 96 bytes, three buffers.  Eight waves, one work-group per CU (four and two where many rounds follow each other).  A fragment of a part serves two or three
-// products, so a 128 x 256 tile needs 24 bytes per clock through the vector memory path and 62 from LDS against the
-// 60 and ~190 they deliver: unlike the one-part bf16 kernel (48 and 96) this one is bound by its matrix instructions:
+// (BM + BN) * 96 bytes, three buffers.  Eight waves, one work-group per CU (four and two where many rounds follow each
+// other).  A fragment of a part serves two or three products, so a 128 x 256 tile needs 24 bytes per clock through the vector
+// memory path and 62 from LDS against the 60 and ~190 they deliver: unlike the one-part bf16 kernel (48 and 96) this one is
+// bound by its matrix instructions:
 // 71 % of its cycles, at a clock that the power limit holds to 1.94 GHz (1.38 of the 1.77 that the pipe sustains alone on
 // random operands).  384 -> 384 channels 3x3, N = 128, whole call (preparation 26 us): forward 452 -> 273 us, backward-data
 // 450 -> 269; N = 2: 78 -> 33; two columns 48 -> 128 5x5, N = 128: forward 474 -> 278, backward-data 499 -> 379 (48 rows

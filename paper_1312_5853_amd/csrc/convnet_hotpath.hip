@@ -551,9 +551,9 @@ int launch_finish_wgrad(const float *part, float *dw, int K, int C, int RS, int 
     } else if (quads) {
         const int count = groups * K * (ncols / 4);
         const bool idle = grid1d(count, 256) < 128;
-        hipLaunchKernelGGL(idle ? finish_wgrad_x4<4> : finish_wgrad_x4<1>, dim3(grid1d(count, idle ? 64 : 256)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
-                           make_fastdiv((uint32_t)(K * (ncols / 4))), make_fastdiv((uint32_t)(ncols / 4)),
-                           make_fastdiv((uint32_t)C));
+        hipLaunchKernelGGL(idle ? finish_wgrad_x4<4> : finish_wgrad_x4<1>, dim3(grid1d(count, idle ? 64 : 256)), dim3(256), 0,
+                           st, part, dw, K, C, RS, nsplit, groups, make_fastdiv((uint32_t)(K * (ncols / 4))),
+                           make_fastdiv((uint32_t)(ncols / 4)), make_fastdiv((uint32_t)C));
     } else {
         const int count = groups * K * ncols;
         hipLaunchKernelGGL(finish_wgrad, dim3(grid1d(count, 64)), dim3(256), 0, st, part, dw, K, C, RS, nsplit, groups,
@@ -1317,26 +1317,24 @@ static int run_grouped(int op, const void *a, const void *b, void *out, int N, i
         if (!aligned(ws, 256)) return kErrMisaligned;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool together = groups == 1 || (pl.fused_groups && !pl.direct);
-    if (together && !(pl.lin && groups > 1))
-        return op == kOpBwdFilter ? run_wgrad(a, b, out, pb, pl, ws, st) : run_colgemm(op, a, b, out, pb, pl, ws, st);
-    // one column after the other (also where one launch could take them all but a column is small enough for the vector
-    // units, so that columns give the same bits together and alone): element sizes of the three tensors of this pass
+    // byte distance between the columns' slices of the three tensors
     const int in_b = pb.dtype == kDtypeBf16 ? 2 : 4;
     const int out_b = (pb.out_bf16 && op != kOpBwdFilter) ? 2 : 4;
-    Problem one = pb;
-    one.groups = 1;
-    // byte distance between the columns' slices of the three tensors
     int64_t sa, sb, so;
     if (op == kOpFwd) { sa = pb.x_gs * in_b; sb = pb.w_gs * in_b; so = pb.y_gs * out_b; }
     else if (op == kOpBwdData) { sa = pb.y_gs * in_b; sb = pb.w_gs * in_b; so = pb.x_gs * out_b; }
     else { sa = pb.x_gs * in_b; sb = pb.y_gs * in_b; so = pb.w_gs * 4; }
-    // every column's base must keep the alignment the kernels rely on (the fused ones rely on none): checked for all
-    // columns before the first
-    // one is enqueued
-    for (int g = 1; g < groups && (!pl.fused_groups || pl.lin); ++g)
-        if ((g * sa) % 16 != 0 || (g * sb) % 16 != 0 || (g * so) % 16 != 0) return kErrMisaligned;
-    if (together) return run_wgrad(a, b, out, pb, pl, ws, st);
+    // every column's base must keep the alignment that the kernels of a column alone rely on (those of a launch for all columns
+    // rely on none, but a bf16 backward-filter is accepted the same either way): checked before anything is enqueued
+    if (!pl.fused_groups || pl.lin)
+        for (int g = 1; g < groups; ++g)
+            if ((g * sa) % 16 != 0 || (g * sb) % 16 != 0 || (g * so) % 16 != 0) return kErrMisaligned;
+    // one column after the other also where one launch could take them all but a column is small enough for the vector units,
+    // so that columns give the same bits together and alone
+    if (groups == 1 || (pl.fused_groups && !pl.direct))
+        return op == kOpBwdFilter ? run_wgrad(a, b, out, pb, pl, ws, st) : run_colgemm(op, a, b, out, pb, pl, ws, st);
+    Problem one = pb;
+    one.groups = 1;
     for (int g = 0; g < groups; ++g) {
         const char *pa = static_cast<const char *>(a) + g * sa, *pbp = static_cast<const char *>(b) + g * sb;
         char *po = static_cast<char *>(out) + g * so;

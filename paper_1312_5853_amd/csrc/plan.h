@@ -385,7 +385,7 @@ inline void plan_window(int op, const Problem &pb, Plan &pl)
     // borders fill only in tensors where the narrower tile takes less)
     for (int tn = multi && ncb == 3 ? 2 : 3; tn >= 2; --tn) {
         const int bn = tn * 32 * (bm == 64 ? 4 : 2);
-        const int64_t win = window_bytes(pb.N, OH, OW, pb.R, (int)hp, (int)wp, bn, multi ? 8192 : 1024);     // (rounds of eight waves' loads)
+        const int64_t win = window_bytes(pb.N, OH, OW, pb.R, (int)hp, (int)wp, bn, multi ? 8192 : 1024);   // (a round of loads)
         int64_t lds = (multi ? 6 : 2) * (int64_t)ncb * bm * 32 + (multi ? 2 : 1) * ncb * win;
         if (multi) lds = std::max<int64_t>(lds, 8 * tn * 4096);          // the sums that the two groups of waves trade
         // (a round of every block per step, none in a chunk's last two steps)
@@ -508,8 +508,9 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             const int kpad = round_up(pb.K, 128);
             const int64_t dy_bytes = (int64_t)kpad * steps * 64 * 2, x_bytes = (int64_t)2 * pb.C * pb.N * jx * 2;
             if (jy >= 64 && dy_bytes < kMaxSpanBytes && x_bytes < kMaxSpanBytes) {
-                // the columns of a grouped layer in one launch of each kernel (two of 48 -> 128 channels 5x5, N = 64: 80 -> 60 us),
-                // where their packed copies together can still be indexed
+                // the columns of a grouped layer in one launch of each kernel, where their packed copies together can still be
+                // indexed: two of 48 -> 128 channels 5x5, apart / together, N = 16 56 / 30 us, 64 78 / 60, 128 119 / 99, 192 159 /
+                // 154, 224 175 / 177, 256 210 / 206; 41 drawn layers of two to four columns 0.28 to 0.99 of their time apart
                 pl.fused_groups = G > 1 && three_part && dy_bytes * G < kMaxSpanBytes && x_bytes * G < kMaxSpanBytes;
                 const int GF = pl.fused_groups ? G : 1;
                 pl.lin = true;
@@ -734,8 +735,10 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.nsplit = ceil_div(steps, pl.chunks_per_split);
             // More than two rounds of tiles with short reductions: half the width on four waves, two work-groups to a CU, so that
             // one's first loads and stores pass under the other's matrix instructions (whole layers, 8 -> 4 waves: 128 x 3 x 224 x
-            // 224, 96 filters 11x11, 27 steps 404 -> 397 us; two columns 48 -> 128 5x5, 75 and 100 steps 1069 -> 1077; the line lies
-            // between them).  In one round it costs more: 384 -> 384 3x3, kernel 231 -> 241, 384 -> 256 172 -> 213.
+            // 224, 96 filters 11x11, 27 steps 404 -> 397 us; two columns 48 -> 128 5x5, 75 and 100 steps 1069 -> 1077).  On 91
+            // drawn passes up to the line it takes 0.80 to 1.02 of the wider tiles' time, 0.92 in the mean; on 57 beyond it
+            // 0.89 to 1.04: the line is where it stops losing nowhere.  In one round it costs more: 384 -> 384 3x3, kernel 231
+            // -> 241, 384 -> 256 172 -> 213.
             if (bn == 256 && pl.chunks_per_split <= 45 && (int64_t)(mpad / bm) * ((ncols + 255) / 256) * pl.nsplit * GF > 512) {
                 pl.sp_pair = true;
                 pl.sp_bn = 128;
