@@ -508,18 +508,33 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             const int kpad = round_up(pb.K, 128);
             const int64_t dy_bytes = (int64_t)kpad * steps * 64 * 2, x_bytes = (int64_t)2 * pb.C * pb.N * jx * 2;
             if (jy >= 64 && dy_bytes < kMaxSpanBytes && x_bytes < kMaxSpanBytes) {
-                // the columns of a grouped layer in one launch of each kernel, where their packed copies together can still be
-                // indexed: two of 48 -> 128 channels 5x5, apart / together, N = 16 56 / 30 us, 64 78 / 60, 128 119 / 99, 192 159 /
-                // 154, 224 175 / 177, 256 210 / 206; 41 drawn layers of two to four columns 0.28 to 0.99 of their time apart
-                pl.fused_groups = G > 1 && three_part && dy_bytes * G < kMaxSpanBytes && x_bytes * G < kMaxSpanBytes;
+                // splits of the reduction that fill the CUs once, of at least four steps; returned: steps one after the other on a CU
+                const int tiles1 = (kpad / 128) * ceil_div(pl.Kg, 256);
+                auto pick_splits = [&](int columns, int &per_split, int &nsplit_) {
+                    const int ns = std::max(1, std::min(256 / (tiles1 * columns), (int)(steps / 4)));
+                    per_split = ceil_div((int)steps, ns);
+                    nsplit_ = ceil_div((int)steps, per_split);
+                    return (double)per_split * (((int64_t)tiles1 * nsplit_ * columns + 255) / 256);
+                };
+                // The columns of a grouped layer in one launch of each kernel, where their packed copies together can still be
+                // indexed: it saves about 14 us a further column, and costs about 0.6 us for each step that a CU does more of
+                // than apart, where whole tiles of all columns leave no splits to even out the CUs.  Long reductions gain
+                // nothing, and lose where the copies of all columns, read once a tap, are more than the 256 MB cache holds
+                // beside what passes through it (a 1x1 layer reads them once).  Apart / together, us: two columns of 48 -> 128
+                // channels 5x5, N = 16 56 / 30, 64 78 / 60, 128 120 / 100, 192 162 / 157, 208 (156 MB) 171 / 170, 240 191 / 195;
+                // two of 160 -> 384 7x7 on 17x24, N = 71, 515 steps either way 437 / 422; two of 496 -> 512 3x3 on 38x32, N = 42,
+                // 825 steps for 550 624 / 957; three of 304 -> 384 5x5 on 30x16, N = 134, 2278 for 1710 1485 / 2842.  Over 212
+                // layers of two to eight columns this takes 0.83 of their time apart (always together 1.04).
+                int per1, n1, per_all, n_all;
+                const double apart = G * pick_splits(1, per1, n1), all = pick_splits(G, per_all, n_all);
+                pl.fused_groups = G > 1 && three_part && dy_bytes * G < kMaxSpanBytes && x_bytes * G < kMaxSpanBytes &&
+                                  (RS == 1 || (dy_bytes + x_bytes) * G < (int64_t)155000000) && all <= 200.0 &&
+                                  0.6 * (all - apart) < 14.0 * (G - 1);
                 const int GF = pl.fused_groups ? G : 1;
                 pl.lin = true;
                 pl.lin_wq = wq; pl.lin_jy = jy; pl.lin_jx = jx; pl.lin_steps = (int)steps;
-                want = 256 / ((kpad / 128) * ceil_div(pl.Kg, 256) * GF);
-                int ns = want < (int)(steps / 4) ? want : (int)(steps / 4);     // at least 4 steps per split
-                if (ns < 1) ns = 1;
-                pl.chunks_per_split = ceil_div((int)steps, ns);
-                pl.nsplit = ceil_div((int)steps, pl.chunks_per_split);
+                pl.chunks_per_split = pl.fused_groups ? per_all : per1;
+                pl.nsplit = pl.fused_groups ? n_all : n1;
                 pl.lin_dy_off = off; pl.lin_dy_bytes = (size_t)dy_bytes * GF; off += round_up64(pl.lin_dy_bytes, 256);
                 pl.lin_x_off = off; pl.lin_x_bytes = (size_t)x_bytes * GF; off += round_up64(pl.lin_x_bytes, 256);
             }

@@ -200,6 +200,22 @@ def test_route_of_the_bf16_window_kernel(route):
         assert route(1, N, 96, 27, 27, 256, 5, 1, 2, groups=2, dtype=1).kernels == "window"
 
 
+def test_route_of_the_grouped_bf16_backward_filter(route):
+    """The columns in one launch of each kernel where that saves more than it costs: not where whole tiles of all columns leave
+    CUs without work for long, nor where their packed copies outgrow the cache."""
+    together = lambda N, C, H, W, K, R, G: route(2, N, C, H, W, K, R, 1, R // 2, groups=G, dtype=1).together
+    for N in (1, 16, 64, 128, 192):
+        assert together(N, 96, 27, 27, 256, 5, 2), N
+    # apart / together 191 / 195 us and, with 825 steps of a CU for 550, 2278 for 1710 and 890 for 512: 624 / 957, 1485 / 2842,
+    # 710 / 1029
+    assert not together(240, 96, 27, 27, 256, 5, 2)
+    assert not together(42, 992, 38, 32, 1024, 3, 2)
+    assert not together(134, 912, 30, 16, 1152, 5, 3)
+    assert not together(113, 1408, 12, 40, 512, 5, 4)
+    # 235 / 201, 153 / 97 and, 1x1 with 219 MB of copies, 202 / 135
+    assert together(13, 1536, 39, 24, 1536, 3, 4) and together(40, 896, 38, 16, 512, 3, 4) and together(39, 336, 51, 52, 384, 1, 3)
+
+
 SAN_FLAGS = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
 # leak checking off (the OpenMP runtime keeps its thread pool); the link-order check is off because the test
 # harness may preload a library of its own ahead of the sanitizer runtime
