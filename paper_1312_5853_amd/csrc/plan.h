@@ -356,10 +356,10 @@ inline int64_t window_bytes(int N, int OH, int OW, int R, int hp, int wp, int bn
 //   - one chunk: two of four waves in 80 KB of LDS, else one, which then has nobody beside it and takes 1.3 times as long a
 //     slice (4 x 64 x 19 x 49, two columns of 167 filters 9x9: 51 us, staged 38).
 // The rule takes 0.85 of the register-staged kernel's time over those 700, the better of the two each time would take 0.82; of
-// the 358 passes that it sends here 13 are 3 to 10 % slower, and of 394 further ones 10, by up to 21 %: where the estimate of
-// the register-staged kernel is off (it is good to 17 %).  Measured on both sides of
-// the line, window / staged: 58x80x21x28, 64 channels 3x3 19 / 32 us; 27 x 112 x 44 x 36, 125 filters 5x5 50 / 72; 8 x 208 x 16 x 25, 295 filters 5x5 57 /
-// 56; 7 x 208 x 24 x 14, 144 filters 7x7 95 / 77; 1 x 128 x 14 x 12, 80 filters 5x5 32 / 19.
+// the 358 passes that it sends here 13 are 3 to 10 % slower, and of 434 further ones 16, by up to 21 %: where the estimate of
+// the register-staged kernel is off (it is good to 17 %; constants fitted anew do no better).  Measured on both sides of the
+// line, window / staged: 58 x 80 x 21 x 28, 64 channels 3x3 19 / 32 us; 27 x 112 x 44 x 36, 125 filters 5x5 50 / 72; 8 x 208 x
+// 16 x 25, 295 filters 5x5 57 / 56; 7 x 208 x 24 x 14, 144 filters 7x7 95 / 77; 1 x 128 x 14 x 12, 80 filters 5x5 32 / 19.
 inline void plan_window(int op, const Problem &pb, Plan &pl)
 {
     const bool fwd = op == kOpFwd;

@@ -104,6 +104,33 @@ def same_pattern(got, ref):
     assert np.abs(g[fin].astype(np.float64) - ref[fin]).max() <= 1e-5 * max(np.abs(ref[fin]).max(), 1e-300)
 
 
+# ... with the layer's epilogues in their stores, on channel slices of wider tensors, two columns together: the plain pass's bits;
+# and special values, which a work-group of four waves computes again
+def test_split_passes_of_many_rounds_with_epilogues_slices_and_columns(route):
+    N, C, H, W, K, R, st, pad = shape = 192, 32, 33, 31, 128, 3, 1, 1
+    assert route(0, *shape).columns == 128
+    x, w = torch.randn(N, C + 8, H, W, device="cuda"), torch.randn(K, C, R, R, device="cuda") * 0.05
+    dense = x[:, 4:4 + C].contiguous()
+    y = hp.conv_fwd(dense, w, st, pad)
+    wide = torch.full((N, K + 8, H, W), 7.0, device="cuda")
+    hp.conv_fwd(x[:, 4:4 + C], w, st, pad, y=wide[:, 4:4 + K])
+    assert torch.equal(wide[:, 4:4 + K], y) and bool((wide[:, :4] == 7.0).all()) and bool((wide[:, 4 + K:] == 7.0).all())
+    bias = torch.randn(K, device="cuda")
+    assert torch.equal(hp.conv_fwd_bias_relu(dense, w, bias, st, pad), torch.relu(y + bias[:, None, None]))
+    back = 133, 60, 33, 31, 48, 3, 1, 1
+    assert route(1, *back).columns == 128
+    dy, wb = torch.randn(133, 48, 33, 31, device="cuda"), torch.randn(48, 60, 3, 3, device="cuda") * 0.05
+    act = torch.relu(torch.randn(133, 60, 33, 31, device="cuda"))
+    dx = hp.conv_bwd_data(dy, wb, 33, 31, 1, 1)
+    assert torch.equal(hp.conv_bwd_data_relu(dy, wb, act, 1, 1), torch.where(act > 0, dx, torch.zeros_like(dx)))
+    two = 128, 64, 33, 31, 256, 3, 1, 1
+    assert route(0, *two, groups=2).columns == 128 and route(0, 128, 32, 33, 31, 128, 3, 1, 1).columns == 256
+    x2, w2 = torch.randn(128, 64, 33, 31, device="cuda"), torch.randn(256, 32, 3, 3, device="cuda") * 0.05
+    y2 = hp.conv_fwd_grouped(x2, w2, 1, 1, 2)
+    for g in range(2):
+        assert torch.equal(y2[:, 128 * g:128 * (g + 1)], hp.conv_fwd(x2[:, 32 * g:32 * (g + 1)], w2[128 * g:128 * (g + 1)], 1, 1))
+
+
 STRIDE1 = 3, 96, 13, 13, 96, 3, 1, 1         # both passes on the three-part kernels
 
 
@@ -117,6 +144,18 @@ def test_split_passes_give_infinities_and_nan_as_fp32_does(value, route):
     with np.errstate(all="ignore"):
         same_pattern(hp.conv_fwd(dev(x), dev(w), 1, 1), oracle.conv_fwd(x, w, 1, 1))
         same_pattern(hp.conv_bwd_data(dev(x), dev(w), 13, 13, 1, 1), oracle.conv_bwd_data(x, w, 13, 13, 1, 1))
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3.4e38])
+def test_split_passes_of_many_rounds_give_infinities_and_nan_as_fp32_does(value, route):
+    shape = N, C, H, W, K, R, st, pad = 192, 32, 33, 31, 128, 3, 1, 1
+    assert route(0, *shape).columns == 128
+    x, w = synth.gaussian((N, C, H, W), 913), np.abs(synth.gaussian((K, C, R, R), 914)) + np.float32(0.5)
+    x[101, 17, 16, 30] = value
+    y = hp.conv_fwd(dev(x), dev(w), st, pad)
+    with np.errstate(all="ignore"):
+        same_pattern(y[99:104], oracle.conv_fwd(x[99:104], w, st, pad))
+    assert bool(torch.isfinite(y[:99]).all()) and bool(torch.isfinite(y[104:]).all())
 
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-34, 1e-37])
@@ -271,6 +310,18 @@ def test_split_row_kernel_repeats_itself_where_a_staged_row_is_not_finite(value,
     # in fp32 a product passes through the sum of its work-group's positions and that of the 256 work-groups, one rounding each
     bound = (N * P * Q / 256 + 256 + 24) * 2.0 ** -24 * ref_abs
     assert (np.abs(g[ok].astype(np.float64) - ref[ok]) <= bound[ok]).all()
+
+
+def test_split_row_kernel_on_channel_slices(route):
+    """Input and output gradient as channel slices of wider tensors: the bits of dense ones."""
+    shape = N, C, H, W, K, R, st, pad = 86, 3, 40, 120, 96, 11, 4, 2
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, R, st, pad)
+    assert route(2, *shape).kernels == "split"
+    x, dy = torch.randn(N, C + 5, H, W, device="cuda"), torch.randn(N, K + 8, P, Q, device="cuda")
+    xs, dys = x[:, 4:4 + C], dy[:, 4:4 + K]
+    x[:, :4], x[:, 4 + C:], dy[:, :4], dy[:, 4 + K:] = float("nan"), float("nan"), float("nan"), float("nan")
+    got = hp.conv_bwd_filter(xs, dys, R, R, st, pad, dw=nan_like((K, C, R, R)))
+    assert torch.equal(got, hp.conv_bwd_filter(xs.contiguous(), dys.contiguous(), R, R, st, pad))
 
 
 # Every instance (one to four blocks of 16 positions) keeps its operands in registers: a call on shorter rows takes no longer than
