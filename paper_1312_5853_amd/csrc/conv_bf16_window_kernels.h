@@ -26,8 +26,9 @@
 // A wave owns 64 rows x 32 TN positions: with TN = 3 it reads five fragments for six matrix instructions.
 // Two columns 48 -> 128 channels 5x5 on 27x27, both together, preparation + kernel, against the register-staged kernel: forward
 // N = 64 57 -> 41 us (9 + 32), N = 128 94 -> 70; backward-data N = 64 79 -> 54 (12 + 42), N = 128 137 -> 98.  Bound: matrix
-// instructions in the loop (87 % of its clocks forward, N = 64); 4.6k clocks of set-up and first window and 11k of stores beside
-// its 33k; backward-data pads 48 rows to 64.  The preparation is bound by memory (5 TB/s at N = 128).
+// instructions in the loop; of the cycles in which a CU holds work-groups the matrix unit is busy 56 % forward and 49 % backward-data
+// (N = 64), the others being set-up, first window and stores.  Backward-data pads 48 rows to 64.  10 % of the cycles are LDS
+// bank conflicts.  The preparation is bound by memory (5 TB/s at N = 128).
 
 struct ColGemmWindowArgs {
     const char *At, *xb;

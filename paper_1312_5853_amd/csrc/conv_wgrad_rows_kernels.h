@@ -613,7 +613,7 @@ __global__ __launch_bounds__(kRowsF32Threads, 1) void wgrad_rows_f32_kernel(cons
 // not finite the sum becomes NaN, and the rule below computes it again unless a NaN of its own explains it.
 // Bound: matrix instructions (128 x 3 x 224 x 224, 96 filters 11 x 11: 30 x 110 x 32 clocks x 2 waves = 106 us at 2 GHz).
 // Measured: that layer's calls (forward and this) 488 -> 397 us; kernel in the running network 267 -> 175 us; matrix unit busy
-// 64 % of its cycles; error against 64 bits 7.0e-7 -> 2.6e-7.  What was costly on the way: bounds and indexes worked out at each
+// 64 % of the cycles in which a CU holds work-groups, 55 % of the duration; error against 64 bits 7.0e-7 -> 2.6e-7.  What was costly on the way: bounds and indexes worked out at each
 // load (506 vector instructions per wave and row, 214 now), masks on the operand of the last block, and sums that spilled.
 // ---------------------------------------------------------------------------
 constexpr int kRowsSplitDyPart = kRowsM * kRowsPitch;
