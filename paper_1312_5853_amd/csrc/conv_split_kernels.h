@@ -1,5 +1,6 @@
-// fp32 forward / stride-1 backward-data on the bf16 matrix instruction: every fp32 operand is split into three bfloat16
-// parts whose sum it is, and the six products that matter are accumulated in fp32.
+// fp32 forward / stride-1 backward-data on the 16-bit matrix instructions: every fp32 operand is split into three bfloat16
+// parts whose sum it is, and the six products that matter are accumulated in fp32; or, for long sums of operands of like
+// magnitudes, into two half-precision parts and three products (see operand_range below).
 // Part of convnet_hotpath.hip: included there, inside its anonymous namespace, after conv_bf16_dma_kernels.h.
 //
 // Why: an fp32 matrix instruction occupies the pipe 16 times as long per product as a bf16 one.  x = h + m + l with
@@ -16,6 +17,14 @@
 // all their bits, whatever lies beside them or multiplies them.  What no longer fits, operands from 2^104 and sums from 2^80
 // on, makes its sum infinite or NaN, and the work-group computes such a tile again from the fp32 tensors with the fp32 matrix
 // instruction (split_finish), so that large values, infinities and NaN come out as fp32 arithmetic gives them.
+
+template <int V> using I = std::integral_constant<int, V>;
+template <typename F, int... V>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, V...>) { (f(I<V>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
 
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
@@ -42,6 +51,139 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
         unsigned h, m, l;
         split_pair(v[2 * t], v[2 * t + 1], h, m, l);
         o[0][t] = h; o[1][t] = m; o[2][t] = l;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Two half-precision parts: h = f16(s x), l = f16((s x - h) 2^12), s a power of two that brings the largest operand of the
+// tensor into [2^14, 2^15).  s x = h + 2^-12 l up to 2^-23 of itself (11 + 11 significand bits and l's sign) where the operand is
+// within 2^-28 of the largest, 2^-20 at 2^-32 of it; three products, h h' into one accumulator, h l' and l h' into another.  A
+// call takes them where every operand of both tensors is zero or within these 2^-32 and the largest lie between 2^-45 and
+// 2^41; any other call, and so every one with an infinity, a NaN or a value whose products could leave fp32's range, keeps the
+// three bfloat16 parts.  operand_range looks at the tensors, on the GPU, and the kernels branch on what it found.
+// ---------------------------------------------------------------------------
+constexpr int kRangeBlocks = 256, kRangeThreads = 512;       // per tensor
+constexpr float kHalfLow = 0x1p12f, kHalfLowInv = 0x1p-12f;
+
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// What the kernels of a call read in memory: per block of operand_range the largest magnitude and the smallest that is not zero
+// less one (as integers, so zero is the largest), of both tensors; and what follows from them.
+struct SplitInfo {
+    int two;                   // two parts
+    float unscale;             // of a sum
+    float sa, sb;              // of the tensors' operands
+};
+struct SplitRanges {
+    unsigned big[2][kRangeBlocks], small[2][kRangeBlocks];
+    SplitInfo info;            // written by the preparation, or by whoever needs it past the first kernel
+};
+
+struct RangeArgs {
+    const float *t[2];
+    int64_t bs[2];             // elements between samples
+    unsigned len[2], quads[2]; // elements of a sample (four and more), its groups of four
+    unsigned total[2];         // groups of four in all
+    FastDiv div_quads[2];
+    SplitRanges *out;
+};
+
+template <int CTRL> __device__ __forceinline__ unsigned dpp(unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+}
+// largest (smallest) value over a wavefront whose lanes are all active
+__device__ __forceinline__ unsigned wave_max(unsigned v)
+{
+    v = max(v, dpp<0x111>(v)); v = max(v, dpp<0x112>(v)); v = max(v, dpp<0x114>(v)); v = max(v, dpp<0x118>(v));
+    v = max(v, dpp<0x142>(v)); v = max(v, dpp<0x143>(v));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned wave_min(unsigned v) { return ~wave_max(~v); }
+
+// Bound: HBM, four bytes per operand; every operand is read once here and once by what follows, from the 256 MB cache where the
+// tensors fit.  A group of four that would reach past a sample's end is moved back: operands seen twice change nothing.
+__global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p)
+{
+    typedef unsigned quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    const int which = (int)blockIdx.x >= kRangeBlocks, b = (int)blockIdx.x - which * kRangeBlocks;
+    const float *const t = p.t[which];
+    const int64_t bs = p.bs[which];
+    const unsigned len = p.len[which], quads = p.quads[which], total = p.total[which];
+    const FastDiv div = p.div_quads[which];
+    unsigned big = 0, small = 0xffffffffu;
+    constexpr int UN = 4;
+    constexpr unsigned step = kRangeBlocks * kRangeThreads;
+    for (unsigned i = b * kRangeThreads + threadIdx.x; i < total; i += UN * step) {
+        quad_t v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const unsigned q = min(i + u * step, total - 1);
+            const unsigned n = fastdiv(q, div);
+            v[u] = *reinterpret_cast<const quad_t *>(t + (int64_t)n * bs + min((q - n * quads) * 4, len - 4));
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned m = v[u][k] & 0x7fffffffu;
+                big = max(big, m);
+                small = min(small, m - 1u);
+            }
+    }
+    __shared__ unsigned words[2][kRangeThreads / 64];
+    big = wave_max(big);
+    small = wave_min(small);
+    if ((threadIdx.x & 63) == 0) { words[0][threadIdx.x >> 6] = big; words[1][threadIdx.x >> 6] = small; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < kRangeThreads / 64; ++w) { big = max(big, words[0][w]); small = min(small, words[1][w]); }
+        p.out->big[which][b] = big;
+        p.out->small[which][b] = small;
+    }
+}
+
+// from the blocks' findings, by a wavefront whose lanes are all active
+__device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane)
+{
+    SplitInfo o;
+    o.two = 1;
+    int e[2];
+    float scale[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const u32x4 b = reinterpret_cast<const u32x4 *>(r->big[t])[lane], s = reinterpret_cast<const u32x4 *>(r->small[t])[lane];
+        const unsigned big = wave_max(max(max(b[0], b[1]), max(b[2], b[3])));
+        const unsigned small = wave_min(min(min(s[0], s[1]), min(s[2], s[3])));
+        e[t] = big == 0 ? 0 : (int)(big >> 23) - 127;
+        const int es = big == 0 ? 0 : (int)((small + 1u) >> 23) - 127;
+        if (e[t] < -45 || e[t] > 40 || es < e[t] - 31) o.two = 0;
+        scale[t] = __uint_as_float((unsigned)(127 + 14 - e[t]) << 23);
+    }
+    o.sa = scale[0];
+    o.sb = scale[1];
+    o.unscale = __uint_as_float((unsigned)(127 - 28 + e[0] + e[1]) << 23);
+    return o;
+}
+static_assert(kRangeBlocks == 256, "four blocks to a lane");
+
+// two scaled operands -> their parts, two to a word
+__device__ __forceinline__ void split_pair_two(float a, float b, unsigned &h, unsigned &l)
+{
+    const f16x2 hh = __builtin_convertvector((f32x2){a, b}, f16x2);
+    h = __builtin_bit_cast(unsigned, hh);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector(
+            (f32x2){(a - (float)hh[0]) * kHalfLow, (b - (float)hh[1]) * kHalfLow}, f16x2));
+}
+__device__ __forceinline__ void split_eight_two(const float (&v)[8], float s, u32x4 (&o)[3])
+{
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        unsigned h, l;
+        split_pair_two(v[2 * t] * s, v[2 * t + 1] * s, h, l);
+        o[0][t] = h; o[1][t] = l;
     }
 }
 
@@ -150,6 +292,7 @@ struct SplitPrepArgs {
     int64_t w_gs;              // floats between the columns' filters
     int Cin, R, S, rows, cols;               // fold > 1: input channels, the filter's and the input's extents
     int pairs;                 // fold > 1: two columns b, b + 1 are inside or outside together and 8-byte aligned
+    SplitRanges *ranges;       // or null: three parts
     FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs, div_sv;
 };
 
@@ -168,6 +311,12 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {
     float v[8];
     u32x4 o[3];
+    SplitInfo info = {0, 0.f, 0.f, 0.f};
+    if (p.ranges) {
+        info = split_info(p.ranges, threadIdx.x & 63);
+        if (blockIdx.x == 0 && threadIdx.x == 0) p.ranges->info = info;
+    }
+    const unsigned parts = info.two ? 2 : 3;
     if ((int)blockIdx.x < p.xb_blocks) {
         const unsigned e = blockIdx.x * 256u + threadIdx.x;
         const unsigned i = e >> 1, half = e & 1;
@@ -203,11 +352,12 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = load_or_zero(x, e + (int64_t)k * LHW, in && c0 + k < p.Cg);
         }
-        split_eight(v, o);
+        if (info.two) split_eight_two(v, info.sa, o); else split_eight(v, o);
         const unsigned plane = (unsigned)p.Hp * (unsigned)p.Wp;
-        u32x4 *dst = p.xs + ((size_t)t2 * 3 * plane + (i - t2 * plane)) * 2 + half;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) dst[(size_t)c * plane * 2] = o[c];
+        u32x4 *dst = p.xs + ((size_t)t2 * parts * plane + (i - t2 * plane)) * 2 + half;
+        dst[0] = o[0];
+        dst[(size_t)plane * 2] = o[1];
+        if (!info.two) dst[(size_t)2 * plane * 2] = o[2];
         return;
     }
     const unsigned e = (blockIdx.x - (unsigned)p.xb_blocks) * 256u + threadIdx.x;
@@ -232,10 +382,11 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
             v[k] = load_or_zero(w, (p.transposed ? (int64_t)ch * p.C + m : (int64_t)m * p.C + ch) * p.RS + rs, m < p.M && ch < p.Cg);
         }
     }
-    split_eight(v, o);
-    u32x4 *dst = p.wt + ((size_t)t2 * 3 * p.Mpad + m) * 2 + (half ^ ((m >> 3) & 1));
-#pragma unroll
-    for (int c = 0; c < 3; ++c) dst[(size_t)c * p.Mpad * 2] = o[c];
+    if (info.two) split_eight_two(v, info.sb, o); else split_eight(v, o);
+    u32x4 *dst = p.wt + ((size_t)t2 * parts * p.Mpad + m) * 2 + (half ^ ((m >> 3) & 1));
+    dst[0] = o[0];
+    dst[(size_t)p.Mpad * 2] = o[1];
+    if (!info.two) dst[(size_t)2 * p.Mpad * 2] = o[2];
 }
 
 // ---------------------------------------------------------------------------
@@ -249,6 +400,13 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 // random operands).  384 -> 384 channels 3x3, N = 128, whole call (preparation 26 us): forward 452 -> 273 us, backward-data
 // 450 -> 269; N = 2: 78 -> 33; two columns 48 -> 128 5x5, N = 128: forward 474 -> 278, backward-data 499 -> 379 (48 rows
 // padded to 64).
+// Two parts: half the matrix work on two thirds of the bytes.  Where the next step lies is one addition from this one's place:
+// multiplied out at each step, with fields of the arguments reloaded, it was 79 scalar instructions a wave and step ahead of the
+// first of 12 matrix instructions.  Kernels, three parts -> two so -> two with additions: 384 -> 384 channels 228 -> 181 -> 160
+// us, backward-data of the two columns 375 -> 327 -> 250; whole layers (three passes) 851 -> 645 and 1055 -> 796 us, first layer
+// (three parts) 395 -> 386.  What bounds it: power (half-precision operands sustain 1.62 PFLOP/s against bfloat16's 1.76;
+// this kernel reaches 1.1), not the loads (left out: the same time) nor the LDS reads (left out: 5 % less).  A fourth
+// buffer changes nothing.
 // Order inside a step: h h', h l', l h', h m' while the loads of step + 2 are issued; then every fragment of the step
 // has been read, so the barrier that frees its buffer comes here; m h', m m' cover the barrier and the reads of the next
 // step's h and h' (each into the registers that held this step's).
@@ -281,7 +439,8 @@ struct ColGemmSplitArgs {
     int tap_r, tap_s, RS;      // filter taps between rows, columns of a class's taps; taps of a filter
     int Wp;
     unsigned plane_bytes;      // one part of one channel block: Hp * Wp * 32
-    unsigned n_bytes;          // one sample: channel blocks of all columns * 3 * plane_bytes
+    unsigned n_blocks;         // channel blocks of all columns
+    const SplitInfo *info;     // kernels with TWO
     int N, sign;               // sign +1: tap (r, s) reads padded (oh*mul + r, ow*mul + s); -1: see SplitClass
     int cblocks;               // channel blocks per column
     int dst_bs;
@@ -297,17 +456,22 @@ struct ColGemmSplitArgs {
     SplitClass cls[kMaxClasses];
 };
 
-template <int TM, int TN, int WM, int WN>
+// LDS of a work-group: three buffers of a step's operands, two parts with the sums put aside
+template <int TM, int TN, int WM, int WN, bool TWO>
+constexpr int split_lds()
+{
+    const int rows = (TM * WM + TN * WN) * 32, three = 3 * rows * 96, two = 3 * rows * 64 + TM * TN * WM * WN * 64 * 32;
+    return TWO && two > three ? two : three;
+}
+
+template <int TM, int TN, int WM, int WN, bool TWO>
 __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_split_kernel(const ColGemmSplitArgs p)
 {
     constexpr int NW = WM * WN;
     constexpr int BM = TM * WM * 32, BN = TN * WN * 32;
-    constexpr int QA = BM * 3 / 32, QB = BN * 3 / 32;          // 1 KB loads per step: filters, activations
-    constexpr int NL = (QA + QB + NW - 1) / NW;                // ... per wave (the last may repeat an earlier one)
-    constexpr int BUF = (BM + BN) * 96;
     constexpr int MPG = TM * TN;                               // matrix instructions per product
     static_assert(NW == 8 || NW == 4, "eight waves, or four and two work-groups per CU");
-    static_assert(3 * BUF * (8 / NW) <= 160 * 1024, "three LDS buffers");
+    static_assert(split_lds<TM, TN, WM, WN, TWO>() * (8 / NW) <= 160 * 1024, "LDS buffers");
 
     extern __shared__ __attribute__((aligned(16))) float lds_fast[];
     const char *const lds = reinterpret_cast<const char *>(lds_fast);
@@ -329,9 +493,32 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
     const int mt = tile % p.mtiles, nt = tile / p.mtiles;
     const int m0 = mt * BM, n0 = nt * BN;
 
+    SplitInfo info = {0, 0.f, 0.f, 0.f};
+    if constexpr (TWO) {
+        info.two = uniform(p.info->two);
+        info.unscale = __int_as_float(uniform(__float_as_int(p.info->unscale)));
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = uniform(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
+
+    const int step_begin = ks * q.steps_per_split;
+    const int nsteps = max(0, min(p.cblocks * q.R * q.S - step_begin, q.steps_per_split));
+    f32x16 acc[TM][TN], low[TM][TN];           // sums of h h'; of the five smaller products
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[i][jn][v] = 0.f; low[i][jn][v] = 0.f; }
+
+    const int l32 = lane & 31, half = lane >> 5;
+
+    auto contract = [&](auto parts_c) {
+    constexpr unsigned PARTS = decltype(parts_c)::value;
+    constexpr int QA = BM * PARTS / 32, QB = BN * PARTS / 32;  // 1 KB loads per step: filters, activations
+    constexpr int NL = (QA + QB + NW - 1) / NW;                // ... per wave (the last may repeat an earlier one)
+    constexpr int BUF = (BM + BN) * PARTS * 32;
 
     // Load i of this wave is 1 KB block q of the step: 32 rows of one part, filters first.  LDS block q lies at q * 1024.
     unsigned voff[NL], lq[NL];
@@ -339,9 +526,9 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
         int lb = i * NW + wave;
-        if (lb >= QA + QB) lb -= NW;                             // repeats this wave's previous load
+        if ((i + 1) * NW > QA + QB && lb >= QA + QB) lb -= NW;   // repeats this wave's previous load
         lq[i] = (unsigned)lb * 1024u;
-        isa[i] = lb < QA;
+        isa[i] = (i + 1) * NW <= QA || (i * NW < QA && lb < QA);
         if (isa[i]) {
             const int c = lb / (BM / 32), b = lb - c * (BM / 32);
             voff[i] = (unsigned)((c * p.Mpad + b * 32) * 32 + lane * 16);
@@ -356,83 +543,170 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
             const int rem = j - n * (q.OH * q.OW);
             const int oh = (int)fastdiv((uint32_t)rem, q.div_ow);
             const int ow = rem - oh * q.OW;
-            voff[i] = (unsigned)n * p.n_bytes + (unsigned)c * p.plane_bytes +
+            voff[i] = (unsigned)n * p.n_blocks * (PARTS * p.plane_bytes) + (unsigned)c * p.plane_bytes +
                       (unsigned)((oh * p.mul * p.Wp + ow * p.mul) * 32 + chunk * 16);
         }
     }
 
-    const int step_begin = ks * q.steps_per_split;
-    const int nsteps = max(0, min(p.cblocks * q.R * q.S - step_begin, q.steps_per_split));
-    const size_t a_step_bytes = (size_t)p.Mpad * 96;
-    const char *const a_first = static_cast<const char *>(p.At) +
-                                ((size_t)gcol * p.cblocks * p.RS + q.tap0) * a_step_bytes + (size_t)m0 * 32;
-    const char *a_base = a_first;
-    const char *const x_base = static_cast<const char *>(p.xs) + (size_t)gcol * p.cblocks * 3 * p.plane_bytes;
-    int r, s, cb;                                                // next step to load
-    {
-        cb = (int)fastdiv((uint32_t)step_begin, q.div_rs);
-        const int rs = step_begin - cb * (q.R * q.S);
-        r = (int)fastdiv((uint32_t)rs, q.div_s);
-        s = rs - r * q.S;
-    }
-    const char *xs = nullptr;
-    unsigned lbuf = 0;
-    auto begin_step_loads = [&](int buf) {
+    // Where the next step to load lies, and how far it is to the one after: the next column of taps, the next row, the next
+    // channel block (one addition each: a wave issues one scalar instruction in four clocks and has few clocks a step).
+    const int CR = q.R, CS = q.S;
+    const int a_step_bytes = p.Mpad * (int)(PARTS * 32);
+    const int64_t cb_bytes = (int64_t)PARTS * p.plane_bytes;
+    const char *a_base = nullptr, *xs = nullptr;
+    int left_r = 0, left_s = 0;                                  // rows and columns of taps from here on
+    auto seek = [&](int st) {
+        const int cb = (int)fastdiv((uint32_t)st, q.div_rs);
+        const int rs = st - cb * (CR * CS);
+        const int r = (int)fastdiv((uint32_t)rs, q.div_s), s = rs - r * CS;
+        a_base = static_cast<const char *>(p.At) + (size_t)m0 * 32 +
+                 ((int64_t)(gcol * p.cblocks + cb) * p.RS + q.tap0 + r * p.tap_r + s * p.tap_s) * a_step_bytes;
         const int ar = p.sign > 0 ? r : q.ty - r, as = p.sign > 0 ? s : q.tx - s;
-        a_base = a_first + (size_t)(cb * p.RS + r * p.tap_r + s * p.tap_s) * a_step_bytes;
-        xs = x_base + (size_t)cb * 3 * p.plane_bytes + (ar * p.Wp + as) * 32;
-        lbuf = lds_base + buf * BUF;
+        xs = static_cast<const char *>(p.xs) + (gcol * p.cblocks + cb) * cb_bytes + (ar * p.Wp + as) * 32;
+        left_r = CR - r; left_s = CS - s;
     };
-    auto load_one = [&](int i) { dma16(isa[i] ? a_base : xs, voff[i], lbuf + lq[i]); };
-    auto end_step_loads = [&]() {
-        s += 1;
-        if (s == q.S) { s = 0; r += 1; }
-        if (r == q.R) { r = 0; cb += 1; }
+    const int a_s = p.tap_s * a_step_bytes, a_r = (p.tap_r - (CS - 1) * p.tap_s) * a_step_bytes;
+    const int a_c = (p.RS - (CR - 1) * p.tap_r - (CS - 1) * p.tap_s) * a_step_bytes;
+    const int x_s = p.sign * 32, x_r = p.sign * (p.Wp - (CS - 1)) * 32;
+    const int x_c = (int)cb_bytes - p.sign * ((CR - 1) * p.Wp + CS - 1) * 32;     // (one block: wraps, and is not used)
+    auto advance = [&]() {
+        int da = a_s, dx = x_s;
+        left_s -= 1;
+        if (left_s == 0) {
+            left_s = CS; da = a_r; dx = x_r;
+            left_r -= 1;
+            if (left_r == 0) { left_r = CR; da = a_c; dx = x_c; }
+        }
+        a_base += da; xs += dx;
     };
+    auto load_one = [&](int i, unsigned lbuf) { dma16(isa[i] ? a_base : xs, voff[i], lbuf + lq[i]); };
     auto load_step = [&](int buf) {
-        begin_step_loads(buf);
 #pragma unroll
-        for (int i = 0; i < NL; ++i) load_one(i);
-        end_step_loads();
+        for (int i = 0; i < NL; ++i) load_one(i, lds_base + buf * BUF);
+        advance();
     };
 
-    f32x16 acc[TM][TN], low[TM][TN];           // sums of h h'; of the five smaller products
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[i][jn][v] = 0.f; low[i][jn][v] = 0.f; }
-
-    const int l32 = lane & 31, half = lane >> 5;
     const int choff = (half ^ ((l32 >> 3) & 1)) * 16;
     const int a_row = (wm * TM * 32 + l32) * 32 + choff;
-    const int b_row = BM * 96 + (wn * TN * 32 + l32) * 32 + choff;
-
-    u32x4 fa[3][TM], fb[3][TN];                                // fragments, by part
-    auto read_a = [&](const char *bufp, int c, u32x4 (&f)[TM]) {
+    const int b_row = BM * PARTS * 32 + (wn * TN * 32 + l32) * 32 + choff;
+    auto read_a = [&](int bufo, int c, u32x4 (&f)[TM]) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) f[i] = *reinterpret_cast<const u32x4 *>(bufp + a_row + (c * BM + i * 32) * 32);
+        for (int i = 0; i < TM; ++i) f[i] = *reinterpret_cast<const u32x4 *>(lds + bufo + a_row + (c * BM + i * 32) * 32);
     };
-    auto read_b = [&](const char *bufp, int c, u32x4 (&f)[TN]) {
+    auto read_b = [&](int bufo, int c, u32x4 (&f)[TN]) {
 #pragma unroll
-        for (int jn = 0; jn < TN; ++jn) f[jn] = *reinterpret_cast<const u32x4 *>(bufp + b_row + (c * BN + jn * 32) * 32);
+        for (int jn = 0; jn < TN; ++jn) f[jn] = *reinterpret_cast<const u32x4 *>(lds + bufo + b_row + (c * BN + jn * 32) * 32);
     };
 
+    seek(step_begin);
     if (nsteps > 0) load_step(0);
     if (nsteps > 1) load_step(1);
     if (nsteps > 1) wait_vmcnt<NL>(); else wait_vmcnt<0>();
     __syncthreads();
-    if (nsteps > 0) { read_a(lds, 0, fa[0]); read_b(lds, 0, fb[0]); }
+    int step = 0, bufo = 0;                                      // this step's buffer, in bytes
+    const auto after = [&](int o) { return o == 2 * BUF ? 0 : o + BUF; };
 
+    if constexpr (PARTS == 2) {
+        // Order inside a step: h h' and h l' while the loads of step + 2 are issued; the barrier, behind which the next step's
+        // h and h' are read into a second set of registers; l h'.
+        constexpr int SLOTS = 2 * MPG, SPACING = SLOTS / NL > 0 ? SLOTS / NL : 1;
+        u32x4 ha[2][TM], hb[2][TN], la[TM], lb[TN];
+        if (nsteps > 0) { read_a(0, 0, ha[0]); read_b(0, 0, hb[0]); }
+        // (the last steps load the last one again: one form of the step, or the sums change registers between its forms)
+        int to_load = nsteps - 2;
+        if (to_load <= 0) seek(step_begin + nsteps - 1);
+        auto do_step = [&](auto set_c) {
+            constexpr int set = decltype(set_c)::value;
+            const int bufo1 = after(bufo);
+            const unsigned lbuf = lds_base + after(bufo1);
+            auto product = [&](const u32x4 (&xa)[TM], const u32x4 (&xb)[TN], auto g_c) {
+                constexpr int g = decltype(g_c)::value;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int jn = 0; jn < TN; ++jn) {
+                        f32x16 &sum = g == 0 ? acc[i][jn] : low[i][jn];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, xa[i]),
+                                                                     __builtin_bit_cast(f16x8, xb[jn]), sum, 0, 0, 0);
+                        const int m = g * MPG + i * TN + jn;
+                        if (g < 2) {
+#pragma unroll
+                            for (int u = 0; u < NL; ++u)
+                                if ((u * SPACING < SLOTS ? u * SPACING : SLOTS - 1) == m) {
+                                    __builtin_amdgcn_sched_barrier(0);
+                                    load_one(u, lbuf);
+                                    __builtin_amdgcn_sched_barrier(0);
+                                }
+                        }
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            read_b(bufo, 1, lb);
+            read_a(bufo, 1, la);
+            __builtin_amdgcn_sched_barrier(0);
+            product(ha[set], hb[set], I<0>{});
+            product(ha[set], lb, I<1>{});
+            to_load -= 1;
+            if (to_load > 0) advance();
+            wait_vmcnt<NL>();
+            asm volatile("s_waitcnt lgkmcnt(0)");
+            __syncthreads();
+            read_a(bufo1, 0, ha[set ^ 1]);
+            read_b(bufo1, 0, hb[set ^ 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            product(la, hb[set], I<2>{});
+            ++step;
+            bufo = bufo1;
+        };
+        // A product of two halves has 22 significant bits, so every instruction rounds the sum of the leading products (those
+        // of bfloat16 have 16, and leave most of their sums exact).  Half way the leading 8 bits of that sum are put aside,
+        // in LDS: what follows adds to a small number again, and the roundings of the whole weigh 0.7 times as much.
+        char *const aside = const_cast<char *>(lds) + 3 * BUF + tid * 16;
+        auto put_aside = [&]() {
+#pragma unroll
+            for (int t = 0; t < MPG * 2; ++t) {
+                f32x16 &sum = acc[t / 2 / TN][t / 2 % TN];
+                u32x4 o;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int v = t % 2 * 8 + 2 * k;
+                    o[k] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){sum[v], sum[v + 1]}, bf16x2));
+                    sum[v] -= __uint_as_float(o[k] << 16);
+                    sum[v + 1] -= __uint_as_float(o[k] & 0xffff0000u);
+                }
+                *reinterpret_cast<u32x4 *>(aside + t * (NW * 64 * 16)) = o;
+            }
+        };
+        const int mid = nsteps / 2 & ~1;
+        while (step + 1 < nsteps) {
+            if (step == mid) put_aside();
+            do_step(I<0>{});
+            do_step(I<1>{});
+        }
+        if (step < nsteps) do_step(I<0>{});
+        if (nsteps < 2) put_aside();
+        wait_vmcnt<0>();
+#pragma unroll
+        for (int t = 0; t < MPG * 2; ++t) {
+            f32x16 &sum = acc[t / 2 / TN][t / 2 % TN];
+            const f32x16 &rest = low[t / 2 / TN][t / 2 % TN];
+            const u32x4 o = *reinterpret_cast<const u32x4 *>(aside + t * (NW * 64 * 16));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int v = t % 2 * 8 + 2 * k;
+                sum[v] = (__uint_as_float(o[k] << 16) + fmaf(rest[v], kHalfLowInv, sum[v])) * info.unscale;
+                sum[v + 1] = (__uint_as_float(o[k] & 0xffff0000u) + fmaf(rest[v + 1], kHalfLowInv, sum[v + 1])) * info.unscale;
+            }
+        }
+    } else {
     constexpr int SLOTS = 4 * MPG;                              // matrix instructions before the barrier
     constexpr int SPACING = SLOTS / NL > 0 ? SLOTS / NL : 1;
-    int step = 0, buf = 0;
+    u32x4 fa[3][TM], fb[3][TN];                                // fragments, by part
+    if (nsteps > 0) { read_a(0, 0, fa[0]); read_b(0, 0, fb[0]); }
     auto do_step = [&](auto more_c) {                           // more: the loads of step + 2 exist
         constexpr bool more = decltype(more_c)::value;
-        const int buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf1 == 2 ? 0 : buf1 + 1;
-        const char *bufp = lds + buf * BUF;
-        const char *nextp = lds + buf1 * BUF;
+        const int bufo1 = after(bufo);
+        const unsigned lbuf = lds_base + after(bufo1);
         const bool next = more || step + 1 < nsteps;
         // product g of this step: part ca of the filters with part cb of the activations
         auto product = [&](int ca, int cb, int g) {
@@ -449,36 +723,35 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
                         for (int u = 0; u < NL; ++u)
                             if ((u * SPACING < SLOTS ? u * SPACING : SLOTS - 1) == m) {
                                 __builtin_amdgcn_sched_barrier(0);
-                                load_one(u);
+                                load_one(u, lbuf);
                                 __builtin_amdgcn_sched_barrier(0);
                             }
                     }
                 }
             __builtin_amdgcn_sched_barrier(0);
         };
-        read_b(bufp, 2, fb[2]);
-        read_a(bufp, 2, fa[2]);
-        __builtin_amdgcn_sched_barrier(0);                      // the reads go out ahead of the scalar work for the loads
-        if (more) begin_step_loads(buf2);
+        read_b(bufo, 2, fb[2]);
+        read_a(bufo, 2, fa[2]);
+        __builtin_amdgcn_sched_barrier(0);
         product(0, 0, 0);
-        read_b(bufp, 1, fb[1]);
-        read_a(bufp, 1, fa[1]);
+        read_b(bufo, 1, fb[1]);
+        read_a(bufo, 1, fa[1]);
         __builtin_amdgcn_sched_barrier(0);
         product(0, 2, 1);
         product(2, 0, 2);
         product(0, 1, 3);
-        if (more) end_step_loads();
+        if (more) advance();
         if (more) wait_vmcnt<NL>(); else wait_vmcnt<0>();
         asm volatile("s_waitcnt lgkmcnt(0)");
         __syncthreads();
-        if (next) read_a(nextp, 0, fa[0]);
+        if (next) read_a(bufo1, 0, fa[0]);
         __builtin_amdgcn_sched_barrier(0);
         product(1, 0, 4);
-        if (next) read_b(nextp, 0, fb[0]);
+        if (next) read_b(bufo1, 0, fb[0]);
         __builtin_amdgcn_sched_barrier(0);
         product(1, 1, 5);
         ++step;
-        buf = buf1;
+        bufo = bufo1;
     };
     while (step + 2 < nsteps) do_step(std::true_type{});
     while (step < nsteps) do_step(std::false_type{});
@@ -494,11 +767,7 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
             const bool padded = p.fold > 1 && (p.fR % p.fold != 0 || p.fS % p.fold != 0);
 #pragma unroll 1
             for (int st = step_begin; st < step_begin + nsteps; ++st) {
-                cb = (int)fastdiv((uint32_t)st, q.div_rs);
-                const int rs = st - cb * (q.R * q.S);
-                r = (int)fastdiv((uint32_t)rs, q.div_s);
-                s = rs - r * q.S;
-                begin_step_loads(0);
+                seek(st);
 #pragma unroll
                 for (int i = 0; i < NL; ++i) {                   // the blocks of h parts: rows b * 32 + lane / 2
                     const int lb = (int)(lq[i] / 1024u), b = isa[i] ? lb : lb - QA;
@@ -583,6 +852,15 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
                 }
             }
         }
+    }
+
+    }
+    };
+    if constexpr (TWO) {
+        if (info.two) contract(std::integral_constant<unsigned, 2>{});
+        else contract(std::integral_constant<unsigned, 3>{});
+    } else {
+        contract(std::integral_constant<unsigned, 3>{});
     }
 
     float *const dst_c = p.dst + (size_t)gcol * p.dst_gs;

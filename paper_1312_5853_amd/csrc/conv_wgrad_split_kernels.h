@@ -27,14 +27,6 @@
 // descriptor's extent and reads as zero.
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-template <int V> using I = std::integral_constant<int, V>;
-template <typename F, int... V>
-__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, V...>) { (f(I<V>{}), ...); }
-template <int N, typename F> __device__ __forceinline__ void static_for(F &&f)
-{
-    static_for_seq(f, std::make_integer_sequence<int, N>{});
-}
-
 struct WgradSplitArgs {
     const float *dy, *x;
     float *part;               // [nsplit][K][R*S*C], columns in (r, s, c) order

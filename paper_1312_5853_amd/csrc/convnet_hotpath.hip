@@ -322,6 +322,19 @@ int run_colgemm_window(int op, const void *act, const void *w, void *out, const 
     return check_launch();
 }
 
+// What magnitudes the operands of two tensors have: the first `len` elements of n samples bs apart, and the nw of w
+int find_ranges(SplitRanges *out, const float *act, int64_t bs, int64_t len, int n, const float *w, int64_t nw, hipStream_t st)
+{
+    static_assert(sizeof(SplitRanges) <= kSplitRangeBytes, "workspace");
+    RangeArgs a;
+    a.t[0] = act; a.bs[0] = bs; a.len[0] = (unsigned)len; a.quads[0] = (unsigned)((len + 3) / 4); a.total[0] = a.quads[0] * (unsigned)n;
+    a.t[1] = w; a.bs[1] = 0; a.len[1] = (unsigned)nw; a.quads[1] = (unsigned)((nw + 3) / 4); a.total[1] = a.quads[1];
+    for (int t = 0; t < 2; ++t) a.div_quads[t] = make_fastdiv(a.quads[t]);
+    a.out = out;
+    hipLaunchKernelGGL(operand_range, dim3(2 * kRangeBlocks), dim3(kRangeThreads), 0, st, a);
+    return check_launch();
+}
+
 // fp32 forward / stride-1 backward-data in three bfloat16 parts: one preparation launch, the contraction, and the sum of
 // the partial outputs where the reduction is split
 int run_colgemm_split(int op, const float *act, const float *w, float *out, const Problem &pb, const Plan &pl, void *ws,
@@ -351,6 +364,12 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     q.div_wp = make_fastdiv((uint32_t)q.Wp); q.div_hp = make_fastdiv((uint32_t)q.Hp);
     q.div_cbt = make_fastdiv((uint32_t)q.CBt); q.div_cbg = make_fastdiv((uint32_t)q.CBg);
     q.div_mpad = make_fastdiv((uint32_t)q.Mpad); q.div_rs = make_fastdiv((uint32_t)RS);
+    q.ranges = nullptr;
+    if (pl.sp_two) {
+        q.ranges = reinterpret_cast<SplitRanges *>(wsb + pl.sp_range_off);
+        const int rc = find_ranges(q.ranges, act, q.src_bs, (int64_t)Cr * GF * q.LH * q.LW, pb.N, w, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, st);
+        if (rc != kStatusOk) return rc;
+    }
     const dim3 prep_grid(q.xb_blocks + grid1d(q.wt_chunks, 256));
     if (fold == 4) hipLaunchKernelGGL(split_prepare<4>, prep_grid, dim3(256), 0, st, q);
     else if (fold == 3) hipLaunchKernelGGL(split_prepare<3>, prep_grid, dim3(256), 0, st, q);
@@ -367,7 +386,8 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     a.src_mul = fwd ? pb.stride : 1; a.fold = fold; a.fR = pb.R; a.fS = pb.S;
     a.out_w = OW; a.out_plane = OH * OW; a.out_step = fwd ? 1 : pb.stride;
     a.RS = RS; a.tap_r = a.out_step * S; a.tap_s = a.out_step;
-    a.Wp = q.Wp; a.plane_bytes = (unsigned)q.Hp * (unsigned)q.Wp * 32u; a.n_bytes = (unsigned)q.CBt * 3u * a.plane_bytes;
+    a.Wp = q.Wp; a.plane_bytes = (unsigned)q.Hp * (unsigned)q.Wp * 32u; a.n_blocks = (unsigned)q.CBt;
+    a.info = q.ranges ? &q.ranges->info : nullptr;
     a.sign = fwd ? 1 : -1;
     a.cblocks = pl.sp_cb;
     a.dst_bs = (int)(fwd ? pb.y_bs : pb.x_bs);
@@ -400,20 +420,26 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     a.epi = ep ? *ep : Epilogue{};
     *ep_applied = a.epi_on;
     a.tiles_per_xcd = ceil_div(a.units * GF, 8);
-    const int grid = 8 * a.tiles_per_xcd, lds = 3 * (pl.sp_bm + pl.sp_bn) * 96;
-    auto go = [&](auto kern) {
+    const int grid = 8 * a.tiles_per_xcd;
+    auto launch = [&](auto kern, int waves, int lds) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(pl.sp_pair ? 256 : 512), lds, st, a);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(waves * 64), lds, st, a);
     };
-    if (pl.sp_pair && pl.sp_bm == 128) go(colgemm_split_kernel<2, 2, 2, 2>);
-    else if (pl.sp_pair && pl.sp_bm == 96) go(colgemm_split_kernel<3, 1, 1, 4>);
-    else if (pl.sp_pair) go(colgemm_split_kernel<2, 1, 1, 4>);
-    else if (pl.sp_bm == 128 && pl.sp_bn == 256) go(colgemm_split_kernel<2, 2, 2, 4>);
-    else if (pl.sp_bm == 128 && pl.sp_bn == 192) go(colgemm_split_kernel<1, 3, 4, 2>);
-    else if (pl.sp_bm == 128) go(colgemm_split_kernel<2, 1, 2, 4>);
-    else if (pl.sp_bm == 96) go(colgemm_split_kernel<3, 1, 1, 8>);
-    else if (pl.sp_bm == 64) go(colgemm_split_kernel<2, 1, 1, 8>);
-    else go(colgemm_split_kernel<1, 2, 1, 8>);
+    auto go = [&](auto tm, auto tn, auto wm, auto wn) {
+        constexpr int TM = decltype(tm)::value, TN = decltype(tn)::value, WM = decltype(wm)::value, WN = decltype(wn)::value;
+        if constexpr (WM * WN == 8)              // (four waves: short reductions only, which stay in three parts)
+            if (pl.sp_two) return launch(colgemm_split_kernel<TM, TN, WM, WN, true>, 8, split_lds<TM, TN, WM, WN, true>());
+        launch(colgemm_split_kernel<TM, TN, WM, WN, false>, WM * WN, split_lds<TM, TN, WM, WN, false>());
+    };
+    if (pl.sp_pair && pl.sp_bm == 128) go(I<2>{}, I<2>{}, I<2>{}, I<2>{});
+    else if (pl.sp_pair && pl.sp_bm == 96) go(I<3>{}, I<1>{}, I<1>{}, I<4>{});
+    else if (pl.sp_pair) go(I<2>{}, I<1>{}, I<1>{}, I<4>{});
+    else if (pl.sp_bm == 128 && pl.sp_bn == 256) go(I<2>{}, I<2>{}, I<2>{}, I<4>{});
+    else if (pl.sp_bm == 128 && pl.sp_bn == 192) go(I<1>{}, I<3>{}, I<4>{}, I<2>{});
+    else if (pl.sp_bm == 128) go(I<2>{}, I<1>{}, I<2>{}, I<4>{});
+    else if (pl.sp_bm == 96) go(I<3>{}, I<1>{}, I<1>{}, I<8>{});
+    else if (pl.sp_bm == 64) go(I<2>{}, I<1>{}, I<1>{}, I<8>{});
+    else go(I<1>{}, I<2>{}, I<1>{}, I<8>{});
     rc = check_launch();
     if (rc != kStatusOk || a.ksplit == 1) return rc;
     const int per_sample = a.M * a.out_plane;

@@ -172,6 +172,9 @@ struct Plan {
     // sp_fold > 1: the stride x stride input positions under an output position are channels (forward of few channels)
     // sp_pair: four-wave work-groups, two to a CU
     bool sp_pair;
+    // sp_two: in two half-precision parts where the operands' range lets it; what was found of it lies at sp_range_off
+    bool sp_two;
+    size_t sp_range_off;
     int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad, sp_fold;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
     // bf16 stride-1 forward / backward-data with the input window of a tile in LDS (colgemm_bf16_window_kernel): 64 or 128 rows,
@@ -229,6 +232,19 @@ inline int least_padding(int rows)
     for (int b : {96, 64, 32})
         if (round_up(rows, b) < round_up(rows, bm)) bm = b;
     return bm;
+}
+
+// Two half-precision parts instead of three bfloat16 ones (conv_split_kernels.h) where the operands let it.  A pass asks for that
+// from kTwoPartSteps steps of 16 products a sum on: the error of both grows with the root of the steps, but two parts start from
+// the 7e-8 that the parts leave out (2-norm against 64 bits, three and two parts: 23 steps 8.1e-8 and 1.1e-7, 54 steps 1.7e-7 and
+// 1.5e-7, 75 steps 2.0e-7 and 1.7e-7, 216 steps 2.8e-7 and 2.6e-7).  And where about a quarter of the contraction's three-part time
+// (kernel, 216 steps of 128 x 256 tiles in one round: 228 -> 165 us) is more than the launch that looks at the operands costs
+// (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 7.7 us).
+constexpr int kTwoPartSteps = 48;
+constexpr size_t kSplitRangeBytes = 4352;      // SplitRanges
+inline bool two_parts_pay(int steps, double kernel_us, double elements)
+{
+    return steps >= kTwoPartSteps && 0.25 * kernel_us > 4.5 + 4.0 * elements / 5e6;
 }
 
 // Width, split count and time estimate (us, returned) of the three-part fp32 kernel on tiles of bm rows for one column of
@@ -722,6 +738,7 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
         const int steps = strided ? ceil_div(cb * RS, pb.stride * pb.stride) : cb * RS_;      // strided: mean over the classes
         int bm, bn, ks;
         double us = pick_split_tile(pl.M, ncols, steps, GF, bm, bn, ks);
+        const double tile_us = us;
         us += 2.0 + ((double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) * 4.0 + (double)pb.N * cb * hp * wp * 96.0) / 3.8e6;
         // a stride beyond the filter: most positions get a zero, and the stores, every stride-th word of a row, decide
         // (192 channels at 89x35x31, 51 filters 1x1 stride 3: 71 us, fp32 44; 224 at 100x29x39, 96 filters stride 2: 88, 120)
@@ -763,6 +780,12 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.part_off = pl.sp_x_off + round_up64(x_bytes, 256);
             pl.part_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * ncols * pl.M * 4 : 0;
             pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
+            const int least = strided ? cb * (pb.R / pb.stride) * (pb.S / pb.stride) / pl.nsplit : pl.chunks_per_split;
+            if (two_parts_pay(least, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
+                pl.sp_two = true;
+                pl.sp_range_off = pl.total;
+                pl.total += kSplitRangeBytes;
+            }
         }
     }
     // fp32 backward-filter through the bf16 matrix instruction, where that is estimated to be faster than the fp32 kernels
@@ -805,7 +828,11 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
 // has less, but as much as those take, gets those.
 inline Plan plan_for_workspace(int op, const Problem &pb, size_t ws_bytes)
 {
-    const Plan pl = make_plan(op, pb);
+    Plan pl = make_plan(op, pb);
+    if (pl.sp_two && ws_bytes < pl.total && ws_bytes >= pl.total - kSplitRangeBytes) {     // a workspace of three parts' size
+        pl.sp_two = false;
+        pl.total -= kSplitRangeBytes;
+    }
     if (!(pl.sp || pl.win || (pl.lin && pl.fused_groups)) || ws_bytes >= pl.total) return pl;
     const Plan fp32 = make_plan(op, pb, false);
     return ws_bytes >= fp32.total ? fp32 : pl;

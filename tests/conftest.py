@@ -32,7 +32,7 @@ def pytest_collection_modifyitems(config, items):
             item.add_marker(skip)
 
 
-Route = collections.namedtuple("Route", "kernels fold nsplit rows columns workspace blocks chunks together")
+Route = collections.namedtuple("Route", "kernels fold nsplit rows columns workspace blocks chunks together two_part")
 
 
 @pytest.fixture(scope="session")
@@ -40,14 +40,15 @@ def route(tmp_path_factory):
     """route(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0, workspace=None, S=None): what the planner does with such a
     pass (and a workspace of so many bytes; filters R x S, or R x R), so that a test written for one set of kernels ("fp32",
     "split", "direct" or "window") can assert that it reaches them.  Of the window kernel also the channel blocks per step and
-    the chunks; together: a grouped bf16 backward-filter in one launch of each kernel."""
+    the chunks; together: a grouped bf16 backward-filter in one launch of each kernel; two_part: a split pass that runs on two
+    half-precision parts where its operands' range lets it."""
     so = str(tmp_path_factory.mktemp("plan") / "plan_query.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "plan_query.cpp")],
                    check=True)
     query = ctypes.CDLL(so).plan_query
 
     def ask(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0, workspace=None, S=None):
-        out = (ctypes.c_longlong * 9)()
+        out = (ctypes.c_longlong * 10)()
         assert query(op, N, C, H, W, K, R, R if S is None else S, stride, pad, groups, dtype,
                      ctypes.c_longlong(-1 if workspace is None else workspace), out) == 0
         return Route(("fp32", "split", "direct", "window")[out[0]], *list(out)[1:])
