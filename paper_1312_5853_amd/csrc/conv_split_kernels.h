@@ -68,16 +68,19 @@ constexpr float kHalfLow = 0x1p12f, kHalfLowInv = 0x1p-12f;
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-// What the kernels of a call read in memory: per block of operand_range the largest magnitude and the smallest that is not zero
-// less one (as integers, so zero is the largest), of both tensors; and what follows from them.
+// What the kernels of a call read in memory: per block of operand_range the largest magnitude, the smallest that is not zero less
+// one (as integers, so zero is the largest), the zeros and the OR of all bits (the sign), of both tensors; and what follows from
+// them.
 struct SplitInfo {
-    int two;                   // two parts
+    int segments;              // two parts, the sums of h h' in so many segments; or 0: three parts
     float unscale;             // of a sum
     float sa, sb;              // of the tensors' operands
 };
 struct SplitRanges {
-    unsigned big[2][kRangeBlocks], small[2][kRangeBlocks];
-    SplitInfo info;            // written by the preparation, or by whoever needs it past the first kernel
+    unsigned big[2][kRangeBlocks], small[2][kRangeBlocks], zeros[2][kRangeBlocks], signs[2][kRangeBlocks];
+    float operands[2];         // in all
+    int none;                  // nothing was looked at
+    SplitInfo info;            // by the preparation
 };
 
 struct RangeArgs {
@@ -86,6 +89,7 @@ struct RangeArgs {
     unsigned len[2], quads[2]; // elements of a sample (four and more), its groups of four
     unsigned total[2];         // groups of four in all
     FastDiv div_quads[2];
+    int signed_only;           // tensor 0 without a negative operand among a sample: three parts, and nothing is looked at
     SplitRanges *out;
 };
 
@@ -101,7 +105,21 @@ __device__ __forceinline__ unsigned wave_max(unsigned v)
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 __device__ __forceinline__ unsigned wave_min(unsigned v) { return ~wave_max(~v); }
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned dpp_or_zero(unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ unsigned wave_sum(unsigned v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v); v += dpp_or_zero<0x112, 0xf>(v); v += dpp_or_zero<0x114, 0xf>(v); v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v); v += dpp_or_zero<0x143, 0xc>(v);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
 
+// A forward pass keeps three parts for an input of one sign (the output of a ReLU or of pooling): for such inputs the error of
+// two is the smaller one by 5 to 25 % only, and a pooling window behind the layer, or a ReLU, that decides between values closer
+// than a rounding sends a gradient elsewhere, so that another rounding of a network's forward pass, however small its errors, moves
+// its gradients by 1e-3 either way.
 // Bound: HBM, four bytes per operand; every operand is read once here and once by what follows, from the 256 MB cache where the
 // tensors fit.  A group of four that would reach past a sample's end is moved back: operands seen twice change nothing.
 __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p)
@@ -112,7 +130,17 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
     const int64_t bs = p.bs[which];
     const unsigned len = p.len[which], quads = p.quads[which], total = p.total[which];
     const FastDiv div = p.div_quads[which];
-    unsigned big = 0, small = 0xffffffffu;
+    if (p.signed_only) {       // every block looks at the same 2048 operands: a group of four in each 512th of the tensor
+        const unsigned q = (unsigned)((uint64_t)threadIdx.x * p.total[0] / kRangeThreads);
+        const unsigned n = fastdiv(q, p.div_quads[0]);
+        const quad_t v = *reinterpret_cast<const quad_t *>(p.t[0] + (int64_t)n * p.bs[0] + min((q - n * p.quads[0]) * 4, p.len[0] - 4));
+        if (!__syncthreads_or((int)(v[0] | v[1] | v[2] | v[3]) < 0)) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 1;
+            return;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 0;
+    unsigned big = 0, small = 0xffffffffu, zeros = 0, signs = 0;
     constexpr int UN = 4;
     constexpr unsigned step = kRangeBlocks * kRangeThreads;
     for (unsigned i = b * kRangeThreads + threadIdx.x; i < total; i += UN * step) {
@@ -124,44 +152,77 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
             v[u] = *reinterpret_cast<const quad_t *>(t + (int64_t)n * bs + min((q - n * quads) * 4, len - 4));
         }
 #pragma unroll
-        for (int u = 0; u < UN; ++u)
+        for (int u = 0; u < UN; ++u) {
+            unsigned none = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const unsigned m = v[u][k] & 0x7fffffffu;
+                signs |= v[u][k];
                 big = max(big, m);
                 small = min(small, m - 1u);
+                none += m == 0;
             }
+            zeros += i + u * step < total ? none : 0;
+        }
     }
-    __shared__ unsigned words[2][kRangeThreads / 64];
+    __shared__ unsigned words[4][kRangeThreads / 64];
     big = wave_max(big);
     small = wave_min(small);
-    if ((threadIdx.x & 63) == 0) { words[0][threadIdx.x >> 6] = big; words[1][threadIdx.x >> 6] = small; }
+    zeros = wave_sum(zeros);
+    signs = __ballot(signs >> 31) ? 1 : 0;
+    if ((threadIdx.x & 63) == 0) {
+        const int w = threadIdx.x >> 6;
+        words[0][w] = big; words[1][w] = small; words[2][w] = zeros; words[3][w] = signs;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int w = 1; w < kRangeThreads / 64; ++w) { big = max(big, words[0][w]); small = min(small, words[1][w]); }
+        for (int w = 1; w < kRangeThreads / 64; ++w) {
+            big = max(big, words[0][w]);
+            small = min(small, words[1][w]);
+            zeros += words[2][w];
+            signs |= words[3][w];
+        }
         p.out->big[which][b] = big;
         p.out->small[which][b] = small;
+        p.out->zeros[which][b] = zeros;
+        p.out->signs[which][b] = signs;
+        if (b == 0) p.out->operands[which] = 4.f * (float)total;
     }
 }
 
-// from the blocks' findings, by a wavefront whose lanes are all active
-__device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane)
+// From the blocks' findings, by a wavefront whose lanes are all active, for sums of `steps` steps of 16 products.
+// Segments: a product of two halves has 22 significant bits, so every instruction rounds the sum of the leading products; those of
+// bfloat16 have 16, and leave many of their sums exact, the more the more operands are zero.  In 1e-14, squares of 2-norm errors
+// against 64 bits (fitted to 170 layers, with the output of a ReLU or of pooling for input, with gradients that such layers leave
+// zeros in): three parts 0.061 steps k - 0.2, k the share of products without a zero to the power of 3/4 and at most 0.7 for
+// a tensor of one sign; two parts 0.058 (steps / segments + segments) + 0.95.  As few segments as make the second at most 0.92 of
+// the first, each of at least 16 steps (the end of a segment costs as much as two to four steps), or three parts.
+// dense: the share of products that no padding makes zero.
+__device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane, int steps, float dense)
 {
-    SplitInfo o;
-    o.two = 1;
+    SplitInfo o = {0, 0.f, 0.f, 0.f};
+    if (uniform(r->none)) return o;
+    bool fits = true, one_sign = false;
     int e[2];
-    float scale[2];
+    float scale[2], kept = dense;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const u32x4 b = reinterpret_cast<const u32x4 *>(r->big[t])[lane], s = reinterpret_cast<const u32x4 *>(r->small[t])[lane];
+        const u32x4 z = reinterpret_cast<const u32x4 *>(r->zeros[t])[lane], n = reinterpret_cast<const u32x4 *>(r->signs[t])[lane];
         const unsigned big = wave_max(max(max(b[0], b[1]), max(b[2], b[3])));
         const unsigned small = wave_min(min(min(s[0], s[1]), min(s[2], s[3])));
+        kept *= 1.f - fminf((float)wave_sum(z[0] + z[1] + z[2] + z[3]) / r->operands[t], 1.f);
+        one_sign = one_sign || !__ballot((n[0] | n[1] | n[2] | n[3]) != 0);
         e[t] = big == 0 ? 0 : (int)(big >> 23) - 127;
         const int es = big == 0 ? 0 : (int)((small + 1u) >> 23) - 127;
-        if (e[t] < -45 || e[t] > 40 || es < e[t] - 31) o.two = 0;
+        fits = fits && e[t] >= -45 && e[t] <= 40 && es >= e[t] - 31;
         scale[t] = __uint_as_float((unsigned)(127 + 14 - e[t]) << 23);
     }
+    kept = fminf(sqrtf(kept * sqrtf(kept)), one_sign ? 0.7f : 1.f);
+    const float n = (float)steps, three = 0.92f * (0.061f * n * kept - 0.2f);
+    for (int g = 8; g >= 2; g /= 2)
+        if (fits && steps >= 16 * g && 0.058f * (n / (float)g + (float)g) + 0.95f <= three) o.segments = g;
     o.sa = scale[0];
     o.sb = scale[1];
     o.unscale = __uint_as_float((unsigned)(127 - 28 + e[0] + e[1]) << 23);
@@ -169,20 +230,21 @@ __device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane)
 }
 static_assert(kRangeBlocks == 256, "four blocks to a lane");
 
-// two scaled operands -> their parts, two to a word
-__device__ __forceinline__ void split_pair_two(float a, float b, unsigned &h, unsigned &l)
+// two operands -> the parts of s times them, two to a word; s4096 = 4096 s.  Seven instructions, of which the last two, remainder
+// and conversion in one, issue at half rate.
+__device__ __forceinline__ void split_pair_two(float a, float b, float s, float s4096, unsigned &h, unsigned &l)
 {
-    const f16x2 hh = __builtin_convertvector((f32x2){a, b}, f16x2);
-    h = __builtin_bit_cast(unsigned, hh);
-    l = __builtin_bit_cast(unsigned, __builtin_convertvector(
-            (f32x2){(a - (float)hh[0]) * kHalfLow, (b - (float)hh[1]) * kHalfLow}, f16x2));
+    const float a4 = a * s4096, b4 = b * s4096;
+    h = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a * s, b * s}, f16x2));
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(l) : "v"(h), "s"(-kHalfLow), "v"(a4));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(l) : "v"(h), "s"(-kHalfLow), "v"(b4));
 }
 __device__ __forceinline__ void split_eight_two(const float (&v)[8], float s, u32x4 (&o)[3])
 {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         unsigned h, l;
-        split_pair_two(v[2 * t] * s, v[2 * t + 1] * s, h, l);
+        split_pair_two(v[2 * t], v[2 * t + 1], s, s * kHalfLow, h, l);
         o[0][t] = h; o[1][t] = l;
     }
 }
@@ -261,6 +323,51 @@ __device__ __forceinline__ bool split_finish(f32x16 (&acc)[TM][TN], const f32x16
     return split_group_or<NW>(words, wave, lane, __ballot(open) ? 1 : 0) != 0;
 }
 
+// The end of a segment: the leading 8 bits of the sum of the leading products are put aside, in LDS, and what follows adds to a
+// small number again.  `aside`: this thread's first 16 bytes of TM * TN * 2 rows of NW * 64, zero at first.
+template <int NW, int TM, int TN>
+__device__ __forceinline__ void split_clear_aside(char *aside)
+{
+#pragma unroll
+    for (int t = 0; t < TM * TN * 2; ++t) *reinterpret_cast<u32x4 *>(aside + t * (NW * 64 * 16)) = (u32x4){0, 0, 0, 0};
+}
+template <int NW, int TM, int TN>
+__device__ __forceinline__ void split_put_aside(f32x16 (&acc)[TM][TN], char *aside)
+{
+#pragma unroll
+    for (int t = 0; t < TM * TN * 2; ++t) {
+        f32x16 &sum = acc[t / 2 / TN][t / 2 % TN];
+        u32x4 *const at = reinterpret_cast<u32x4 *>(aside + t * (NW * 64 * 16));
+        u32x4 o = *at;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int v = t % 2 * 8 + 2 * k;
+            const float a = sum[v] + __uint_as_float(o[k] << 16), b = sum[v + 1] + __uint_as_float(o[k] & 0xffff0000u);
+            o[k] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
+            sum[v] = a - __uint_as_float(o[k] << 16);
+            sum[v + 1] = b - __uint_as_float(o[k] & 0xffff0000u);
+        }
+        *at = o;
+    }
+}
+// acc becomes the sums
+template <int NW, int TM, int TN>
+__device__ __forceinline__ void split_take_back(f32x16 (&acc)[TM][TN], const f32x16 (&low)[TM][TN], const char *aside, float unscale)
+{
+#pragma unroll
+    for (int t = 0; t < TM * TN * 2; ++t) {
+        f32x16 &sum = acc[t / 2 / TN][t / 2 % TN];
+        const f32x16 &rest = low[t / 2 / TN][t / 2 % TN];
+        const u32x4 o = *reinterpret_cast<const u32x4 *>(aside + t * (NW * 64 * 16));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int v = t % 2 * 8 + 2 * k;
+            sum[v] = (__uint_as_float(o[k] << 16) + fmaf(rest[v], kHalfLowInv, sum[v])) * unscale;
+            sum[v + 1] = (__uint_as_float(o[k] & 0xffff0000u) + fmaf(rest[v + 1], kHalfLowInv, sum[v + 1])) * unscale;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Preparation, one launch:
 //   blocks [0, xb_blocks): xs[n][channel block of 16][part][Hp][Wp][16] from NCHW fp32 src (samples src_bs elements
@@ -292,7 +399,9 @@ struct SplitPrepArgs {
     int64_t w_gs;              // floats between the columns' filters
     int Cin, R, S, rows, cols;               // fold > 1: input channels, the filter's and the input's extents
     int pairs;                 // fold > 1: two columns b, b + 1 are inside or outside together and 8-byte aligned
-    SplitRanges *ranges;       // or null: three parts
+    SplitRanges *ranges;       // TWO
+    int steps;                 // of a sum
+    float dense;               // see split_info
     FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs, div_sv;
 };
 
@@ -305,22 +414,41 @@ __device__ __forceinline__ float load_or_zero(const float *base, int64_t i, bool
     return ok ? e : 0.f;
 }
 
-// FOLD: the stride, or 1
-template <int FOLD>
+// FOLD: the stride, or 1.  TWO: in two parts where the operands' range lets it; one wavefront of a block puts together what was
+// found of it while the operands are on their way (each wavefront for itself: 20 -> 24 us and 40 -> 49; a launch of its own: 5 us).
+template <int FOLD, bool TWO>
 __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {
     float v[8];
     u32x4 o[3];
-    SplitInfo info = {0, 0.f, 0.f, 0.f};
-    if (p.ranges) {
-        info = split_info(p.ranges, threadIdx.x & 63);
-        if (blockIdx.x == 0 && threadIdx.x == 0) p.ranges->info = info;
-    }
-    const unsigned parts = info.two ? 2 : 3;
+    auto split = [&](u32x4 *dst, size_t part, size_t unit, int t, bool ok) {    // part: pieces from one part to the next; dst: of unit 0
+        SplitInfo info = {0, 0.f, 0.f, 0.f};
+        if constexpr (TWO) {
+            __shared__ SplitInfo found;
+            if (threadIdx.x < 64) {
+                info = split_info(p.ranges, threadIdx.x, p.steps, p.dense);
+                if (threadIdx.x == 0) found = info;
+                if (blockIdx.x == 0 && threadIdx.x == 0) p.ranges->info = info;
+            }
+            __syncthreads();
+            info.segments = uniform(found.segments);
+            info.sa = __int_as_float(uniform(__float_as_int(t ? found.sb : found.sa)));
+        }
+        if (!ok) return;
+        if (TWO && info.segments) {
+            split_eight_two(v, info.sa, o);
+            dst += unit * 2 * part;
+        } else {
+            split_eight(v, o);
+            dst += unit * 3 * part;
+            dst[2 * part] = o[2];
+        }
+        dst[0] = o[0];
+        dst[part] = o[1];
+    };
     if ((int)blockIdx.x < p.xb_blocks) {
         const unsigned e = blockIdx.x * 256u + threadIdx.x;
-        const unsigned i = e >> 1, half = e & 1;
-        if (i >= p.positions) return;
+        const unsigned i = min(e >> 1, p.positions - 1), half = e & 1;
         const unsigned t1 = fastdiv(i, p.div_wp);                    // (n*CBt + blk)*Hp + hp
         const int wp = (int)(i - t1 * (unsigned)p.Wp);
         const unsigned t2 = fastdiv(t1, p.div_hp);                    // n*CBt + blk
@@ -352,16 +480,11 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = load_or_zero(x, e + (int64_t)k * LHW, in && c0 + k < p.Cg);
         }
-        if (info.two) split_eight_two(v, info.sa, o); else split_eight(v, o);
         const unsigned plane = (unsigned)p.Hp * (unsigned)p.Wp;
-        u32x4 *dst = p.xs + ((size_t)t2 * parts * plane + (i - t2 * plane)) * 2 + half;
-        dst[0] = o[0];
-        dst[(size_t)plane * 2] = o[1];
-        if (!info.two) dst[(size_t)2 * plane * 2] = o[2];
+        split(p.xs + (size_t)(i - t2 * plane) * 2 + half, (size_t)plane * 2, t2, 0, (e >> 1) < p.positions);
         return;
     }
-    const unsigned e = (blockIdx.x - (unsigned)p.xb_blocks) * 256u + threadIdx.x;
-    if (e >= p.wt_chunks) return;
+    const unsigned all = (blockIdx.x - (unsigned)p.xb_blocks) * 256u + threadIdx.x, e = min(all, p.wt_chunks - 1);
     const int half = (int)(e & 1);
     const unsigned t1 = e >> 1;                                        // ((g*CBg + cb)*RS + rs)*Mpad + m
     const unsigned t2 = fastdiv(t1, p.div_mpad);
@@ -382,11 +505,7 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
             v[k] = load_or_zero(w, (p.transposed ? (int64_t)ch * p.C + m : (int64_t)m * p.C + ch) * p.RS + rs, m < p.M && ch < p.Cg);
         }
     }
-    if (info.two) split_eight_two(v, info.sb, o); else split_eight(v, o);
-    u32x4 *dst = p.wt + ((size_t)t2 * parts * p.Mpad + m) * 2 + (half ^ ((m >> 3) & 1));
-    dst[0] = o[0];
-    dst[(size_t)p.Mpad * 2] = o[1];
-    if (!info.two) dst[(size_t)2 * p.Mpad * 2] = o[2];
+    split(p.wt + (size_t)m * 2 + (half ^ ((m >> 3) & 1)), (size_t)p.Mpad * 2, t2, 1, all < p.wt_chunks);
 }
 
 // ---------------------------------------------------------------------------
@@ -495,7 +614,7 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
 
     SplitInfo info = {0, 0.f, 0.f, 0.f};
     if constexpr (TWO) {
-        info.two = uniform(p.info->two);
+        info.segments = uniform(p.info->segments);
         info.unscale = __int_as_float(uniform(__float_as_int(p.info->unscale)));
     }
     const int tid = threadIdx.x, lane = tid & 63;
@@ -658,46 +777,21 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
             ++step;
             bufo = bufo1;
         };
-        // A product of two halves has 22 significant bits, so every instruction rounds the sum of the leading products (those
-        // of bfloat16 have 16, and leave most of their sums exact).  Half way the leading 8 bits of that sum are put aside,
-        // in LDS: what follows adds to a small number again, and the roundings of the whole weigh 0.7 times as much.
         char *const aside = const_cast<char *>(lds) + 3 * BUF + tid * 16;
-        auto put_aside = [&]() {
-#pragma unroll
-            for (int t = 0; t < MPG * 2; ++t) {
-                f32x16 &sum = acc[t / 2 / TN][t / 2 % TN];
-                u32x4 o;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int v = t % 2 * 8 + 2 * k;
-                    o[k] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){sum[v], sum[v + 1]}, bf16x2));
-                    sum[v] -= __uint_as_float(o[k] << 16);
-                    sum[v + 1] -= __uint_as_float(o[k] & 0xffff0000u);
-                }
-                *reinterpret_cast<u32x4 *>(aside + t * (NW * 64 * 16)) = o;
-            }
-        };
-        const int mid = nsteps / 2 & ~1;
+        split_clear_aside<NW, TM, TN>(aside);
+        const int segment = nsteps / info.segments;
+        int segment_end = segment;
         while (step + 1 < nsteps) {
-            if (step == mid) put_aside();
+            if (step >= segment_end) {
+                split_put_aside<NW>(acc, aside);
+                segment_end += segment;
+            }
             do_step(I<0>{});
             do_step(I<1>{});
         }
         if (step < nsteps) do_step(I<0>{});
-        if (nsteps < 2) put_aside();
         wait_vmcnt<0>();
-#pragma unroll
-        for (int t = 0; t < MPG * 2; ++t) {
-            f32x16 &sum = acc[t / 2 / TN][t / 2 % TN];
-            const f32x16 &rest = low[t / 2 / TN][t / 2 % TN];
-            const u32x4 o = *reinterpret_cast<const u32x4 *>(aside + t * (NW * 64 * 16));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int v = t % 2 * 8 + 2 * k;
-                sum[v] = (__uint_as_float(o[k] << 16) + fmaf(rest[v], kHalfLowInv, sum[v])) * info.unscale;
-                sum[v + 1] = (__uint_as_float(o[k] & 0xffff0000u) + fmaf(rest[v + 1], kHalfLowInv, sum[v + 1])) * info.unscale;
-            }
-        }
+        split_take_back<NW>(acc, low, aside, info.unscale);
     } else {
     constexpr int SLOTS = 4 * MPG;                              // matrix instructions before the barrier
     constexpr int SPACING = SLOTS / NL > 0 ? SLOTS / NL : 1;
@@ -857,7 +951,7 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
     }
     };
     if constexpr (TWO) {
-        if (info.two) contract(std::integral_constant<unsigned, 2>{});
+        if (info.segments) contract(std::integral_constant<unsigned, 2>{});
         else contract(std::integral_constant<unsigned, 3>{});
     } else {
         contract(std::integral_constant<unsigned, 3>{});

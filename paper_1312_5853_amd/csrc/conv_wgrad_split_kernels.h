@@ -38,22 +38,29 @@ struct WgradSplitArgs {
     int mtiles, ntiles, nunits, units_per_xcd, nsplit;
     unsigned dy_bytes, x_bytes;       // bytes from a column's first element to its last
     int64_t dy_gs, x_gs, part_gs;     // elements between the columns of a grouped layer
+    const SplitRanges *ranges;        // of dy and x, kernels with TWO
+    float dense;
     FastDiv div_plane, div_q, div_cb, div_s;
 };
 
 // TAIL: K or C is no multiple of 16, so that a piece may reach past the end of its tensor: the channel's offset is then
 // part of the checked offset instead of the scalar one.
-template <int TM, int TN, int WM, int WN, bool TAIL>
+// TWO: two half-precision parts where the operands' range lets it.
+template <int TM, int TN, int WM, int WN, bool TWO> constexpr int wgrad_split_lds()
+{
+    const int rows = (TM * WM + TN * WN) * 32, three = 2 * rows * 192, two = 2 * rows * 128 + TM * TN * WM * WN * 64 * 32;
+    return TWO && two > three ? two : three;
+}
+template <int TM, int TN, int WM, int WN, bool TAIL, bool TWO>
 __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const WgradSplitArgs p)
 {
     constexpr int NW = WM * WN;
     constexpr int BM = TM * WM * 32, BN = TN * WN * 32;
     constexpr int QA = BM / 16, QB = BN / 16;                  // staged blocks per step
     constexpr int NT = (QA + QB + NW - 1) / NW;                // ... per wave
-    constexpr int BUF = (BM + BN) * 192;
     constexpr int MPG = TM * TN;                               // matrix instructions per product
     static_assert(NW == 8, "eight waves");
-    static_assert(2 * BUF <= 160 * 1024, "two LDS buffers");
+    static_assert(wgrad_split_lds<TM, TN, WM, WN, TWO>() <= 160 * 1024, "LDS buffers");
     constexpr unsigned kOutside = 0x80000000u;
 
     extern __shared__ __attribute__((aligned(16))) float lds_fast[];
@@ -72,6 +79,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
     const int m0 = mt * BM, n0 = nt * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
+    SplitInfo info = {0, 0.f, 0.f, 0.f};
+    if constexpr (TWO) info = split_info(p.ranges, lane, 2 * p.steps_per_split, p.dense);
     const int wave = uniform(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int PQ = p.P * p.Q;
@@ -82,6 +91,29 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
 
     const float *const dyg = p.dy + (size_t)gcol * p.dy_gs;
     const float *const xg = p.x + (size_t)gcol * p.x_gs;
+
+    f32x16 acc[TM][TN], low[TM][TN];           // sums of h h'; of the five smaller products
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[i][jn][v] = 0.f; low[i][jn][v] = 0.f; }
+
+    const int l32 = lane & 31, half = lane >> 5;
+
+    // column of this lane in block column jn of the wave: (r, s) tap and channel
+    auto column = [&](int jn, int &rs, int &ch) {
+        const int blk = n0 / 16 + (wn * TN + jn) * 2 + (l32 >> 4);
+        rs = (int)fastdiv((uint32_t)blk, p.div_cb);
+        ch = (blk - rs * p.CB) * 16 + (l32 & 15);
+        return blk < p.nblocks && ch < p.C;
+    };
+
+    auto contract = [&](auto parts_c) {
+    constexpr int PARTS = decltype(parts_c)::value;
+    constexpr int BUF = (BM + BN) * PARTS * 64;
+
     const auto rsrc_dy = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(dyg), 0, (int)p.dy_bytes, 0x00020000);
     const auto rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(xg), 0, (int)p.x_bytes, 0x00020000);
     auto rsrc_of = [&](bool a) {           // by value: a conditional of the two names would keep both in memory
@@ -112,7 +144,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
             tap_r[u] = (int)fastdiv((uint32_t)rs, p.div_s);
             tap_s[u] = rs - tap_r[u] * p.S;
             row_off[u] = (unsigned)(cb * 16 + oct * 8) * (unsigned)(p.H * p.W * 4);
-            st_off[u] = (unsigned)(BM * 192 + b * 1024 + (pos ^ ((b & 1) * 4)) * 32 + (oct ^ ((pos >> 2) & 1)) * 16);
+            st_off[u] = (unsigned)(BM * (PARTS * 64) + b * 1024 + (pos ^ ((b & 1) * 4)) * 32 + (oct ^ ((pos >> 2) & 1)) * 16);
         }
     }
 
@@ -151,19 +183,25 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
         const unsigned v = TAIL ? voff[u] + (unsigned)(k * plane) : voff[u];
         st[u][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, TAIL ? 0 : k * plane, 0));
     };
-    u32x4 sp[3];
+    u32x4 sp[PARTS];
     auto split_two = [&](int u, int t) {
         if (none[u]) return;
         unsigned h, m, l;
-        split_pair(st[u][2 * t], st[u][2 * t + 1], h, m, l);
-        sp[0][t] = h; sp[1][t] = m; sp[2][t] = l;
+        if constexpr (PARTS == 2) {
+            const float s = isa[u] ? info.sa : info.sb;
+            split_pair_two(st[u][2 * t], st[u][2 * t + 1], s, s * kHalfLow, h, l);
+            sp[0][t] = h; sp[1][t] = l;
+        } else {
+            split_pair(st[u][2 * t], st[u][2 * t + 1], h, m, l);
+            sp[0][t] = h; sp[1][t] = m; sp[2][t] = l;
+        }
     };
     auto store_piece = [&](int u, int buf) {
         if (none[u]) return;
         const int part_bytes = (isa[u] ? QA : QB) * 1024;
         char *const d = lds + buf * BUF + st_off[u];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x4 *>(d + c * part_bytes) = sp[c];
+        for (int c = 0; c < PARTS; ++c) *reinterpret_cast<u32x4 *>(d + c * part_bytes) = sp[c];
     };
     auto load_step = [&]() {
         next_position();
@@ -175,40 +213,21 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
         }
     };
 
-    f32x16 acc[TM][TN], low[TM][TN];           // sums of h h'; of the five smaller products
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[i][jn][v] = 0.f; low[i][jn][v] = 0.f; }
-
     // Fragment reads: the 16 lanes of group g = lane / 16 read four positions of block g % 2; lanes 0..31 hold positions
     // 0..7 of a half step, lanes 32..63 positions 12..15 and 8..11 (the same order for both operands).
-    const int l32 = lane & 31, half = lane >> 5;
     const int sub = (lane >> 4) & 1;
     const unsigned frag0 = (unsigned)(sub * 1024 + ((((half ? 12 : 0)) ^ (sub * 4)) + ((lane & 15) >> 2)) * 32 +
                                       ((lane & 3) ^ (half * 2)) * 8);
     typedef __attribute__((address_space(3))) char *lds_bytes;
     typedef __attribute__((address_space(3))) s16x4 *lds_quad;
     const lds_bytes frag_lo = (lds_bytes)lds + frag0, frag_hi = (lds_bytes)lds + (frag0 ^ 144u);   // 4 positions on
-    const int a_frag = wm * TM * 2 * 1024, b_frag = BM * 192 + wn * TN * 2 * 1024;
+    const int a_frag = wm * TM * 2 * 1024, b_frag = BM * (PARTS * 64) + wn * TN * 2 * 1024;
     auto read_tr = [&](int off) {
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad)(frag_lo + off));
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad)(frag_hi + off));
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
     typedef decltype(__builtin_shufflevector(s16x4{}, s16x4{}, 0, 1, 2, 3, 4, 5, 6, 7)) frag_t;
-    frag_t fa[3][TM], fb[3][TN];
-    auto read_a = [&](int buf, int t, int c) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[c][i] = read_tr(a_frag + buf * BUF + t * 512 + (c * QA + i * 2) * 1024);
-    };
-    auto read_b = [&](int buf, int t, int c) {
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn) fb[c][jn] = read_tr(b_frag + buf * BUF + t * 512 + (c * QB + jn * 2) * 1024);
-    };
-
     load_step();
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
@@ -219,6 +238,83 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
     load_step();
     next_position();
     __syncthreads();
+    if constexpr (PARTS == 2) {
+        // A half step: h h' and h l', the barrier at the end of a step, the next half's h and h' into the other set, l h'
+        frag_t ha[2][TM], hb[2][TN], la[TM], lb[TN];
+        auto read = [&](int buf, int t, int c, frag_t (&a)[TM], frag_t (&b)[TN]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) a[i] = read_tr(a_frag + buf * BUF + t * 512 + (c * QA + i * 2) * 1024);
+#pragma unroll
+            for (int jn = 0; jn < TN; ++jn) b[jn] = read_tr(b_frag + buf * BUF + t * 512 + (c * QB + jn * 2) * 1024);
+        };
+        read(0, 0, 0, ha[0], hb[0]);
+        char *const aside = lds + 2 * BUF + tid * 16;
+        split_clear_aside<NW, TM, TN>(aside);
+        const int segment = nsteps / info.segments;
+        int segment_end = segment;
+        constexpr int SLOTS = 5 * MPG, WORK = NT * 13, PER = (WORK + SLOTS - 1) / SLOTS;
+        for (int step = 0; step < nsteps; ++step) {
+            const int buf = step & 1;
+            if (step >= segment_end) {
+                split_put_aside<NW>(acc, aside);
+                segment_end += segment;
+            }
+            auto work = [&](auto i_c) {
+                // a piece's thirteen: S0 L0 L1 S1 L2 L3 S2 L4 L5 S3 store L6 L7 (a load goes where its registers have been split)
+                constexpr int u = decltype(i_c)::value / 13, s = decltype(i_c)::value % 13;
+                if constexpr (u < NT) {
+                    if constexpr (s == 0) piece_offset(u);
+                    if constexpr (s % 3 == 0 && s < 12) split_two(u, s / 3);
+                    else if constexpr (s == 10) store_piece(u, buf ^ 1);
+                    else load_one(u, s < 10 ? s / 3 * 2 + s % 3 - 1 : s - 5);
+                }
+            };
+            auto product = [&](const frag_t (&xa)[TM], const frag_t (&xb)[TN], auto g_c) {
+                constexpr int g = decltype(g_c)::value;
+                static_for<MPG>([&](auto q_c) {
+                    constexpr int i = decltype(q_c)::value / TN, jn = decltype(q_c)::value % TN, m = g * MPG + decltype(q_c)::value;
+                    f32x16 &sum = g % 3 == 0 ? acc[i][jn] : low[i][jn];
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, xa[i]), __builtin_bit_cast(f16x8, xb[jn]),
+                                                                 sum, 0, 0, 0);
+                    if constexpr (m < SLOTS && m * PER < WORK) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        static_for<PER>([&](auto w_c) { work(I<m * PER + decltype(w_c)::value>{}); });
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto half_step = [&](auto t_c) {
+                constexpr int t = decltype(t_c)::value;
+                read(buf, t, 1, la, lb);
+                __builtin_amdgcn_sched_barrier(0);
+                product(ha[t], hb[t], I<t * 3>{});
+                product(ha[t], lb, I<t * 3 + 1>{});
+                if constexpr (t == 1) {
+                    asm volatile("s_waitcnt lgkmcnt(0)");
+                    __syncthreads();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                read(t == 1 ? buf ^ 1 : buf, t ^ 1, 0, ha[t ^ 1], hb[t ^ 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                product(la, hb[t], I<t * 3 + 2>{});
+                if constexpr (t == 1) next_position();
+            };
+            half_step(I<0>{});
+            half_step(I<1>{});
+        }
+        split_take_back<NW>(acc, low, aside, info.unscale);
+    } else {
+    frag_t fa[3][TM], fb[3][TN];
+    auto read_a = [&](int buf, int t, int c) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[c][i] = read_tr(a_frag + buf * BUF + t * 512 + (c * QA + i * 2) * 1024);
+    };
+    auto read_b = [&](int buf, int t, int c) {
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) fb[c][jn] = read_tr(b_frag + buf * BUF + t * 512 + (c * QB + jn * 2) * 1024);
+    };
+
     read_a(0, 0, 0);
     read_b(0, 0, 0);
 
@@ -282,14 +378,6 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
         half_step(I<0>{});
         half_step(I<1>{});
     }
-
-    // column of this lane in block column jn of the wave: (r, s) tap and channel
-    auto column = [&](int jn, int &rs, int &ch) {
-        const int blk = n0 / 16 + (wn * TN + jn) * 2 + (l32 >> 4);
-        rs = (int)fastdiv((uint32_t)blk, p.div_cb);
-        ch = (blk - rs * p.CB) * 16 + (l32 & 15);
-        return blk < p.nblocks && ch < p.C;
-    };
 
     // sums that call for fp32 arithmetic: the whole work-group computes its tile again
     {
@@ -374,6 +462,15 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
                             acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][i], b[t][jn], acc[i][jn], 0, 0, 0);
             }
         }
+    }
+
+    }
+    };
+    if constexpr (TWO) {
+        if (info.segments) contract(I<2>{});
+        else contract(I<3>{});
+    } else {
+        contract(I<3>{});
     }
 
     float *const out = p.part + (size_t)gcol * p.part_gs + (size_t)split * p.K * p.ncols;

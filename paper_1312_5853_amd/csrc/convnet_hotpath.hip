@@ -322,14 +322,24 @@ int run_colgemm_window(int op, const void *act, const void *w, void *out, const 
     return check_launch();
 }
 
-// What magnitudes the operands of two tensors have: the first `len` elements of n samples bs apart, and the nw of w
-int find_ranges(SplitRanges *out, const float *act, int64_t bs, int64_t len, int n, const float *w, int64_t nw, hipStream_t st)
+// What magnitudes the operands of two tensors have: of each the first `len` elements of n samples bs apart
+struct RangeTensor {
+    const float *t;
+    int64_t bs, len;
+    int n;
+};
+int find_ranges(SplitRanges *out, const RangeTensor &t0, const RangeTensor &t1, bool signed_only, hipStream_t st)
 {
     static_assert(sizeof(SplitRanges) <= kSplitRangeBytes, "workspace");
     RangeArgs a;
-    a.t[0] = act; a.bs[0] = bs; a.len[0] = (unsigned)len; a.quads[0] = (unsigned)((len + 3) / 4); a.total[0] = a.quads[0] * (unsigned)n;
-    a.t[1] = w; a.bs[1] = 0; a.len[1] = (unsigned)nw; a.quads[1] = (unsigned)((nw + 3) / 4); a.total[1] = a.quads[1];
-    for (int t = 0; t < 2; ++t) a.div_quads[t] = make_fastdiv(a.quads[t]);
+    int i = 0;
+    for (const RangeTensor *t : {&t0, &t1}) {
+        a.t[i] = t->t; a.bs[i] = t->bs; a.len[i] = (unsigned)t->len; a.quads[i] = (unsigned)((t->len + 3) / 4);
+        a.total[i] = a.quads[i] * (unsigned)t->n;
+        a.div_quads[i] = make_fastdiv(a.quads[i]);
+        ++i;
+    }
+    a.signed_only = signed_only;
     a.out = out;
     hipLaunchKernelGGL(operand_range, dim3(2 * kRangeBlocks), dim3(kRangeThreads), 0, st, a);
     return check_launch();
@@ -365,16 +375,23 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     q.div_cbt = make_fastdiv((uint32_t)q.CBt); q.div_cbg = make_fastdiv((uint32_t)q.CBg);
     q.div_mpad = make_fastdiv((uint32_t)q.Mpad); q.div_rs = make_fastdiv((uint32_t)RS);
     q.ranges = nullptr;
+    q.steps = pl.sp_two_steps; q.dense = pl.sp_dense;
     if (pl.sp_two) {
         q.ranges = reinterpret_cast<SplitRanges *>(wsb + pl.sp_range_off);
-        const int rc = find_ranges(q.ranges, act, q.src_bs, (int64_t)Cr * GF * q.LH * q.LW, pb.N, w, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, st);
+        const int rc = find_ranges(q.ranges, {act, q.src_bs, (int64_t)Cr * GF * q.LH * q.LW, pb.N},
+                                   {w, 0, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, 1}, fwd, st);
         if (rc != kStatusOk) return rc;
     }
     const dim3 prep_grid(q.xb_blocks + grid1d(q.wt_chunks, 256));
-    if (fold == 4) hipLaunchKernelGGL(split_prepare<4>, prep_grid, dim3(256), 0, st, q);
-    else if (fold == 3) hipLaunchKernelGGL(split_prepare<3>, prep_grid, dim3(256), 0, st, q);
-    else if (fold == 2) hipLaunchKernelGGL(split_prepare<2>, prep_grid, dim3(256), 0, st, q);
-    else hipLaunchKernelGGL(split_prepare<1>, prep_grid, dim3(256), 0, st, q);
+    auto prepare = [&](auto fold_c) {
+        constexpr int F = decltype(fold_c)::value;
+        if (pl.sp_two) hipLaunchKernelGGL((split_prepare<F, true>), prep_grid, dim3(256), 0, st, q);
+        else hipLaunchKernelGGL((split_prepare<F, false>), prep_grid, dim3(256), 0, st, q);
+    };
+    if (fold == 4) prepare(I<4>{});
+    else if (fold == 3) prepare(I<3>{});
+    else if (fold == 2) prepare(I<2>{});
+    else prepare(I<1>{});
     int rc = check_launch();
     if (rc != kStatusOk) return rc;
 
@@ -609,17 +626,32 @@ int run_wgrad_split(const float *x, const float *dy, float *dw, const Problem &p
     a.div_q = make_fastdiv((uint32_t)pb.Q);
     a.div_cb = make_fastdiv((uint32_t)a.CB);
     a.div_s = make_fastdiv((uint32_t)pb.S);
-    const int grid = 8 * a.units_per_xcd, lds = 2 * (pl.sp_bm + pl.sp_bn) * 192;
+    a.ranges = nullptr; a.dense = pl.sp_dense;
+    if (pl.sp_two) {
+        SplitRanges *const ranges = reinterpret_cast<SplitRanges *>(static_cast<char *>(ws) + pl.sp_range_off);
+        const int rc = find_ranges(ranges, {dy, pb.y_bs, (int64_t)GF * pb.K * pb.P * pb.Q, pb.N},
+                                   {x, pb.x_bs, (int64_t)GF * pb.C * pb.H * pb.W, pb.N}, false, st);
+        if (rc != kStatusOk) return rc;
+        a.ranges = ranges;
+    }
+    const int grid = 8 * a.units_per_xcd;
     const bool tail = pb.K % 16 != 0 || pb.C % 16 != 0;
-    auto go = [&](auto whole, auto ragged) {
-        auto kern = tail ? ragged : whole;
+    auto launch = [&](auto kern, int lds) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
     };
-    if (pl.sp_bm == 128) go(wgrad_split_kernel<2, 2, 2, 4, false>, wgrad_split_kernel<2, 2, 2, 4, true>);
-    else if (pl.sp_bm == 96) go(wgrad_split_kernel<3, 1, 1, 8, false>, wgrad_split_kernel<3, 1, 1, 8, true>);
-    else if (pl.sp_bm == 64) go(wgrad_split_kernel<2, 1, 1, 8, false>, wgrad_split_kernel<2, 1, 1, 8, true>);
-    else go(wgrad_split_kernel<1, 1, 1, 8, false>, wgrad_split_kernel<1, 1, 1, 8, true>);
+    auto go = [&](auto tm, auto tn, auto wm, auto wn) {
+        constexpr int TM = decltype(tm)::value, TN = decltype(tn)::value, WM = decltype(wm)::value, WN = decltype(wn)::value;
+        constexpr int two = wgrad_split_lds<TM, TN, WM, WN, true>(), three = wgrad_split_lds<TM, TN, WM, WN, false>();
+        if (pl.sp_two && tail) launch(wgrad_split_kernel<TM, TN, WM, WN, true, true>, two);
+        else if (pl.sp_two) launch(wgrad_split_kernel<TM, TN, WM, WN, false, true>, two);
+        else if (tail) launch(wgrad_split_kernel<TM, TN, WM, WN, true, false>, three);
+        else launch(wgrad_split_kernel<TM, TN, WM, WN, false, false>, three);
+    };
+    if (pl.sp_bm == 128) go(I<2>{}, I<2>{}, I<2>{}, I<4>{});
+    else if (pl.sp_bm == 96) go(I<3>{}, I<1>{}, I<1>{}, I<8>{});
+    else if (pl.sp_bm == 64) go(I<2>{}, I<1>{}, I<1>{}, I<8>{});
+    else go(I<1>{}, I<1>{}, I<1>{}, I<8>{});
     const int rc = check_launch();
     if (rc != kStatusOk) return rc;
     return launch_finish_wgrad(a.part, dw, pb.K, pb.C, pb.R * pb.S, pl.nsplit, GF, st);
@@ -1454,7 +1486,8 @@ int conv_bwd_filter_noalloc(const void *x, const void *dy, void *dw, int N, int 
     int rc = make_problem(pb, N, C, H, W, K, R, S, stride, pad, 0, 0, dtype);
     if (rc != kStatusOk) return rc;
     if (!aligned(x, 16) || !aligned(dy, 16) || !aligned(dw, 16)) return kErrMisaligned;
-    const Plan pl = make_plan(kOpBwdFilter, pb);
+    Plan pl = make_plan(kOpBwdFilter, pb);
+    fit_two_parts(pl, (size_t)CONV_NOALLOC_SCRATCH_BYTES);
     if (pl.total > (size_t)CONV_NOALLOC_SCRATCH_BYTES) return kErrScratchLimit;
     void *ws = nullptr;
     rc = noalloc_scratch(&ws);

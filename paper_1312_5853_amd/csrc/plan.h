@@ -174,6 +174,8 @@ struct Plan {
     bool sp_pair;
     // sp_two: in two half-precision parts where the operands' range lets it; what was found of it lies at sp_range_off
     bool sp_two;
+    int sp_two_steps;          // of the shortest sum (forward, backward-data)
+    float sp_dense;            // share of the products that no padding makes zero
     size_t sp_range_off;
     int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad, sp_fold;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
@@ -236,16 +238,31 @@ inline int least_padding(int rows)
 
 // Two half-precision parts instead of three bfloat16 ones (conv_split_kernels.h) where the operands let it.  A pass asks for that
 // from kTwoPartSteps steps of 16 products a sum on: the error of both grows with the root of the steps, but two parts start from
-// the 7e-8 that the parts leave out (2-norm against 64 bits, three and two parts: 23 steps 8.1e-8 and 1.1e-7, 54 steps 1.7e-7 and
-// 1.5e-7, 75 steps 2.0e-7 and 1.7e-7, 216 steps 2.8e-7 and 2.6e-7).  And where about a quarter of the contraction's three-part time
-// (kernel, 216 steps of 128 x 256 tiles in one round: 228 -> 165 us) is more than the launch that looks at the operands costs
-// (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 7.7 us).
-constexpr int kTwoPartSteps = 48;
-constexpr size_t kSplitRangeBytes = 4352;      // SplitRanges
-inline bool two_parts_pay(int steps, double kernel_us, double elements)
+// the 7e-8 that the parts leave out (2-norm against 64 bits, three and two parts: forward 23 steps 8.1e-8 and 1.1e-7, 54 steps
+// 1.7e-7 and 1.6e-7, 75 steps 2.0e-7 and 1.7e-7, 216 steps 2.8e-7 and 2.6e-7; backward-filter 39 steps 1.49e-7 and 1.52e-7, 233
+// steps 3.8e-7 and 3.0e-7).  And where `share` of the contraction's estimated three-part time is more than the launch that looks at
+// the operands costs (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 7.7 us).  On 170 drawn passes of enough
+// steps two parts took, of three parts' time: forward 0.71 and backward-data 0.65 (each of 104 less; under the line, which
+// the smallest calls are, up to 0.98), backward-filter 0.77 (0.95 and less above the line, up to 1.10 under it: its share is the
+// smaller one, the operands of its short sums being the most).
+constexpr int kTwoPartSteps = 52;
+constexpr double kTwoPartShare = 0.45, kTwoPartWgradShare = 0.25;
+inline bool two_parts_pay(double share, double kernel_us, double elements) { return share * kernel_us > 4.5 + 4.0 * elements / 5e6; }
+// Share of (output position, tap) pairs that lie inside the image
+inline double taps_inside(const Problem &pb)
 {
-    return steps >= kTwoPartSteps && 0.25 * kernel_us > 4.5 + 4.0 * elements / 5e6;
+    auto axis = [&](int out, int taps, int in) {
+        int64_t n = 0;
+        for (int r = 0; r < taps; ++r) {                 // o * stride + r - pad in [0, in)
+            const int first = std::max(0, (pb.pad - r + pb.stride - 1) / pb.stride);
+            const int last = in - 1 + pb.pad - r < 0 ? -1 : std::min(out - 1, (in - 1 + pb.pad - r) / pb.stride);
+            n += std::max(0, last - first + 1);
+        }
+        return (double)n / ((double)out * taps);
+    };
+    return axis(pb.P, pb.R, pb.H) * axis(pb.Q, pb.S, pb.W);
 }
+constexpr size_t kSplitRangeBytes = 8448;      // SplitRanges
 
 // Width, split count and time estimate (us, returned) of the three-part fp32 kernel on tiles of bm rows for one column of
 // `steps` steps; `groups` columns share the launch.  The split count decides the order of the sums, so it must not depend on
@@ -781,8 +798,10 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.part_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * ncols * pl.M * 4 : 0;
             pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
             const int least = strided ? cb * (pb.R / pb.stride) * (pb.S / pb.stride) / pl.nsplit : pl.chunks_per_split;
-            if (two_parts_pay(least, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
+            if (least >= kTwoPartSteps && two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
                 pl.sp_two = true;
+                pl.sp_two_steps = least;
+                pl.sp_dense = (float)(taps_inside(pb) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
                 pl.sp_range_off = pl.total;
                 pl.total += kSplitRangeBytes;
             }
@@ -817,10 +836,24 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.nsplit = ceil_div(2 * steps, pl.chunks_per_split);
             pl.part_off = 0; pl.part_bytes = (size_t)pl.nsplit * out_bytes;
             pl.total = round_up64(pl.part_bytes * GF, 256);
+            if (pl.chunks_per_split >= kTwoPartSteps && two_parts_pay(kTwoPartWgradShare, us, (double)pb.N * (pb.C * pb.H * pb.W + pb.K * pb.P * pb.Q))) {
+                pl.sp_two = true;
+                pl.sp_dense = (float)taps_inside(pb);
+                pl.sp_range_off = pl.total;
+                pl.total += kSplitRangeBytes;
+            }
         }
     }
     if (three_part && !pl.direct) plan_window(op, pb, pl);
     return pl;
+}
+
+// A workspace that three parts fit into, but not what the operands' range is found with: three parts
+inline void fit_two_parts(Plan &pl, size_t ws_bytes)
+{
+    if (!pl.sp_two || ws_bytes >= pl.total || ws_bytes < pl.total - kSplitRangeBytes) return;
+    pl.sp_two = false;
+    pl.total -= kSplitRangeBytes;
 }
 
 // The plan of a call that brings ws_bytes of workspace.  The three-part kernels want up to six bytes per padded input element,
@@ -829,10 +862,7 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
 inline Plan plan_for_workspace(int op, const Problem &pb, size_t ws_bytes)
 {
     Plan pl = make_plan(op, pb);
-    if (pl.sp_two && ws_bytes < pl.total && ws_bytes >= pl.total - kSplitRangeBytes) {     // a workspace of three parts' size
-        pl.sp_two = false;
-        pl.total -= kSplitRangeBytes;
-    }
+    fit_two_parts(pl, ws_bytes);
     if (!(pl.sp || pl.win || (pl.lin && pl.fused_groups)) || ws_bytes >= pl.total) return pl;
     const Plan fp32 = make_plan(op, pb, false);
     return ws_bytes >= fp32.total ? fp32 : pl;
