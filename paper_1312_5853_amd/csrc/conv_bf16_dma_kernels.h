@@ -112,39 +112,42 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void colgemm_bf16_dma_kernel(con
     const int nsteps = min(p.cblocks * p.R * p.S - step_begin, p.steps_per_split);
     const size_t a_step_bytes = (size_t)p.Mpad * RB;
     const char *a_base = static_cast<const char *>(p.At) + (size_t)step_begin * a_step_bytes + (size_t)m0 * RB;
-    // next step to load: channel block, tap
-    int r, s, cb;
+    // The activations of the next step to load (tap and channel block applied), and how far it is to those of the one after: the
+    // next column of taps, the next row, the next channel block.
+    const int CR = p.R, CS = p.S;
+    const char *xs;
+    int left_r, left_s;              // rows and columns of taps from here on
     {
-        cb = (int)fastdiv((uint32_t)step_begin, p.div_rs);
-        const int rs = step_begin - cb * (p.R * p.S);
-        r = (int)fastdiv((uint32_t)rs, p.div_s);
-        s = rs - r * p.S;
+        const int cb = (int)fastdiv((uint32_t)step_begin, p.div_rs);
+        const int rs = step_begin - cb * (CR * CS);
+        const int r = (int)fastdiv((uint32_t)rs, p.div_s), s = rs - r * CS;
+        const int ar = p.sign > 0 ? r : CR - 1 - r, as = p.sign > 0 ? s : CS - 1 - s;
+        xs = static_cast<const char *>(p.xb) + (size_t)cb * (KC / 16) * p.cb_bytes + (ar * p.Wp + as) * 32;
+        left_r = CR - r; left_s = CS - s;
     }
+    const int x_s = p.sign * 32, x_r = p.sign * (p.Wp - (CS - 1)) * 32;
+    const int x_c = (KC / 16) * p.cb_bytes - p.sign * ((CR - 1) * p.Wp + CS - 1) * 32;
+    auto advance = [&]() {
+        int dx = x_s;
+        left_s -= 1;
+        if (left_s == 0) {
+            left_s = CS; dx = x_r;
+            left_r -= 1;
+            if (left_r == 0) { left_r = CR; dx = x_c; }
+        }
+        xs += dx;
+        a_base += a_step_bytes;
+    };
     // The NL loads of a step are issued one at a time (load_one), spread between the matrix instructions: a wave
     // that issues them in a burst stalls on the full memory queue, and with it its matrix pipe.
-    const char *xs = nullptr;        // activation base of the step being loaded (tap and channel block applied)
-    unsigned la = 0, lb = 0;         // LDS addresses of that step's filter / activation rows of this wave
-    auto begin_step_loads = [&](int buf) {
-        const int ar = p.sign > 0 ? r : p.R - 1 - r, as = p.sign > 0 ? s : p.S - 1 - s;
-        xs = static_cast<const char *>(p.xb) + (size_t)cb * (KC / 16) * p.cb_bytes + (ar * p.Wp + as) * 32;
-        la = lds_base + buf * BUF + wave * NA * 1024;
-        lb = lds_base + buf * BUF + BM * RB + wave * NB * 1024;
-    };
-    auto load_one = [&](int i) {     // i < NL, compile-time after unrolling
-        if (i < NA) dma16(a_base, aoff + i * 1024, la + i * 1024);
-        else dma16(xs, boff[i - NA], lb + (i - NA) * 1024);
-    };
-    auto end_step_loads = [&]() {
-        a_base += a_step_bytes;
-        s += 1;
-        if (s == p.S) { s = 0; r += 1; }
-        if (r == p.R) { r = 0; cb += 1; }
+    auto load_one = [&](int i, unsigned lbuf) {      // i < NL, compile-time after unrolling; lbuf: the buffer
+        if (i < NA) dma16(a_base, aoff + i * 1024, lbuf + wave * NA * 1024 + i * 1024);
+        else dma16(xs, boff[i - NA], lbuf + BM * RB + wave * NB * 1024 + (i - NA) * 1024);
     };
     auto load_step = [&](int buf) {
-        begin_step_loads(buf);
 #pragma unroll
-        for (int i = 0; i < NL; ++i) load_one(i);
-        end_step_loads();
+        for (int i = 0; i < NL; ++i) load_one(i, lds_base + buf * BUF);
+        advance();
     };
 
     f32x16 acc[TM][TN];
@@ -186,12 +189,16 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void colgemm_bf16_dma_kernel(con
     constexpr int SLOTS = (NK - 1) * MPS;              // ... in the slices that carry loads
     constexpr int SPACING = SLOTS / NL > 0 ? SLOTS / NL : 1;
     static_assert(NL <= SLOTS, "one load per matrix instruction at most");
-    int step = 0;
+    // Where step + 3 lies is found behind the first of the last slice's matrix instructions: at the start of a step, multiplied
+    // out, it held up that step's first ones (74 scalar instructions a wave and step of 16 matrix instructions).
+    int step = 0, bufo = 0;                            // bufo: this step's buffer, in bytes
+    const auto after = [&](int o) { return o == 2 * BUF ? 0 : o + BUF; };
     auto do_step = [&](auto more_c) {                  // more: the loads of step + 2 exist (compile-time)
         constexpr bool more = decltype(more_c)::value;
-        const char *bufp = lds + (step % 3) * BUF;
-        const char *nextp = lds + ((step + 1) % 3) * BUF;
-        if (more) begin_step_loads((step + 2) % 3);
+        const int bufo1 = after(bufo);
+        const unsigned lbuf = lds_base + after(bufo1);
+        const char *bufp = lds + bufo;
+        const char *nextp = lds + bufo1;
 #pragma unroll
         for (int t = 0; t < NK; ++t) {
             if (t + 1 < NK) {
@@ -213,14 +220,19 @@ __global__ __launch_bounds__(WM * WN * 64, OCC) void colgemm_bf16_dma_kernel(con
                     const int m = t * MPS + i * TN + jn;           // index among the step's matrix instructions
                     if (more && t + 1 < NK && m % SPACING == SPACING - 1 && m / SPACING < NL) {
                         __builtin_amdgcn_sched_barrier(0);
-                        load_one(m / SPACING);
+                        load_one(m / SPACING, lbuf);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (more && m == SLOTS) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        advance();
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (more) end_step_loads();
         ++step;
+        bufo = bufo1;
     };
     while (step + 2 < nsteps) do_step(std::true_type{});
     while (step < nsteps) do_step(std::false_type{});

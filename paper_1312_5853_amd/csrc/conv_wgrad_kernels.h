@@ -749,8 +749,8 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
     const char *a_base = reinterpret_cast<const char *>(p.dyT) + ((size_t)gcol * p.steps + step_begin) * a_step_bytes + (size_t)m0 * RB;
     const char *const xpb = reinterpret_cast<const char *>(p.xp);
 
-    unsigned la = 0, lb = 0, pos[2] = {0u, 0u};
-    auto begin_step_loads = [&](int buf) {
+    unsigned pos[2];
+    auto locate = [&]() {            // the next step to load
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             pos[e] = 2u * (unsigned)(min(pn[e], p.N - 1) * p.Jx + pg[e] * 8);   // steps past the last image: zero dy
@@ -759,20 +759,18 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
             pg[e] -= wrap ? p.G : 0;
             pn[e] += wrap ? 1 : 0;
         }
-        la = lds_base + buf * BUF + wave * NA * 1024;
-        lb = lds_base + buf * BUF + BM * RB + wave * NB * 1024;
     };
-    auto load_one = [&](int i) {     // i < NL, compile-time after unrolling
-        if (i < NA) dma16(a_base, aoff + i * 1024, la + i * 1024);
-        else dma16(xpb, bbase[i - NA] + pos[(i - NA) & 1], lb + (i - NA) * 1024);
+    auto load_one = [&](int i, unsigned lbuf) {      // i < NL, compile-time after unrolling; lbuf: the buffer
+        if (i < NA) dma16(a_base, aoff + i * 1024, lbuf + wave * NA * 1024 + i * 1024);
+        else dma16(xpb, bbase[i - NA] + pos[(i - NA) & 1], lbuf + BM * RB + wave * NB * 1024 + (i - NA) * 1024);
     };
-    auto end_step_loads = [&]() { a_base += a_step_bytes; };
+    auto advance = [&]() { a_base += a_step_bytes; locate(); };
     auto load_step = [&](int buf) {
-        begin_step_loads(buf);
 #pragma unroll
-        for (int i = 0; i < NL; ++i) load_one(i);
-        end_step_loads();
+        for (int i = 0; i < NL; ++i) load_one(i, lds_base + buf * BUF);
+        advance();
     };
+    locate();
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -810,12 +808,14 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
     constexpr int SLOTS = (NK - 1) * MPS;
     constexpr int SPACING = SLOTS / NL > 0 ? SLOTS / NL : 1;
     static_assert(NL <= SLOTS, "one load per matrix instruction at most");
-    int step = 0;
+    int step = 0, bufo = 0;
+    const auto after = [&](int o) { return o == 2 * BUF ? 0 : o + BUF; };
     auto do_step = [&](auto more_c) {
         constexpr bool more = decltype(more_c)::value;
-        const char *bufp = lds + (step % 3) * BUF;
-        const char *nextp = lds + ((step + 1) % 3) * BUF;
-        if (more) begin_step_loads((step + 2) % 3);
+        const int bufo1 = after(bufo);
+        const unsigned lbuf = lds_base + after(bufo1);
+        const char *bufp = lds + bufo;
+        const char *nextp = lds + bufo1;
 #pragma unroll
         for (int t = 0; t < NK; ++t) {
             if (t + 1 < NK) {
@@ -837,14 +837,19 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_bf16_lin_dma_kernel(con
                     const int m = t * MPS + i * TN + jn;
                     if (more && t + 1 < NK && m % SPACING == SPACING - 1 && m / SPACING < NL) {
                         __builtin_amdgcn_sched_barrier(0);
-                        load_one(m / SPACING);
+                        load_one(m / SPACING, lbuf);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (more && m == SLOTS) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        advance();
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (more) end_step_loads();
         ++step;
+        bufo = bufo1;
     };
     while (step + 2 < nsteps) do_step(std::true_type{});
     while (step < nsteps) do_step(std::false_type{});
