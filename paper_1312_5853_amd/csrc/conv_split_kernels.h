@@ -89,7 +89,9 @@ struct RangeArgs {
     unsigned len[2], quads[2]; // elements of a sample (four and more), its groups of four
     unsigned total[2];         // groups of four in all
     FastDiv div_quads[2];
-    int signed_only;           // tensor 0 without a negative operand among a sample: three parts, and nothing is looked at
+    int signed_only;           // three parts where tensor 0 has no negative operand
+    int steps;                 // see split_segments
+    float dense;
     SplitRanges *out;
 };
 
@@ -130,14 +132,33 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
     const int64_t bs = p.bs[which];
     const unsigned len = p.len[which], quads = p.quads[which], total = p.total[which];
     const FastDiv div = p.div_quads[which];
-    if (p.signed_only) {       // every block looks at the same 2048 operands: a group of four in each 512th of the tensor
-        const unsigned q = (unsigned)((uint64_t)threadIdx.x * p.total[0] / kRangeThreads);
-        const unsigned n = fastdiv(q, p.div_quads[0]);
-        const quad_t v = *reinterpret_cast<const quad_t *>(p.t[0] + (int64_t)n * p.bs[0] + min((q - n * p.quads[0]) * 4, p.len[0] - 4));
-        if (!__syncthreads_or((int)(v[0] | v[1] | v[2] | v[3]) < 0)) {
+    // Every block looks at the same 2048 operands of each tensor first, in four runs: where these say that three parts are to
+    // compute, that is all.
+    __shared__ unsigned words[4][kRangeThreads / 64];
+    {
+        unsigned none = 0, negative = 0;                         // zeros of tensor 0, + 2^16 of tensor 1
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const unsigned q = min((threadIdx.x >> 7) * (p.total[u] >> 2) + (threadIdx.x & 127), p.total[u] - 1);
+            const unsigned n = fastdiv(q, p.div_quads[u]);
+            const quad_t v = *reinterpret_cast<const quad_t *>(p.t[u] + (int64_t)n * p.bs[u] + min((q - n * p.quads[u]) * 4, p.len[u] - 4));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) none += (v[k] & 0x7fffffffu) == 0 ? 1u << 16 * u : 0;
+            if (u == 0) negative = (v[0] | v[1] | v[2] | v[3]) >> 31;
+        }
+        none = wave_sum(none);
+        negative = __ballot(negative != 0) ? 1 : 0;
+        if ((threadIdx.x & 63) == 0) { words[0][threadIdx.x >> 6] = none; words[1][threadIdx.x >> 6] = negative; }
+        __syncthreads();
+        none = negative = 0;
+#pragma unroll
+        for (int w = 0; w < kRangeThreads / 64; ++w) { none += words[0][w]; negative |= words[1][w]; }
+        const float kept = p.dense * (1.f - (none & 0xffff) / (4.f * kRangeThreads)) * (1.f - (none >> 16) / (4.f * kRangeThreads));
+        if ((p.signed_only && !negative) || split_segments(kept, false, p.steps) == 0) {
             if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 1;
             return;
         }
+        __syncthreads();
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 0;
     unsigned big = 0, small = 0xffffffffu, zeros = 0, signs = 0;
@@ -165,7 +186,6 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
             zeros += i + u * step < total ? none : 0;
         }
     }
-    __shared__ unsigned words[4][kRangeThreads / 64];
     big = wave_max(big);
     small = wave_min(small);
     zeros = wave_sum(zeros);
@@ -191,14 +211,8 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
     }
 }
 
-// From the blocks' findings, by a wavefront whose lanes are all active, for sums of `steps` steps of 16 products.
-// Segments: a product of two halves has 22 significant bits, so every instruction rounds the sum of the leading products; those of
-// bfloat16 have 16, and leave many of their sums exact, the more the more operands are zero.  In 1e-14, squares of 2-norm errors
-// against 64 bits (fitted to 170 layers, with the output of a ReLU or of pooling for input, with gradients that such layers leave
-// zeros in): three parts 0.061 steps k - 0.2, k the share of products without a zero to the power of 3/4 and at most 0.7 for
-// a tensor of one sign; two parts 0.058 (steps / segments + segments) + 0.95.  As few segments as make the second at most 0.92 of
-// the first, each of at least 16 steps (the end of a segment costs as much as two to four steps), or three parts.
-// dense: the share of products that no padding makes zero.
+// From the blocks' findings, by a wavefront whose lanes are all active, for sums of `steps` steps of 16 products; dense: the
+// share of these that no padding makes zero.
 __device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane, int steps, float dense)
 {
     SplitInfo o = {0, 0.f, 0.f, 0.f};
@@ -219,10 +233,7 @@ __device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane, 
         fits = fits && e[t] >= -45 && e[t] <= 40 && es >= e[t] - 31;
         scale[t] = __uint_as_float((unsigned)(127 + 14 - e[t]) << 23);
     }
-    kept = fminf(sqrtf(kept * sqrtf(kept)), one_sign ? 0.7f : 1.f);
-    const float n = (float)steps, three = 0.92f * (0.061f * n * kept - 0.2f);
-    for (int g = 8; g >= 2; g /= 2)
-        if (fits && steps >= 16 * g && 0.058f * (n / (float)g + (float)g) + 0.95f <= three) o.segments = g;
+    o.segments = fits ? split_segments(kept, one_sign, steps) : 0;
     o.sa = scale[0];
     o.sb = scale[1];
     o.unscale = __uint_as_float((unsigned)(127 - 28 + e[0] + e[1]) << 23);

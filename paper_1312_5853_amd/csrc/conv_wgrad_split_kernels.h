@@ -116,9 +116,16 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
 
     const auto rsrc_dy = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(dyg), 0, (int)p.dy_bytes, 0x00020000);
     const auto rsrc_x = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(xg), 0, (int)p.x_bytes, 0x00020000);
-    auto rsrc_of = [&](bool a) {           // by value: a conditional of the two names would keep both in memory
+    // of piece u: a wave's pieces are blocks of dy, then blocks of x; where the two meet inside a piece's row of waves, this wave's
+    // choice is made here, once
+    const auto rsrc_edge = [&](bool a) {   // by value: a conditional of the two names would keep both in memory
         if (a) return rsrc_dy;
         return rsrc_x;
+    }(QA / NW * NW + wave < QA);
+    auto rsrc_of = [&](int u) {
+        if ((u + 1) * NW <= QA) return rsrc_dy;
+        if (u * NW >= QA) return rsrc_x;
+        return rsrc_edge;
     };
 
     // Piece u of this wave: block q = u * 8 + wave of the step (filters first), position lane % 32, rows
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
     auto load_one = [&](int u, int k) {
         if (none[u]) return;
         const int plane = (isa[u] ? PQ : p.H * p.W) * 4;
-        const auto rsrc = rsrc_of(isa[u]);
+        const auto rsrc = rsrc_of(u);
         // outside: 0x80000000 + 7 * plane stays past the extent (tensors and planes are shorter than 2^31 bytes together)
         const unsigned v = TAIL ? voff[u] + (unsigned)(k * plane) : voff[u];
         st[u][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, TAIL ? 0 : k * plane, 0));
@@ -395,7 +402,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
                 for (int u = 0; u < NT; ++u) {
                     if (none[u]) continue;
                     const int plane = (isa[u] ? PQ : p.H * p.W) * 4, b = u * NW + wave;
-                    const auto rsrc = rsrc_of(isa[u]);
+                    const auto rsrc = rsrc_of(u);
                     int *const mark = (isa[u] ? nan_rows + b * 16 : nan_cols + (b - QA) * 16) + oct * 8;
                     piece_offset(u);
                     unsigned nans = 0;

@@ -328,7 +328,8 @@ struct RangeTensor {
     int64_t bs, len;
     int n;
 };
-int find_ranges(SplitRanges *out, const RangeTensor &t0, const RangeTensor &t1, bool signed_only, hipStream_t st)
+int find_ranges(SplitRanges *out, const RangeTensor &t0, const RangeTensor &t1, bool signed_only, int steps, float dense,
+                hipStream_t st)
 {
     static_assert(sizeof(SplitRanges) <= kSplitRangeBytes, "workspace");
     RangeArgs a;
@@ -339,7 +340,7 @@ int find_ranges(SplitRanges *out, const RangeTensor &t0, const RangeTensor &t1, 
         a.div_quads[i] = make_fastdiv(a.quads[i]);
         ++i;
     }
-    a.signed_only = signed_only;
+    a.signed_only = signed_only; a.steps = steps; a.dense = dense;
     a.out = out;
     hipLaunchKernelGGL(operand_range, dim3(2 * kRangeBlocks), dim3(kRangeThreads), 0, st, a);
     return check_launch();
@@ -379,7 +380,7 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     if (pl.sp_two) {
         q.ranges = reinterpret_cast<SplitRanges *>(wsb + pl.sp_range_off);
         const int rc = find_ranges(q.ranges, {act, q.src_bs, (int64_t)Cr * GF * q.LH * q.LW, pb.N},
-                                   {w, 0, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, 1}, fwd, st);
+                                   {w, 0, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, 1}, fwd, q.steps, q.dense, st);
         if (rc != kStatusOk) return rc;
     }
     const dim3 prep_grid(q.xb_blocks + grid1d(q.wt_chunks, 256));
@@ -630,7 +631,7 @@ int run_wgrad_split(const float *x, const float *dy, float *dw, const Problem &p
     if (pl.sp_two) {
         SplitRanges *const ranges = reinterpret_cast<SplitRanges *>(static_cast<char *>(ws) + pl.sp_range_off);
         const int rc = find_ranges(ranges, {dy, pb.y_bs, (int64_t)GF * pb.K * pb.P * pb.Q, pb.N},
-                                   {x, pb.x_bs, (int64_t)GF * pb.C * pb.H * pb.W, pb.N}, false, st);
+                                   {x, pb.x_bs, (int64_t)GF * pb.C * pb.H * pb.W, pb.N}, false, 2 * a.steps_per_split, a.dense, st);
         if (rc != kStatusOk) return rc;
         a.ranges = ranges;
     }

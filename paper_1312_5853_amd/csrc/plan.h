@@ -236,16 +236,30 @@ inline int least_padding(int rows)
     return bm;
 }
 
-// Two half-precision parts instead of three bfloat16 ones (conv_split_kernels.h) where the operands let it.  A pass asks for that
-// from kTwoPartSteps steps of 16 products a sum on: the error of both grows with the root of the steps, but two parts start from
-// the 7e-8 that the parts leave out (2-norm against 64 bits, three and two parts: forward 23 steps 8.1e-8 and 1.1e-7, 54 steps
-// 1.7e-7 and 1.6e-7, 75 steps 2.0e-7 and 1.7e-7, 216 steps 2.8e-7 and 2.6e-7; backward-filter 39 steps 1.49e-7 and 1.52e-7, 233
-// steps 3.8e-7 and 3.0e-7).  And where `share` of the contraction's estimated three-part time is more than the launch that looks at
-// the operands costs (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 7.7 us).  On 170 drawn passes of enough
-// steps two parts took, of three parts' time: forward 0.71 and backward-data 0.65 (each of 104 less; under the line, which
-// the smallest calls are, up to 0.98), backward-filter 0.77 (0.95 and less above the line, up to 1.10 under it: its share is the
-// smaller one, the operands of its short sums being the most).
-constexpr int kTwoPartSteps = 52;
+// Segments: a product of two halves has 22 significant bits, so every instruction rounds the sum of the leading products; those of
+// bfloat16 have 16, and leave many of their sums exact, the more the more operands are zero.  In 1e-14, squares of 2-norm errors
+// against 64 bits (fitted to 170 layers, with the output of a ReLU or of pooling for input, with gradients that such layers leave
+// zeros in): three parts 0.061 steps k - 0.2, k the share of products without a zero to the power of 3/4 and at most 0.7 for
+// a tensor of one sign; two parts 0.058 (steps / segments + segments) + 0.95.  As few segments as make the second at most 0.92 of
+// the first, each of at least 16 steps (the end of a segment costs as much as two to four steps), or three parts.
+// kept: the share of products without a zero among their operands; steps: of 16 products a sum.
+CONVNET_HD int split_segments(float kept, bool one_sign, int steps)
+{
+    kept = __builtin_sqrtf(kept * __builtin_sqrtf(kept));
+    if (one_sign && kept > 0.7f) kept = 0.7f;
+    const float n = (float)steps, three = 0.92f * (0.061f * n * kept - 0.2f);
+    int segments = 0;
+    for (int g = 8; g >= 2; g /= 2)
+        if (steps >= 16 * g && 0.058f * (n / (float)g + (float)g) + 0.95f <= three) segments = g;
+    return segments;
+}
+
+// Two half-precision parts instead of three bfloat16 ones (conv_split_kernels.h) where the operands let it: a pass asks for that
+// where split_segments finds that dense operands would do, and where `share` of the contraction's estimated three-part time is
+// more than the launch that looks at the operands costs (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 7.7 us).
+// On 170 drawn passes of enough steps two parts took, of three parts' time: forward 0.71 and backward-data 0.65 (each of 104 less;
+// under the line, which the smallest calls are, up to 0.98), backward-filter 0.77 (0.95 and less above the line, up to 1.10 under
+// it: its share is the smaller one, the operands of its short sums being the most).
 constexpr double kTwoPartShare = 0.45, kTwoPartWgradShare = 0.25;
 inline bool two_parts_pay(double share, double kernel_us, double elements) { return share * kernel_us > 4.5 + 4.0 * elements / 5e6; }
 // Share of (output position, tap) pairs that lie inside the image
@@ -798,10 +812,11 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.part_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * ncols * pl.M * 4 : 0;
             pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
             const int least = strided ? cb * (pb.R / pb.stride) * (pb.S / pb.stride) / pl.nsplit : pl.chunks_per_split;
-            if (least >= kTwoPartSteps && two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
+            const float dense = (float)(taps_inside(pb) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
+            if (split_segments(dense, false, least) > 0 && two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
                 pl.sp_two = true;
                 pl.sp_two_steps = least;
-                pl.sp_dense = (float)(taps_inside(pb) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
+                pl.sp_dense = dense;
                 pl.sp_range_off = pl.total;
                 pl.total += kSplitRangeBytes;
             }
@@ -836,9 +851,10 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.nsplit = ceil_div(2 * steps, pl.chunks_per_split);
             pl.part_off = 0; pl.part_bytes = (size_t)pl.nsplit * out_bytes;
             pl.total = round_up64(pl.part_bytes * GF, 256);
-            if (pl.chunks_per_split >= kTwoPartSteps && two_parts_pay(kTwoPartWgradShare, us, (double)pb.N * (pb.C * pb.H * pb.W + pb.K * pb.P * pb.Q))) {
+            const float dense = (float)taps_inside(pb);
+            if (split_segments(dense, false, pl.chunks_per_split) > 0 && two_parts_pay(kTwoPartWgradShare, us, (double)pb.N * (pb.C * pb.H * pb.W + pb.K * pb.P * pb.Q))) {
                 pl.sp_two = true;
-                pl.sp_dense = (float)taps_inside(pb);
+                pl.sp_dense = dense;
                 pl.sp_range_off = pl.total;
                 pl.total += kSplitRangeBytes;
             }
