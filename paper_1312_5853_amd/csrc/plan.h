@@ -812,7 +812,9 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.part_bytes = pl.nsplit > 1 ? (size_t)pl.nsplit * ncols * pl.M * 4 : 0;
             pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
             const int least = strided ? cb * (pb.R / pb.stride) * (pb.S / pb.stride) / pl.nsplit : pl.chunks_per_split;
-            const float dense = (float)(taps_inside(pb) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
+            // of the positions and taps that the pass goes over (backward-data: a share 1 / stride^2 of the taps at each)
+            const double inside = taps_inside(pb) * (fwd ? 1.0 : (double)pb.P * pb.Q * pb.stride * pb.stride / ((double)pb.H * pb.W));
+            const float dense = (float)(std::min(inside, 1.0) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
             if (split_segments(dense, false, least) > 0 && two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
                 pl.sp_two = true;
                 pl.sp_two_steps = least;

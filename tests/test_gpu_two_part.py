@@ -123,7 +123,8 @@ def test_two_parts_stay_within_the_error_bound(op, shape, route):
 # Dense operands, the output of a ReLU or of pooling for input, gradients with such layers' zeros: two parts (in two to eight
 # segments) are no further from 64 bits than three, or three parts compute (None: either)
 @pytest.mark.parametrize("op,shape", [(0, (40, 256, 13, 13, 256, 3, 1, 1)), (0, (128, 256, 13, 13, 384, 3, 1, 1)),
-                                      (1, (64, 96, 13, 13, 256, 5, 1, 2)), (2, (21, 176, 17, 48, 16, 7, 1, 3)), (2, (120, 32, 40, 41, 256, 3, 1, 1))])
+                                      (1, (64, 96, 13, 13, 256, 5, 1, 2)), (2, (21, 176, 17, 48, 16, 7, 1, 3)), (2, (120, 32, 40, 41, 256, 3, 1, 1)),
+                                      (1, (40, 96, 17, 17, 256, 5, 1, 0))])
 @pytest.mark.parametrize("kept_a,kept_w,sign,two", [(1.0, 1.0, False, True), (0.5, 1.0, False, None), (0.5, 1.0, True, None),
                                                     (0.9, 1.0, True, None), (0.5, 0.5, True, None), (0.02, 1.0, False, False)])
 def test_two_parts_are_no_further_from_64_bits_than_three(op, shape, kept_a, kept_w, sign, two, route):
