@@ -198,16 +198,20 @@ int run_colgemm_dma(int op, const void *act, const void *w, void *out, const Pro
     // plane groups through LDS where they are 16-byte aligned and fit 64 KB; else one thread per position
     const int plane_lds = 32 * LH * LW;
     q.xb_planes = (q.src_bs % 8 == 0 && plane_lds <= 64 * 1024) ? 1 : 0;
-    q.xb_blocks = q.xb_planes ? pb.N * q.CB : grid1d(positions, 256);
+    // four or two channel blocks per work-group where two work-groups per CU are left, six of which fit its LDS
+    for (int g = 4; g > 1 && q.xb_planes == 1; g /= 2)
+        if (q.CB % g == 0 && g * plane_lds <= 24 * 1024 && (int64_t)pb.N * q.CB / g >= 512) q.xb_planes = g;
+    q.xb_blocks = q.xb_planes ? pb.N * q.CB / q.xb_planes : grid1d(positions, 256);
     q.w = static_cast<const unsigned short *>(w);
     q.wt = reinterpret_cast<unsigned short *>(wsb + pl.wt_off);
     q.M = pl.M; q.Mpad = pl.Mpad; q.cblocks = Cr / kc; q.RS = RS; q.C = pb.C; q.transposed = fwd ? 0 : 1; q.kc = kc;
     q.div_wp = make_fastdiv((uint32_t)q.Wp);
     q.div_hp = make_fastdiv((uint32_t)q.Hp);
     q.div_cb = make_fastdiv((uint32_t)q.CB);
+    q.div_pp = make_fastdiv((uint32_t)(q.Hp * q.Wp));
     const int64_t wt_elems = (int64_t)pl.Mpad * Cr * RS;
     hipLaunchKernelGGL(bf16_dma_prepare, dim3(q.xb_blocks + grid1d(wt_elems / 8, 256)), dim3(256),
-                       q.xb_planes ? plane_lds : 0, st, q);
+                       q.xb_planes * plane_lds, st, q);
     int rc = check_launch();
     if (rc != kStatusOk) return rc;
 

@@ -176,6 +176,23 @@ def test_bf16_small_integers_are_exact():
     np.testing.assert_array_equal(dw, oracle.conv_bwd_filter(x, dy, R, S, st, pad))
 
 
+# The re-laid copy of a bf16 tensor, with four, two and one channel block of 16 planes staged by a work-group: as many blocks as
+# leave 512 work-groups, planes that fill less and more than one round of its loads, and the largest that two fit (14 x 14) and
+# that one does (28 x 27)
+@pytest.mark.parametrize("shape", [(256, 128, 5, 4, 112, 3, 3, 1, 1), (255, 128, 2, 3, 128, 3, 3, 1, 2),
+                                   (257, 128, 7, 6, 112, 3, 3, 2, 1), (129, 160, 5, 7, 128, 2, 3, 1, 1),
+                                   (64, 128, 14, 14, 128, 1, 1, 1, 0), (9, 128, 28, 27, 160, 1, 2, 1, 0)])
+def test_bf16_relaid_copy_is_exact(shape):
+    N, C, H, W, K, R, S, st, pad = shape
+    P, Q = hp.out_extent(H, R, st, pad), hp.out_extent(W, S, st, pad)
+    x = synth.small_integers((N, C, H, W), 117)
+    w = synth.small_integers((K, C, R, S), 118)
+    dy = synth.small_integers((N, K, P, Q), 119)
+    y, dx, _ = run_three(x, w, dy, st, pad, "bf16")
+    np.testing.assert_array_equal(y, oracle.conv_fwd(x, w, st, pad))
+    np.testing.assert_array_equal(dx, oracle.conv_bwd_data(dy, w, H, W, st, pad))
+
+
 @pytest.mark.parametrize("shape", [(5, 64, 13, 13, 96, 3, 3, 1, 1),      # bf16 kernels
                                    (3, 3, 20, 21, 24, 5, 5, 2, 2),       # widened inputs, fp32 kernels
                                    (4, 48, 9, 9, 40, 3, 3, 1, 1),
