@@ -1491,8 +1491,7 @@ int conv_bwd_filter_noalloc(const void *x, const void *dy, void *dw, int N, int 
     int rc = make_problem(pb, N, C, H, W, K, R, S, stride, pad, 0, 0, dtype);
     if (rc != kStatusOk) return rc;
     if (!aligned(x, 16) || !aligned(dy, 16) || !aligned(dw, 16)) return kErrMisaligned;
-    Plan pl = make_plan(kOpBwdFilter, pb);
-    fit_two_parts(pl, (size_t)CONV_NOALLOC_SCRATCH_BYTES);
+    const Plan pl = make_plan(kOpBwdFilter, pb);
     if (pl.total > (size_t)CONV_NOALLOC_SCRATCH_BYTES) return kErrScratchLimit;
     void *ws = nullptr;
     rc = noalloc_scratch(&ws);

@@ -813,9 +813,11 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.total = pl.part_off + round_up64(pl.part_bytes * GF, 256);
             const int least = strided ? cb * (pb.R / pb.stride) * (pb.S / pb.stride) / pl.nsplit : pl.chunks_per_split;
             // of the positions and taps that the pass goes over (backward-data: a share 1 / stride^2 of the taps at each)
-            const double inside = taps_inside(pb) * (fwd ? 1.0 : (double)pb.P * pb.Q * pb.stride * pb.stride / ((double)pb.H * pb.W));
+            const double inside =
+                taps_inside(pb) * (fwd ? 1.0 : (double)pb.P * pb.Q * pb.stride * pb.stride / ((double)pb.H * pb.W));
             const float dense = (float)(std::min(inside, 1.0) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
-            if (split_segments(dense, false, least) > 0 && two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
+            if (split_segments(dense, false, least) > 0 &&
+                two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
                 pl.sp_two = true;
                 pl.sp_two_steps = least;
                 pl.sp_dense = dense;
@@ -854,7 +856,10 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.part_off = 0; pl.part_bytes = (size_t)pl.nsplit * out_bytes;
             pl.total = round_up64(pl.part_bytes * GF, 256);
             const float dense = (float)taps_inside(pb);
-            if (split_segments(dense, false, pl.chunks_per_split) > 0 && two_parts_pay(kTwoPartWgradShare, us, (double)pb.N * (pb.C * pb.H * pb.W + pb.K * pb.P * pb.Q))) {
+            // (three parts where only their partial sums fit the library's own scratch: a call on that gives the same bits)
+            const bool fits = (int64_t)pl.total > kWgradPartLimit || (int64_t)pl.total + kSplitRangeBytes <= kWgradPartLimit;
+            if (fits && split_segments(dense, false, pl.chunks_per_split) > 0 &&
+                two_parts_pay(kTwoPartWgradShare, us, (double)pb.N * (pb.C * pb.H * pb.W + pb.K * pb.P * pb.Q))) {
                 pl.sp_two = true;
                 pl.sp_dense = dense;
                 pl.sp_range_off = pl.total;

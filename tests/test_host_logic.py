@@ -223,6 +223,18 @@ SAN_ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:verify_asan_link_order=0
                UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1", OMP_NUM_THREADS="4")
 
 
+def test_two_parts_keep_a_pass_within_the_own_scratch(route):
+    """A backward-filter whose partial sums fill the 48 MiB of conv_bwd_filter_noalloc wants no more for looking at its operands:
+    both entry points then run the same plan.  Beside it, with smaller and with larger sums, two parts."""
+    limit = 48 << 20
+    for shape in [(130, 768, 36, 36, 64, 4, 1, 2), (57, 1024, 8, 8, 768, 4, 1, 1)]:
+        r = route(2, *shape)
+        assert r.workspace == limit and not r.two_part
+    for C in (752, 784):
+        r = route(2, 130, C, 36, 36, 64, 4, 1, 2)
+        assert r.two_part and r.workspace < limit
+
+
 def test_oracle_runs_clean_under_address_and_ub_sanitizers(tmp_path):
     """The C oracle built with AddressSanitizer + UndefinedBehaviorSanitizer: all entry points on exactly-sized heap
     tensors (padding beyond the filter, strides that leave rows unread, 1x1 outputs), checked by closed forms."""
