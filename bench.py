@@ -29,8 +29,9 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3      # MI355X dense fp32 matrix peak (published)
 PEAK_BF16_MFMA_TFLOPS = 2500.0     # MI355X dense bf16 matrix peak (published)
-# fp32 convolutions whose operands are split into three bfloat16 parts: six bf16 products per fp32 product.  Fractions of the
-# fp32 peak above can therefore exceed 1.
+# fp32 convolutions whose operands are split into three bfloat16 parts: six bf16 products per fp32 product (backward-data and
+# backward-filter of the larger layers: two half-precision parts, three products, where the operands' range lets them).
+# Fractions of the fp32 peak above can therefore exceed 1.
 PEAK_SPLIT_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6
 PEAK_HBM_TBS = 8.0                 # MI355X HBM3E peak (published)
 TIMED_LAUNCHES = 50                # per-pass protocol: 10 warm-ups, then the median / minimum of 50 launches
@@ -399,12 +400,13 @@ def main():
                                                     PEAK_BF16_MFMA_TFLOPS if args.stack_dtype == "bf16"
                                                     else PEAK_FP32_MFMA_TFLOPS)
 
-    # dominant kernel.  fp32: the three-part implicit-GEMM kernel on its 128-row tiles, which runs forward of conv2 (both
-    # columns in one launch), conv3, conv4, conv5 and backward-data of conv3, conv4, conv5 (7 launches per step).  bf16 profiling
-    # run: the direct-to-LDS kernel (forward and backward-data of conv3, conv4, conv5; 6 launches per step).
+    # dominant kernel.  fp32: the split implicit-GEMM kernel in three parts, which runs forward of conv2 (both columns in one
+    # launch), conv3, conv4, conv5 (4 launches per step; their inputs have no negative values, which keeps them in three parts,
+    # while backward-data runs on two, at another peak).  bf16 profiling run: the direct-to-LDS kernel (forward and backward-data of conv3, conv4, conv5;
+    # 6 launches per step).
     bf16_run = args.stack_dtype == "bf16"
-    dom_keys = [k for k in samples if k[1] in ("fwd", "dgrad") and k[0] != "conv1"]
-    dom_keys = [k for k in dom_keys if not (k[0] == "conv2" and (k[1] == "dgrad" or bf16_run))]
+    dom_keys = [k for k in samples if k[1] in (("fwd", "dgrad") if bf16_run else ("fwd",)) and k[0] != "conv1"]
+    dom_keys = [k for k in dom_keys if not (k[0] == "conv2" and bf16_run)]
     dom_flops = sum(pass_flops(k[0]) for k in dom_keys)
     dom_ms = sum(sum(samples[k]) for k in dom_keys) / reps          # mean launch duration over the timed region
     achieved = dom_flops / dom_ms / 1e9
@@ -412,7 +414,7 @@ def main():
     roofline = {
         "bound": "mfma",
         "kernel": ("colgemm_bf16_dma_kernel (fwd and dgrad of conv3-5)" if bf16_run else
-                   "colgemm_split_kernel, 128-row tiles (fwd of conv2-5, dgrad of conv3-5)"),
+                   "colgemm_split_kernel in three parts (fwd of conv2-5)"),
         "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
         "frac": round(achieved / peak, 4),
         "traffic": None if bf16_run else traffic_from_profile(N),
@@ -482,7 +484,8 @@ def main():
                                % (N, "fp32" if args.stack_dtype == "f32" else "bf16"),
                    "batch": N, "conv_gflop_per_step": round(flops / 1e9, 2)},
         "frac_fp32_mfma_peak": round(value / PEAK_FP32_MFMA_TFLOPS, 4) if args.stack_dtype == "f32" else None,
-        # the convolutions' own denominators: six bf16 products per fp32 one, published and as the probe sustains them
+        # the convolutions' own denominators: six bf16 products per fp32 one, published and as the probe sustains them (the
+        # backward passes on two half-precision parts make three)
         "frac_three_part_peak": round(value / PEAK_SPLIT_TFLOPS, 4) if args.stack_dtype == "f32" else None,
         "mfma_ceiling_tflops": ceiling,
         "frac_of_measured_mfma_ceiling": measured_fraction(value, ceiling, args.stack_dtype),

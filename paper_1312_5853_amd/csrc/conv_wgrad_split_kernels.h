@@ -1,5 +1,6 @@
-// fp32 backward-filter on the bf16 matrix instruction, operands split into three bfloat16 parts (six products, two
-// accumulators: see conv_split_kernels.h for the arithmetic, its error and its range).
+// fp32 backward-filter on the 16-bit matrix instructions, operands split into three bfloat16 parts (six products, two
+// accumulators) or, where the tensors' range lets them, two half-precision parts (three products): see conv_split_kernels.h for
+// the arithmetic, its error and its range.
 // Part of convnet_hotpath.hip: included there, inside its anonymous namespace, after conv_split_kernels.h.
 //
 // dw[k][(r, s, c)] = sum over positions j = (n, p, q) of dy[n][k][p][q] * x[n][c][p*stride + r - pad][q*stride + s - pad].
@@ -20,8 +21,14 @@
 //
 // Measured (whole call): 384 -> 384 channels 3x3 on 13x13, N = 128: 625 -> 304 us; two columns 48 -> 128 5x5 on 27x27,
 // N = 128: 640 -> 357 us (kernel 349: 267 TFLOP/s of six-product work at its padded 1280 columns); 384 -> 256, N = 33:
-// 121 -> 77 us; error of that 384-channel layer's results against 64 bits 1.0e-6 -> 3.5e-7.  Bound: matrix instructions, 61 % of its cycles, no LDS bank
-// conflicts; the six-product work and the splitting share the vector issue port.
+// 121 -> 77 us; error of that 384-channel layer's results against 64 bits 1.0e-6 -> 3.5e-7.  Bound: matrix instructions, 61 % of
+// its cycles, no LDS bank conflicts; the six-product work and the splitting share the vector issue port.
+// Two parts: half the matrix work, two thirds of the LDS traffic, 9 instead of 11 instructions to split a pair (the high halves
+// by a packed conversion, the low ones by mixed-precision multiply-adds: with these for both, which issue at half rate, 215
+// instead of 206 us).  The kernel of the 384-channel layer 310 -> 206 us.  Bound: no one unit but the sum of a wave's issue, 1100
+// clocks of loads, splits, stores and reads beside 384 of matrix instructions each half step; of 215 us, without the loads 215,
+// without splitting 190, without LDS reads 196, without stores 205, with one product of three 193.  One wave's matrix
+// instructions against its neighbour's other work, a barrier a turn: 265.
 //
 // Loads are raw buffer loads: a piece outside the image or past the range of this split has its offset set past the
 // descriptor's extent and reads as zero.
