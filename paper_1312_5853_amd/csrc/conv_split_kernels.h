@@ -697,15 +697,15 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
     };
     const int a_s = p.tap_s * a_step_bytes, a_r = (p.tap_r - (CS - 1) * p.tap_s) * a_step_bytes;
     const int a_c = (p.RS - (CR - 1) * p.tap_r - (CS - 1) * p.tap_s) * a_step_bytes;
-    const int x_s = p.sign * 32, x_r = p.sign * (p.Wp - (CS - 1)) * 32;
-    const int x_c = (int)cb_bytes - p.sign * ((CR - 1) * p.Wp + CS - 1) * 32;     // (one block: wraps, and is not used)
+    const SplitSteps x_step = split_steps(PARTS, p.plane_bytes, p.Wp, CR, CS, p.sign);
     auto advance = [&]() {
-        int da = a_s, dx = x_s;
+        int da = a_s;
+        int64_t dx = x_step.s;
         left_s -= 1;
         if (left_s == 0) {
-            left_s = CS; da = a_r; dx = x_r;
+            left_s = CS; da = a_r; dx = x_step.r;
             left_r -= 1;
-            if (left_r == 0) { left_r = CR; da = a_c; dx = x_c; }
+            if (left_r == 0) { left_r = CR; da = a_c; dx = x_step.c; }
         }
         a_base += da; xs += dx;
     };

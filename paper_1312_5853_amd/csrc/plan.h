@@ -278,6 +278,18 @@ inline double taps_inside(const Problem &pb)
 }
 constexpr size_t kSplitRangeBytes = 8448;      // SplitRanges
 
+// Bytes from the activations of one step of colgemm_split_kernel to those of the next, in the re-laid copy (rows of Wp positions of
+// 32 bytes, planes of plane_bytes, `parts` planes to a channel block): the next column of the taps_r x taps_s taps, the next row,
+// the next channel block.  In 64 bits: a block of large planes is close to 2^31 bytes, and backward-data (sign -1, taps against the
+// planes' order) adds the taps' extent to it.
+struct SplitSteps {
+    int64_t s, r, c;
+};
+CONVNET_HD SplitSteps split_steps(int parts, unsigned plane_bytes, int Wp, int taps_r, int taps_s, int sign)
+{
+    return {sign * 32, sign * (Wp - (taps_s - 1)) * 32, (int64_t)parts * plane_bytes - (int64_t)sign * (((taps_r - 1) * Wp + taps_s - 1) * 32)};
+}
+
 // Width, split count and time estimate (us, returned) of the three-part fp32 kernel on tiles of bm rows for one column of
 // `steps` steps; `groups` columns share the launch.  The split count decides the order of the sums, so it must not depend on
 // how many columns run together: it is chosen for one column, the tile width (which changes no sum) for all of them.

@@ -36,16 +36,22 @@ Route = collections.namedtuple("Route", "kernels fold nsplit rows columns worksp
 
 
 @pytest.fixture(scope="session")
-def route(tmp_path_factory):
+def planner(tmp_path_factory):
+    """tests/plan_query.cpp, built."""
+    so = str(tmp_path_factory.mktemp("plan") / "plan_query.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "plan_query.cpp")],
+                   check=True)
+    return ctypes.CDLL(so)
+
+
+@pytest.fixture(scope="session")
+def route(planner):
     """route(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0, workspace=None, S=None): what the planner does with such a
     pass (and a workspace of so many bytes; filters R x S, or R x R), so that a test written for one set of kernels ("fp32",
     "split", "direct" or "window") can assert that it reaches them.  Of the window kernel also the channel blocks per step and
     the chunks; together: a grouped bf16 backward-filter in one launch of each kernel; two_part: a split pass that runs on two
     half-precision parts where its operands' range lets it."""
-    so = str(tmp_path_factory.mktemp("plan") / "plan_query.so")
-    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "plan_query.cpp")],
-                   check=True)
-    query = ctypes.CDLL(so).plan_query
+    query = planner.plan_query
 
     def ask(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0, workspace=None, S=None):
         out = (ctypes.c_longlong * 10)()
