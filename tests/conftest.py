@@ -32,7 +32,7 @@ def pytest_collection_modifyitems(config, items):
             item.add_marker(skip)
 
 
-Route = collections.namedtuple("Route", "kernels fold nsplit rows columns workspace blocks chunks together two_part")
+Route = collections.namedtuple("Route", "kernels fold nsplit rows columns workspace blocks chunks together two_part pair")
 
 
 @pytest.fixture(scope="session")
@@ -50,11 +50,11 @@ def route(planner):
     pass (and a workspace of so many bytes; filters R x S, or R x R), so that a test written for one set of kernels ("fp32",
     "split", "direct" or "window") can assert that it reaches them.  Of the window kernel also the channel blocks per step and
     the chunks; together: a grouped bf16 backward-filter in one launch of each kernel; two_part: a split pass that runs on two
-    half-precision parts where its operands' range lets it."""
+    half-precision parts where its operands' range lets it; pair: one on four-wave tiles."""
     query = planner.plan_query
 
     def ask(op, N, C, H, W, K, R, stride, pad, groups=1, dtype=0, workspace=None, S=None):
-        out = (ctypes.c_longlong * 10)()
+        out = (ctypes.c_longlong * 11)()
         assert query(op, N, C, H, W, K, R, R if S is None else S, stride, pad, groups, dtype,
                      ctypes.c_longlong(-1 if workspace is None else workspace), out) == 0
         return Route(("fp32", "split", "direct", "window")[out[0]], *list(out)[1:])

@@ -7,7 +7,7 @@ using namespace convnet;
 // ws_bytes: what the call brings, or -1: as much as it wants.  out: 0 fp32 kernels, 1 three-part kernels, 2 vector units, 3
 // bf16 with the input window in LDS; fold; splits of the reduction; rows, columns of a tile; workspace; of the window kernel
 // channel blocks per step and chunks; whether the columns of a bf16 backward-filter run in one launch; whether a three-part pass
-// looks for operands that two parts hold
+// looks for operands that two parts hold; whether it runs on the four-wave tiles
 extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups, int dtype,
                           long long ws_bytes, long long *out)
 {
@@ -28,8 +28,9 @@ extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int 
     out[5] = (long long)pl.total;
     out[6] = pl.win ? pl.win_ncb : 0;
     out[7] = pl.win ? pl.win_cb / pl.win_ncb : 0;
-    out[9] = pl.sp_two;
     out[8] = pl.lin && pl.fused_groups && !pl.direct;
+    out[9] = pl.sp_two;
+    out[10] = pl.sp_pair;
     return kStatusOk;
 }
 

@@ -227,6 +227,17 @@ def test_split_kernels_walk_their_copy_in_place(planner, parts):
         assert walk(*shape, parts) == 0, shape
 
 
+def test_four_wave_tiles_never_meet_two_parts(route):
+    """The four-wave kernels read three parts only.  Many rounds of tiles, and reductions on both sides of where two parts begin."""
+    seen = set()
+    for C in range(56, 128, 4):
+        for op, shape in [(0, (256, C, 28, 28, 128, 3, 1, 1)), (1, (256, 128, 28, 28, C, 3, 1, 1)), (0, (256, C, 28, 28, 64, 3, 1, 1))]:
+            r = route(op, *shape)
+            assert not (r.pair and r.two_part), (op, shape)
+            seen.add((r.pair, r.two_part))
+    assert {(True, False), (False, True)} <= seen
+
+
 SAN_FLAGS = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
 # leak checking off (the OpenMP runtime keeps its thread pool); the link-order check is off because the test
 # harness may preload a library of its own ahead of the sanitizer runtime
