@@ -63,6 +63,7 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
 // three bfloat16 parts.  operand_range looks at the tensors, on the GPU, and the kernels branch on what it found.
 // ---------------------------------------------------------------------------
 constexpr int kRangeBlocks = 256, kRangeThreads = 512;       // per tensor
+static_assert(kRangeThreads == 4 * 128, "128 places of the sample");
 constexpr float kHalfLow = 0x1p12f, kHalfLowInv = 0x1p-12f;
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -132,14 +133,16 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
     const int64_t bs = p.bs[which];
     const unsigned len = p.len[which], quads = p.quads[which], total = p.total[which];
     const FastDiv div = p.div_quads[which];
-    // Every block looks at the same 2048 operands of each tensor first, in four runs: where these say that three parts are to
-    // compute, that is all.
+    // Every block looks at the same 2048 operands of each tensor first, sixteen at each of 128 places, one in each 128th of the
+    // tensor at a distance from its start that is another in each (with one distance, places fall on the same rows of a channel
+    // in sample after sample): where these say that three parts are to compute, that is all.
     __shared__ unsigned words[4][kRangeThreads / 64];
     {
         unsigned none = 0, negative = 0;                         // zeros of tensor 0, + 2^16 of tensor 1
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const unsigned q = min((threadIdx.x >> 7) * (p.total[u] >> 2) + (threadIdx.x & 127), p.total[u] - 1);
+            const unsigned place = threadIdx.x >> 2, share = p.total[u] >> 7;
+            const unsigned q = min(place * share + __umulhi(place * 0x9e3779b9u, share) + (threadIdx.x & 3), p.total[u] - 1);
             const unsigned n = fastdiv(q, p.div_quads[u]);
             const quad_t v = *reinterpret_cast<const quad_t *>(p.t[u] + (int64_t)n * p.bs[u] + min((q - n * p.quads[u]) * 4, p.len[u] - 4));
 #pragma unroll

@@ -197,6 +197,18 @@ def test_small_operands_beside_one_large_one(op, shape, low, route):
 
 
 @pytest.mark.parametrize("op,shape", SMALL)
+@pytest.mark.parametrize("second", [False, True])
+@pytest.mark.parametrize("what", ["zero", "one sign"])
+def test_the_first_channels_do_not_decide_alone(op, shape, second, what, route):
+    # the first rows of every sample (filter) are no picture of the tensor: dead channels, channels of one sign
+    p = Pass(op, shape)
+    a, w = p.operands(1045)
+    t = w if second else a
+    t[:, :6] = 0.0 if what == "zero" else np.abs(t[:, :6])
+    assert not torch.equal(p.check(a, w), p.three(dev(a), dev(w), route))
+
+
+@pytest.mark.parametrize("op,shape", SMALL)
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
 def test_infinities_and_nan_come_out_as_fp32_gives_them(op, shape, value):
     p = Pass(op, shape)
