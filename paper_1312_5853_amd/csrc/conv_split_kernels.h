@@ -58,30 +58,48 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&o)[3])
 // Two half-precision parts: h = f16(s x), l = f16((s x - h) 2^12), s a power of two that brings the largest operand of the
 // tensor into [2^14, 2^15).  s x = h + 2^-12 l up to 2^-23 of itself (11 + 11 significand bits and l's sign) where the operand is
 // within 2^-28 of the largest, 2^-20 at 2^-32 of it; three products, h h' into one accumulator, h l' and l h' into another.  A
-// call takes them where every operand of both tensors is zero or within these 2^-32 and the largest lie between 2^-45 and
-// 2^41; any other call, and so every one with an infinity, a NaN or a value whose products could leave fp32's range, keeps the
-// three bfloat16 parts.  operand_range looks at the tensors, on the GPU, and the kernels branch on what it found.
+// call takes them where, in both tensors, every operand is zero or within these 2^-32, nearly all of them (kMostTiny) within 2^-27,
+// the largest lie between 2^-45 and 2^41, and magnitudes spread far enough (kLeastFine); any other call, and so every one with an
+// infinity, a NaN or a value whose products could leave fp32's range, keeps the three bfloat16 parts.  operand_range looks at the
+// tensors, on the GPU, and the kernels branch on what it found.
 // ---------------------------------------------------------------------------
 constexpr int kRangeBlocks = 256, kRangeThreads = 512;       // per tensor
-static_assert(kRangeThreads == 4 * 128, "128 places of the sample");
+// The largest operand of a tensor may lie 2^7 above the mean magnitude of its sample (in normal, uniform and Laplace draws of 2^23 it
+// lies 2^5 above), and a share of 2^-14 of the operands, less than a sample, a channel or a filter, 2^-20 below it: the others are
+// within 2^-27 of the largest, which two parts hold in 23 bits.  Errors against 64 bits of two parts and three: both tensors 2^-31
+// to 2^-29 below one operand, sums of 2304, 1.4e-7 and 7.1e-8; filters exp(2 z) of normal z, sums of 864, few products that
+// decide, 2.2e-7 and 1.7e-7.
+constexpr int kMostAbove = 7;
+constexpr unsigned kTinyBinades = 20;
+constexpr float kMostTiny = 0x1p-14f;
+// The sums of h h' of bfloat16 parts stay exact, and theirs is the smaller error, while every product is a multiple of the sum's
+// last bit: where magnitudes lie within few binades, or have few bits.  An operand is fine below an eighth of the mean magnitude
+// of its tensor's sample; c: the share of products with a fine operand.  Errors of two parts over those of three, sums of 54 to 300
+// steps, of c: both tensors' magnitudes in [0.25, 1) 0: 4.4; in [1/16, 1) 0.01: 1.34; [0.5, 1) by a normal tensor 0.08: 1.13; mean
+// of 3 deviations by normal 0.083: 1.09; of 2 deviations 0.105: 1.02 to 1.04; 95 % in [0.5, 1), 5 % about 0.01, by normal 0.126:
+// 0.97 to 1.01; uniform by normal 0.138: 0.80 to 0.93; normal by normal 0.153: 0.80 to 0.94; Laplace 0.22: 0.76 to 0.86.  And three
+// parts compute where most of the sample's fine operands end, in bfloat16, in two zero bits (8-bit integers by normal: 1.30).
+constexpr float kFineShare = 0.125f, kLeastFine = 0.129f;
 constexpr float kHalfLow = 0x1p12f, kHalfLowInv = 0x1p-12f;
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-// What the kernels of a call read in memory: per block of operand_range the largest magnitude, the smallest that is not zero less
-// one (as integers, so zero is the largest), the zeros and the OR of all bits (the sign), of both tensors; and what follows from
-// them.
+// What the kernels of a call read in memory: what each block of operand_range found of its part of each tensor, and what follows.
 struct SplitInfo {
     int segments;              // two parts, the sums of h h' in so many segments; or 0: three parts
     float unscale;             // of a sum
     float sa, sb;              // of the tensors' operands
 };
 struct SplitRanges {
-    unsigned big[2][kRangeBlocks], small[2][kRangeBlocks], zeros[2][kRangeBlocks], signs[2][kRangeBlocks];
-    float operands[2];         // in all
-    int none;                  // nothing was looked at
-    SplitInfo info;            // by the preparation
+    unsigned ends[2][kRangeBlocks];          // exponent of the largest, 255 less that of the smallest that is not zero, tiny ones
+    unsigned zeros[2][kRangeBlocks];         // and whether any is negative, the highest bit
+    unsigned fine[2][kRangeBlocks];
+    float operand[2];                        // one as a share of all
+    int most_big[2];                         // the exponent that the largest may have
+    int few_bits[2];                         // most of the sample's fine operands have few bits
+    int none;                                // nothing was looked at
+    SplitInfo info;                          // by the preparation
 };
 
 struct RangeArgs {
@@ -118,6 +136,27 @@ __device__ __forceinline__ unsigned wave_sum(unsigned v)
     v += dpp_or_zero<0x142, 0xa>(v); v += dpp_or_zero<0x143, 0xc>(v);
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
+// over lanes 0 to 31 in lane 31, over lanes 32 to 63 in lane 63
+__device__ __forceinline__ unsigned half_max(unsigned v)
+{
+    v = max(v, dpp<0x111>(v)); v = max(v, dpp<0x112>(v)); v = max(v, dpp<0x114>(v)); v = max(v, dpp<0x118>(v));
+    return max(v, dpp_or_zero<0x142, 0xa>(v));
+}
+__device__ __forceinline__ unsigned half_sum(unsigned v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v); v += dpp_or_zero<0x112, 0xf>(v); v += dpp_or_zero<0x114, 0xf>(v); v += dpp_or_zero<0x118, 0xf>(v);
+    return v + dpp_or_zero<0x142, 0xa>(v);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_or_zero(float v)
+{
+    return __uint_as_float(dpp_or_zero<CTRL, ROWS>(__float_as_uint(v)));
+}
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v); v += dpp_or_zero<0x112, 0xf>(v); v += dpp_or_zero<0x114, 0xf>(v); v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v); v += dpp_or_zero<0x143, 0xc>(v);
+    return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+}
 
 // A forward pass keeps three parts for an input of one sign (the output of a ReLU or of pooling): for such inputs the error of
 // two is the smaller one by 5 to 25 % only, and a pooling window behind the layer, or a ReLU, that decides between values closer
@@ -130,41 +169,75 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
     typedef unsigned quad_t __attribute__((ext_vector_type(4), aligned(4)));
     const int which = (int)blockIdx.x >= kRangeBlocks, b = (int)blockIdx.x - which * kRangeBlocks;
     const float *const t = p.t[which];
-    const int64_t bs = p.bs[which];
-    const unsigned len = p.len[which], quads = p.quads[which], total = p.total[which];
-    const FastDiv div = p.div_quads[which];
+    const unsigned total = p.total[which];
+    // element that group q of tensor u begins with
+    const auto place_of = [&](int u, unsigned q) {
+        const unsigned n = fastdiv(q, p.div_quads[u]);
+        return (int64_t)n * p.bs[u] + min((q - n * p.quads[u]) * 4, p.len[u] - 4);
+    };
     // Every block looks at the same 2048 operands of each tensor first, sixteen at each of 128 places, one in each 128th of the
     // tensor at a distance from its start that is another in each (with one distance, places fall on the same rows of a channel
     // in sample after sample): where these say that three parts are to compute, that is all.
-    __shared__ unsigned words[4][kRangeThreads / 64];
+    __shared__ unsigned words[6][kRangeThreads / 64];
+    unsigned tiny_line, fine_line;                               // of this block's tensor; operands less one below are tiny / fine
     {
         unsigned none = 0, negative = 0;                         // zeros of tensor 0, + 2^16 of tensor 1
+        float sum = 0.f;                                         // of the magnitudes of this block's tensor
+        quad_t mine;                                             // its operands of this thread
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const unsigned place = threadIdx.x >> 2, share = p.total[u] >> 7;
+            const unsigned place = threadIdx.x >> 2, share = p.total[u] / (kRangeThreads / 4);
             const unsigned q = min(place * share + __umulhi(place * 0x9e3779b9u, share) + (threadIdx.x & 3), p.total[u] - 1);
-            const unsigned n = fastdiv(q, p.div_quads[u]);
-            const quad_t v = *reinterpret_cast<const quad_t *>(p.t[u] + (int64_t)n * p.bs[u] + min((q - n * p.quads[u]) * 4, p.len[u] - 4));
+            const quad_t v = *reinterpret_cast<const quad_t *>(p.t[u] + place_of(u, q));
 #pragma unroll
             for (int k = 0; k < 4; ++k) none += (v[k] & 0x7fffffffu) == 0 ? 1u << 16 * u : 0;
             if (u == 0) negative = (v[0] | v[1] | v[2] | v[3]) >> 31;
+            if (u == which) mine = v & 0x7fffffffu;
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum += __uint_as_float(mine[k]);
         none = wave_sum(none);
+        sum = wave_sum(sum);
         negative = __ballot(negative != 0) ? 1 : 0;
-        if ((threadIdx.x & 63) == 0) { words[0][threadIdx.x >> 6] = none; words[1][threadIdx.x >> 6] = negative; }
+        if ((threadIdx.x & 63) == 0) {
+            const int w = threadIdx.x >> 6;
+            words[0][w] = none; words[1][w] = negative; words[2][w] = __float_as_uint(sum);
+        }
         __syncthreads();
         none = negative = 0;
+        sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < kRangeThreads / 64; ++w) { none += words[0][w]; negative |= words[1][w]; }
+        for (int w = 0; w < kRangeThreads / 64; ++w) {
+            none += words[0][w]; negative |= words[1][w]; sum += __uint_as_float(words[2][w]);
+        }
+        const unsigned left = 4 * kRangeThreads - (which ? none >> 16 : none & 0xffff);
+        const unsigned mean = __float_as_uint(sum / (float)left);
+        tiny_line = mean > kTinyBinades << 23 ? mean - (kTinyBinades << 23) : 0;
+        fine_line = __float_as_uint(__uint_as_float(mean) * kFineShare);
         const float kept = p.dense * (1.f - (none & 0xffff) / (4.f * kRangeThreads)) * (1.f - (none >> 16) / (4.f * kRangeThreads));
         if ((p.signed_only && !negative) || split_segments(kept, false, p.steps) == 0) {
             if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 1;
             return;
         }
+        if (b == 0) {
+            unsigned below = 0;                                  // fine ones, + 2^16 of those with few bits
+#pragma unroll
+            for (int k = 0; k < 4; ++k) below += mine[k] - 1u >= fine_line ? 0 : (mine[k] & 0x30000u) == 0 ? 0x10001u : 1u;
+            below = wave_sum(below);
+            if ((threadIdx.x & 63) == 0) words[3][threadIdx.x >> 6] = below;
+            __syncthreads();
+            below = 0;
+#pragma unroll
+            for (int w = 0; w < kRangeThreads / 64; ++w) below += words[3][w];
+            if (threadIdx.x == 0) {
+                p.out->most_big[which] = (int)(mean >> 23) + kMostAbove;
+                p.out->few_bits[which] = 2 * (below >> 16) > (below & 0xffffu);
+            }
+        }
         __syncthreads();
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 0;
-    unsigned big = 0, small = 0xffffffffu, zeros = 0, signs = 0;
+    unsigned big = 0, small = 0xffffffffu, zeros = 0, signs = 0, tiny = 0, fine = 0;
     constexpr int UN = 4;
     constexpr unsigned step = kRangeBlocks * kRangeThreads;
     for (unsigned i = b * kRangeThreads + threadIdx.x; i < total; i += UN * step) {
@@ -172,30 +245,37 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const unsigned q = min(i + u * step, total - 1);
-            const unsigned n = fastdiv(q, div);
-            v[u] = *reinterpret_cast<const quad_t *>(t + (int64_t)n * bs + min((q - n * quads) * 4, len - 4));
+            v[u] = *reinterpret_cast<const quad_t *>(t + place_of(which, q));
         }
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            unsigned none = 0;
+            unsigned none = 0, little = 0, least = 0xffffffffu;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const unsigned m = v[u][k] & 0x7fffffffu;
                 signs |= v[u][k];
                 big = max(big, m);
-                small = min(small, m - 1u);
+                least = min(least, m - 1u);
                 none += m == 0;
+                little += m - 1u < fine_line;
             }
-            zeros += i + u * step < total ? none : 0;
+            if (i + u * step < total) { zeros += none; fine += little; }
+            small = min(small, least);
+            if (__ballot(least < tiny_line) != 0) {              // seldom
+#pragma unroll
+                for (int k = 0; k < 4; ++k) tiny += (v[u][k] & 0x7fffffffu) - 1u < tiny_line && i + u * step < total;
+            }
         }
     }
     big = wave_max(big);
     small = wave_min(small);
     zeros = wave_sum(zeros);
+    tiny = wave_sum(tiny);
+    fine = wave_sum(fine);
     signs = __ballot(signs >> 31) ? 1 : 0;
     if ((threadIdx.x & 63) == 0) {
         const int w = threadIdx.x >> 6;
-        words[0][w] = big; words[1][w] = small; words[2][w] = zeros; words[3][w] = signs;
+        words[0][w] = big; words[1][w] = small; words[2][w] = zeros; words[3][w] = signs; words[4][w] = tiny; words[5][w] = fine;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -205,44 +285,70 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
             small = min(small, words[1][w]);
             zeros += words[2][w];
             signs |= words[3][w];
+            tiny += words[4][w];
+            fine += words[5][w];
         }
-        p.out->big[which][b] = big;
-        p.out->small[which][b] = small;
-        p.out->zeros[which][b] = zeros;
-        p.out->signs[which][b] = signs;
-        if (b == 0) p.out->operands[which] = 4.f * (float)total;
+        // (a block's tiny ones need counting up to what condemns the tensor: 2^29 operands, 2^-14 of them)
+        const unsigned low = small == 0xffffffffu ? 255u : (small + 1u) >> 23;
+        p.out->ends[which][b] = big >> 23 | (255u - low) << 8 | min(tiny, 0xffffu) << 16;
+        p.out->zeros[which][b] = zeros | signs << 31;
+        p.out->fine[which][b] = fine;
+        if (b == 0) p.out->operand[which] = 0.25f / (float)total;
     }
 }
 
-// From the blocks' findings, by a wavefront whose lanes are all active, for sums of `steps` steps of 16 products; dense: the
-// share of these that no padding makes zero.
+// From the blocks' findings, by a wavefront whose lanes are all active (each half for one tensor), for sums of `steps` steps of 16
+// products; dense: the share of these that no padding makes zero.  Latency at the head of its kernels: all loads go out together.
 __device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane, int steps, float dense)
 {
-    SplitInfo o = {0, 0.f, 0.f, 0.f};
-    if (uniform(r->none)) return o;
-    bool fits = true, one_sign = false;
-    int e[2];
-    float scale[2], kept = dense;
+    const int t = lane >> 5, at = (lane & 31) * 2;
+    const u32x4 *const ends = reinterpret_cast<const u32x4 *>(r->ends[t]) + at, *const zeros = reinterpret_cast<const u32x4 *>(r->zeros[t]) + at;
+    const u32x4 *const fine = reinterpret_cast<const u32x4 *>(r->fine[t]) + at;
+    unsigned big = 0, low = 0, tiny = 0, none = 0, few = 0, negative = 0;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const u32x4 b = reinterpret_cast<const u32x4 *>(r->big[t])[lane], s = reinterpret_cast<const u32x4 *>(r->small[t])[lane];
-        const u32x4 z = reinterpret_cast<const u32x4 *>(r->zeros[t])[lane], n = reinterpret_cast<const u32x4 *>(r->signs[t])[lane];
-        const unsigned big = wave_max(max(max(b[0], b[1]), max(b[2], b[3])));
-        const unsigned small = wave_min(min(min(s[0], s[1]), min(s[2], s[3])));
-        kept *= 1.f - fminf((float)wave_sum(z[0] + z[1] + z[2] + z[3]) / r->operands[t], 1.f);
-        one_sign = one_sign || !__ballot((n[0] | n[1] | n[2] | n[3]) != 0);
-        e[t] = big == 0 ? 0 : (int)(big >> 23) - 127;
-        const int es = big == 0 ? 0 : (int)((small + 1u) >> 23) - 127;
-        fits = fits && e[t] >= -45 && e[t] <= 40 && es >= e[t] - 31;
-        scale[t] = __uint_as_float((unsigned)(127 + 14 - e[t]) << 23);
+    for (int k = 0; k < 2; ++k) {
+        const u32x4 e = ends[k], z = zeros[k], f = fine[k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            big = max(big, e[i] & 0xffu);
+            low = max(low, e[i] & 0xff00u);
+            tiny += e[i] >> 16;
+            none += z[i] & 0x7fffffffu;
+            few += f[i];
+            negative |= z[i];
+        }
     }
-    o.segments = fits ? split_segments(kept, one_sign, steps) : 0;
+    big = half_max(big);
+    low = half_max(low);
+    tiny = half_sum(tiny);
+    none = half_sum(none);
+    few = half_sum(few);
+    const uint64_t signs = __ballot(negative >> 31 != 0);
+    const bool one_sign = (unsigned)signs == 0 || (unsigned)(signs >> 32) == 0;
+    bool fits = !uniform(r->none);
+    int e[2];
+    float scale[2], kept = dense, some = 1.f, coarse = 1.f;      // products of the shares that are not zero, not fine
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const auto of = [&](unsigned v) { return (unsigned)__builtin_amdgcn_readlane((int)v, u * 32 + 31); };
+        const float left = 1.f - (float)of(none) * r->operand[u];
+        kept *= left;
+        some *= left;
+        coarse *= left - (float)of(few) * r->operand[u];
+        const int top = (int)of(big);
+        e[u] = top == 0 ? 0 : top - 127;
+        fits = fits && e[u] >= -45 && e[u] <= 40 && 255 - (int)(of(low) >> 8) >= top - 31 &&
+               top <= r->most_big[u] && (float)of(tiny) * r->operand[u] <= kMostTiny * left && !r->few_bits[u];
+        scale[u] = __uint_as_float((unsigned)(127 + 14 - e[u]) << 23);
+    }
+    SplitInfo o;
+    o.segments = fits && coarse <= (1.f - kLeastFine) * some ? split_segments(fmaxf(kept, 0.f), one_sign, steps) : 0;
     o.sa = scale[0];
     o.sb = scale[1];
     o.unscale = __uint_as_float((unsigned)(127 - 28 + e[0] + e[1]) << 23);
     return o;
 }
-static_assert(kRangeBlocks == 256, "four blocks to a lane");
+static_assert(kRangeBlocks == 256, "eight blocks to a lane");
 
 // two operands -> the parts of s times them, two to a word; s4096 = 4096 s.  Seven instructions, of which the last two, remainder
 // and conversion in one, issue at half rate.
@@ -413,7 +519,8 @@ struct SplitPrepArgs {
     int64_t w_gs;              // floats between the columns' filters
     int Cin, R, S, rows, cols;               // fold > 1: input channels, the filter's and the input's extents
     int pairs;                 // fold > 1: two columns b, b + 1 are inside or outside together and 8-byte aligned
-    SplitRanges *ranges;       // TWO
+    SplitRanges *ranges;       // TWO; units of 256 threads' work, of which a work-group then takes per_block
+    int units, per_block;
     int steps;                 // of a sum
     float dense;               // see split_info
     FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs, div_sv;
@@ -429,39 +536,42 @@ __device__ __forceinline__ float load_or_zero(const float *base, int64_t i, bool
 }
 
 // FOLD: the stride, or 1.  TWO: in two parts where the operands' range lets it; one wavefront of a block puts together what was
-// found of it while the operands are on their way (each wavefront for itself: 20 -> 24 us and 40 -> 49; a launch of its own: 5 us).
+// found of it, for several units of 256 threads' work that the block then takes (without what was found 25.0 us, for each unit 31.0,
+// for up to eight 29.0: 128 x 96 x 27 x 27 and its gradient, 128 x 384 x 13 x 13, mean; a launch of its own: 5 us).
 template <int FOLD, bool TWO>
 __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {
+    SplitInfo info = {0, 0.f, 0.f, 0.f};
+    if constexpr (TWO) {
+        __shared__ SplitInfo found;
+        if (threadIdx.x < 64) {
+            info = split_info(p.ranges, threadIdx.x, p.steps, p.dense);
+            if (threadIdx.x == 0) found = info;
+            if (blockIdx.x == 0 && threadIdx.x == 0) p.ranges->info = info;
+        }
+        __syncthreads();
+        info.segments = uniform(found.segments);
+        info.sa = __int_as_float(uniform(__float_as_int(found.sa)));
+        info.sb = __int_as_float(uniform(__float_as_int(found.sb)));
+    }
+    auto piece = [&](const int unit) {
     float v[8];
     u32x4 o[3];
-    auto split = [&](u32x4 *dst, size_t part, size_t unit, int t, bool ok) {    // part: pieces from one part to the next; dst: of unit 0
-        SplitInfo info = {0, 0.f, 0.f, 0.f};
-        if constexpr (TWO) {
-            __shared__ SplitInfo found;
-            if (threadIdx.x < 64) {
-                info = split_info(p.ranges, threadIdx.x, p.steps, p.dense);
-                if (threadIdx.x == 0) found = info;
-                if (blockIdx.x == 0 && threadIdx.x == 0) p.ranges->info = info;
-            }
-            __syncthreads();
-            info.segments = uniform(found.segments);
-            info.sa = __int_as_float(uniform(__float_as_int(t ? found.sb : found.sa)));
-        }
+    auto split = [&](u32x4 *dst, size_t part, size_t block, int t, bool ok) {    // part: pieces from one part to the next; dst: of block 0
         if (!ok) return;
         if (TWO && info.segments) {
-            split_eight_two(v, info.sa, o);
-            dst += unit * 2 * part;
+            split_eight_two(v, t ? info.sb : info.sa, o);
+            dst += block * 2 * part;
         } else {
             split_eight(v, o);
-            dst += unit * 3 * part;
+            dst += block * 3 * part;
             dst[2 * part] = o[2];
         }
         dst[0] = o[0];
         dst[part] = o[1];
     };
-    if ((int)blockIdx.x < p.xb_blocks) {
-        const unsigned e = blockIdx.x * 256u + threadIdx.x;
+    if (unit < p.xb_blocks) {
+        const unsigned e = (unsigned)unit * 256u + threadIdx.x;
         const unsigned i = min(e >> 1, p.positions - 1), half = e & 1;
         const unsigned t1 = fastdiv(i, p.div_wp);                    // (n*CBt + blk)*Hp + hp
         const int wp = (int)(i - t1 * (unsigned)p.Wp);
@@ -498,7 +608,7 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
         split(p.xs + (size_t)(i - t2 * plane) * 2 + half, (size_t)plane * 2, t2, 0, (e >> 1) < p.positions);
         return;
     }
-    const unsigned all = (blockIdx.x - (unsigned)p.xb_blocks) * 256u + threadIdx.x, e = min(all, p.wt_chunks - 1);
+    const unsigned all = (unsigned)(unit - p.xb_blocks) * 256u + threadIdx.x, e = min(all, p.wt_chunks - 1);
     const int half = (int)(e & 1);
     const unsigned t1 = e >> 1;                                        // ((g*CBg + cb)*RS + rs)*Mpad + m
     const unsigned t2 = fastdiv(t1, p.div_mpad);
@@ -520,6 +630,14 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
         }
     }
     split(p.wt + (size_t)m * 2 + (half ^ ((m >> 3) & 1)), (size_t)p.Mpad * 2, t2, 1, all < p.wt_chunks);
+    };
+    if constexpr (TWO) {
+        const int end = min((int)(blockIdx.x + 1) * p.per_block, p.units);
+#pragma unroll 1
+        for (int unit = (int)blockIdx.x * p.per_block; unit < end; ++unit) piece(unit);
+    } else {
+        piece((int)blockIdx.x);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -387,7 +387,9 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
                                    {w, 0, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, 1}, fwd, q.steps, q.dense, st);
         if (rc != kStatusOk) return rc;
     }
-    const dim3 prep_grid(q.xb_blocks + grid1d(q.wt_chunks, 256));
+    q.units = q.xb_blocks + grid1d(q.wt_chunks, 256);
+    q.per_block = pl.sp_two ? std::min(std::max(q.units / 2048, 1), 8) : 1;        // as many as fill the chip are left
+    const dim3 prep_grid(ceil_div(q.units, q.per_block));
     auto prepare = [&](auto fold_c) {
         constexpr int F = decltype(fold_c)::value;
         if (pl.sp_two) hipLaunchKernelGGL((split_prepare<F, true>), prep_grid, dim3(256), 0, st, q);

@@ -276,7 +276,7 @@ inline double taps_inside(const Problem &pb)
     };
     return axis(pb.P, pb.R, pb.H) * axis(pb.Q, pb.S, pb.W);
 }
-constexpr size_t kSplitRangeBytes = 8448;      // SplitRanges
+constexpr size_t kSplitRangeBytes = 6400;       // SplitRanges
 
 // Bytes from the activations of one step of colgemm_split_kernel to those of the next, in the re-laid copy (rows of Wp positions of
 // 32 bytes, planes of plane_bytes, `parts` planes to a channel block): the next column of the taps_r x taps_s taps, the next row,
