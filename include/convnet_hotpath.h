@@ -36,9 +36,10 @@
  *           fp32 matrix instruction, as six products of three bfloat16 parts of
  *           the operands, or as three of two half-precision parts, which hold an
  *           operand to 2^-23.  The last is chosen on the GPU, for the whole of a
- *           tensor, by the magnitudes, the zeros and the signs of both operands:
- *           where operands so spread gave no larger an error (2-norm of a result
- *           against 64 bits) than three parts.  So the last bits of a result can
+ *           tensor (of each column of a grouped layer), by the magnitudes, the
+ *           zeros and the signs of both operands: where operands so spread gave
+ *           no larger an error (2-norm of a result against 64 bits) than three
+ *           parts.  So the last bits of a result can
  *           depend on values that are not in its sum (the same tensors give the
  *           same bits).
  *           CONV_DTYPE_BF16 = x, w, dy hold bfloat16 (2 bytes, already rounded

@@ -85,7 +85,8 @@ constexpr float kHalfLow = 0x1p12f, kHalfLowInv = 0x1p-12f;
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-// What the kernels of a call read in memory: what each block of operand_range found of its part of each tensor, and what follows.
+// What the kernels of a call read in memory, for each column of a grouped layer: what each block of operand_range found of its part
+// of each tensor, and what follows.
 struct SplitInfo {
     int segments;              // two parts, the sums of h h' in so many segments; or 0: three parts
     float unscale;             // of a sum
@@ -104,7 +105,8 @@ struct SplitRanges {
 
 struct RangeArgs {
     const float *t[2];
-    int64_t bs[2];             // elements between samples
+    unsigned bs[2];            // elements between samples (tensors have less than 2^29)
+    int64_t gs[2];             // elements between columns
     unsigned len[2], quads[2]; // elements of a sample (four and more), its groups of four
     unsigned total[2];         // groups of four in all
     FastDiv div_quads[2];
@@ -164,16 +166,20 @@ __device__ __forceinline__ float wave_sum(float v)
 // its gradients by 1e-3 either way.
 // Bound: HBM, four bytes per operand; every operand is read once here and once by what follows, from the 256 MB cache where the
 // tensors fit.  A group of four that would reach past a sample's end is moved back: operands seen twice change nothing.
-__global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p)
+// 128 x 384 x 13 x 13 and its filters 10.8 us, with as large a gradient 14.6, ended by the sample 5.2; two columns of 128 x 48 x 27 x 27
+// and 128 x 128 x 27 x 27 21.5 a pass in the mean (one look for both 19.8; four groups of a thread in flight instead of two 21.9).
+// A column of a grouped layer (blockIdx.y) is looked at by itself, so that it takes the parts that it takes in a call of its own.
+__global__ __launch_bounds__(kRangeThreads, 8) void operand_range(const RangeArgs p)
 {
     typedef unsigned quad_t __attribute__((ext_vector_type(4), aligned(4)));
     const int which = (int)blockIdx.x >= kRangeBlocks, b = (int)blockIdx.x - which * kRangeBlocks;
-    const float *const t = p.t[which];
+    const float *const t = p.t[which] + blockIdx.y * p.gs[which];
+    SplitRanges *const out = p.out + blockIdx.y;
     const unsigned total = p.total[which];
     // element that group q of tensor u begins with
     const auto place_of = [&](int u, unsigned q) {
         const unsigned n = fastdiv(q, p.div_quads[u]);
-        return (int64_t)n * p.bs[u] + min((q - n * p.quads[u]) * 4, p.len[u] - 4);
+        return n * p.bs[u] + min((q - n * p.quads[u]) * 4, p.len[u] - 4);
     };
     // Every block looks at the same 2048 operands of each tensor first, sixteen at each of 128 places, one in each 128th of the
     // tensor at a distance from its start that is another in each (with one distance, places fall on the same rows of a channel
@@ -188,7 +194,7 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
         for (int u = 0; u < 2; ++u) {
             const unsigned place = threadIdx.x >> 2, share = p.total[u] / (kRangeThreads / 4);
             const unsigned q = min(place * share + __umulhi(place * 0x9e3779b9u, share) + (threadIdx.x & 3), p.total[u] - 1);
-            const quad_t v = *reinterpret_cast<const quad_t *>(p.t[u] + place_of(u, q));
+            const quad_t v = *reinterpret_cast<const quad_t *>(p.t[u] + blockIdx.y * p.gs[u] + place_of(u, q));
 #pragma unroll
             for (int k = 0; k < 4; ++k) none += (v[k] & 0x7fffffffu) == 0 ? 1u << 16 * u : 0;
             if (u == 0) negative = (v[0] | v[1] | v[2] | v[3]) >> 31;
@@ -216,7 +222,7 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
         fine_line = __float_as_uint(__uint_as_float(mean) * kFineShare);
         const float kept = p.dense * (1.f - (none & 0xffff) / (4.f * kRangeThreads)) * (1.f - (none >> 16) / (4.f * kRangeThreads));
         if ((p.signed_only && !negative) || split_segments(kept, false, p.steps) == 0) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 1;
+            if (blockIdx.x == 0 && threadIdx.x == 0) out->none = 1;
             return;
         }
         if (b == 0) {
@@ -230,15 +236,15 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
 #pragma unroll
             for (int w = 0; w < kRangeThreads / 64; ++w) below += words[3][w];
             if (threadIdx.x == 0) {
-                p.out->most_big[which] = (int)(mean >> 23) + kMostAbove;
-                p.out->few_bits[which] = 2 * (below >> 16) > (below & 0xffffu);
+                out->most_big[which] = (int)(mean >> 23) + kMostAbove;
+                out->few_bits[which] = 2 * (below >> 16) > (below & 0xffffu);
             }
         }
         __syncthreads();
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) p.out->none = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) out->none = 0;
     unsigned big = 0, small = 0xffffffffu, zeros = 0, signs = 0, tiny = 0, fine = 0;
-    constexpr int UN = 4;
+    constexpr int UN = 2;
     constexpr unsigned step = kRangeBlocks * kRangeThreads;
     for (unsigned i = b * kRangeThreads + threadIdx.x; i < total; i += UN * step) {
         quad_t v[UN];
@@ -290,10 +296,10 @@ __global__ __launch_bounds__(kRangeThreads) void operand_range(const RangeArgs p
         }
         // (a block's tiny ones need counting up to what condemns the tensor: 2^29 operands, 2^-14 of them)
         const unsigned low = small == 0xffffffffu ? 255u : (small + 1u) >> 23;
-        p.out->ends[which][b] = big >> 23 | (255u - low) << 8 | min(tiny, 0xffffu) << 16;
-        p.out->zeros[which][b] = zeros | signs << 31;
-        p.out->fine[which][b] = fine;
-        if (b == 0) p.out->operand[which] = 0.25f / (float)total;
+        out->ends[which][b] = big >> 23 | (255u - low) << 8 | min(tiny, 0xffffu) << 16;
+        out->zeros[which][b] = zeros | signs << 31;
+        out->fine[which][b] = fine;
+        if (b == 0) out->operand[which] = 0.25f / (float)total;
     }
 }
 
@@ -520,7 +526,7 @@ struct SplitPrepArgs {
     int Cin, R, S, rows, cols;               // fold > 1: input channels, the filter's and the input's extents
     int pairs;                 // fold > 1: two columns b, b + 1 are inside or outside together and 8-byte aligned
     SplitRanges *ranges;       // TWO; units of 256 threads' work, of which a work-group then takes per_block
-    int units, per_block;
+    int units, per_block, groups;
     int steps;                 // of a sum
     float dense;               // see split_info
     FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs, div_sv;
@@ -537,34 +543,40 @@ __device__ __forceinline__ float load_or_zero(const float *base, int64_t i, bool
 
 // FOLD: the stride, or 1.  TWO: in two parts where the operands' range lets it; one wavefront of a block puts together what was
 // found of it, for several units of 256 threads' work that the block then takes (without what was found 25.0 us, for each unit 31.0,
-// for up to eight 29.0: 128 x 96 x 27 x 27 and its gradient, 128 x 384 x 13 x 13, mean; a launch of its own: 5 us).
+// for up to eight 29.0: 128 x 96 x 27 x 27 and its gradient, 128 x 384 x 13 x 13, mean; two columns 1.5 more; a launch of its own: 5).
 template <int FOLD, bool TWO>
 __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {
-    SplitInfo info = {0, 0.f, 0.f, 0.f};
+    // up to four columns from `first` on: all; or those of this block's one unit, whose 128 positions lie in no more (a column with
+    // sums long enough for two parts has 47 positions of 16 channels and more)
+    __shared__ SplitInfo found[4];
+    unsigned first = 0;
     if constexpr (TWO) {
-        __shared__ SplitInfo found;
-        if (threadIdx.x < 64) {
-            info = split_info(p.ranges, threadIdx.x, p.steps, p.dense);
-            if (threadIdx.x == 0) found = info;
-            if (blockIdx.x == 0 && threadIdx.x == 0) p.ranges->info = info;
+        const unsigned n = (unsigned)p.groups;
+        if (FOLD == 1 && n > 4) {
+            const bool x = (int)blockIdx.x < p.xb_blocks;
+            const unsigned i = min(blockIdx.x * 128u, p.positions - 1), k = (blockIdx.x - (unsigned)p.xb_blocks) * 128u;
+            const unsigned u = x ? fastdiv(fastdiv(i, p.div_wp), p.div_hp) : fastdiv(fastdiv(k, p.div_mpad), p.div_rs);
+            first = fastdiv(x ? u - fastdiv(u, p.div_cbt) * (unsigned)p.CBt : u, p.div_cbg);
+        }
+        const unsigned c = first + (threadIdx.x >> 6);
+        if (threadIdx.x >> 6 < n) {
+            const SplitInfo info = split_info(p.ranges + (c < n ? c : c - n), threadIdx.x & 63, p.steps, p.dense);
+            if ((threadIdx.x & 63) == 0) found[threadIdx.x >> 6] = info;
         }
         __syncthreads();
-        info.segments = uniform(found.segments);
-        info.sa = __int_as_float(uniform(__float_as_int(found.sa)));
-        info.sb = __int_as_float(uniform(__float_as_int(found.sb)));
     }
+    const auto found_of = [&](unsigned g) -> const SplitInfo & { return found[g >= first ? g - first : g + p.groups - first]; };
     auto piece = [&](const int unit) {
     float v[8];
     u32x4 o[3];
-    auto split = [&](u32x4 *dst, size_t part, size_t block, int t, bool ok) {    // part: pieces from one part to the next; dst: of block 0
+    // part: pieces from one part to the next (blocks lie three parts apart, also in two: columns differ)
+    auto split = [&](u32x4 *dst, size_t part, unsigned g, int t, bool ok) {
         if (!ok) return;
-        if (TWO && info.segments) {
-            split_eight_two(v, t ? info.sb : info.sa, o);
-            dst += block * 2 * part;
+        if (TWO && found_of(g).segments) {
+            split_eight_two(v, t ? found_of(g).sb : found_of(g).sa, o);
         } else {
             split_eight(v, o);
-            dst += block * 3 * part;
             dst[2 * part] = o[2];
         }
         dst[0] = o[0];
@@ -605,7 +617,7 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
             for (int k = 0; k < 8; ++k) v[k] = load_or_zero(x, e + (int64_t)k * LHW, in && c0 + k < p.Cg);
         }
         const unsigned plane = (unsigned)p.Hp * (unsigned)p.Wp;
-        split(p.xs + (size_t)(i - t2 * plane) * 2 + half, (size_t)plane * 2, t2, 0, (e >> 1) < p.positions);
+        split(p.xs + ((size_t)t2 * 3 * plane + (i - t2 * plane)) * 2 + half, (size_t)plane * 2, g, 0, (e >> 1) < p.positions);
         return;
     }
     const unsigned all = (unsigned)(unit - p.xb_blocks) * 256u + threadIdx.x, e = min(all, p.wt_chunks - 1);
@@ -629,7 +641,8 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
             v[k] = load_or_zero(w, (p.transposed ? (int64_t)ch * p.C + m : (int64_t)m * p.C + ch) * p.RS + rs, m < p.M && ch < p.Cg);
         }
     }
-    split(p.wt + (size_t)m * 2 + (half ^ ((m >> 3) & 1)), (size_t)p.Mpad * 2, t2, 1, all < p.wt_chunks);
+    split(p.wt + ((size_t)t2 * 3 * p.Mpad + m) * 2 + (half ^ ((m >> 3) & 1)), (size_t)p.Mpad * 2, g, 1, all < p.wt_chunks);
+    if (TWO && all < p.wt_chunks && t3 == g * (unsigned)p.CBg && rs == 0 && m == 0 && half == 0) p.ranges[g].info = found_of(g);
     };
     if constexpr (TWO) {
         const int end = min((int)(blockIdx.x + 1) * p.per_block, p.units);
@@ -691,7 +704,7 @@ struct ColGemmSplitArgs {
     int Wp;
     unsigned plane_bytes;      // one part of one channel block: Hp * Wp * 32
     unsigned n_blocks;         // channel blocks of all columns
-    const SplitInfo *info;     // kernels with TWO
+    const SplitRanges *ranges; // kernels with TWO
     int N, sign;               // sign +1: tap (r, s) reads padded (oh*mul + r, ow*mul + s); -1: see SplitClass
     int cblocks;               // channel blocks per column
     int dst_bs;
@@ -746,8 +759,8 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
 
     SplitInfo info = {0, 0.f, 0.f, 0.f};
     if constexpr (TWO) {
-        info.segments = uniform(p.info->segments);
-        info.unscale = __int_as_float(uniform(__float_as_int(p.info->unscale)));
+        info.segments = uniform(p.ranges[gcol].info.segments);
+        info.unscale = __int_as_float(uniform(__float_as_int(p.ranges[gcol].info.unscale)));
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = uniform(tid >> 6);
@@ -794,7 +807,7 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
             const int rem = j - n * (q.OH * q.OW);
             const int oh = (int)fastdiv((uint32_t)rem, q.div_ow);
             const int ow = rem - oh * q.OW;
-            voff[i] = (unsigned)n * p.n_blocks * (PARTS * p.plane_bytes) + (unsigned)c * p.plane_bytes +
+            voff[i] = (unsigned)n * p.n_blocks * (3 * p.plane_bytes) + (unsigned)c * p.plane_bytes +
                       (unsigned)((oh * p.mul * p.Wp + ow * p.mul) * 32 + chunk * 16);
         }
     }
@@ -802,8 +815,8 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
     // Where the next step to load lies, and how far it is to the one after: the next column of taps, the next row, the next
     // channel block (one addition each: a wave issues one scalar instruction in four clocks and has few clocks a step).
     const int CR = q.R, CS = q.S;
-    const int a_step_bytes = p.Mpad * (int)(PARTS * 32);
-    const int64_t cb_bytes = (int64_t)PARTS * p.plane_bytes;
+    const int a_step_bytes = p.Mpad * 96;
+    const int64_t cb_bytes = (int64_t)3 * p.plane_bytes;
     const char *a_base = nullptr, *xs = nullptr;
     int left_r = 0, left_s = 0;                                  // rows and columns of taps from here on
     auto seek = [&](int st) {
@@ -818,7 +831,7 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) void colgemm_sp
     };
     const int a_s = p.tap_s * a_step_bytes, a_r = (p.tap_r - (CS - 1) * p.tap_s) * a_step_bytes;
     const int a_c = (p.RS - (CR - 1) * p.tap_r - (CS - 1) * p.tap_s) * a_step_bytes;
-    const SplitSteps x_step = split_steps(PARTS, p.plane_bytes, p.Wp, CR, CS, p.sign);
+    const SplitSteps x_step = split_steps(p.plane_bytes, p.Wp, CR, CS, p.sign);
     auto advance = [&]() {
         int da = a_s;
         int64_t dx = x_step.s;

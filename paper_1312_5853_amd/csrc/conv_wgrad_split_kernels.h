@@ -87,7 +87,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void wgrad_split_kernel(const Wgra
 
     const int tid = threadIdx.x, lane = tid & 63;
     SplitInfo info = {0, 0.f, 0.f, 0.f};
-    if constexpr (TWO) info = split_info(p.ranges, lane, 2 * p.steps_per_split, p.dense);
+    if constexpr (TWO) info = split_info(p.ranges + gcol, lane, 2 * p.steps_per_split, p.dense);
     const int wave = uniform(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int PQ = p.P * p.Q;

@@ -326,27 +326,28 @@ int run_colgemm_window(int op, const void *act, const void *w, void *out, const 
     return check_launch();
 }
 
-// What magnitudes the operands of two tensors have: of each the first `len` elements of n samples bs apart
+// What magnitudes the operands of two tensors have, in each of `groups` columns: of each the first `len` elements of n samples bs
+// apart, columns gs apart
 struct RangeTensor {
     const float *t;
-    int64_t bs, len;
+    int64_t bs, gs, len;
     int n;
 };
 int find_ranges(SplitRanges *out, const RangeTensor &t0, const RangeTensor &t1, bool signed_only, int steps, float dense,
-                hipStream_t st)
+                int groups, hipStream_t st)
 {
     static_assert(sizeof(SplitRanges) <= kSplitRangeBytes, "workspace");
     RangeArgs a;
     int i = 0;
     for (const RangeTensor *t : {&t0, &t1}) {
-        a.t[i] = t->t; a.bs[i] = t->bs; a.len[i] = (unsigned)t->len; a.quads[i] = (unsigned)((t->len + 3) / 4);
+        a.t[i] = t->t; a.bs[i] = (unsigned)t->bs; a.gs[i] = t->gs; a.len[i] = (unsigned)t->len; a.quads[i] = (unsigned)((t->len + 3) / 4);
         a.total[i] = a.quads[i] * (unsigned)t->n;
         a.div_quads[i] = make_fastdiv(a.quads[i]);
         ++i;
     }
     a.signed_only = signed_only; a.steps = steps; a.dense = dense;
     a.out = out;
-    hipLaunchKernelGGL(operand_range, dim3(2 * kRangeBlocks), dim3(kRangeThreads), 0, st, a);
+    hipLaunchKernelGGL(operand_range, dim3(2 * kRangeBlocks, groups), dim3(kRangeThreads), 0, st, a);
     return check_launch();
 }
 
@@ -383,12 +384,14 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     q.steps = pl.sp_two_steps; q.dense = pl.sp_dense;
     if (pl.sp_two) {
         q.ranges = reinterpret_cast<SplitRanges *>(wsb + pl.sp_range_off);
-        const int rc = find_ranges(q.ranges, {act, q.src_bs, (int64_t)Cr * GF * q.LH * q.LW, pb.N},
-                                   {w, 0, (int64_t)GF * pb.K * pb.C * pb.R * pb.S, 1}, fwd, q.steps, q.dense, st);
+        const int rc = find_ranges(q.ranges, {act, q.src_bs, fwd ? pb.x_gs : pb.y_gs, (int64_t)Cr * q.LH * q.LW, pb.N},
+                                   {w, 0, pb.w_gs, (int64_t)pb.K * pb.C * pb.R * pb.S, 1}, fwd, q.steps, q.dense, GF, st);
         if (rc != kStatusOk) return rc;
     }
+    q.groups = GF;
     q.units = q.xb_blocks + grid1d(q.wt_chunks, 256);
-    q.per_block = pl.sp_two ? std::min(std::max(q.units / 2048, 1), 8) : 1;        // as many as fill the chip are left
+    // as many work-groups as fill the chip are left; more columns than a block has wavefronts for: see split_prepare
+    q.per_block = pl.sp_two && GF <= 4 ? std::min(std::max(q.units / 2048, 1), 8) : 1;
     const dim3 prep_grid(ceil_div(q.units, q.per_block));
     auto prepare = [&](auto fold_c) {
         constexpr int F = decltype(fold_c)::value;
@@ -411,7 +414,7 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     a.out_w = OW; a.out_plane = OH * OW; a.out_step = fwd ? 1 : pb.stride;
     a.RS = RS; a.tap_r = a.out_step * S; a.tap_s = a.out_step;
     a.Wp = q.Wp; a.plane_bytes = (unsigned)q.Hp * (unsigned)q.Wp * 32u; a.n_blocks = (unsigned)q.CBt;
-    a.info = q.ranges ? &q.ranges->info : nullptr;
+    a.ranges = q.ranges;
     a.sign = fwd ? 1 : -1;
     a.cblocks = pl.sp_cb;
     a.dst_bs = (int)(fwd ? pb.y_bs : pb.x_bs);
@@ -636,8 +639,8 @@ int run_wgrad_split(const float *x, const float *dy, float *dw, const Problem &p
     a.ranges = nullptr; a.dense = pl.sp_dense;
     if (pl.sp_two) {
         SplitRanges *const ranges = reinterpret_cast<SplitRanges *>(static_cast<char *>(ws) + pl.sp_range_off);
-        const int rc = find_ranges(ranges, {dy, pb.y_bs, (int64_t)GF * pb.K * pb.P * pb.Q, pb.N},
-                                   {x, pb.x_bs, (int64_t)GF * pb.C * pb.H * pb.W, pb.N}, false, 2 * a.steps_per_split, a.dense, st);
+        const int rc = find_ranges(ranges, {dy, pb.y_bs, pb.y_gs, (int64_t)pb.K * pb.P * pb.Q, pb.N},
+                                   {x, pb.x_bs, pb.x_gs, (int64_t)pb.C * pb.H * pb.W, pb.N}, false, 2 * a.steps_per_split, a.dense, GF, st);
         if (rc != kStatusOk) return rc;
         a.ranges = ranges;
     }

@@ -176,7 +176,7 @@ struct Plan {
     bool sp_two;
     int sp_two_steps;          // of the shortest sum (forward, backward-data)
     float sp_dense;            // share of the products that no padding makes zero
-    size_t sp_range_off;
+    size_t sp_range_off, sp_range_bytes;
     int sp_bm, sp_bn, sp_cb, sp_hp, sp_wp, sp_ph, sp_pw, sp_mpad, sp_fold;
     size_t sp_w_off, sp_w_bytes, sp_x_off, sp_x_bytes;
     // bf16 stride-1 forward / backward-data with the input window of a tile in LDS (colgemm_bf16_window_kernel): 64 or 128 rows,
@@ -256,7 +256,7 @@ CONVNET_HD int split_segments(float kept, bool one_sign, int steps)
 
 // Two half-precision parts instead of three bfloat16 ones (conv_split_kernels.h) where the operands let it: a pass asks for that
 // where split_segments finds that dense operands would do, and where `share` of the contraction's estimated three-part time is
-// more than the launch that looks at the operands costs (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 7.7 us).
+// more than the launch that looks at the operands costs (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 10.8 us).
 // On 170 drawn passes of enough steps two parts took, of three parts' time: forward 0.71 and backward-data 0.65 (each of 104 less;
 // under the line, which the smallest calls are, up to 0.98), backward-filter 0.77 (0.95 and less above the line, up to 1.10 under
 // it: its share is the smaller one, the operands of its short sums being the most).
@@ -276,18 +276,18 @@ inline double taps_inside(const Problem &pb)
     };
     return axis(pb.P, pb.R, pb.H) * axis(pb.Q, pb.S, pb.W);
 }
-constexpr size_t kSplitRangeBytes = 6400;       // SplitRanges
+constexpr size_t kSplitRangeBytes = 6400;       // SplitRanges, of which each column has one
 
 // Bytes from the activations of one step of colgemm_split_kernel to those of the next, in the re-laid copy (rows of Wp positions of
-// 32 bytes, planes of plane_bytes, `parts` planes to a channel block): the next column of the taps_r x taps_s taps, the next row,
+// 32 bytes, planes of plane_bytes, three planes to a channel block): the next column of the taps_r x taps_s taps, the next row,
 // the next channel block.  In 64 bits: a block of large planes is close to 2^31 bytes, and backward-data (sign -1, taps against the
 // planes' order) adds the taps' extent to it.
 struct SplitSteps {
     int64_t s, r, c;
 };
-CONVNET_HD SplitSteps split_steps(int parts, unsigned plane_bytes, int Wp, int taps_r, int taps_s, int sign)
+CONVNET_HD SplitSteps split_steps(unsigned plane_bytes, int Wp, int taps_r, int taps_s, int sign)
 {
-    return {sign * 32, sign * (Wp - (taps_s - 1)) * 32, (int64_t)parts * plane_bytes - (int64_t)sign * (((taps_r - 1) * Wp + taps_s - 1) * 32)};
+    return {sign * 32, sign * (Wp - (taps_s - 1)) * 32, (int64_t)3 * plane_bytes - (int64_t)sign * (((taps_r - 1) * Wp + taps_s - 1) * 32)};
 }
 
 // Width, split count and time estimate (us, returned) of the three-part fp32 kernel on tiles of bm rows for one column of
@@ -835,7 +835,8 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 pl.sp_two_steps = least;
                 pl.sp_dense = dense;
                 pl.sp_range_off = pl.total;
-                pl.total += kSplitRangeBytes;
+                pl.sp_range_bytes = kSplitRangeBytes * GF;
+                pl.total += pl.sp_range_bytes;
             }
         }
     }
@@ -870,13 +871,14 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
             pl.total = round_up64(pl.part_bytes * GF, 256);
             const float dense = (float)taps_inside(pb);
             // (three parts where only their partial sums fit the library's own scratch: a call on that gives the same bits)
-            const bool fits = (int64_t)pl.total > kWgradPartLimit || (int64_t)pl.total + kSplitRangeBytes <= kWgradPartLimit;
+            const bool fits = (int64_t)pl.total > kWgradPartLimit || (int64_t)(pl.total + kSplitRangeBytes * GF) <= kWgradPartLimit;
             if (fits && split_segments(dense, false, pl.chunks_per_split) > 0 &&
                 two_parts_pay(kTwoPartWgradShare, us, (double)pb.N * (pb.C * pb.H * pb.W + pb.K * pb.P * pb.Q))) {
                 pl.sp_two = true;
                 pl.sp_dense = dense;
                 pl.sp_range_off = pl.total;
-                pl.total += kSplitRangeBytes;
+                pl.sp_range_bytes = kSplitRangeBytes * GF;
+                pl.total += pl.sp_range_bytes;
             }
         }
     }
@@ -887,9 +889,9 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
 // A workspace that three parts fit into, but not what the operands' range is found with: three parts
 inline void fit_two_parts(Plan &pl, size_t ws_bytes)
 {
-    if (!pl.sp_two || ws_bytes >= pl.total || ws_bytes < pl.total - kSplitRangeBytes) return;
+    if (!pl.sp_two || ws_bytes >= pl.total || ws_bytes < pl.total - pl.sp_range_bytes) return;
     pl.sp_two = false;
-    pl.total -= kSplitRangeBytes;
+    pl.total -= pl.sp_range_bytes;
 }
 
 // The plan of a call that brings ws_bytes of workspace.  The three-part kernels want up to six bytes per padded input element,

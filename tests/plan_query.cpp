@@ -34,26 +34,26 @@ extern "C" int plan_query(int op, int N, int C, int H, int W, int K, int R, int 
     return kStatusOk;
 }
 
-// Walks a split forward / stride-1 backward-data pass in `parts` parts from step to step as its kernel does, by split_steps: how many
+// Walks a split forward / stride-1 backward-data pass from step to step as its kernel does, by split_steps: how many
 // steps read from elsewhere than the place that their channel block and tap have in the re-laid copy, or from outside it.  -1: the
 // pass runs on other kernels.
-extern "C" long long split_walk(int op, int N, int C, int H, int W, int K, int R, int pad, int parts)
+extern "C" long long split_walk(int op, int N, int C, int H, int W, int K, int R, int pad)
 {
     Problem pb;
     if (make_problem(pb, N, C, H, W, K, R, R, 1, pad, 0, 0, kDtypeF32) != kStatusOk) return -1;
     const Plan pl = make_plan(op, pb);
     if (!pl.sp || op == kOpBwdFilter) return -1;
     const int sign = op == kOpFwd ? 1 : -1;
-    const int64_t plane = (int64_t)pl.sp_hp * pl.sp_wp * 32, copy = pl.sp_cb * parts * plane;
+    const int64_t plane = (int64_t)pl.sp_hp * pl.sp_wp * 32, copy = pl.sp_cb * 3 * plane;
     const ClassGrid h = class_grid(op == kOpFwd, H, R, 1, pad, 0), w = class_grid(op == kOpFwd, W, R, 1, pad, 0);
     const int ty = h.first + pl.sp_ph, tx = w.first + pl.sp_pw;
-    const SplitSteps d = split_steps(parts, (unsigned)plane, pl.sp_wp, R, R, sign);
+    const SplitSteps d = split_steps((unsigned)plane, pl.sp_wp, R, R, sign);
     long long wrong = 0;
     int64_t at = sign > 0 ? 0 : ((int64_t)ty * pl.sp_wp + tx) * 32;
     for (int cb = 0; cb < pl.sp_cb; ++cb)
         for (int r = 0; r < R; ++r)
             for (int s = 0; s < R; ++s) {
-                const int64_t place = cb * parts * plane + ((int64_t)(sign > 0 ? r : ty - r) * pl.sp_wp + (sign > 0 ? s : tx - s)) * 32;
+                const int64_t place = cb * 3 * plane + ((int64_t)(sign > 0 ? r : ty - r) * pl.sp_wp + (sign > 0 ? s : tx - s)) * 32;
                 wrong += at != place || at < 0 || at >= copy;
                 at += s + 1 < R ? d.s : r + 1 < R ? d.r : d.c;
             }

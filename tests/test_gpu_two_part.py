@@ -324,6 +324,41 @@ def test_slices_columns_and_epilogues(route):
         assert torch.equal(y2[:, K * g:K * (g + 1)], hp.conv_fwd(x2[:, C * g:C * (g + 1)], w2[K * g:K * (g + 1)], 1, 2))
 
 
+# Columns of different operands: each takes two parts or three, and the scale, that it takes in a call of its own.  Two columns; six,
+# which a preparing work-group looks up as it needs them (8 x 8 planes of one channel block: three columns within 128 positions)
+@pytest.mark.parametrize("op,N,C,H,K,R,pad,groups", [(0, 5, 640, 20, 640, 5, 2, 2), (1, 5, 640, 20, 640, 5, 2, 2), (0, 4096, 96, 8, 768, 7, 0, 6),
+                                                     (0, 48, 1152, 20, 768, 3, 1, 6), (1, 48, 768, 20, 1152, 3, 1, 6)])
+def test_columns_of_different_operands_give_the_bits_of_separate_calls(op, N, C, H, K, R, pad, groups, route):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    assert route(op, N, C, H, H, K, R, 1, pad, groups=groups).two_part
+    P = H + 2 * pad - R + 1
+    act = torch.randn((N, C, H, H) if op == 0 else (N, K, P, P), device="cuda", generator=gen)
+    w = torch.randn((K, C // groups, R, R), device="cuda", generator=gen) * 0.1
+    a_cols, w_cols = act.chunk(groups, 1), w.chunk(groups, 0)
+    a_cols[1][0, 3, 2, 1] = 2.0 ** 30                          # further above the others than two parts hold
+    if groups > 2:
+        w_cols[2][1, 2, 0, 1] = float("inf")
+        a_cols[4].mul_(2.0 ** 12)
+        a_cols[5].abs_()
+    one = lambda a, u: hp.conv_fwd(a, u, 1, pad) if op == 0 else hp.conv_bwd_data(a, u, H, H, 1, pad)
+    got = hp.conv_fwd_grouped(act, w, 1, pad, groups) if op == 0 else hp.conv_bwd_data_grouped(act, w, H, H, 1, pad, groups)
+    for g, y in enumerate(got.chunk(groups, 1)):
+        want = one(a_cols[g].contiguous(), w_cols[g].contiguous())
+        assert torch.equal(y.contiguous().view(torch.int32), want.view(torch.int32)), g
+
+
+def test_a_column_does_not_change_the_backward_filter_of_another():
+    N, C, H, K, R = 64, 96, 27, 256, 5
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    x, dy = (torch.randn(s, device="cuda", generator=gen) for s in ((N, C, H, H), (N, K, H, H)))
+    dw = hp.conv_bwd_filter_grouped(x, dy, R, R, 1, 2, 2)
+    x[0, 50, 3, 3], dy[0, 200, 2, 2] = float("inf"), 2.0 ** -40
+    again = hp.conv_bwd_filter_grouped(x, dy, R, R, 1, 2, 2)
+    assert torch.equal(again[:K // 2], dw[:K // 2]) and not torch.equal(again[K // 2:], dw[K // 2:])
+
+
 def test_a_call_can_be_captured_and_follows_its_operands(route):
     """What the operands' range says is found by each call on the GPU: a replayed graph takes two parts or three as they are then."""
     p = Pass(*SMALL[0])

@@ -216,15 +216,14 @@ def test_route_of_the_grouped_bf16_backward_filter(route):
     assert together(13, 1536, 39, 24, 1536, 3, 4) and together(40, 896, 38, 16, 512, 3, 4) and together(39, 336, 51, 52, 384, 1, 3)
 
 
-@pytest.mark.parametrize("parts", [2, 3])
-def test_split_kernels_walk_their_copy_in_place(planner, parts):
+def test_split_kernels_walk_their_copy_in_place(planner):
     """Each step of a split pass, reached by additions, reads where its channel block and tap lie, also where a block's planes fill
     close to 2^31 bytes and backward-data's taps lead further still."""
     walk = planner.split_walk
     walk.restype = ctypes.c_longlong
     for shape in [(1, 1, 24, 4596, 4858, 17, 5, 2), (1, 1, 17, 4650, 4790, 23, 11, 5), (0, 1, 24, 4596, 4858, 17, 5, 2),
                   (0, 128, 384, 13, 13, 384, 3, 1), (1, 128, 384, 13, 13, 384, 3, 1), (1, 4, 96, 27, 27, 256, 5, 0)]:
-        assert walk(*shape, parts) == 0, shape
+        assert walk(*shape) == 0, shape
 
 
 def test_four_wave_tiles_never_meet_two_parts(route):
