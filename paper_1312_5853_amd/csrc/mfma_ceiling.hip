@@ -86,9 +86,12 @@ __global__ __launch_bounds__(256) void rate_kernel(const float *src, float *out,
     for (int it = 0; it < iters; ++it) {
         f32x4 v[8];
         if (MODE == 0) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) asm volatile("ds_read_b128 %0, %1" : "=v"(v[u]) : "v"(laddr));
-            asm volatile("s_waitcnt lgkmcnt(0)");
+            // (one block: the registers are the loads' until the wait has passed)
+            asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %8\n\tds_read_b128 %2, %8\n\tds_read_b128 %3, %8\n\t"
+                         "ds_read_b128 %4, %8\n\tds_read_b128 %5, %8\n\tds_read_b128 %6, %8\n\tds_read_b128 %7, %8\n\t"
+                         "s_waitcnt lgkmcnt(0)"
+                         : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                         : "v"(laddr));
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc += v[u];
         } else if (MODE == 1) {
@@ -96,10 +99,13 @@ __global__ __launch_bounds__(256) void rate_kernel(const float *src, float *out,
             for (int u = 0; u < 8; ++u) asm volatile("ds_write_b128 %0, %1" :: "v"(laddr), "v"(w) : "memory");
         } else if (MODE == 2) {
             const char *gi = g + (it & 1) * 8192;
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v[u]) : "v"(gi + u * 1024));
-            asm volatile("s_waitcnt vmcnt(0)");
+            asm volatile("global_load_dwordx4 %0, %8, off\n\tglobal_load_dwordx4 %1, %8, off offset:1024\n\t"
+                         "global_load_dwordx4 %2, %8, off offset:2048\n\tglobal_load_dwordx4 %3, %8, off offset:3072\n\t"
+                         "global_load_dwordx4 %4, %9, off\n\tglobal_load_dwordx4 %5, %9, off offset:1024\n\t"
+                         "global_load_dwordx4 %6, %9, off offset:2048\n\tglobal_load_dwordx4 %7, %9, off offset:3072\n\t"
+                         "s_waitcnt vmcnt(0)"
+                         : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                         : "v"(gi), "v"(gi + 4096));
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc += v[u];
         } else {
