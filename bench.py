@@ -57,7 +57,7 @@ def mfma_ceiling():
         raise RuntimeError("mfma_ceiling failed: %s" % res.stderr.strip())
     out = {}
     for line in res.stdout.splitlines():
-        m = re.match(r"(burst|sustained|bf16_sustained_random_operands|bf16_sustained_constant_operands)\s.*"
+        m = re.match(r"(burst|sustained|(?:bf16|f16)_sustained_(?:random|constant)_operands)\s.*"
                      r"TFLOP/s=([0-9.]+)", line)
         if m:
             out[m.group(1)] = float(m.group(2))

@@ -668,7 +668,7 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 // multiplied out at each step, with fields of the arguments reloaded, it was 79 scalar instructions a wave and step ahead of the
 // first of 12 matrix instructions.  Kernels, three parts -> two so -> two with additions: 384 -> 384 channels 228 -> 181 -> 160
 // us, backward-data of the two columns 375 -> 327 -> 250; whole layers (three passes) 851 -> 645 and 1055 -> 796 us, first layer
-// (three parts) 395 -> 386.  What bounds it: power (half-precision operands sustain 1.62 PFLOP/s against bfloat16's 1.76;
+// (three parts) 395 -> 386.  What bounds it: power (random half-precision operands sustain 1.70 PFLOP/s against bfloat16's 1.85;
 // this kernel reaches 1.1), not the loads (left out: the same time) nor the LDS reads (left out: 5 % less).  A fourth
 // buffer changes nothing.
 // Order inside a step: h h', h l', l h', h m' while the loads of step + 2 are issued; then every fragment of the step

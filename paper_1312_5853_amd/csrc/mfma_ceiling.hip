@@ -1,7 +1,7 @@
 // Register-resident MFMA loops: what the matrix cores of this GPU sustain with
-// no memory traffic at all, fp32 (v_mfma_f32_32x32x2_f32) and bf16
-// (v_mfma_f32_32x32x16_bf16; with operands that never change, and with eight
-// sets of pseudo-random operands cycled, which is what real data costs in
+// no memory traffic at all, fp32 (v_mfma_f32_32x32x2_f32), bf16 and f16
+// (v_mfma_f32_32x32x16_bf16 / _f16; with operands that never change, and with
+// eight sets of pseudo-random operands cycled, which is what real data costs in
 // power and therefore in clock).  bench.py reports them as second denominators
 // next to the published peaks.  It also measures what one CU moves per clock
 // through its LDS (ds_read_b128, ds_write_b128 from registers) and through the
@@ -33,14 +33,18 @@ __global__ __launch_bounds__(256) void mfma_loop(float *out, int iters, float a,
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ unsigned mix(unsigned x) { x ^= x >> 16; x *= 0x7feb352dU; x ^= x >> 15; x *= 0x846ca68bU; x ^= x >> 16; return x; }
-// a pair of bf16 values with magnitudes in [1, 2) and random signs and fractions (sums stay finite)
-__device__ unsigned bf16_pair(unsigned s) { return 0x3F803F80u | (mix(s) & 0x807F807Fu); }
+// a pair of bf16 (f16) values with magnitudes in [1, 2), random signs and fractions where s is not 0 (sums stay finite)
+template <bool F16> __device__ unsigned pair_of(unsigned s)
+{
+    return F16 ? 0x3C003C00u | (s ? mix(s) & 0x83FF83FFu : 0u) : 0x3F803F80u | (s ? mix(s) & 0x807F807Fu : 0u);
+}
 
-template <bool RANDOM>
-__global__ __launch_bounds__(256) void mfma_bf16_loop(float *out, int iters)
+template <bool RANDOM, bool F16>
+__global__ __launch_bounds__(256) void mfma_half_loop(float *out, int iters)
 {
     f32x16 acc[4];
     for (int i = 0; i < 4; ++i)
@@ -48,17 +52,22 @@ __global__ __launch_bounds__(256) void mfma_bf16_loop(float *out, int iters)
     u32x4 a[8], b[8];
     for (int s = 0; s < 8; ++s)
         for (int k = 0; k < 4; ++k) {
-            a[s][k] = RANDOM ? bf16_pair(threadIdx.x * 131 + s * 17 + k) : 0x3F803F80u;
-            b[s][k] = RANDOM ? bf16_pair(threadIdx.x * 257 + s * 29 + k + 99) : 0x3F803F80u;
+            a[s][k] = pair_of<F16>(RANDOM ? threadIdx.x * 131 + s * 17 + k + 1 : 0);
+            b[s][k] = pair_of<F16>(RANDOM ? threadIdx.x * 257 + s * 29 + k + 99 : 0);
         }
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[(u + i) & 7]),
-                                                                 __builtin_bit_cast(bf16x8, b[(u * 3 + i) & 7]),
-                                                                 acc[i], 0, 0, 0);
+                if constexpr (F16)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[(u + i) & 7]),
+                                                                    __builtin_bit_cast(f16x8, b[(u * 3 + i) & 7]),
+                                                                    acc[i], 0, 0, 0);
+                else
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[(u + i) & 7]),
+                                                                     __builtin_bit_cast(bf16x8, b[(u * 3 + i) & 7]),
+                                                                     acc[i], 0, 0, 0);
     }
     float s = 0.f;
     for (int i = 0; i < 4; ++i)
@@ -149,21 +158,22 @@ int main()
     CHECK(hipEventSynchronize(e1));
     CHECK(hipEventElapsedTime(&ms, e0, e1));
     printf("sustained  wgs=%d launches=10 ms=%.3f TFLOP/s=%.1f\n", wgs, ms, 10.0 * flops / ms / 1e9);
-    // bf16: 512 work-groups (two waves per SIMD), 0.1 s each
+    // bf16 and f16: 512 work-groups (two waves per SIMD), 0.1 s each
     const int bwgs = 512, biters = 10000;
     const double bflops = (double)bwgs * 4 * biters * 32 * 32768.0;      // waves x iterations x MFMAs x 32*32*16*2
-    for (int rnd = 0; rnd < 2; ++rnd) {
-        if (rnd) hipLaunchKernelGGL(mfma_bf16_loop<true>, dim3(bwgs), dim3(256), 0, 0, d, 100);
-        else hipLaunchKernelGGL(mfma_bf16_loop<false>, dim3(bwgs), dim3(256), 0, 0, d, 100);
+    void (*const halves[])(float *, int) = {mfma_half_loop<false, false>, mfma_half_loop<true, false>, mfma_half_loop<false, true>,
+                                            mfma_half_loop<true, true>};
+    const char *const half_names[] = {"bf16_sustained_constant_operands", "bf16_sustained_random_operands  ",
+                                      "f16_sustained_constant_operands ", "f16_sustained_random_operands   "};
+    for (int rnd = 0; rnd < 4; ++rnd) {
+        hipLaunchKernelGGL(halves[rnd], dim3(bwgs), dim3(256), 0, 0, d, 100);
         CHECK(hipDeviceSynchronize());
         CHECK(hipEventRecord(e0));
-        if (rnd) hipLaunchKernelGGL(mfma_bf16_loop<true>, dim3(bwgs), dim3(256), 0, 0, d, biters);
-        else hipLaunchKernelGGL(mfma_bf16_loop<false>, dim3(bwgs), dim3(256), 0, 0, d, biters);
+        hipLaunchKernelGGL(halves[rnd], dim3(bwgs), dim3(256), 0, 0, d, biters);
         CHECK(hipEventRecord(e1));
         CHECK(hipEventSynchronize(e1));
         CHECK(hipEventElapsedTime(&ms, e0, e1));
-        printf("%s wgs=%d ms=%.3f TFLOP/s=%.1f\n", rnd ? "bf16_sustained_random_operands  " : "bf16_sustained_constant_operands",
-               bwgs, ms, bflops / ms / 1e9);
+        printf("%s wgs=%d ms=%.3f TFLOP/s=%.1f\n", half_names[rnd], bwgs, ms, bflops / ms / 1e9);
     }
     // bytes per clock and CU (at the 2.4 GHz peak clock) of LDS reads, LDS writes from registers, cache-resident
     // 16-byte loads into registers, and the same loads straight into LDS
