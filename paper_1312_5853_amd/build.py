@@ -17,11 +17,9 @@ DEPS = [SRC] + [os.path.join(_HERE, "csrc", h) for h in (
     "conv_bf16_window_kernels.h", "conv_split_kernels.h", "conv_wgrad_split_kernels.h", "conv_direct_kernels.h",
     "conv_wgrad_rows_kernels.h", "conv_wgrad_kernels.h", "fc_kernels.h", "glue_kernels.h")] + [os.path.join(os.path.dirname(_HERE), "include", "convnet_hotpath.h")]
 
-HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC", "-Wall",
-    # no packed-fp32 instruction selection
-    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-]
+# no packed-fp32 instruction selection
+DEVICE_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+HIPCC_FLAGS = DEVICE_FLAGS + ["-shared", "-fPIC", "-Wall"]
 
 
 def is_stale():
@@ -42,8 +40,7 @@ def build(verbose=False):
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + err)
     # the stand-alone MFMA ceiling probe (no inputs, prints TFLOP/s)
-    res = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-o", CEILING_EXE, CEILING_SRC],
-                         capture_output=True, text=True)
+    res = subprocess.run([hipcc] + DEVICE_FLAGS + ["-o", CEILING_EXE, CEILING_SRC], capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stderr)
     return LIB
