@@ -400,28 +400,31 @@ def main():
                                                     PEAK_BF16_MFMA_TFLOPS if args.stack_dtype == "bf16"
                                                     else PEAK_FP32_MFMA_TFLOPS)
 
-    # dominant kernel.  fp32: the split implicit-GEMM kernel in three parts, which runs forward of conv2 (both columns in one
-    # launch), conv3, conv4, conv5 (4 launches per step; their inputs have no negative values, which keeps them in three parts,
-    # while backward-data runs on two, at another peak).  bf16 profiling run: the direct-to-LDS kernel (forward and backward-data of conv3, conv4, conv5;
-    # 6 launches per step).
-    bf16_run = args.stack_dtype == "bf16"
-    dom_keys = [k for k in samples if k[1] in (("fwd", "dgrad") if bf16_run else ("fwd",)) and k[0] != "conv1"]
-    dom_keys = [k for k in dom_keys if not (k[0] == "conv2" and bf16_run)]
-    dom_flops = sum(pass_flops(k[0]) for k in dom_keys)
-    dom_ms = sum(sum(samples[k]) for k in dom_keys) / reps          # mean launch duration over the timed region
-    achieved = dom_flops / dom_ms / 1e9
-    peak = PEAK_BF16_MFMA_TFLOPS if bf16_run else round(PEAK_SPLIT_TFLOPS, 1)
-    roofline = {
-        "bound": "mfma",
-        "kernel": ("colgemm_bf16_dma_kernel (fwd and dgrad of conv3-5)" if bf16_run else
-                   "colgemm_split_kernel in three parts (fwd of conv2-5)"),
-        "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
-        "frac": round(achieved / peak, 4),
-        "traffic": None if bf16_run else traffic_from_profile(N),
-        "traffic_source": "profiles/stack_n128_fp32_hbm_traffic.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE)",
-        "launches_per_step": len(dom_keys), "avg_launch_ms": round(dom_ms / len(dom_keys), 4),
-        "flops_per_launch": dom_flops / len(dom_keys), "timed_launches_each": reps,
-    }
+    # dominant kernel.  fp32: the split implicit-GEMM kernel where it runs in three parts: forward of conv2 (both columns in one
+    # launch) to conv5, whose inputs have no negative values, and backward-data of conv5 and conv2, whose gradients come from
+    # pooling and are mostly zeros (6 launches per step; one set of passes, one peak).  Backward-data of conv4 and conv3 runs
+    # on two parts, against another peak, and is reported beside it.  bf16 profiling run: the direct-to-LDS kernel (forward
+    # and backward-data of conv3, conv4, conv5; 6 launches per step).
+    def roofline_of(kernel, keys, peak):
+        nominal = sum(pass_flops(k[0]) for k in keys)
+        ms = sum(sum(samples[k]) for k in keys) / reps              # mean launch duration over the timed region
+        achieved = nominal / ms / 1e9
+        return {"bound": "mfma", "kernel": kernel, "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+                "frac": round(achieved / peak, 4), "launches_per_step": len(keys), "avg_launch_ms": round(ms / len(keys), 4),
+                "flops_per_launch": nominal / len(keys), "timed_launches_each": reps}
+
+    if args.stack_dtype == "bf16":
+        roofline = roofline_of("colgemm_bf16_dma_kernel (fwd and dgrad of conv3-5)",
+                               [(n, p) for n in ("conv3", "conv4", "conv5") for p in ("fwd", "dgrad")], PEAK_BF16_MFMA_TFLOPS)
+        roofline["traffic"] = roofline_two = None
+    else:
+        roofline = roofline_of("colgemm_split_kernel in three parts (fwd of conv2-5, dgrad of conv5 and conv2)",
+                               [(n, "fwd") for n in ("conv2", "conv3", "conv4", "conv5")] + [("conv5", "dgrad"), ("conv2", "dgrad")],
+                               round(PEAK_SPLIT_TFLOPS, 1))
+        roofline["traffic"] = traffic_from_profile(N)
+        roofline["traffic_source"] = "profiles/stack_n128_fp32_hbm_traffic.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE)"
+        roofline_two = roofline_of("colgemm_split_kernel in two parts (dgrad of conv4 and conv3)",
+                                   [("conv4", "dgrad"), ("conv3", "dgrad")], round(2 * PEAK_SPLIT_TFLOPS, 1))
 
     def bf16_block():
         out = {}
@@ -499,6 +502,7 @@ def main():
                            "inside its time" % (WARMUP_LAUNCHES, TIMED_LAUNCHES, Timer.GROUP),
         "per_pass": per_pass,
         "roofline": roofline,
+        "roofline_two_parts": roofline_two,
         "per_config": per_config,
         "two_column_conv4_conv5_fp32": columns,
         "bf16_in_fp32_acc": bf16,
