@@ -307,6 +307,7 @@ __global__ __launch_bounds__(kRangeThreads, 8) void operand_range(const RangeArg
 // products; dense: the share of these that no padding makes zero.  Latency at the head of its kernels: all loads go out together.
 __device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane, int steps, float dense)
 {
+    if (uniform(r->none)) return {0, 0.f, 0.f, 0.f};
     const int t = lane >> 5, at = (lane & 31) * 2;
     const u32x4 *const ends = reinterpret_cast<const u32x4 *>(r->ends[t]) + at, *const zeros = reinterpret_cast<const u32x4 *>(r->zeros[t]) + at;
     const u32x4 *const fine = reinterpret_cast<const u32x4 *>(r->fine[t]) + at;
@@ -331,7 +332,7 @@ __device__ __forceinline__ SplitInfo split_info(const SplitRanges *r, int lane, 
     few = half_sum(few);
     const uint64_t signs = __ballot(negative >> 31 != 0);
     const bool one_sign = (unsigned)signs == 0 || (unsigned)(signs >> 32) == 0;
-    bool fits = !uniform(r->none);
+    bool fits = true;
     int e[2];
     float scale[2], kept = dense, some = 1.f, coarse = 1.f;      // products of the shares that are not zero, not fine
 #pragma unroll
@@ -525,8 +526,8 @@ struct SplitPrepArgs {
     int64_t w_gs;              // floats between the columns' filters
     int Cin, R, S, rows, cols;               // fold > 1: input channels, the filter's and the input's extents
     int pairs;                 // fold > 1: two columns b, b + 1 are inside or outside together and 8-byte aligned
-    SplitRanges *ranges;       // TWO; units of 256 threads' work, of which a work-group then takes per_block
-    int units, per_block, groups;
+    SplitRanges *ranges;       // TWO; units of 256 threads' work
+    int units, groups;
     int steps;                 // of a sum
     float dense;               // see split_info
     FastDiv div_wp, div_hp, div_cbt, div_cbg, div_mpad, div_rs, div_sv;
@@ -541,9 +542,10 @@ __device__ __forceinline__ float load_or_zero(const float *base, int64_t i, bool
     return ok ? e : 0.f;
 }
 
-// FOLD: the stride, or 1.  TWO: in two parts where the operands' range lets it; one wavefront of a block puts together what was
-// found of it, for several units of 256 threads' work that the block then takes (without what was found 25.0 us, for each unit 31.0,
-// for up to eight 29.0: 128 x 96 x 27 x 27 and its gradient, 128 x 384 x 13 x 13, mean; two columns 1.5 more; a launch of its own: 5).
+// FOLD: the stride, or 1.  TWO: in two parts where the operands' range lets it; one wavefront of a block (for each column) puts
+// together what was found of it, for up to four units of 256 threads' work, a grid apart.  128 x 384 x 13 x 13 and 128 x 96 x 27 x
+// 27, forward and backward-data, mean: without what was found 25.0 us, looked up for each unit 31.0, for four 29.9 (launch of its
+// own: 5 more).  Consecutive units cost 5 us where three parts of 128 x 256 x 27 x 27 are written (49.5 -> 55), four a grid apart 3.
 template <int FOLD, bool TWO>
 __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {
@@ -645,9 +647,8 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
     if (TWO && all < p.wt_chunks && t3 == g * (unsigned)p.CBg && rs == 0 && m == 0 && half == 0) p.ranges[g].info = found_of(g);
     };
     if constexpr (TWO) {
-        const int end = min((int)(blockIdx.x + 1) * p.per_block, p.units);
 #pragma unroll 1
-        for (int unit = (int)blockIdx.x * p.per_block; unit < end; ++unit) piece(unit);
+        for (int unit = (int)blockIdx.x; unit < p.units; unit += (int)gridDim.x) piece(unit);
     } else {
         piece((int)blockIdx.x);
     }

@@ -391,8 +391,7 @@ int run_colgemm_split(int op, const float *act, const float *w, float *out, cons
     q.groups = GF;
     q.units = q.xb_blocks + grid1d(q.wt_chunks, 256);
     // as many work-groups as fill the chip are left; more columns than a block has wavefronts for: see split_prepare
-    q.per_block = pl.sp_two && GF <= 4 ? std::min(std::max(q.units / 2048, 1), 8) : 1;
-    const dim3 prep_grid(ceil_div(q.units, q.per_block));
+    const dim3 prep_grid(ceil_div(q.units, pl.sp_two && GF <= 4 ? std::min(std::max(q.units / 2048, 1), 4) : 1));
     auto prepare = [&](auto fold_c) {
         constexpr int F = decltype(fold_c)::value;
         if (pl.sp_two) hipLaunchKernelGGL((split_prepare<F, true>), prep_grid, dim3(256), 0, st, q);
