@@ -614,9 +614,9 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
                 }
             }
         } else {
-            const int64_t e = (int64_t)((int)g * p.Cg + c0) * LHW + h * p.LW + w;
+            int64_t e = (int64_t)((int)g * p.Cg + c0) * LHW + h * p.LW + w;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = load_or_zero(x, e + (int64_t)k * LHW, in && c0 + k < p.Cg);
+            for (int k = 0; k < 8; ++k, e += LHW) v[k] = load_or_zero(x, e, in && c0 + k < p.Cg);
         }
         const unsigned plane = (unsigned)p.Hp * (unsigned)p.Wp;
         split(p.xs + ((size_t)t2 * 3 * plane + (i - t2 * plane)) * 2 + half, (size_t)plane * 2, g, 0, (e >> 1) < p.positions);
@@ -632,15 +632,17 @@ __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
     const unsigned g = fastdiv(t3, p.div_cbg);
     const int ch0 = (int)(t3 - g * (unsigned)p.CBg) * 16 + half * 8;
     const float *w = p.w + (int64_t)g * p.w_gs;
+    int64_t at = (p.transposed ? (int64_t)ch0 * p.C + m : (int64_t)m * p.C + ch0) * p.RS + rs;
+    const int next = p.transposed ? p.C * p.RS : p.RS;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < 8; ++k, at += next) {
         const int ch = ch0 + k;
         if constexpr (FOLD > 1) {
             const int rv = (int)fastdiv((uint32_t)rs, p.div_sv), sv = rs - rv * (int)p.div_sv.d;
             const int c = ch / (FOLD * FOLD), r = rv * FOLD + ch / FOLD % FOLD, sx = sv * FOLD + ch % FOLD;
             v[k] = load_or_zero(w, ((int64_t)(m * p.Cin + c) * p.R + r) * p.S + sx, m < p.M && c < p.Cin && r < p.R && sx < p.S);
         } else {
-            v[k] = load_or_zero(w, (p.transposed ? (int64_t)ch * p.C + m : (int64_t)m * p.C + ch) * p.RS + rs, m < p.M && ch < p.Cg);
+            v[k] = load_or_zero(w, at, m < p.M && ch < p.Cg);
         }
     }
     split(p.wt + ((size_t)t2 * 3 * p.Mpad + m) * 2 + (half ^ ((m >> 3) & 1)), (size_t)p.Mpad * 2, g, 1, all < p.wt_chunks);
