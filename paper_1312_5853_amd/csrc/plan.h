@@ -259,7 +259,10 @@ CONVNET_HD int split_segments(float kept, bool one_sign, int steps)
 // more than the launch that looks at the operands costs (4.5 us and their bytes; 128 x 384 x 13 x 13 with 384 filters 3x3: 10.8 us).
 // On 170 drawn passes of enough steps two parts took, of three parts' time: forward 0.71 and backward-data 0.65 (each of 104 less;
 // under the line, which the smallest calls are, up to 0.98), backward-filter 0.77 (0.95 and less above the line, up to 1.10 under
-// it: its share is the smaller one, the operands of its short sums being the most).
+// it: its share is the smaller one, the operands of its short sums being the most).  Where the look finds that three parts are to
+// compute, it costs its call 4 to 5 us: 1.02 to 1.07 of 50 to 380 us forward over the output of a ReLU, 1.01 to 1.10 backward-data
+// of a gradient that is mostly zeros, 1.01 to 1.07 backward-filter of both.  A higher line would spare the small calls these and
+// take 0.75 to 0.85 from them where their operands suit.
 constexpr double kTwoPartShare = 0.45, kTwoPartWgradShare = 0.25;
 inline bool two_parts_pay(double share, double kernel_us, double elements) { return share * kernel_us > 4.5 + 4.0 * elements / 5e6; }
 // Share of (output position, tap) pairs that lie inside the image
