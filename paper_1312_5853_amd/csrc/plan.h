@@ -832,7 +832,8 @@ inline Plan make_plan(int op, const Problem &pb, bool three_part = true)
                 taps_inside(pb) * (fwd ? 1.0 : (double)pb.P * pb.Q * pb.stride * pb.stride / ((double)pb.H * pb.W));
             const float dense = (float)(std::min(inside, 1.0) * Cr * RS / (16.0 * cb * (strided ? RS : RS_)));
             // (the four-wave kernels read three parts: without this their 45 steps would have to stay below what two parts begin at)
-            if (!pl.sp_pair && split_segments(dense, false, least) > 0 &&
+            // (and a preparing work-group's 128 positions lie in four columns at most: 47 steps are as many positions and more)
+            if (!pl.sp_pair && (GF <= 4 || cb * hp * wp >= 43) && split_segments(dense, false, least) > 0 &&
                 two_parts_pay(kTwoPartShare, tile_us, (double)pb.N * Cr * (fwd ? pb.H * pb.W : pb.P * pb.Q) + (double)pb.K * pb.C * RS)) {
                 pl.sp_two = true;
                 pl.sp_two_steps = least;
