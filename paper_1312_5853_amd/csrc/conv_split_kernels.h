@@ -545,7 +545,7 @@ __device__ __forceinline__ float load_or_zero(const float *base, int64_t i, bool
 // FOLD: the stride, or 1.  TWO: in two parts where the operands' range lets it; one wavefront of a block (for each column) puts
 // together what was found of it, for up to four units of 256 threads' work, a grid apart.  128 x 384 x 13 x 13 and 128 x 96 x 27 x
 // 27, forward and backward-data, mean: without what was found 25.0 us, looked up for each unit 31.0, for four 29.9 (launch of its
-// own: 5 more).  Consecutive units cost 5 us where three parts of 128 x 256 x 27 x 27 are written (49.5 -> 55), four a grid apart 3.
+// own: 5 more).  Consecutive units cost 5 us where three parts of 128 x 256 x 27 x 27 are written (49.5 -> 55), four a grid apart 4.
 template <int FOLD, bool TWO>
 __global__ __launch_bounds__(256) void split_prepare(const SplitPrepArgs p)
 {

@@ -214,8 +214,8 @@ def test_other_magnitudes_are_no_further_from_64_bits_than_three(op, shape, draw
     assert err[0] <= err[1]
 
 
-# Operands down to the line (2^-31 of the largest, and so half-precision subnormals), on it, and below: there, and wherever a
-# tensor's largest operand is too small, too large, infinite or NaN, three parts compute
+# One operand down to the line (2^-31 of the largest, and so half-precision subnormals), on it, and below; one up to 2^7 above the
+# mean, and above: there, and wherever a tensor's largest operand is too small, too large, infinite or NaN, three parts compute
 @pytest.mark.parametrize("op,shape", SMALL)
 @pytest.mark.parametrize("second", [False, True])
 @pytest.mark.parametrize("low,high,two", [(1.0, 1.0, True), (2.0 ** -31, 1.9, True), (2.0 ** -33, 1.0, False), (1.0, 2.0 ** 41, False),
